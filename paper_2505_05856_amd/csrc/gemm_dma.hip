@@ -6,9 +6,19 @@
 //   TN: C[M,N] = A[K,M]^T * B[K,N]
 // fp32 accumulation, bf16 out.
 //
-// Preconditions (checked by gemm_dma_supported): K % 64 == 0, M >= BM, N >= BN for the
-// tile chosen, 16-byte aligned operands and rows.  Ragged edge tiles are shifted back
-// inside the matrix, so no load is ever guarded.  No split-K: the summation order is fixed.
+// Preconditions (checked by gemm_dma_supported): K >= 64, M >= BM, N >= BN for the tile chosen,
+// 16-byte aligned operands and rows.  Ragged edge tiles are shifted back inside the matrix and
+// a ragged last k-step inside the operands, so no load is ever guarded.  No split-K: the
+// summation order is fixed.
+//
+// What bounds it.  On real operands the chip lowers its clock to stay inside its power budget: the
+// matrix instructions alone, fed from registers, sustain 1.46-1.70 PFLOP/s as v_mfma_f32_32x32x16 and
+// 1.92-1.98 as v_mfma_f32_16x16x32 (one probe, same data), which is why the 16x16 form is used; a wave
+// owns as large a part of the tile as its registers hold (128x128 of 256x256, four waves) because every
+// byte read from LDS, and every instruction beside an MFMA, costs clock: [16384 x 4096] x 4096 NT 422 us
+// with 32x32 MFMAs and eight waves of 64x128, 374 us (1.47 PFLOP/s) now; [4096 x 12288] x 16384 TN
+// 1261 -> 1128 us.  The same kernel without its operand requests runs at 1.76 GHz instead of 1.56,
+// without its LDS reads at 1.75, without both at 1.86.
 //
 // LDS layout.  The load unit writes the 64 lanes of a request to 1 KB of consecutive LDS,
 // so rows cannot be padded; bank conflicts are avoided by swizzling 16-byte chunks
@@ -19,34 +29,55 @@
 //       spreads any 16 consecutive rows of one logical chunk (one 16-byte fragment read)
 //       over all 16 chunk positions of the 256-byte bank period.
 //   TN: a stage holds the tiles as loaded, [64 k rows][BM] and [64 k rows][BN]; fragments
-//       come through the transpose read (ds_read_b64_tr_b16), one of which touches four
-//       consecutive k rows x 64 bytes per half wave.  Chunk c of k row r sits at
-//       c ^ ((r & 3) << 2): the four rows land in the four 64-byte quarters of the bank
-//       period.
+//       come through the transpose read (ds_read_b64_tr_b16); see tn_swizzle.
 #include "common.h"
 #include "kernels.h"
 
 #include <cstdlib>
 #include <cstring>
 #include <type_traits>
+#include <utility>
 
 namespace dp {
 
 namespace {
 
-constexpr int kKAlign = 64;      // K must be a multiple of this (every stage depth divides it)
+// The kernel's lambdas hold its accumulators and fragments by reference: one that is not inlined would put them in memory.
+#define DP_INLINE __attribute__((always_inline))
+
+// f(integral_constant<int, 0>) .. f(integral_constant<int, N-1>): a loop whose index is a constant in every pass,
+// whatever its length (the compiler's own unrolling gives up on bodies as long as a slice of 64 MFMAs, and the
+// accumulators then go to memory)
+template <typename F, int... I> __device__ __forceinline__ void static_for(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
+  static_for(f, std::make_integer_sequence<int, N>{});
+}
+template <int N> using Count = std::integral_constant<int, N>;
+
+#ifndef KCUS
+#define KCUS 256
+#endif
+constexpr int kCus = KCUS;        // compute units: one 160 KB workgroup each
+constexpr int kMinK = 64;        // one whole k-step
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 // One request: lane l fetches 16 bytes from uniform_base + byte_off and the unit stores
-// them at LDS byte lds_base + 16*l.  Invisible to the compiler's wait-count pass; the
-// kernel counts them itself (vmcnt retires in order).  M0 is reserved by the compiler (never
-// allocated), and nothing else in this file makes it emit an M0 user, so it is simply overwritten.
-__device__ __forceinline__ void dma16(unsigned lds_base, unsigned byte_off, const void *uniform_base) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_base), "v"(byte_off), "s"(uniform_base) : "m0", "memory");
+// them at LDS byte M0 + 16*l.  Invisible to the compiler's wait-count pass; the kernel counts
+// them itself (vmcnt retires in order).  M0 is reserved by the compiler (never allocated), and
+// nothing else in this file makes it emit an M0 user, so it is simply overwritten; one instruction
+// has to stand between its write and the request (a no-op, or an MFMA of the main loop).
+// The immediate OFF counts on both sides: it is added to the LDS address and to the global one.
+template <int ADD> __device__ __forceinline__ void dma_m0(unsigned lds_base) {
+  asm volatile("s_add_u32 m0, %0, %1" :: "s"(lds_base), "n"(ADD) : "m0", "scc", "memory");
 }
+template <int OFF> __device__ __forceinline__ void dma_load(unsigned byte_off, const void *uniform_base) {
+  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(byte_off), "s"(uniform_base), "n"(OFF) : "memory");
+}
+__device__ __forceinline__ void dma_gap() { asm volatile("s_nop 0" ::: "memory"); }
 template <int N> __device__ __forceinline__ void wait_vmcnt_mem() {
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
@@ -57,27 +88,27 @@ __device__ __forceinline__ const char *uniform_ptr(const char *p) {
   return (const char *)(((uint64_t)hi << 32) | lo);
 }
 
-// TN: chunk-position swizzle of k row r of a tile whose rows are ROWB bytes.  256- and
-// 512-byte rows: the four rows of a transpose read go to the four 64-byte quarters of the
-// bank period.  128-byte rows (two rows a period): rows r and r+2 swap 64-byte halves.
+// TN: chunk-position swizzle of k row r of a tile whose rows are ROWB bytes.  A half wave's
+// transpose read touches k rows {0..3, 8..11} (or those 16 further) x 32 bytes: bits 0 and 1 of the
+// row choose the 64-byte quarter of the bank period, bit 3 the 32-byte half of it.  With 128-byte
+// rows (two rows a period) bit 0 of the row is part of the address already.
 template <int ROWB> __device__ __forceinline__ constexpr int tn_swizzle(int r) {
-  return ROWB == 128 ? ((r >> 1) & 1) << 2 : (r & 3) << 2;
+  return (ROWB == 128 ? ((r >> 1) & 1) << 2 : (r & 3) << 2) | ((r >> 3) & 1) << 1;
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool ACT, bool TN, int BK, bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool ACT, bool TN, bool SPLIT>
 __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amdgpu_flat_work_group_size(64 * WGM * WGN, 64 * WGM * WGN))) void gemm_dma_kernel(
     const bf16 *__restrict__ A, const bf16 *__restrict__ B, const bf16 *__restrict__ bias,
     const bf16 *__restrict__ res, bf16 *__restrict__ C, bf16 *__restrict__ C2, int gelu_kind, int M, int N, int K,
     int tiles_m, int tiles_n) {
+  constexpr int BK = 64;
   constexpr int NW = WGM * WGN;
-  constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 32, FN = WN / 32;
-  static_assert(BK == 64 || BK == 32, "stage depth");
+  constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
   constexpr int kRowBytes = BK * 2;                  // NT: one LDS row
-  constexpr int CPR = BK / 8, RP = 16 / CPR;         // NT: chunks per row, rows per 256-byte bank period
+  constexpr int CPR = BK / 8;                        // NT: chunks per row
   constexpr int A_BYTES = BM * kRowBytes, B_BYTES = BN * kRowBytes, STAGE_BYTES = A_BYTES + B_BYTES;
   constexpr int ROWB_A = BM * 2, ROWB_B = BN * 2;   // TN: bytes of one k row of a tile
   constexpr int NIA = A_BYTES / 1024 / NW, NIB = B_BYTES / 1024 / NW;   // requests per wave per stage
-  static_assert(NIA >= 1 && NIB >= 1, "every wave issues requests for both operands");
   constexpr int NI = NIA + NIB;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
 
@@ -94,275 +125,287 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   const int gsz = min(tiles_m - first_m, GM);
   const int tm = first_m + (pid % (GM * tiles_n)) % gsz;
   const int tn = (pid % (GM * tiles_n)) / gsz;
-  const int m0 = min(tm * BM, M - BM), n0 = min(tn * BN, N - BN);
+  const int m0 = min(tm * BM, M - BM), n0 = min(tn * BN, N - BN);   // (ragged edge tiles are shifted back inside the matrix)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
 
   // ---- request addressing -------------------------------------------------------------
-  // Request j of this wave for operand A fills LDS bytes 1024*(wave*NIA + j) .. +1023 of
-  // the A tile.  Consecutive requests alternate between two lane offsets ("even"/"odd"
-  // request groups) wherever the swizzle depends on the group's parity.
+  // A tile is A_BYTES / 1024 requests of 1 KB of consecutive LDS; which NIA of them a wave issues
+  // is chosen so that their lane offsets take two values, one for its even and one for its odd
+  // requests (the swizzle of a row depends on its low four bits).
   //   NT: a request is 8 operand rows x 128 bytes; lane l is row l/8, chunk position l%8
-  //       and fetches logical chunk (l%8) ^ ((row >> 1) & 7).
+  //       and fetches logical chunk (l%8) ^ ((row >> 1) & 7).  Request j of a wave is number
+  //       wave*NIA + j of the tile.
   //   TN: a request is RPR = 1024/ROWB k rows of ROWB bytes; lane l is k row l/(64/RPR),
-  //       chunk position l%(64/RPR) and fetches logical chunk position ^ ((krow & 3) << 2).
+  //       chunk position l%(64/RPR) and fetches logical chunk position ^ tn_swizzle(krow).  A wave
+  //       takes whole groups of 8 k rows, every NW-th (their numbers are then all even or all odd).
   const unsigned lda = (unsigned)(TN ? M : K) * 2u, ldb = (unsigned)(TN ? N : K) * 2u;   // operand row bytes
+  constexpr int RPA = TN ? 1024 / ROWB_A : 8, RPB = TN ? 1024 / ROWB_B : 8;              // rows per request
+  constexpr int GA = TN ? 8 / RPA : 1, GB = TN ? 8 / RPB : 1;                            // requests per group
+  static_assert(RPA >= 2 && RPA <= 8 && RPB >= 2 && RPB <= 8, "tile width 64, 128 or 256");
+  static_assert(NIA % GA == 0 && NIB % GB == 0 && NW % 2 == 0 && NIA % 2 == 0 && NIB % 2 == 0, "requests of a wave");
+  // request j of a wave is number (the wave's first) + rel(j) of the tile
+  const int first_a = wave * (TN ? GA : NIA), first_b = wave * (TN ? GB : NIB);
+  auto rel = [](int j, int g) constexpr { return TN ? NW * (j / g) * g + j % g : j; };
+  // requests with consecutive numbers share an M0 (that of their first, the lead); the request's immediate says
+  // how far on it is, and its base pointer makes up for that
+  auto lead = [](int j, int g) constexpr { return TN ? j / g * g : j / 4 * 4; };
   unsigned voa[2], vob[2];
-  if (!TN) {
-    constexpr int RPQ = 64 / CPR;   // operand rows per request
 #pragma unroll
-    for (int v = 0; v < 2; ++v) {
+  for (int v = 0; v < 2; ++v) {
+    if (!TN) {
       const int r = lane / CPR, pc = lane % CPR;
-      voa[v] = vob[v] = (unsigned)r * lda + (unsigned)((pc ^ (((RPQ * v + r) / RP) % CPR)) << 4);
-    }
-  } else {
-    constexpr int RPA = 1024 / ROWB_A, RPB = 1024 / ROWB_B;
-    static_assert(RPA == 2 || RPA == 4 || RPA == 8, "tile width 64, 128 or 256");
-    static_assert(RPB == 2 || RPB == 4 || RPB == 8, "tile width 64, 128 or 256");
-#pragma unroll
-    for (int v = 0; v < 2; ++v) {
+      voa[v] = vob[v] = (unsigned)r * lda + (unsigned)((pc ^ (((8 * v + r) >> 1) % CPR)) << 4);
+    } else {
       const int ka = lane / (64 / RPA), pa_ = lane % (64 / RPA);
-      voa[v] = (unsigned)ka * lda + (unsigned)((pa_ ^ tn_swizzle<ROWB_A>(RPA * v + ka)) << 4);
+      voa[v] = (unsigned)ka * lda + (unsigned)((pa_ ^ tn_swizzle<ROWB_A>(8 * (wave & 1) + RPA * (v % GA) + ka)) << 4);
       const int kb = lane / (64 / RPB), pb_ = lane % (64 / RPB);
-      vob[v] = (unsigned)kb * ldb + (unsigned)((pb_ ^ tn_swizzle<ROWB_B>(RPB * v + kb)) << 4);
+      vob[v] = (unsigned)kb * ldb + (unsigned)((pb_ ^ tn_swizzle<ROWB_B>(8 * (wave & 1) + RPB * (v % GB) + kb)) << 4);
     }
   }
   const char *pa[NIA], *pb[NIB];
 #pragma unroll
   for (int j = 0; j < NIA; ++j)
-    pa[j] = TN ? uniform_ptr((const char *)A + (size_t)((1024 / ROWB_A) * (wave * NIA + j)) * lda + (size_t)m0 * 2)
-               : uniform_ptr((const char *)A + (size_t)(m0 + (64 / CPR) * (wave * NIA + j)) * lda);
+    pa[j] = uniform_ptr((TN ? (const char *)A + (size_t)(RPA * (first_a + rel(j, GA))) * lda + (size_t)m0 * 2
+                            : (const char *)A + (size_t)(m0 + RPA * (first_a + rel(j, GA))) * lda) - 1024 * (j - lead(j, GA)));
 #pragma unroll
   for (int j = 0; j < NIB; ++j)
-    pb[j] = TN ? uniform_ptr((const char *)B + (size_t)((1024 / ROWB_B) * (wave * NIB + j)) * ldb + (size_t)n0 * 2)
-               : uniform_ptr((const char *)B + (size_t)(n0 + (64 / CPR) * (wave * NIB + j)) * ldb);
-  const unsigned lds_a = (unsigned)(wave * NIA) * 1024u, lds_b = (unsigned)A_BYTES + (unsigned)(wave * NIB) * 1024u;
+    pb[j] = uniform_ptr((TN ? (const char *)B + (size_t)(RPB * (first_b + rel(j, GB))) * ldb + (size_t)n0 * 2
+                            : (const char *)B + (size_t)(n0 + RPB * (first_b + rel(j, GB))) * ldb) - 1024 * (j - lead(j, GB)));
 
-  // request i (0 .. NI-1) of this wave for the stage at LDS byte `sb`
-  auto request = [&](int i, unsigned sb) {
-    if (i < NIA) dma16(sb + lds_a + (unsigned)i * 1024u, voa[(wave * NIA + i) & 1], pa[i]);
-    else dma16(sb + lds_b + (unsigned)(i - NIA) * 1024u, vob[(wave * NIB + i - NIA) & 1], pb[i - NIA]);
-  };
-  auto advance_k = [&]() {
-    const unsigned da = TN ? BK * lda : BK * 2, db = TN ? BK * ldb : BK * 2;
-    voa[0] += da; voa[1] += da; vob[0] += db; vob[1] += db;
-  };
+  const int nk = (K + BK - 1) / BK;
+  // A K that is no multiple of 64: the k-steps from the second on are shifted back by `dup` elements
+  // like ragged edge tiles, and the elements the first step has in common with the second count as zero
+  // in the first.
+  const int dup = nk * BK - K;
+  const unsigned step_a = TN ? BK * lda : BK * 2u, step_b = TN ? BK * ldb : BK * 2u;
+  const unsigned back_a = (unsigned)dup * (TN ? lda : 2u), back_b = (unsigned)dup * (TN ? ldb : 2u);
+  // request j for the A (B) tile at LDS byte `at`, in the two parts an MFMA goes between
+  const unsigned la0 = (unsigned)first_a * 1024u, lb0 = (unsigned)first_b * 1024u;
+  auto m0_a = [&](auto j, unsigned at) DP_INLINE { dma_m0<1024 * rel(lead(j, GA), GA)>(at + la0); };
+  auto m0_b = [&](auto j, unsigned at) DP_INLINE { dma_m0<1024 * rel(lead(j, GB), GB)>(at + lb0); };
+  auto ld_a = [&](auto j) DP_INLINE { dma_load<1024 * (j - lead(j, GA))>(voa[j & 1], pa[j]); };
+  auto ld_b = [&](auto j) DP_INLINE { dma_load<1024 * (j - lead(j, GB))>(vob[j & 1], pb[j]); };
+  auto req_a = [&](auto j, unsigned at) DP_INLINE { m0_a(j, at); dma_gap(); ld_a(j); };
+  auto req_b = [&](auto j, unsigned at) DP_INLINE { m0_b(j, at); dma_gap(); ld_b(j); };
+  // lane offsets of the next k-step (from the first to the second: less by what they have in common)
+  auto adv_a = [&](bool first) DP_INLINE { const unsigned d = first ? step_a - back_a : step_a; voa[0] += d; voa[1] += d; };
+  auto adv_b = [&](bool first) DP_INLINE { const unsigned d = first ? step_b - back_b : step_b; vob[0] += d; vob[1] += d; };
 
   // ---- fragment addressing --------------------------------------------------------------
-  // NT: lane l reads row (l%32) of a 32-row block, logical chunk 2*ks + l/32 of slice ks; with
-  //     the swizzle that is byte ((row*128) + x0) ^ (ks << 5) of the tile.
+  // A fragment is 16 rows (or columns) x 32 contraction elements: lane l holds row l%16, elements
+  // 8*(l/16) .. +7; a k-step has two slices of 32.
+  // NT: logical chunk 4*ks + l/16 of that row; with the swizzle that is byte (row*128 + x0) ^ (ks << 6).
   // TN: a 16-lane group fetches 4 k rows x 16 columns per transpose read; lane i of the group
   //     supplies the address of k row i/4, columns 4*(i%4).. and receives column i of all
-  //     four rows.  Lanes 16..31 take the next 16 columns, lanes 32..63 the k rows 8 further;
-  //     a second read 4 rows on completes the 8 contraction elements of the operand.
-  const unsigned x0 = (unsigned)(((lane >> 5) ^ (((lane & 31) / RP) % CPR)) << 4);
-  const unsigned fa = (unsigned)(wm + (lane & 31)) * kRowBytes + x0;
-  const unsigned fb = (unsigned)A_BYTES + (unsigned)(wn + (lane & 31)) * kRowBytes + x0;
-  const int ti = lane & 15, tt = ti >> 2;                                    // TN: k row within the four
-  const unsigned tlow = (unsigned)((2 * ((lane >> 4) & 1) + ((ti & 3) >> 1)) * 16 + (ti & 1) * 8);
-  const unsigned trow = (unsigned)(8 * (lane >> 5) + tt);
-  auto frag = [&](unsigned base, int blk, int ks, bool is_b) -> bf16x8 {
+  //     four rows.  Group g starts at k row 8*g; a second read 4 rows on completes the 8
+  //     contraction elements of the operand.
+  const unsigned x0 = (unsigned)(((lane >> 4) ^ ((lane & 15) >> 1)) << 4);
+  const unsigned fa = (unsigned)(wm + (lane & 15)) * kRowBytes + x0;
+  const unsigned fb = (unsigned)(wn + (lane & 15)) * kRowBytes + x0;
+  const int ti = lane & 15, trow = 8 * (lane >> 4) + (ti >> 2);              // TN: k row within the slice
+  const unsigned tlow = (unsigned)(((ti & 3) >> 1) * 16 + (ti & 1) * 8);
+  // fragment `blk` of slice ks of the A (B) tile at LDS byte `base`
+  auto frag = [&](unsigned base, int blk, int ks, bool is_b) DP_INLINE -> bf16x8 {
     if (!TN) {
       // the block offset has no bits below 128, so it can stay outside the xor (an immediate of the read)
-      return *reinterpret_cast<const bf16x8 *>(lds + (((base + (is_b ? fb : fa)) ^ (unsigned)(ks << 5)) + (unsigned)blk * 32u * kRowBytes));
+      return *reinterpret_cast<const bf16x8 *>(lds + (((base + (is_b ? fb : fa)) ^ (unsigned)(ks << 6)) + (unsigned)blk * 16u * kRowBytes));
     }
     const unsigned rowb = is_b ? ROWB_B : ROWB_A;
-    const unsigned cw = (unsigned)((is_b ? wn : wm) / 8 + blk * 4);        // first chunk of the 32-column block
-    const unsigned sw = is_b ? (unsigned)tn_swizzle<ROWB_B>(tt) : (unsigned)tn_swizzle<ROWB_A>(tt);
-    const unsigned off = base + (is_b ? (unsigned)A_BYTES : 0u) + trow * rowb + ((cw ^ sw) << 4) + tlow +
-                         (unsigned)ks * 16u * rowb;
+    const unsigned cw = (unsigned)((is_b ? wn : wm) / 8 + blk * 2);        // first chunk of the 16-column block
+    const unsigned sw = is_b ? (unsigned)tn_swizzle<ROWB_B>(trow) : (unsigned)tn_swizzle<ROWB_A>(trow);
+    const unsigned off = base + (unsigned)trow * rowb + ((cw ^ sw) << 4) + tlow + (unsigned)ks * 32u * rowb;
     union { s16x4 h[2]; bf16x8 v; } u;
     u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + off));
     u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + off + 4u * rowb));
     return u.v;
   };
 
-  f32x16 acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  f32x4 acc[FM][FN];
+  static_for<FM * FN>([&](auto g) DP_INLINE { acc[g / FN][g % FN] = f32x4{0.f, 0.f, 0.f, 0.f}; });
 
-  const int nk = K / BK;
-  constexpr int KS = BK / 16;                      // 16-deep MFMA slices of a k-step
-  // The main loop is software-pipelined by hand over "slices" of SK MFMA k-slices: the
-  // fragments of slice s+1 are read from LDS into the other half of a register double buffer
-  // before the MFMAs of slice s are issued, so an LDS read has a whole slice of MFMAs (at
-  // least four per wave) to complete.  Scheduling barriers pin that order: left alone, the
-  // compiler reuses one set of fragment registers and waits for every read right before its
-  // first MFMA.
-  constexpr int SK = FM * FN >= 8 ? 1 : (FM * FN >= 4 ? 1 : 2);
-  constexpr int NS = KS / SK;                      // slices of a k-step
-  constexpr int MPS = SK * FM * FN;                // MFMAs of a slice
-  static_assert(KS % SK == 0 && NS % 2 == 0, "the fragment double buffer keeps its parity across steps");
-  bf16x8 a[2][SK][FM], b[2][SK][FN];
-  // fragments of slice s of the tiles at LDS bytes base_a / base_b (frag adds A_BYTES for B)
-  auto read_slice = [&](auto buf_tag, unsigned base_a, unsigned base_b, int s) {
-    constexpr int BUF = decltype(buf_tag)::value;
-#pragma unroll
-    for (int q = 0; q < SK; ++q) {
-#pragma unroll
-      for (int i = 0; i < FM; ++i) a[BUF][q][i] = frag(base_a, i, s * SK + q, false);
-#pragma unroll
-      for (int j = 0; j < FN; ++j) b[BUF][q][j] = frag(base_b, j, s * SK + q, true);
-    }
-  };
-  // the MFMAs of one slice; req(g) issues the operand requests that go behind MFMA g
-  auto mfma_slice = [&](auto buf_tag, auto &&req) {
-    constexpr int BUF = decltype(buf_tag)::value;
-#pragma unroll
-    for (int q = 0; q < SK; ++q)
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[BUF][q][i], b[BUF][q][j], acc[i][j], 0, 0, 0);
-          req((q * FM + i) * FN + j);
-        }
-  };
-  auto no_req = [](int) {};
+  // The main loop is software-pipelined by hand over the slices: while the MFMAs of a slice issue,
+  // the fragments of the next one are read into the other half of a register double buffer and the
+  // operand requests of the pass go out, both spread evenly between the MFMAs (a burst of either
+  // would hold the wave, and its MFMAs behind them, at the issue of each).  Scheduling barriers pin
+  // that order.
+  constexpr int MF = FM * FN, NR = FM + FN;   // MFMAs and fragment reads of a slice
+  bf16x8 a[2][FM], b[2][FN];
   using Buf0 = std::integral_constant<int, 0>;
   using Buf1 = std::integral_constant<int, 1>;
+  using Yes = std::true_type;
+  using No = std::false_type;
+  // MFMAs of the slice held in buffer USE (if MUL), beside the reads of slice ks of the tiles at
+  // base_a, base_b into the other buffer (if READ) and the requests R0 .. R1-1 of the pass: first the B
+  // tile's (to LDS byte to_b), then the A tile's (to to_a).  Request r goes out between MFMAs
+  // req_at(r) and req_at(r) + 1, its M0 is written before MFMA req_at(r).
+  auto slice = [&](auto use_tag, auto mul_tag, auto read_tag, unsigned base_a, unsigned base_b, int ks, auto r0_tag,
+                   auto r1_tag, auto nb_tag, unsigned to_b, unsigned to_a) DP_INLINE {
+    constexpr int USE = decltype(use_tag)::value, R0 = decltype(r0_tag)::value, R1 = decltype(r1_tag)::value;
+    constexpr int NB = decltype(nb_tag)::value, NREQ = R1 - R0;   // NB: requests of the pass that are B's
+    constexpr bool MUL = decltype(mul_tag)::value, READ = decltype(read_tag)::value;
+    static_assert(NREQ <= MF, "one request a gap: its M0 is the only one written before its MFMA");
+    auto read = [&](auto q_tag) DP_INLINE {   // in the order the next slice needs them: the first row block, all columns, the other rows
+      constexpr int q = decltype(q_tag)::value;
+      if constexpr (q == 0) a[USE ^ 1][0] = frag(base_a, 0, ks, false);
+      else if constexpr (q <= FN) b[USE ^ 1][q - 1] = frag(base_b, q - 1, ks, true);
+      else a[USE ^ 1][q - FN] = frag(base_a, q - FN, ks, false);
+    };
+    auto m0 = [&](auto r_tag) DP_INLINE {
+      constexpr int r = decltype(r_tag)::value + R0;
+      if constexpr (r < NB) {
+        if constexpr (lead(r, GB) == r) m0_b(Count<r>{}, to_b);
+      } else {
+        if constexpr (lead(r - NB, GA) == r - NB) m0_a(Count<r - NB>{}, to_a);
+      }
+    };
+    auto ld = [&](auto r_tag) DP_INLINE {
+      constexpr int r = decltype(r_tag)::value + R0;
+      if constexpr (r < NB) ld_b(Count<r>{}); else ld_a(Count<r - NB>{});
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!MUL) {
+      if constexpr (READ) static_for<NR>(read);
+      static_for<NREQ>([&](auto r_tag) DP_INLINE {
+        constexpr int r = decltype(r_tag)::value + R0;
+        if constexpr (r < NB) req_b(Count<r>{}, to_b); else req_a(Count<r - NB>{}, to_a);
+      });
+    } else {
+      static_for<MF>([&](auto g_tag) DP_INLINE {
+        constexpr int g = decltype(g_tag)::value;
+        static_for<NREQ>([&](auto r_tag) DP_INLINE {
+          if constexpr ((2 * decltype(r_tag)::value + 1) * MF / (2 * NREQ) == g) m0(r_tag);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        acc[g / FN][g % FN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[USE][g % FN], a[USE][g / FN], acc[g / FN][g % FN], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<NREQ>([&](auto r_tag) DP_INLINE {
+          if constexpr ((2 * decltype(r_tag)::value + 1) * MF / (2 * NREQ) == g) ld(r_tag);
+        });
+        if constexpr (READ)
+          static_for<NR>([&](auto q_tag) DP_INLINE {
+            if constexpr (decltype(q_tag)::value * MF * 3 / 4 / NR == g) read(q_tag);
+          });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // the first k-step of a ragged K: its last dup elements belong to the second
+  auto mask = [&](auto buf_tag, int ks) DP_INLINE {
+    constexpr int BUF = decltype(buf_tag)::value;
+    if (dup > 0) {
+      const int keep = BK - dup - (32 * ks + 8 * (lane >> 4));   // how many of this lane's elements count
+      auto cut = [&](bf16x8 &f) DP_INLINE {
+        union { bf16x8 v; unsigned u[4]; } x;
+        x.v = f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          x.u[e] &= keep >= 2 * e + 2 ? 0xffffffffu : keep == 2 * e + 1 ? 0xffffu : 0u;
+        f = x.v;
+      };
+#pragma unroll
+      for (int i = 0; i < FM; ++i) cut(a[BUF][i]);
+#pragma unroll
+      for (int j = 0; j < FN; ++j) cut(b[BUF][j]);
+    }
+  };
   // One pass of the loop, for k-step kt, entered right behind the barrier that certified
   // stage kt (so no LDS read is in flight on entry, nor at the loop's back edge: the
   // compiler's wait-count pass only places exact partial waits inside straight-line code):
-  //   read slice 0 of stage kt, under the MFMAs of the LAST slice of step kt-1, whose
-  //     fragments are still in buffer 1 (not FIRST), with req_first's requests between them;
-  //   slices 0 .. NS-2: read the next slice, then the MFMAs of this one, req_inner between them;
+  //   the MFMAs of the second slice of step kt-1 (not FIRST), beside the reads of the first slice of kt;
+  //   the MFMAs of the first slice of kt, beside the reads of its second;
   //   every LDS read of stage kt has now been issued: wait for stage kt+1 and pass the
-  //     barrier that certifies it and frees stage kt (NEXT); the MFMAs of slice NS-1 follow
-  //     in the next pass (or behind the loop).
-  auto pass = [&](auto first_tag, auto next_tag, unsigned base_a, unsigned base_b, auto &&wait_next,
-                  auto &&req_first, auto &&req_inner) {
+  //     barrier that certifies it and frees stage kt (NEXT); the MFMAs of the second slice
+  //     follow in the next pass (or behind the loop).
+  // The pass's NB + NA requests (B's first) go out over its two slices, `EARLY` of them in the first.
+  auto pass = [&](auto first_tag, auto next_tag, unsigned base_a, unsigned base_b, auto &&wait_next, auto nb_tag,
+                  auto na_tag, auto early_tag, unsigned to_b, unsigned to_a) DP_INLINE {
     constexpr bool FIRST = decltype(first_tag)::value, NEXT = decltype(next_tag)::value;
-    read_slice(Buf0{}, base_a, base_b, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (!FIRST) {
-      mfma_slice(Buf1{}, req_first);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-#pragma unroll
-    for (int s = 0; s + 1 < NS; ++s) {
-      if (s & 1) read_slice(Buf0{}, base_a, base_b, s + 1); else read_slice(Buf1{}, base_a, base_b, s + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (s & 1) mfma_slice(Buf1{}, [&](int g) { req_inner(s * MPS + g); });
-      else mfma_slice(Buf0{}, [&](int g) { req_inner(s * MPS + g); });
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    constexpr int NB = decltype(nb_tag)::value, NA = decltype(na_tag)::value;
+    constexpr int EARLY = decltype(early_tag)::value < NB + NA ? decltype(early_tag)::value : NB + NA;
+    slice(Buf1{}, std::integral_constant<bool, !FIRST>{}, Yes{}, base_a, base_b, 0, Count<0>{}, Count<EARLY>{}, nb_tag, to_b, to_a);
+    if (FIRST) mask(Buf0{}, 0);
+    if (MF >= 32) __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): the reads are in by now; one wait instead of one before each use
+    slice(Buf0{}, Yes{}, Yes{}, base_a, base_b, 1, Count<EARLY>{}, Count<NB + NA>{}, nb_tag, to_b, to_a);
+    if (FIRST) mask(Buf1{}, 1);
     if (NEXT) {
       wait_next();
       __syncthreads();
     }
   };
-  // a request pinned in place between the MFMAs around it
-  auto pinned = [&](auto &&issue) {
-    __builtin_amdgcn_sched_barrier(0);
-    issue();
-    __builtin_amdgcn_sched_barrier(0);
+  auto last_slice = [&]() DP_INLINE {   // the MFMAs of the last slice of the last k-step
+    slice(Buf1{}, Yes{}, No{}, 0u, 0u, 0, Count<0>{}, Count<0>{}, Count<0>{}, 0u, 0u);
   };
-  constexpr int INNER = (NS - 1) * MPS;   // MFMAs of a pass that can carry its spread-out requests
-  using Yes = std::true_type;
-  using No = std::false_type;
+
   if constexpr (SPLIT) {
-    // ---- ring of five operand tiles ---------------------------------------------------
+    // ---- ring of five operand tiles -------------------------------------------------------
     // A 256x256 k-step fills 64 KB of LDS, so only two whole stages fit.  With the A and B
     // tiles as separate ring entries a fifth tile fits: slot (2k) % 5 holds A(k), slot
     // (2k+1) % 5 holds B(k).  Request order A0 B0 A1 B1 A2 | B2 A3 | B3 A4 ...: pass k asks
-    // for B(k+1) right behind the barrier that freed A(k-1)'s slot, and for A(k+2), spread
-    // over its inner slices, into the slot B(k-1) left; a B tile so has one step to land
-    // and an A tile one to two.  (The launcher sends K < 3 * BK elsewhere.)
+    // for B(k+1) behind the barrier that freed A(k-1)'s slot, and for A(k+2) into the slot
+    // B(k-1) left; a B tile so has one step to land and an A tile one to two.  (The
+    // launcher sends K < 3 * BK elsewhere.)
     static_assert(BM == BN, "the ring entries are of one size");
     constexpr unsigned TILE = A_BYTES;
-    auto req_a = [&](int i, unsigned slot) {
-        dma16(slot * TILE + lds_a + (unsigned)i * 1024u, voa[(wave * NIA + i) & 1], pa[i]);
-    };
-    auto req_b = [&](int i, unsigned slot) {
-        dma16(slot * TILE + (lds_b - (unsigned)A_BYTES) + (unsigned)i * 1024u, vob[(wave * NIB + i) & 1], pb[i]);
-    };
-    const unsigned da = TN ? BK * lda : BK * 2, db = TN ? BK * ldb : BK * 2;
-    auto adv_a = [&]() { voa[0] += da; voa[1] += da; };
-    auto adv_b = [&]() { vob[0] += db; vob[1] += db; };
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-#pragma unroll
-      for (int i = 0; i < NIA; ++i) req_a(i, 2u * t);
-      adv_a();
-#pragma unroll
-      for (int i = 0; i < NIB; ++i) req_b(i, 2u * t + 1u);
-      adv_b();
-    }
+    constexpr int EARLY_REQ = (NIA + NIB) * 3 / 4;   // requests of a pass that go out beside its first slice's MFMAs
+    static_for<2>([&](auto t) DP_INLINE {
+      static_for<NIA>([&](auto i) DP_INLINE { req_a(i, 2u * t * TILE); });
+      adv_a(t == 0);
+      static_for<NIB>([&](auto i) DP_INLINE { req_b(i, (2u * t + 1u) * TILE); });
+      adv_b(t == 0);
+    });
     wait_vmcnt_mem<NIA + NIB>();
     __syncthreads();
-    unsigned sa = 0, sbk = 1;   // slots of A(kt), B(kt)
-    auto ring = [](unsigned s, unsigned d) { return s + d >= 5 ? s + d - 5 : s + d; };
+    // the ring, in LDS bytes: A(kt), B(kt), A(kt+1), B(kt+1), A(kt+2)
+    unsigned s0 = 0, s1 = TILE, s2 = 2 * TILE, s3 = 3 * TILE, s4 = 4 * TILE;
     // MORE: k-step kt+2 exists (its A tile is requested in this pass)
-    auto step = [&](auto first_tag, auto next_tag, auto more_tag) {
+    auto step = [&](auto first_tag, auto next_tag, auto more_tag) DP_INLINE {
       constexpr bool FIRST = decltype(first_tag)::value, NEXT = decltype(next_tag)::value,
                      MORE = decltype(more_tag)::value;
-      const unsigned to_b = ring(sbk, 2), to_a = ring(sa, 4);   // slots of B(kt+1), A(kt+2)
-      pass(first_tag, next_tag, sa * TILE, sbk * TILE - (unsigned)A_BYTES,
-           [&]() { if (MORE) wait_vmcnt_mem<NIA>(); else wait_vmcnt_mem<0>(); },
-           [&](int g) {
-             if (NEXT && g < NIB) pinned([&]() { req_b(g, to_b); });
-           },
-           [&](int p) {
-             if (MORE) {
-#pragma unroll
-               for (int q = 0; q < NIA; ++q)
-                 if (((q + 1) * INNER + NIA - 1) / NIA - 1 == p) pinned([&]() { req_a(q, to_a); });
-             }
-           });
-      if (!FIRST && NEXT) adv_b();
-      if (MORE) adv_a();
-      sa = ring(sa, 2);
-      sbk = ring(sbk, 2);
+      pass(first_tag, next_tag, s0, s1,
+           [&]() DP_INLINE { if (MORE) wait_vmcnt_mem<NIA>(); else wait_vmcnt_mem<0>(); },
+           Count<(!FIRST && NEXT ? NIB : 0)>{}, Count<(MORE ? NIA : 0)>{}, Count<EARLY_REQ>{}, s3, s4);
+      if (!FIRST && NEXT) adv_b(false);
+      if (MORE) adv_a(false);
+      const unsigned t0 = s0, t1 = s1;
+      s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;
     };
-    static_assert(NIB <= MPS, "the B requests of a pass ride the MFMAs of one slice");
     step(Yes{}, Yes{}, Yes{});
-    int kt = 1;
-    for (; kt + 2 < nk; ++kt) step(No{}, Yes{}, Yes{});
+    for (int left = nk - 3; left > 0; --left) step(No{}, Yes{}, Yes{});
     step(No{}, Yes{}, No{});
     step(No{}, No{}, No{});
   } else {
     // ---- ring of STAGES whole stages ------------------------------------------------------
     // Stage k sits in slot k % STAGES.  Stages 0 .. STAGES-2 are requested up front; pass kt
-    // asks for stage kt+STAGES-1, spread over its inner slices, into the slot the barrier
+    // asks for stage kt+STAGES-1, spread over its two slices, into the slot the barrier
     // before it freed, so a stage has STAGES-2 steps and more to land.
     static_assert(STAGES >= 3, "the barrier of a step certifies the next stage");
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s) {
       if (s < nk) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) request(i, (unsigned)s * STAGE_BYTES);
-        advance_k();
+        static_for<NIA>([&](auto i) DP_INLINE { req_a(i, (unsigned)s * STAGE_BYTES); });
+        adv_a(s == 0);
+        static_for<NIB>([&](auto i) DP_INLINE { req_b(i, (unsigned)s * STAGE_BYTES + A_BYTES); });
+        adv_b(s == 0);
       }
     }
     if (nk >= STAGES - 1) wait_vmcnt_mem<(STAGES - 2) * NI>(); else wait_vmcnt_mem<0>();
     __syncthreads();
-    int cur = 0;                 // ring slot of k-step kt
-    int nxt = STAGES - 1;        // ring slot the requests of this pass go to
+    unsigned cur = 0;                                          // LDS byte of k-step kt's stage
+    unsigned nxt = (unsigned)(STAGES - 1) * STAGE_BYTES;       // where the requests of this pass go
     // MORE: k-step kt+STAGES-1 exists (requested in this pass; the stages before it then all
     // exist, so the wait for stage kt+1 may leave STAGES-2 stages pending)
-    auto step = [&](auto first_tag, auto next_tag, auto more_tag) {
+    auto step = [&](auto first_tag, auto next_tag, auto more_tag) DP_INLINE {
       constexpr bool MORE = decltype(more_tag)::value;
-      const unsigned sb = (unsigned)cur * STAGE_BYTES, nb = (unsigned)nxt * STAGE_BYTES;
-      pass(first_tag, next_tag, sb, sb,
-           [&]() { if (MORE) wait_vmcnt_mem<(STAGES - 2) * NI>(); else wait_vmcnt_mem<0>(); },
-           no_req,
-           [&](int p) {
-             if (MORE) {
-#pragma unroll
-               for (int q = 0; q < NI; ++q)
-                 if (((q + 1) * INNER + NI - 1) / NI - 1 == p) pinned([&]() { request(q, nb); });
-             }
-           });
-      if (MORE) advance_k();
-      cur = cur + 1 == STAGES ? 0 : cur + 1;
-      nxt = nxt + 1 == STAGES ? 0 : nxt + 1;
+      pass(first_tag, next_tag, cur, cur + A_BYTES,
+           [&]() DP_INLINE { if (MORE) wait_vmcnt_mem<(STAGES - 2) * NI>(); else wait_vmcnt_mem<0>(); },
+           Count<(MORE ? NIB : 0)>{}, Count<(MORE ? NIA : 0)>{}, Count<NI / 2>{}, nxt + A_BYTES, nxt);
+      if (MORE) { adv_a(false); adv_b(false); }
+      cur = cur + STAGE_BYTES == STAGES * STAGE_BYTES ? 0u : cur + STAGE_BYTES;
+      nxt = nxt + STAGE_BYTES == STAGES * STAGE_BYTES ? 0u : nxt + STAGE_BYTES;
     };
     if (nk >= STAGES) step(Yes{}, Yes{}, Yes{});
     else if (nk > 1) step(Yes{}, Yes{}, No{});
@@ -372,99 +415,108 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
     for (; kt + 1 < nk; ++kt) step(No{}, Yes{}, No{});
     if (kt < nk) step(No{}, No{}, No{});
   }
-  // the MFMAs of the last slice of the last k-step
-  __builtin_amdgcn_sched_barrier(0);
-  mfma_slice(Buf1{}, no_req);
+  last_slice();
 
   // ---- epilogue ---------------------------------------------------------------------------
-  // Accumulator element e of lane l is C[8*(e/4) + 4*(l/32) + e%4][l%32] of its 32x32 block:
-  // single elements per lane, 64 contiguous bytes per row and store.  Each wave therefore
-  // turns its tile through LDS, 32 rows at a time (fp32, so that bias and residual are added
-  // before the one rounding): written as held, read back as runs of four columns per lane,
-  // so that the global accesses are 8 bytes a lane and 256..512 contiguous bytes a row.
-  // Column c of row r sits at c ^ (32 * ((r >> 2) & 1)): rows r and r+4, which one write
-  // instruction touches, land in different halves of the banks.
-  constexpr int LPR = WN / 4;            // lanes per row on the way out
-  constexpr int RPI = 64 / LPR;          // rows per read/store instruction
-  constexpr int EPI_BYTES = 32 * WN * 4; // one wave's 32 x WN fp32 block
-  constexpr unsigned ESW = WN >= 64 ? 32u : 0u;   // (a 32-column block has no second half to swap with)
-  static_assert(NW * EPI_BYTES <= (SPLIT ? 5 * A_BYTES : STAGES * STAGE_BYTES), "the epilogue reuses the operand stages");
-  __syncthreads();                       // every wave is done with the operand stages
-  unsigned char *ew = lds + (unsigned)wave * EPI_BYTES;
-  const int orow = lane / LPR, oc4 = (lane % LPR) * 4;
-  const unsigned lane_off = ((unsigned)orow * (unsigned)N + (unsigned)oc4) * 2u;
-  // A tile that was shifted back stores only the part its unshifted position covers: the rest
-  // is its neighbour's (written once, so that C may also be the residual operand).
-  const int skip_rows = tm * BM - m0;
-  const bool col_owned = n0 + wn + oc4 >= tn * BN;
-  float bv[4] = {0.f, 0.f, 0.f, 0.f};
-  if (bias != nullptr) {
-    const bf16x4 b4 = *reinterpret_cast<const bf16x4 *>(bias + n0 + wn + oc4);
+  // The B fragment is the MFMA's first operand, so element e of lane l of acc[i][j] is
+  // C[16*i + l%16][16*j + 4*(l/16) + e] of the wave's part: four consecutive columns of one row.  Lane
+  // group g = l/16 gives its half of block j or j+1 to group g ^ 1 (v_permlane16_swap) and then holds
+  // eight consecutive columns, 16 * (g & 1) + 8 * (g / 2) onward of the two blocks: 16 bytes a lane and
+  // 64 contiguous bytes a row for every global access, straight from the registers.
+  const bool wide16 = ((((uintptr_t)C | (uintptr_t)C2 | (uintptr_t)res) & 15) | (uintptr_t)(N & 7)) == 0;
+  auto swap2 = [](unsigned (&x)[2], unsigned (&y)[2]) DP_INLINE {   // its own inverse
 #pragma unroll
-    for (int q = 0; q < 4; ++q) bv[q] = (float)b4[q];
-  }
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    // the residual of the 32 rows, asked for before the turn through LDS and first used after it
-    // (every tile lies inside the matrix, so rows and columns the tile does not own are read too)
-    bf16x4 r4[32 / RPI];
-    if (res != nullptr) {
-#pragma unroll
-      for (int g = 0; g < 32 / RPI; ++g) {
-        const size_t uoff = ((size_t)(m0 + wm + i * 32 + g * RPI) * (size_t)N + (size_t)(n0 + wn)) * 2 + lane_off;
-        r4[g] = *reinterpret_cast<const bf16x4 *>((const char *)res + uoff);
-      }
+    for (int q = 0; q < 2; ++q) {
+      const auto r = __builtin_amdgcn_permlane16_swap(x[q], y[q], false, false);
+      x[q] = r[0]; y[q] = r[1];
     }
-    // write: element e of block j -> row 8*(e/4) + 4*(l/32) + e%4, column 32*j + l%32
+  };
+  union Half { bf16x4 v; unsigned u[2]; };
+  auto epilogue = [&](auto wide_tag) DP_INLINE {
+    constexpr bool wide = decltype(wide_tag)::value;
+    const int erow = lane & 15, ecol = 16 * ((lane >> 4) & 1) + 8 * (lane >> 5), ebcol = 4 * (lane >> 4);
+    const unsigned elane = ((unsigned)erow * (unsigned)N + (unsigned)ecol) * 2u;
+    // A tile that was shifted back stores only the part its unshifted position covers: the rest
+    // is its neighbour's (written once, so that C may also be the residual operand).
+    const int skip_rows = tm * BM - m0, skip_cols = tn * BN - n0;
+    Half bv[FN];
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int r = 8 * (e >> 2) + (e & 3);            // + 4*(l/32)
-        const unsigned rr = (unsigned)r + 4u * (unsigned)(lane >> 5);
-        const unsigned cc = (unsigned)(32 * j + (lane & 31)) ^ (ESW * ((rr >> 2) & 1u));
-        *reinterpret_cast<float *>(ew + (rr * WN + cc) * 4u) = acc[i][j][e];
-      }
-    // read back (all reads asked for before the first is used), then store
-    f32x4 tb[32 / RPI];
-#pragma unroll
-    for (int g = 0; g < 32 / RPI; ++g) {
-      const unsigned rr = (unsigned)(g * RPI + orow);
-      const unsigned cc = (unsigned)oc4 ^ (ESW * ((rr >> 2) & 1u));
-      tb[g] = *reinterpret_cast<const f32x4 *>(ew + (rr * WN + cc) * 4u);
+    for (int j = 0; j < FN; ++j) {
+      bv[j].u[0] = bv[j].u[1] = 0u;
+      if (bias != nullptr) bv[j].v = *reinterpret_cast<const bf16x4 *>(bias + n0 + wn + 16 * j + ebcol);
     }
-#pragma unroll
-    for (int g = 0; g < 32 / RPI; ++g) {
-      const f32x4 t = tb[g];
-      const size_t uoff = ((size_t)(m0 + wm + i * 32 + g * RPI) * (size_t)N + (size_t)(n0 + wn)) * 2 + lane_off;
-      if (!col_owned || wm + i * 32 + g * RPI + orow < skip_rows) continue;
-      float v[4] = {t[0] + bv[0], t[1] + bv[1], t[2] + bv[2], t[3] + bv[3]};
+    static_for<FM>([&](auto i_tag) DP_INLINE {
+      constexpr int i = decltype(i_tag)::value;
+      const size_t row_off = ((size_t)(m0 + wm + 16 * i) * (size_t)N + (size_t)(n0 + wn)) * 2;
+      // the residual of the 16 rows, asked for before its first use (every tile lies inside the matrix, so
+      // rows and columns the tile does not own are read too)
+      Half r0[FN / 2], r1[FN / 2];
       if (res != nullptr) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] += (float)r4[g][q];
+        for (int p = 0; p < FN / 2; ++p) {
+          const char *at = (const char *)res + row_off + 64 * p + elane;
+          if (wide) {
+            const uint4 q = *reinterpret_cast<const uint4 *>(at);
+            r0[p].u[0] = q.x; r0[p].u[1] = q.y; r1[p].u[0] = q.z; r1[p].u[1] = q.w;
+          } else {
+            r0[p].v = reinterpret_cast<const bf16x4 *>(at)[0];
+            r1[p].v = reinterpret_cast<const bf16x4 *>(at)[1];
+          }
+        }
       }
-      bf16x4 o;
+      static_for<FN / 2>([&](auto p_tag) DP_INLINE {
+        constexpr int p = decltype(p_tag)::value;
+        float v[2][4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = (bf16)v[q];
-      *reinterpret_cast<bf16x4 *>((char *)C + uoff) = o;
-      if (ACT) {
-        // fused activation: computed from the value as stored, so that a later standalone
-        // GELU of C gives the same bits
-        bf16x4 o2;
+        for (int q = 0; q < 4; ++q) {
+          v[0][q] = acc[i][2 * p][q] + (float)bv[2 * p].v[q];
+          v[1][q] = acc[i][2 * p + 1][q] + (float)bv[2 * p + 1].v[q];
+        }
+        if (res != nullptr) {
+          swap2(r0[p].u, r1[p].u);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o2[q] = (bf16)gelu_f((float)o[q], gelu_kind);
-        *reinterpret_cast<bf16x4 *>((char *)C2 + uoff) = o2;
-      }
-    }
-  }
+          for (int q = 0; q < 4; ++q) { v[0][q] += (float)r0[p].v[q]; v[1][q] += (float)r1[p].v[q]; }
+        }
+        Half o0, o1, g0, g1;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { o0.v[q] = (bf16)v[0][q]; o1.v[q] = (bf16)v[1][q]; }
+        if (ACT) {
+          // fused activation: computed from the value as stored, so that a later standalone
+          // GELU of C gives the same bits
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            g0.v[q] = (bf16)gelu_f((float)o0.v[q], gelu_kind);
+            g1.v[q] = (bf16)gelu_f((float)o1.v[q], gelu_kind);
+          }
+          swap2(g0.u, g1.u);
+        }
+        swap2(o0.u, o1.u);
+        const int row = wm + 16 * i + erow, col = wn + 32 * p + ecol;
+        auto put = [&](bf16 *out, const Half &lo, const Half &hi) DP_INLINE {
+          char *at = (char *)out + row_off + 64 * p + elane;
+          if (wide) *reinterpret_cast<uint4 *>(at) = make_uint4(lo.u[0], lo.u[1], hi.u[0], hi.u[1]);
+          else {
+            if (col >= skip_cols) reinterpret_cast<bf16x4 *>(at)[0] = lo.v;
+            if (col + 4 >= skip_cols) reinterpret_cast<bf16x4 *>(at)[1] = hi.v;
+          }
+        };
+        if (row >= skip_rows && col + (wide ? 0 : 4) >= skip_cols) {
+          put(C, o0, o1);
+          if (ACT) put(C2, g0, g1);
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);   // (the row blocks one after the other, or their temporaries add up)
+    });
+  };
+  if (wide16) epilogue(Yes{}); else epilogue(No{});
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool ACT, bool TN, int BK, bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool ACT, bool TN, bool SPLIT>
 hipError_t launch_dma_act(const GemmArgs &a, hipStream_t s) {
-  constexpr size_t smem = SPLIT ? (size_t)5 * BM * BK * 2 : (size_t)STAGES * (BM + BN) * BK * 2;
+  constexpr size_t smem = SPLIT ? (size_t)5 * BM * 128 : (size_t)STAGES * (BM + BN) * 128;
   static_assert(smem <= 160 * 1024, "LDS of one CU");
   static bool attr_set = false;
-  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, STAGES, ACT, TN, BK, SPLIT>;
+  auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, STAGES, ACT, TN, SPLIT>;
   if (!attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -478,11 +530,11 @@ hipError_t launch_dma_act(const GemmArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, int WGM, int WGN, int STAGES, bool TN, int BK = 64, bool SPLIT = false>
+template <int BM, int BN, int WGM, int WGN, int STAGES, bool TN, bool SPLIT = false>
 hipError_t launch_dma_cfg(const GemmArgs &a, hipStream_t s) {
-  if (TN) return launch_dma_act<BM, BN, WGM, WGN, STAGES, false, TN, BK, SPLIT>(a, s);   // no epilogue extras in this form
-  return a.C2 != nullptr ? launch_dma_act<BM, BN, WGM, WGN, STAGES, true, false, BK, SPLIT>(a, s)
-                         : launch_dma_act<BM, BN, WGM, WGN, STAGES, false, false, BK, SPLIT>(a, s);
+  if (TN) return launch_dma_act<BM, BN, WGM, WGN, STAGES, false, TN, SPLIT>(a, s);   // no epilogue extras in this form
+  return a.C2 != nullptr ? launch_dma_act<BM, BN, WGM, WGN, STAGES, true, false, SPLIT>(a, s)
+                         : launch_dma_act<BM, BN, WGM, WGN, STAGES, false, false, SPLIT>(a, s);
 }
 
 template <bool TN>
@@ -492,7 +544,7 @@ hipError_t launch_dma_mode(const GemmArgs &a, hipStream_t s) {
   static const char *force = getenv("DPSTAGE_GEMM_TILE");
   const bool big_ok = a.M >= 256 && a.N >= 256;
   if (force != nullptr) {
-    if (!strcmp(force, "256x256") && big_ok && a.K >= 192) return launch_dma_cfg<256, 256, 4, 2, 2, TN, 64, true>(a, s);
+    if (!strcmp(force, "256x256") && big_ok && a.K >= 192) return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
     if (!strcmp(force, "128x128")) return launch_dma_cfg<128, 128, 4, 2, 4, TN>(a, s);
     if (!strcmp(force, "128x128w4")) return launch_dma_cfg<128, 128, 2, 2, 4, TN>(a, s);
     if (!strcmp(force, "64x64")) return launch_dma_cfg<64, 64, 2, 2, 8, TN>(a, s);
@@ -502,7 +554,7 @@ hipError_t launch_dma_mode(const GemmArgs &a, hipStream_t s) {
   // flop of 128x128 and wins as soon as it gives two thirds of the CUs a workgroup (measured:
   // 175 tiles, the [1600 x 6400] weight gradients, 10-20 % faster than 650 tiles of 128x128;
   // 133 and 112 tiles slower); below that 128x128 with 8 waves and a four-stage ring.
-  if (big_ok && a.K >= 192 && tiles(256, 256) >= 170) return launch_dma_cfg<256, 256, 4, 2, 2, TN, 64, true>(a, s);
+  if (big_ok && a.K >= 192 && tiles(256, 256) >= 170) return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
   // a small output with a long contraction (the out-projection weight gradient) leaves most
   // CUs without a 128x128 tile: 64x64 tiles, several workgroups a CU, then run faster
   if (tiles(128, 128) <= 96) return launch_dma_cfg<64, 64, 2, 2, 8, TN>(a, s);
@@ -512,12 +564,12 @@ hipError_t launch_dma_mode(const GemmArgs &a, hipStream_t s) {
 }  // namespace
 
 bool gemm_dma_supported(const GemmArgs &a) {
-  if (a.M < 128 || a.N < 128 || a.K <= 0 || a.K % kKAlign != 0) return false;
+  if (a.M < 128 || a.N < 128 || a.K < kMinK) return false;
   if ((((uintptr_t)a.A | (uintptr_t)a.B) & 15) != 0) return false;
   // the epilogue moves runs of four columns (8 bytes)
   if (a.N % 4 != 0 || (((uintptr_t)a.C | (uintptr_t)a.C2 | (uintptr_t)a.res | (uintptr_t)a.bias) & 7) != 0) return false;
   // lane offsets are 32-bit
-  if (a.mode == kGemmNT) return (uint64_t)a.K * 2 * 9 + 4096 <= 0xffffffffull;
+  if (a.mode == kGemmNT) return a.K % 8 == 0 && (uint64_t)a.K * 2 * 9 + 4096 <= 0xffffffffull;
   if (a.M % 8 != 0 || a.N % 8 != 0) return false;   // 16-byte rows and tile origins
   const uint64_t ld = (uint64_t)(a.M > a.N ? a.M : a.N) * 2;
   return ((uint64_t)a.K + 4) * ld + 4096 <= 0xffffffffull;

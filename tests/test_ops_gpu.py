@@ -135,6 +135,33 @@ def test_gemm(dt, mode, M, N, K):
     assert O.max_rel_err(host(c), ref + res) < TOL[dt]
 
 
+# K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, the shortest
+# that take the 256x256 tile's operand ring, and C, bias and residual rows of 8-byte alignment only (N a multiple of 4)
+GEMM_RAGGED_K = [(0, 256, 264, 72), (0, 1096, 1304, 248), (0, 3904, 4200, 200), (0, 3904, 4200, 456), (0, 200, 132, 136),
+                 (0, 3904, 4204, 200), (1, 256, 264, 65), (1, 264, 328, 127), (1, 1096, 1304, 250), (1, 3904, 4200, 193),
+                 (1, 3904, 4200, 451), (1, 768, 3072, 1000)]
+
+
+@pytest.mark.parametrize("mode,M,N,K", GEMM_RAGGED_K)
+def test_gemm_ragged_k(mode, M, N, K):
+    dt = torch.bfloat16
+    a = rnd((M, K), 45, dt); b = rnd((K, N), 46, dt)
+    bias = rnd((N,), 47, dt); res = rnd((M, N), 48, dt)
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    ta, tb = (dev(a, dt), dev(b.T, dt)) if mode == 0 else (dev(a.T, dt), dev(b, dt))
+    c = torch.full((M, N), float("nan"), dtype=dt, device=DEV)
+    B.op_gemm(mode, M, N, K, ta, tb, None, None, c)
+    assert O.max_rel_err(host(c), ref) < TOL[dt]
+    B.op_gemm(mode, M, N, K, ta, tb, dev(bias, dt), dev(res, dt), c)
+    assert O.max_rel_err(host(c), ref + bias + res) < TOL[dt]
+    # 8-byte aligned C and residual
+    pad = torch.zeros(M * N + 4, dtype=dt, device=DEV)
+    pad[4:].copy_(dev(res, dt).view(-1))
+    c8 = pad[4:].view(M, N)
+    B.op_gemm(mode, M, N, K, ta, tb, None, c8, c8)
+    assert O.max_rel_err(host(c8), ref + res) < TOL[dt]
+
+
 ATTN_SHAPES = [(1, 8, 1, 8), (2, 5, 2, 16), (2, 64, 2, 64), (1, 200, 3, 64), (2, 96, 2, 128), (1, 384, 2, 64),
                (1, 1024, 3, 64), (1, 2048, 2, 128)]     # the last two: sequence and head width of C3/C4 and of C5
 

@@ -33,8 +33,8 @@
 #include "common.h"
 #include "kernels.h"
 
+#include <cstdio>
 #include <cstdlib>
-#include <cstring>
 #include <type_traits>
 #include <utility>
 
@@ -56,10 +56,6 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
 }
 template <int N> using Count = std::integral_constant<int, N>;
 
-#ifndef KCUS
-#define KCUS 256
-#endif
-constexpr int kCus = KCUS;        // compute units: one 160 KB workgroup each
 constexpr int kMinK = 64;        // one whole k-step
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -537,28 +533,63 @@ hipError_t launch_dma_cfg(const GemmArgs &a, hipStream_t s) {
                          : launch_dma_act<BM, BN, WGM, WGN, STAGES, false, false, SPLIT>(a, s);
 }
 
+// Tile choice: the tile with the smallest estimated time.  A launch runs in rounds of one tile a CU; a
+// round takes a start (pipeline fill, output) plus a time per 64-deep k-step (us, below: between what full
+// rounds take with operands in the caches and with operands from memory, where small tiles, which fetch more
+// bytes per flop, lose more).  A larger tile is faster per flop but covers the output in coarser rounds.
+// Measured, operands in the caches / from memory:
+//   [4096 x 1600] x 6400 NT: 208 tiles of 256x128 71 / 91 us; 416 of 128x128 (the second round half empty) 87 / 116
+//   [4096 x 1600] x 1600 NT: 23 / 29 us against 28 / 35; [1600 x 4800] x 4096 TN: 247 of 128x256 55 / 58, 66 / 80
+//   [4096 x 4800] x 1600 NT: 304 of 256x256 72 / 73 us, 1216 of 128x128 68 / 89, 608 of 128x256 67 / 82
+//   [4096 x 1024] x 1024 NT: 256 of 128x128 10.5 / 13.8 us, 128 of 256x128 15.5 / 19.3, 64 of 256x256 24.5 / 26.9
+//   [2048 x 768] x 3072 NT: 192 of 128x64 17.3 / 24.9 us, 96 of 128x128 20.9 / 31.0, 384 of 64x64 21.4 / 30.3
+//   [1024 x 1024] x 4096 TN: 256 of 64x64 16.0 / 22.8 us, 64 of 128x128 27.8 / 37.0, 128 of 128x64 22.3 / 31.5
+struct TileTime { int bm, bn; float start_us, step_us; };
+enum { k256x256, k256x128, k128x256, k128x128, k128x64, k64x128, k64x64, kTiles };
+constexpr TileTime kTileTimes[kTiles] = {{256, 256, 6.0f, 1.27f}, {256, 128, 4.5f, 0.85f}, {128, 256, 4.5f, 0.85f},
+                                         {128, 128, 2.0f, 0.55f}, {128, 64, 1.5f, 0.40f},  {64, 128, 1.5f, 0.40f},
+                                         {64, 64, 1.5f, 0.26f}};
+constexpr int kCus = 256;
+
+int choose_tile(const GemmArgs &a) {
+  const int nk = (a.K + 63) / 64;
+  int best = -1;
+  float best_us = 0.f;
+  long best_tiles = 0;
+  for (int i = 0; i < kTiles; ++i) {
+    const TileTime &t = kTileTimes[i];
+    if (a.M < t.bm || a.N < t.bn) continue;
+    if (i == k256x256 && nk < 3) continue;   // (its operand ring)
+    const long tiles = (long)((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn);
+    const float us = (float)((tiles + kCus - 1) / kCus) * (t.start_us + t.step_us * (float)nk);
+    if (best < 0 || us < best_us || (us == best_us && tiles < best_tiles)) { best = i; best_us = us; best_tiles = tiles; }
+  }
+  return best;
+}
+
 template <bool TN>
 hipError_t launch_dma_mode(const GemmArgs &a, hipStream_t s) {
-  auto tiles = [&](int bm, int bn) { return (long)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+  int tile = choose_tile(a);
   // DPSTAGE_GEMM_TILE overrides the tile choice (tuning aid)
   static const char *force = getenv("DPSTAGE_GEMM_TILE");
-  const bool big_ok = a.M >= 256 && a.N >= 256;
   if (force != nullptr) {
-    if (!strcmp(force, "256x256") && big_ok && a.K >= 192) return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
-    if (!strcmp(force, "128x128")) return launch_dma_cfg<128, 128, 4, 2, 4, TN>(a, s);
-    if (!strcmp(force, "128x128w4")) return launch_dma_cfg<128, 128, 2, 2, 4, TN>(a, s);
-    if (!strcmp(force, "64x64")) return launch_dma_cfg<64, 64, 2, 2, 8, TN>(a, s);
-
+    int bm = 0, bn = 0;
+    if (sscanf(force, "%dx%d", &bm, &bn) == 2)
+      for (int i = 0; i < kTiles; ++i)
+        if (kTileTimes[i].bm == bm && kTileTimes[i].bn == bn && a.M >= bm && a.N >= bn && (i != k256x256 || a.K > 128)) tile = i;
   }
-  // 256x256 (8 waves, 64x128 a wave, ring of five operand tiles) halves the L1 traffic per
-  // flop of 128x128 and wins as soon as it gives two thirds of the CUs a workgroup (measured:
-  // 175 tiles, the [1600 x 6400] weight gradients, 10-20 % faster than 650 tiles of 128x128;
-  // 133 and 112 tiles slower); below that 128x128 with 8 waves and a four-stage ring.
-  if (big_ok && a.K >= 192 && tiles(256, 256) >= 170) return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
-  // a small output with a long contraction (the out-projection weight gradient) leaves most
-  // CUs without a 128x128 tile: 64x64 tiles, several workgroups a CU, then run faster
-  if (tiles(128, 128) <= 96) return launch_dma_cfg<64, 64, 2, 2, 8, TN>(a, s);
-  return launch_dma_cfg<128, 128, 4, 2, 4, TN>(a, s);
+  switch (tile) {
+    case k256x256: return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
+    case k256x128: return launch_dma_cfg<256, 128, 2, 2, 3, TN>(a, s);
+    case k128x256: return launch_dma_cfg<128, 256, 2, 2, 3, TN>(a, s);
+    // (eight waves: with four, [4096 x 1024] x 4096 NT takes 31.2 us instead of 31.7 with operands in the caches,
+    //  but 41.4 instead of 38.9 from memory)
+    case k128x128: return launch_dma_cfg<128, 128, 4, 2, 4, TN>(a, s);
+    case k128x64: return launch_dma_cfg<128, 64, 2, 2, 3, TN>(a, s);
+    case k64x128: return launch_dma_cfg<64, 128, 2, 2, 3, TN>(a, s);
+    // (four stages: two workgroups a CU; with eight stages, one a CU, [4096 x 1600] x 1600 NT took 44 us, not 41)
+    default: return launch_dma_cfg<64, 64, 2, 2, 4, TN>(a, s);
+  }
 }
 
 }  // namespace

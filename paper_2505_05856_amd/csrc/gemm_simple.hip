@@ -1,5 +1,5 @@
-// Plain LDS-tiled GEMM on the vector ALUs with fp32 accumulation.  This is the
-// fp32 debug mode's GEMM and the fallback for shapes the MFMA kernels do not
+// Plain LDS-tiled GEMM on the vector ALUs with fp32 accumulation: the fallback
+// for shapes and alignments the matrix-core kernels (bf16 and fp32) do not
 // take; it handles any M, N, K through guarded loads.
 #include "common.h"
 #include "kernels.h"

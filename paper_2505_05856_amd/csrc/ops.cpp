@@ -84,6 +84,8 @@ dp_status dp_op_gemm(int32_t dtype, int32_t mode, int32_t M, int32_t N, int32_t 
   const bool simple = !env_mfma_enabled();
   if (dtype == DP_BF16 && !simple && dp::gemm_mfma_supported(a))
     return op_done(dp::launch_gemm_mfma(a, (hipStream_t)hip_stream), "gemm");
+  if (dtype == DP_F32 && !simple && dp::gemm_f32_supported(a))
+    return op_done(dp::launch_gemm_f32(a, (hipStream_t)hip_stream), "gemm");
   return op_done(dp::launch_gemm_simple(dtype, a, (hipStream_t)hip_stream), "gemm");
 }
 

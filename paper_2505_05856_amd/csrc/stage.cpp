@@ -610,6 +610,7 @@ struct Walk {
       a.C2 = gelu_out;
       a.gelu_kind = c.gelu;
       if (c.dtype == DP_BF16 && st->use_mfma && dp::gemm_mfma_supported(a)) check(dp::launch_gemm_mfma(a, cs));
+      else if (c.dtype == DP_F32 && st->use_mfma && dp::gemm_f32_supported(a)) check(dp::launch_gemm_f32(a, cs));
       else check(dp::launch_gemm_simple(c.dtype, a, cs));
     }
     prof_end();

@@ -162,6 +162,30 @@ def test_gemm_ragged_k(mode, M, N, K):
     assert O.max_rel_err(host(c8), ref + res) < TOL[dt]
 
 
+# fp32 on the matrix cores: ragged against the 32- and 64-row parts and the 16-deep chunks, both waves' arrangements
+# (64x64 and 32x32 tiles with a divided contraction; 128x128 TN tiles), fewer chunks than waves, rows of 4
+GEMM_F32 = [(0, 4, 4, 4), (0, 33, 36, 20), (0, 65, 132, 68), (0, 1000, 516, 332), (0, 700, 1100, 1028), (1, 4, 4, 4),
+            (1, 36, 20, 5), (1, 68, 132, 67), (1, 516, 1000, 333), (1, 1412, 1524, 129), (1, 1600, 1604, 31)]
+
+
+@pytest.mark.parametrize("mode,M,N,K", GEMM_F32)
+def test_gemm_f32(mode, M, N, K):
+    dt = torch.float32
+    a = rnd((M, K), 45, dt); b = rnd((K, N), 46, dt)
+    bias = rnd((N,), 47, dt); res = rnd((M, N), 48, dt)
+    ref = a.astype(np.float64) @ b.astype(np.float64)
+    ta, tb = (dev(a, dt), dev(b.T, dt)) if mode == 0 else (dev(a.T, dt), dev(b, dt))
+    c = torch.full((M, N), float("nan"), dtype=dt, device=DEV)
+    tol = 2 * (K + 2) ** 0.5 * 2.0 ** -24     # K roundings of random sign, relative to the largest result
+    B.op_gemm(mode, M, N, K, ta, tb, None, None, c)
+    assert O.max_rel_err(host(c), ref) < tol
+    B.op_gemm(mode, M, N, K, ta, tb, dev(bias, dt), dev(res, dt), c)
+    assert O.max_rel_err(host(c), ref + bias + res) < tol
+    c = dev(res, dt)
+    B.op_gemm(mode, M, N, K, ta, tb, None, c, c)
+    assert O.max_rel_err(host(c), ref + res) < tol
+
+
 ATTN_SHAPES = [(1, 8, 1, 8), (2, 5, 2, 16), (2, 64, 2, 64), (1, 200, 3, 64), (2, 96, 2, 128), (1, 384, 2, 64),
                (1, 1024, 3, 64), (1, 2048, 2, 128)]     # the last two: sequence and head width of C3/C4 and of C5
 

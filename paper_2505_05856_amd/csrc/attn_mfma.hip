@@ -248,8 +248,9 @@ struct BothAddr {
 // ------------------------------------------------------------------ forward
 // DROP: the probabilities are masked after the softmax (the row sums and the log-sum-exp are
 // those of the plain softmax); the scale 1/(1-p) goes into the final normalisation.
-template <int DH, bool CAUSAL, bool DROP>
-__global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnView av, bf16 *__restrict__ o,
+// WPE: waves a SIMD (= workgroups a CU) the registers are cut for.
+template <int DH, bool CAUSAL, bool DROP, int WPE>
+__global__ __launch_bounds__(256, WPE) void attn_fwd_mfma_kernel(AttnView av, bf16 *__restrict__ o,
                                                                float *__restrict__ lse, int nh, float scale,
                                                                DropArgs da) {
   constexpr int ND = DH / 32, NK = DH / 16;
@@ -320,34 +321,40 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnView av, bf16
   // and the reference point for tile t+1 (with the rescaling of the accumulators if it has to follow
   // the maximum) at the head of the next tile.  Every step reads the operand fragments of the step after it;
   // scheduling fences keep the steps in this order; the code of a tile has no branch inside a
-  // stage (MORE = a next tile exists).  (A wave whose queries see no key of the block's last tile
-  // runs it all the same, every logit masked: it would wait for the other waves at the tile
-  // barrier anyway.)
+  // stage.  What differs between tiles is known when it is compiled: whether a next tile exists
+  // (MORE), whether that one can hold hidden keys (MASK; decided when the kernel runs, the masking is
+  // turned into 60 compares and selects of every tile), and the parity of t (PAR), which says in which
+  // buffers the tiles lie and which of the two logit sets is the current one, so that neither
+  // addresses nor logits move between tiles.  Vector instructions per tile of 64 keys at head
+  // dimension 128, beside 32 MFMAs: 152, where there were 253.
+  // (A wave whose queries see no key of the block's last tile runs it all the same, every logit
+  // masked: it would wait for the other waves at the tile barrier anyway.)
   bf16x8 fx[2];                  // fragment double buffer
   auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
-  auto ld_k = [&](int slot, int sub, int kd) { fx[slot] = at.rows(0u, sub * 32, kd); };
-  auto ld_v = [&](int slot, int sub, int j) { fx[slot] = at.cols(VOFF, sub * 32 + (j / ND) * 16, j % ND); };
+  auto ld_k = [&](unsigned buf, int slot, int sub, int kd) { fx[slot] = at.rows(buf, sub * 32, kd); };
+  auto ld_v = [&](unsigned buf, int slot, int sub, int j) { fx[slot] = at.cols(buf, sub * 32 + (j / ND) * 16, j % ND); };
   auto zero = [](f32x16 &v) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = 0.f;
   };
-  // keys past the end and keys the causal mask hides, on the tiles that have any: -inf, P = 0
+  // keys past the end and keys the causal mask hides: -inf, P = 0
   auto mask = [&](f32x16 (&sv)[2], int j0) {
-    if (j0 + BKV > S || (CAUSAL && j0 + BKV - 1 > iw0)) {
 #pragma unroll
-      for (int sub = 0; sub < 2; ++sub) {
-        const int lim = (CAUSAL ? min(S, qi + 1) : S) - j0 - 32 * sub - 4 * hh;   // the lane's first hidden row
+    for (int sub = 0; sub < 2; ++sub) {
+      const int lim = (CAUSAL ? min(S, qi + 1) : S) - j0 - 32 * sub - 4 * hh;   // the lane's first hidden row
 #pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (8 * (e >> 2) + (e & 3) >= lim) sv[sub][e] = -INFINITY;
-      }
+      for (int e = 0; e < 16; ++e)
+        if (8 * (e >> 2) + (e & 3) >= lim) sv[sub][e] = -INFINITY;
     }
   };
-  f32x16 cur[2], nxt[2];   // raw logits of tile t, of tile t+1
+  f32x16 lg[2][2];         // raw logits: those of tile t in lg[t & 1]
   float mx = -INFINITY;    // maximum over the raw logits of the tile about to be worked on (this lane's keys)
 
-  auto tile = [&](int t, auto more_tag) {
-    constexpr bool MORE = decltype(more_tag)::value;
+  auto tile = [&](int t, auto par_tag, auto more_tag, auto mask_tag) {
+    constexpr int PAR = decltype(par_tag)::value;
+    constexpr bool MORE = decltype(more_tag)::value, MASK = decltype(mask_tag)::value;
+    constexpr unsigned KN = (PAR ^ 1) * TILE, V = VOFF + PAR * TILE;   // K of tile t+1, V of tile t
+    f32x16 (&cur)[2] = lg[PAR], (&nxt)[2] = lg[PAR ^ 1];
     const int j0 = t * BKV;
     mx = halves_max(mx);
     const float m_new = fmaxf(m, mx * c);   // (the scale c > 0 is folded into the exponent below)
@@ -384,31 +391,31 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnView av, bf16
       for (int u = 0; u < n; ++u) mx = fmaxf(mx, sv[e0 + u]);
     };
     // stages 1 and 2: NK steps of two MFMAs, 16 / NK elements of P_A a step
-    if (MORE) { zero(nxt[0]); zero(nxt[1]); ld_k(0, 0, 0); ld_k(1, 1, 0); }
+    if (MORE) { zero(nxt[0]); zero(nxt[1]); ld_k(KN, 0, 0, 0); ld_k(KN, 1, 1, 0); }
 #pragma unroll
     for (int kd = 0; kd < NK; ++kd) {
       if (MORE) {
         // one request a step for the tiles on their way: K of tile t+2, then V of tile t+1 (every
         // wave left the buffers they go to at the barrier that ended the last tile); a burst of
         // them at the head of the tile would hold the wave at the issue of each
-        if (kd < NK / 2) dma_req_both<DH>(kd, (unsigned)(t & 1) * TILE, kb, ldb, (t + 2) * BKV, S, wave, lane);
-        else dma_req_both<DH>(kd - NK / 2, VOFF + (unsigned)((t + 1) & 1) * TILE, vb, ldb, (t + 1) * BKV, S, wave, lane);
+        if (kd < NK / 2) dma_req_both<DH>(kd, PAR * TILE, kb, ldb, (t + 2) * BKV, S, wave, lane);
+        else dma_req_both<DH>(kd - NK / 2, VOFF + (PAR ^ 1) * TILE, vb, ldb, (t + 1) * BKV, S, wave, lane);
         const bf16x8 ka = fx[0], kb2 = fx[1];
-        if (kd + 1 < NK) { ld_k(0, 0, kd + 1); ld_k(1, 1, kd + 1); }
+        if (kd + 1 < NK) { ld_k(KN, 0, 0, kd + 1); ld_k(KN, 1, 1, kd + 1); }
         nxt[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[kd], nxt[0], 0, 0, 0);
         nxt[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb2, qf[kd], nxt[1], 0, 0, 0);
       }
-      if (kd + 1 == NK) ld_v(0, 0, 0);   // the first fragment of stage 3
+      if (kd + 1 == NK) ld_v(V, 0, 0, 0);   // the first fragment of stage 3
       soft(cur[0], 0, kd * (16 / NK), 16 / NK);
       fence();
     }
-    if (MORE) mask(nxt, j0 + BKV);
+    if (MORE && MASK) mask(nxt, j0 + BKV);
     bf16x8 pf[2];
     pf[0] = pack8(cur[0], 0); pf[1] = pack8(cur[0], 8);
     // stage 3: NK steps of one MFMA; 8 / NK elements of P_B and 16 / NK of the next maximum a step
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
-      if (j + 1 < NK) ld_v((j + 1) & 1, 0, j + 1); else ld_v((j + 1) & 1, 1, 0);
+      if (j + 1 < NK) ld_v(V, (j + 1) & 1, 0, j + 1); else ld_v(V, (j + 1) & 1, 1, 0);
       acc[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[j & 1], pf[j / ND], acc[j % ND], 0, 0, 0);
       if ((j * 8) % NK == 0) soft(cur[1], 1, j * 8 / NK, 8 / NK >= 1 ? 8 / NK : 1);
       if (MORE) vmax(nxt[0], j * (16 / NK), 16 / NK);
@@ -418,7 +425,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnView av, bf16
     // stage 4: the second half of P_B within the first half of the stage, then the rest of the maximum
 #pragma unroll
     for (int j = 0; j < NK; ++j) {
-      if (j + 1 < NK) ld_v((j + 1) & 1, 1, j + 1);
+      if (j + 1 < NK) ld_v(V, (j + 1) & 1, 1, j + 1);
       if (j == ND) pf[1] = pack8(cur[1], 8);
       acc[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[j & 1], pf[j / ND], acc[j % ND], 0, 0, 0);
       if (j < ND) soft(cur[1], 1, 8 + j * (8 / ND), 8 / ND);
@@ -426,26 +433,42 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(AttnView av, bf16
       fence();
     }
     l += ps;
-    if (MORE) { cur[0] = nxt[0]; cur[1] = nxt[1]; }
-    at.flip(TILE);
     wait_dma();        // this wave's parts of the tiles on their way are in
     __syncthreads();   // everyone's are, and everyone is done with this tile's
   };
 
+  // tiles of this index and beyond can hold keys past the end or (the block's queries start at q0) behind the diagonal
+  const int first_masked = CAUSAL ? min(S, q0) / BKV : S / BKV;
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  using Yes = std::true_type;
+  using No = std::false_type;
   if (nkv > 0) {   // the logits of tile 0 and their maximum
-    zero(cur[0]); zero(cur[1]);
+    zero(lg[0][0]); zero(lg[0][1]);
 #pragma unroll
     for (int kd = 0; kd < NK; ++kd) {
-      cur[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.rows(0u, 0, kd), qf[kd], cur[0], 0, 0, 0);
-      cur[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.rows(0u, 32, kd), qf[kd], cur[1], 0, 0, 0);
+      lg[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.rows(0u, 0, kd), qf[kd], lg[0][0], 0, 0, 0);
+      lg[0][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at.rows(0u, 32, kd), qf[kd], lg[0][1], 0, 0, 0);
     }
-    mask(cur, 0);
+    if (first_masked == 0) mask(lg[0], 0);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, fmaxf(cur[0][e], cur[1][e]));
-    at.flip_rows(TILE);   // the K fragments run one tile ahead of the V fragments
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, fmaxf(lg[0][0][e], lg[0][1][e]));
+    int t = 0;
+    for (; t + 2 < min(nkv, first_masked); t += 2) {
+      tile(t, P0{}, Yes{}, No{});
+      tile(t + 1, P1{}, Yes{}, No{});
+    }
+    for (; t + 2 < nkv; t += 2) {
+      tile(t, P0{}, Yes{}, Yes{});
+      tile(t + 1, P1{}, Yes{}, Yes{});
+    }
+    if (t + 1 < nkv) {
+      tile(t, P0{}, Yes{}, Yes{});
+      tile(t + 1, P1{}, No{}, No{});
+    } else {
+      tile(t, P0{}, No{}, No{});
+    }
   }
-  for (int t = 0; t + 1 < nkv; ++t) tile(t, std::true_type{});
-  if (nkv > 0) tile(nkv - 1, std::false_type{});
 
   l += __shfl_xor(l, 32, 64);
   if (lse != nullptr && hh == 0 && qi < Sq) lse[((long)b * nh + h) * Sq + qi] = (m + __log2f(l)) * kLn2;
@@ -461,28 +484,39 @@ hipError_t set_smem(K kern, size_t smem) {
                              (int)smem);
 }
 
-template <int DH>
-hipError_t fwd_launch(int B, int nh, int causal, const AttnView &av, void *o, float *lse, const DropArgs *drop,
-                      hipStream_t s) {
+template <int DH, bool CAUSAL, bool DROP, int WPE>
+hipError_t fwd_go(int blocks, const AttnView &av, void *o, float *lse, int nh, float scale, const DropArgs &da, hipStream_t s) {
   constexpr size_t smem = 2 * 2 * (size_t)BKV * DH * sizeof(bf16);   // two stages of a K and a V tile
+  auto kern = attn_fwd_mfma_kernel<DH, CAUSAL, DROP, WPE>;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = set_smem(attn_fwd_mfma_kernel<DH, true, false>, smem);
-    if (e == hipSuccess) e = set_smem(attn_fwd_mfma_kernel<DH, false, false>, smem);
-    if (e == hipSuccess) e = set_smem(attn_fwd_mfma_kernel<DH, true, true>, smem);
-    if (e == hipSuccess) e = set_smem(attn_fwd_mfma_kernel<DH, false, true>, smem);
+    const hipError_t e = set_smem(kern, smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  const dim3 grid(((av.Sq + BROWS - 1) / BROWS) * nh * B), block(256);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, av, (bf16 *)o, lse, nh, scale, da);
+  return hipGetLastError();
+}
+
+template <int DH>
+hipError_t fwd_launch(int B, int nh, int causal, const AttnView &av, void *o, float *lse, const DropArgs *drop,
+                      hipStream_t s) {
+  const int blocks = ((av.Sq + BROWS - 1) / BROWS) * nh * B;
   const float scale = 1.0f / sqrtf((float)DH);
   const bool dropping = drop != nullptr && drop->thr != 0;
   const DropArgs da = dropping ? *drop : DropArgs{0u, 0u, 1.f};
-#define DP_FWD(KERN) hipLaunchKernelGGL(KERN, grid, block, smem, s, av, (bf16 *)o, lse, nh, scale, da)
-  if (dropping) { if (causal) DP_FWD((attn_fwd_mfma_kernel<DH, true, true>)); else DP_FWD((attn_fwd_mfma_kernel<DH, false, true>)); }
-  else { if (causal) DP_FWD((attn_fwd_mfma_kernel<DH, true, false>)); else DP_FWD((attn_fwd_mfma_kernel<DH, false, false>)); }
+  // Head dimension 64: the kernel wants 180 registers, two workgroups a CU; cut to 168 (a dozen spilled outside the
+  // tile loop) three fit.  With more workgroups than two a CU the third pays (batch 4, sequence 1024, 25 heads,
+  // causal, 800 of them: 32.9 us with three a CU, 34.0 with two), otherwise it costs (batch 8, sequence 512, 16
+  // heads, 512 of them: 15.3 and 14.3; batch 3, sequence 709, 12 heads, 216: 12.0 and 11.6).
+  constexpr int kCus = 256;
+  const bool three = DH == 64 && blocks > 2 * kCus;
+#define DP_FWD(CAUSAL, DROP)                                                                           \
+  return three ? fwd_go<DH, CAUSAL, DROP, DH == 64 ? 3 : 2>(blocks, av, o, lse, nh, scale, da, s)       \
+               : fwd_go<DH, CAUSAL, DROP, 2>(blocks, av, o, lse, nh, scale, da, s)
+  if (dropping) { if (causal) DP_FWD(true, true); else DP_FWD(false, true); }
+  if (causal) DP_FWD(true, false); else DP_FWD(false, false);
 #undef DP_FWD
-  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ backward

@@ -224,6 +224,26 @@ def test_attention(dt, causal, Bn, S, nh, dh, sharp):
         assert O.max_rel_err(got[:, blk * H:(blk + 1) * H], dq_ref[:, blk * H:(blk + 1) * H]) < 2 * tol, blk
 
 
+# the forward's tile loop: one tile, two, odd and even counts, tiles that end on and just past a boundary, with none, some and
+# all of them masked; the last shape has more than two workgroups a CU
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Bn,S,nh,dh", [(1, s, 2, dh) for dh in (64, 128) for s in (1, 63, 64, 65, 128, 129, 192, 193, 256, 257, 321)]
+                         + [(9, 257, 30, 64)])
+def test_attention_fwd_tiles(Bn, S, nh, dh, causal):
+    dt = torch.bfloat16
+    H = nh * dh
+    qkv = rnd((Bn * S, 3 * H), 53, dt)
+    qkv[:, :H] *= 3.0     # a maximum that moves between tiles
+    qkv = syn.round_to_bf16(qkv)
+    o_ref, lse_ref = O.attention_fwd(qkv.astype(np.float64), Bn, S, nh, causal)
+    o = torch.full((Bn * S, H), float("nan"), dtype=dt, device=DEV)
+    lse = torch.full((Bn, nh, S), float("nan"), dtype=torch.float32, device=DEV)
+    B.op_attention_fwd(dev(qkv, dt), Bn, S, nh, dh, causal, o, lse)
+    assert O.max_rel_err(host(o), o_ref) < 2 * TOL[dt]     # (P is rounded to bf16 as well)
+    assert np.allclose(host(lse), lse_ref, atol=2e-3)
+
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("dh", [64, 128])
 def test_attention_with_a_maximum_that_creeps_and_then_jumps(dt, dh):

@@ -576,7 +576,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
   // The scalar is asked for with the tile and first touched when it is stored, a tile later: a use any
   // earlier would make the wave wait there for every load in flight, the tile's own among them.
   const float *fsrc = (wave & 1) ? drw : lrow;
-  const float fmul = (wave & 1) ? 1.f : kLog2e;
+  const float fmul = (wave & 1) ? (DROP ? 1.f : -1.f) : kLog2e;   // (without dropout dP starts at -D, see below)
   const float fpad = (wave & 1) ? 0.f : INFINITY;   // +inf: P = 0 for padding rows
   float sl = 0.f;
   auto fetch = [&](int t, unsigned buf) {
@@ -620,30 +620,62 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
     fy[slot] = at.cols(0u, sub * 32 + (j / ND) * 16, j % ND);
   };
   auto fence = [] { __builtin_amdgcn_sched_barrier(0); };
-  // The two scalars of the queries a softmax step works on come from LDS one step ahead as well:
-  // softmax step q of a tile (q < NK: sub-tile A, else B) finds them in slot q % 2.
+  // Everything read from LDS before the last N reads is in: one wait a step, for all its operands (left alone, the
+  // compiler waits before each of the step's first uses).  For head dimension 128, where a wave is alone on its SIMD:
+  // backward of batch 8, sequence 2048, 32 heads 1147 -> 1127 us causal, 1834 -> 1776 full; with two waves a SIMD
+  // (head dimension 64) the fences cost more than the waits (85.0 -> 86.8 us at batch 4, sequence 1024, 25 heads).
+  auto reads_in = [](auto n_tag) {
+    if (DH != 128) return;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0xc07f | (decltype(n_tag)::value << 8));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using R0 = std::integral_constant<int, 0>; using R2 = std::integral_constant<int, 2>;
+  using R4 = std::integral_constant<int, 4>; using R6 = std::integral_constant<int, 6>;
+  constexpr int NSC = DROP ? 2 : 1;   // reads of ld_soft
+  using RS = std::integral_constant<int, 2 + NSC>; using CS = std::integral_constant<int, 4 + NSC>;
+  // The log-sum-exps (and under dropout the row dots) of the queries a softmax step works on come from LDS
+  // one step ahead as well: softmax step q of a tile (q < NK: sub-tile A, else B) finds them in slot q % 2.
+  // Without dropout dS = P (dP - D), and the accumulators of dP start at -D: no subtraction, and the row
+  // dots come as four 16-byte reads a sub-tile (a wave has the SIMD to itself at head dimension 128, so every
+  // instruction beside an MFMA costs its four clocks: 434 of them and 64 MFMAs of 32 clocks made the 3800 clocks
+  // a tile measured; 382 now).  With the two-workgroup form of head dimension 64 it saves 3-7 % of the backward
+  // (1 x 2048 x 8 heads causal 68.9 -> 64.1 us, 4 x 1024 x 25 heads 88.3 -> 85.3).
   const float *lds_f = reinterpret_cast<const float *>(smem_b + FBASE);   // the current tile's scalars
   float lsc[2][EPS], dsc[2][EPS];
   auto ld_soft = [&](int q) {
     const int e0 = (q % NK) * EPS, r0 = (q / NK) * 32 + 8 * (e0 >> 2) + 4 * hh + (e0 & 3);
-    if constexpr (EPS == 4) {
-      const float4 l4 = *reinterpret_cast<const float4 *>(lds_f + r0), d4 = *reinterpret_cast<const float4 *>(lds_f + BKV + r0);
-      lsc[q & 1][0] = l4.x; lsc[q & 1][1] = l4.y; lsc[q & 1][2] = l4.z; lsc[q & 1][3] = l4.w;
-      dsc[q & 1][0] = d4.x; dsc[q & 1][1] = d4.y; dsc[q & 1][2] = d4.z; dsc[q & 1][3] = d4.w;
-    } else {
-      const float2 l2 = *reinterpret_cast<const float2 *>(lds_f + r0), d2 = *reinterpret_cast<const float2 *>(lds_f + BKV + r0);
-      lsc[q & 1][0] = l2.x; lsc[q & 1][1] = l2.y; dsc[q & 1][0] = d2.x; dsc[q & 1][1] = d2.y;
+    typedef float vec __attribute__((ext_vector_type(EPS)));
+    const vec l = *reinterpret_cast<const vec *>(lds_f + r0);
+#pragma unroll
+    for (int u = 0; u < EPS; ++u) lsc[q & 1][u] = l[u];
+    if (DROP) {
+      const vec d = *reinterpret_cast<const vec *>(lds_f + BKV + r0);
+#pragma unroll
+      for (int u = 0; u < EPS; ++u) dsc[q & 1][u] = d[u];
     }
   };
-  f32x16 sA, dpA;
+  auto dp_start = [&](f32x16 &v, const float *scalars, int sub) {   // of sub-tile `sub` of the tile with these scalars
+#pragma unroll
+    for (int e4 = 0; e4 < 4; ++e4) {
+      f32x4 d = {0.f, 0.f, 0.f, 0.f};
+      if (!DROP) d = *reinterpret_cast<const f32x4 *>(scalars + BKV + sub * 32 + 8 * e4 + 4 * hh);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[4 * e4 + u] = d[u];
+    }
+  };
+  f32x16 sA, dpA, dpB;
   auto logits_of_a = [&] {   // stage 4 (and the prologue); leaves the first fragments and scalars of stage 1 in flight
     ld_rows(0, 0, 0);
+    dp_start(dpA, lds_f, 0);
     ld_soft(0);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { sA[e] = 0.f; dpA[e] = 0.f; }
+    for (int e = 0; e < 16; ++e) sA[e] = 0.f;
 #pragma unroll
     for (int kd = 0; kd < NK; ++kd) {
       if (kd + 1 < NK) ld_rows((kd + 1) & 1, 0, kd + 1); else ld_rows((kd + 1) & 1, 1, 0);
+      if (kd == NK - 2) dp_start(dpB, lds_f, 1);
+      if (kd == 0) reads_in(RS{}); else if (kd == NK - 2 && !DROP) reads_in(R6{}); else reads_in(R2{});
       sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kd & 1], kf[kd], sA, 0, 0, 0);
       dpA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[kd & 1], vf[kd], dpA, 0, 0, 0);
       fence();
@@ -662,15 +694,15 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
 #pragma unroll
       for (int u = 0; u < EPS; ++u) {
         const int e = e0 + u, i = i0 + r0 + u;
-        const float l = lsc[q & 1][u], dd = dsc[q & 1][u];
+        const float l = lsc[q & 1][u];
         const float pr = fast_exp2(sv[e] * c - l);   // (rows past the end carry lse = +inf: p = 0 by itself)
         if (DROP) {
           const bool keep = drop_bits((uint32_t)i * (uint32_t)Sk + (uint32_t)kj, keys.k0, keys.k1) >= da.thr;
           sv[e] = keep ? pr * da.scale : 0.f;
-          dpv[e] = pr * ((keep ? dpv[e] * da.scale : 0.f) - dd);
+          dpv[e] = pr * ((keep ? dpv[e] * da.scale : 0.f) - dsc[q & 1][u]);
         } else {
           sv[e] = pr;
-          dpv[e] = pr * (dpv[e] - dd);
+          dpv[e] *= pr;
         }
       }
     };
@@ -682,14 +714,15 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
           if (kj > i0 + sub * 32 + acc_row(e, lane)) sv[e] = -INFINITY;
       }
     };
-    f32x16 sB, dpB;
+    f32x16 sB;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { sB[e] = 0.f; dpB[e] = 0.f; }
+    for (int e = 0; e < 16; ++e) sB[e] = 0.f;
     mask(sA, 0);
 #pragma unroll
     for (int kd = 0; kd < NK; ++kd) {   // stage 1
       if (kd + 1 < NK) ld_rows((kd + 1) & 1, 1, kd + 1); else ld_cols((kd + 1) & 1, 0, 0);
       ld_soft(kd + 1);
+      if (kd + 1 < NK) reads_in(RS{}); else reads_in(CS{});
       sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kd & 1], kf[kd], sB, 0, 0, 0);
       dpB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[kd & 1], vf[kd], dpB, 0, 0, 0);
       soft(sA, dpA, kd);
@@ -702,6 +735,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
     for (int j = 0; j < NK; ++j) {      // stage 2
       if (j + 1 < NK) ld_cols((j + 1) & 1, 0, j + 1); else ld_cols((j + 1) & 1, 1, 0);
       if (j + 1 < NK) ld_soft(NK + j + 1);
+      if (j + 1 < NK) reads_in(CS{}); else reads_in(R4{});
       dv[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[j & 1], pf[j / ND], dv[j % ND], 0, 0, 0);
       dk[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[j & 1], dsf[j / ND], dk[j % ND], 0, 0, 0);
       soft(sB, dpB, NK + j);
@@ -711,6 +745,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
 #pragma unroll
     for (int j = 0; j < NK; ++j) {      // stage 3
       if (j + 1 < NK) ld_cols((j + 1) & 1, 1, j + 1);
+      if (j + 1 < NK) reads_in(R4{}); else reads_in(R0{});
       dv[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[j & 1], pf[j / ND], dv[j % ND], 0, 0, 0);
       dk[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[j & 1], dsf[j / ND], dk[j % ND], 0, 0, 0);
       fence();

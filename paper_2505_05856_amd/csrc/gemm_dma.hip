@@ -235,8 +235,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   using No = std::false_type;
   // MFMAs of the slice held in buffer USE (if MUL), beside the reads of slice ks of the tiles at
   // base_a, base_b into the other buffer (if READ) and the requests R0 .. R1-1 of the pass: first the B
-  // tile's (to LDS byte to_b), then the A tile's (to to_a).  Request r goes out between MFMAs
-  // req_at(r) and req_at(r) + 1, its M0 is written before MFMA req_at(r).
+  // tile's (to LDS byte to_b), then the A tile's (to to_a).  Request r of NREQ goes out behind MFMA
+  // (2 r + 1) MF / (2 NREQ), its M0 is written before that MFMA.
   auto slice = [&](auto use_tag, auto mul_tag, auto read_tag, unsigned base_a, unsigned base_b, int ks, auto r0_tag,
                    auto r1_tag, auto nb_tag, unsigned to_b, unsigned to_a) DP_INLINE {
     constexpr int USE = decltype(use_tag)::value, R0 = decltype(r0_tag)::value, R1 = decltype(r1_tag)::value;

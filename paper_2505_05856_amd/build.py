@@ -39,12 +39,17 @@ EXTRA_FLAGS = {"attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inlin
 M0_BY_HAND = {"gemm_dma.hip", "attn_mfma.hip"}
 
 
-def _check_m0(src: str) -> None:
-    asm = os.path.join(OBJ, os.path.splitext(src)[0] + ".s")
+def device_asm(src: str, asm: str) -> None:
+    """The device assembly of one source, as the library's build compiles it, written to the file `asm`."""
     cmd = [HIPCC, *FLAGS, *EXTRA_FLAGS.get(src, []), "-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", asm]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc -S failed for {src}:\n{r.stderr}")
+
+
+def _check_m0(src: str) -> None:
+    asm = os.path.join(OBJ, os.path.splitext(src)[0] + ".s")
+    device_asm(src, asm)
     inside = False
     with open(asm) as f:
         for n, line in enumerate(f, 1):

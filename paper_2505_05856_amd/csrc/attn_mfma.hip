@@ -396,8 +396,9 @@ __global__ __launch_bounds__(256, WPE) void attn_fwd_mfma_kernel(AttnView av, bf
     for (int kd = 0; kd < NK; ++kd) {
       if (MORE) {
         // one request a step for the tiles on their way: K of tile t+2, then V of tile t+1 (every
-        // wave left the buffers they go to at the barrier that ended the last tile); a burst of
-        // them at the head of the tile would hold the wave at the issue of each
+        // wave left the buffers they go to at the barrier that ended the last tile, or, before tile 0,
+        // at the one behind its logits); a burst of them at the head of the tile would hold the wave
+        // at the issue of each
         if (kd < NK / 2) dma_req_both<DH>(kd, PAR * TILE, kb, ldb, (t + 2) * BKV, S, wave, lane);
         else dma_req_both<DH>(kd - NK / 2, VOFF + (PAR ^ 1) * TILE, vb, ldb, (t + 1) * BKV, S, wave, lane);
         const bf16x8 ka = fx[0], kb2 = fx[1];
@@ -453,6 +454,7 @@ __global__ __launch_bounds__(256, WPE) void attn_fwd_mfma_kernel(AttnView av, bf
     if (first_masked == 0) mask(lg[0], 0);
 #pragma unroll
     for (int e = 0; e < 16; ++e) mx = fmaxf(mx, fmaxf(lg[0][0][e], lg[0][1][e]));
+    __syncthreads();   // everyone has read K tile 0: the first tile below refills its buffer with K tile 2
     int t = 0;
     for (; t + 2 < min(nkv, first_masked); t += 2) {
       tile(t, P0{}, Yes{}, No{});

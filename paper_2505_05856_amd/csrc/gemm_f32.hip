@@ -167,13 +167,20 @@ bool gemm_f32_supported(const GemmArgs &a) {
 //   [1024 x 1024] x 1024 NT: 256 tiles of 64x64 23.6 us (91 TFLOP/s of the 147 the instruction reaches alone),
 //   1024 of 32x32 37.0.
 // TN with enough tiles of 128x128 for half the chip: a wave each 64x64, no division ([1024 x 4096] x 4096: 257 us
-// against 311; in NT form, whose loads take 16 rows at a time, the division stays ahead: [4096 x 4096] x 1024 352
-// against 505).  The vector-ALU kernel takes 52, 139, 168, 769 and 545 us for these, and 20 to 70 us where these
-// kernels take under 7 ([128 x 128..512] x 128..512, the products of a stage 128 wide).
+// against 311).  In NT form, whose loads take 16 rows at a time, the division stays ahead ([4096 x 4096] x 1024 352
+// against 505) but for contractions of at most four chunks, which leave its waves one each at most to share the turn
+// of the output through LDS over: [7588 x 3192] x 8, 24, 40, 64: 35.6, 43.8, 58.3, 65.4 us without it and 60.2, 71.6,
+// 78.8, 85.0 with it, [3076 x 1488] 11.0, 13.8, 19.1, 20.1 and 14.3, 17.1, 18.7, 19.6.
+// The vector-ALU kernel takes 52, 139, 168, 769 and 545 us for the products named so far with K > 64, 52.5 to 89.9 and
+// 13.9 to 22.4 us for the two of K <= 64, and 20 to 70 us where these kernels take under 7 ([128 x 128..512] x
+// 128..512, the products of a stage 128 wide).
 hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
   auto tiles = [&](int t) { return (long)((a.M + t - 1) / t) * ((a.N + t - 1) / t); };
+  if (tiles(128) >= 128) {
+    if (a.mode == kGemmTN) return launch_f32<4, 2, true, false>(a, s);
+    if (a.K <= 64) return launch_f32<4, 2, false, false>(a, s);
+  }
   if (a.mode == kGemmTN) {
-    if (tiles(128) >= 128) return launch_f32<4, 2, true, false>(a, s);
     return tiles(64) >= 128 ? launch_f32<4, 2, true, true>(a, s) : launch_f32<2, 4, true, true>(a, s);
   }
   return tiles(64) >= 128 ? launch_f32<4, 2, false, true>(a, s) : launch_f32<2, 4, false, true>(a, s);

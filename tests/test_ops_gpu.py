@@ -163,8 +163,9 @@ def test_gemm_ragged_k(mode, M, N, K):
 
 
 # fp32 on the matrix cores: ragged against the 32- and 64-row parts and the 16-deep chunks, both waves' arrangements
-# (64x64 and 32x32 tiles with a divided contraction; 128x128 TN tiles), fewer chunks than waves, rows of 4
+# (64x64 and 32x32 tiles with a divided contraction; 128x128 tiles, TN and short NT ones), fewer chunks than waves, rows of 4
 GEMM_F32 = [(0, 4, 4, 4), (0, 33, 36, 20), (0, 65, 132, 68), (0, 1000, 516, 332), (0, 700, 1100, 1028), (1, 4, 4, 4),
+            (0, 1413, 1524, 4), (0, 1601, 1604, 20), (0, 1500, 1412, 64), (0, 1500, 1412, 68),
             (1, 36, 20, 5), (1, 68, 132, 67), (1, 516, 1000, 333), (1, 1412, 1524, 129), (1, 1600, 1604, 31)]
 
 

@@ -222,15 +222,15 @@ struct BothAddr {
       col[1][d] = (rc + 8u) * ROWB + (((4u * d + cl) ^ swz_both<DH>(rc + 8u)) << 4) + (i & 1u) * 8u;
     }
   }
-  __device__ __forceinline__ void flip_rows(unsigned stage_bytes) {
-#pragma unroll
-    for (int kd = 0; kd < DH / 16; ++kd) row[kd] ^= stage_bytes;
-  }
   __device__ __forceinline__ void flip_cols(unsigned stage_bytes) {
 #pragma unroll
     for (int d = 0; d < DH / 32; ++d) { col[0][d] ^= stage_bytes; col[1][d] ^= stage_bytes; }
   }
-  __device__ __forceinline__ void flip(unsigned stage_bytes) { flip_rows(stage_bytes); flip_cols(stage_bytes); }
+  __device__ __forceinline__ void flip(unsigned stage_bytes) {
+#pragma unroll
+    for (int kd = 0; kd < DH / 16; ++kd) row[kd] ^= stage_bytes;
+    flip_cols(stage_bytes);
+  }
   // 32 rows from row0 (a multiple of 16) of the tile at byte `tile_off` of the stage, contraction elements 16 kd ..
   // (tile_off, row0, r0, kd, d: constants once the callers' loops are unrolled)
   __device__ __forceinline__ bf16x8 rows(unsigned tile_off, int row0, int kd) const {
@@ -464,12 +464,17 @@ __global__ __launch_bounds__(256, WPE) void attn_fwd_mfma_kernel(AttnView av, bf
       tile(t, P0{}, Yes{}, Yes{});
       tile(t + 1, P1{}, Yes{}, Yes{});
     }
+    // The last tile has one form, that of even t: an odd one is made to look even.  (With a form for each parity the
+    // accumulators met again behind the two in registers that did not fit: 9 to 20 registers a lane went to scratch
+    // memory at head dimension 128.  A launch of one key tile, 26 heads: 5.8 -> 5.6 us, under dropout 7.0 -> 6.3; batch 4,
+    // sequence 1024, 25 heads of 64, causal, in the form for three workgroups a CU: 32.4 -> 30.7.)
     if (t + 1 < nkv) {
       tile(t, P0{}, Yes{}, Yes{});
-      tile(t + 1, P1{}, No{}, No{});
-    } else {
-      tile(t, P0{}, No{}, No{});
+      lg[0][0] = lg[1][0]; lg[0][1] = lg[1][1];
+      at.flip_cols(TILE);
+      ++t;
     }
+    tile(t, P0{}, No{}, No{});
   }
 
   l += __shfl_xor(l, 32, 64);
@@ -507,10 +512,11 @@ hipError_t fwd_launch(int B, int nh, int causal, const AttnView &av, void *o, fl
   const float scale = 1.0f / sqrtf((float)DH);
   const bool dropping = drop != nullptr && drop->thr != 0;
   const DropArgs da = dropping ? *drop : DropArgs{0u, 0u, 1.f};
-  // Head dimension 64: the kernel wants 180 registers, two workgroups a CU; cut to 168 (a dozen spilled outside the
-  // tile loop) three fit.  With more workgroups than two a CU the third pays (batch 4, sequence 1024, 25 heads,
-  // causal, 800 of them: 32.9 us with three a CU, 34.0 with two), otherwise it costs (batch 8, sequence 512, 16
-  // heads, 512 of them: 15.3 and 14.3; batch 3, sequence 709, 12 heads, 216: 12.0 and 11.6).
+  // Head dimension 64: the kernel wants 174 registers (186 under dropout), two workgroups a CU; cut to 168 (up to six of
+  // them spilled, outside the tile loops) three fit.  With more workgroups than two a CU the third pays (batch 4, sequence
+  // 1024, 25 heads, causal, 800 of them: 30.7 us with three a CU, 33.9 with two, under dropout 59.1 and 60.7; over 35 drawn
+  // shapes 5 % on average, over 34 under dropout 3 %), otherwise it costs (batch 5, sequence 140, 16 heads, 160 of them:
+  // 6.5 and 6.2, under dropout 8.9 and 8.6).
   constexpr int kCus = 256;
   const bool three = DH == 64 && blocks > 2 * kCus;
 #define DP_FWD(CAUSAL, DROP)                                                                           \

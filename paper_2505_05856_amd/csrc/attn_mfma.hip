@@ -631,17 +631,17 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
   // Everything read from LDS before the last N reads is in: one wait a step, for all its operands (left alone, the
   // compiler waits before each of the step's first uses).  For head dimension 128, where a wave is alone on its SIMD:
   // backward of batch 8, sequence 2048, 32 heads 1147 -> 1127 us causal, 1834 -> 1776 full; with two waves a SIMD
-  // (head dimension 64) the fences cost more than the waits (85.0 -> 86.8 us at batch 4, sequence 1024, 25 heads).
+  // (head dimension 64) the fences cost more than the waits (85.0 -> 86.8 us at batch 4, sequence 1024, 25 heads), and so
+  // they do under dropout, whose masks are most of a step (batch 8, sequence 1576, 12 heads, causal 383 -> 387 us).
   auto reads_in = [](auto n_tag) {
-    if (DH != 128) return;
+    if (DH != 128 || DROP) return;
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt(0xc07f | (decltype(n_tag)::value << 8));
     __builtin_amdgcn_sched_barrier(0);
   };
   using R0 = std::integral_constant<int, 0>; using R2 = std::integral_constant<int, 2>;
-  using R4 = std::integral_constant<int, 4>; using R6 = std::integral_constant<int, 6>;
-  constexpr int NSC = DROP ? 2 : 1;   // reads of ld_soft
-  using RS = std::integral_constant<int, 2 + NSC>; using CS = std::integral_constant<int, 4 + NSC>;
+  using R3 = std::integral_constant<int, 3>; using R4 = std::integral_constant<int, 4>;
+  using R5 = std::integral_constant<int, 5>; using R6 = std::integral_constant<int, 6>;
   // The log-sum-exps (and under dropout the row dots) of the queries a softmax step works on come from LDS
   // one step ahead as well: softmax step q of a tile (q < NK: sub-tile A, else B) finds them in slot q % 2.
   // Without dropout dS = P (dP - D), and the accumulators of dP start at -D: no subtraction, and the row
@@ -682,8 +682,8 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
 #pragma unroll
     for (int kd = 0; kd < NK; ++kd) {
       if (kd + 1 < NK) ld_rows((kd + 1) & 1, 0, kd + 1); else ld_rows((kd + 1) & 1, 1, 0);
-      if (kd == NK - 2) dp_start(dpB, lds_f, 1);
-      if (kd == 0) reads_in(RS{}); else if (kd == NK - 2 && !DROP) reads_in(R6{}); else reads_in(R2{});
+      if (!DROP && kd == NK - 2) dp_start(dpB, lds_f, 1);
+      if (kd == 0) reads_in(R3{}); else if (kd == NK - 2) reads_in(R6{}); else reads_in(R2{});
       sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kd & 1], kf[kd], sA, 0, 0, 0);
       dpA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[kd & 1], vf[kd], dpA, 0, 0, 0);
       fence();
@@ -725,12 +725,13 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
     f32x16 sB;
 #pragma unroll
     for (int e = 0; e < 16; ++e) sB[e] = 0.f;
+    if (DROP) dp_start(dpB, lds_f, 1);   // (zeros: not held over the barrier)
     mask(sA, 0);
 #pragma unroll
     for (int kd = 0; kd < NK; ++kd) {   // stage 1
       if (kd + 1 < NK) ld_rows((kd + 1) & 1, 1, kd + 1); else ld_cols((kd + 1) & 1, 0, 0);
       ld_soft(kd + 1);
-      if (kd + 1 < NK) reads_in(RS{}); else reads_in(CS{});
+      if (kd + 1 < NK) reads_in(R3{}); else reads_in(R5{});
       sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[kd & 1], kf[kd], sB, 0, 0, 0);
       dpB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[kd & 1], vf[kd], dpB, 0, 0, 0);
       soft(sA, dpA, kd);
@@ -743,7 +744,7 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
     for (int j = 0; j < NK; ++j) {      // stage 2
       if (j + 1 < NK) ld_cols((j + 1) & 1, 0, j + 1); else ld_cols((j + 1) & 1, 1, 0);
       if (j + 1 < NK) ld_soft(NK + j + 1);
-      if (j + 1 < NK) reads_in(CS{}); else reads_in(R4{});
+      if (j + 1 < NK) reads_in(R5{}); else reads_in(R4{});
       dv[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[j & 1], pf[j / ND], dv[j % ND], 0, 0, 0);
       dk[j % ND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fy[j & 1], dsf[j / ND], dk[j % ND], 0, 0, 0);
       soft(sB, dpB, NK + j);

@@ -92,15 +92,16 @@ def _compile(src: str) -> str:
         raise RuntimeError(f"hipcc failed for {src}:\n{err}")
     if err.strip():
         sys.stderr.write(err + "\n")
-    if src in M0_BY_HAND:
-        _check_m0(src)
     return obj
 
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        checks = [ex.submit(_check_m0, src) for src in SOURCES if src in M0_BY_HAND]
         objs = list(ex.map(_compile, SOURCES))
+        for check in checks:
+            check.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -56,6 +56,21 @@ template <int N, typename F> __device__ __forceinline__ void static_for(F &&f) {
 }
 template <int N> using Count = std::integral_constant<int, N>;
 
+// Where requests and fragment reads of a slice of `mfmas` MFMAs go: request r of n behind MFMA (2 r + 1) mfmas / (2 n),
+// read q of n behind MFMA 3/4 q mfmas / n.  Asked the other way round, by plain loops (the request behind MFMA g, or -1;
+// the first read behind MFMA g or later): a pack expansion over requests and reads inside the one over MFMAs made this
+// file take 2.5 minutes to compile.
+constexpr int request_at(int g, int mfmas, int n) {
+  for (int r = 0; r < n; ++r)
+    if ((2 * r + 1) * mfmas / (2 * n) == g) return r;
+  return -1;
+}
+constexpr int first_read(int g, int mfmas, int n) {
+  int q = 0;
+  while (q < n && q * mfmas * 3 / 4 / n < g) ++q;
+  return q;
+}
+
 constexpr int kMinK = 64;        // one whole k-step
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -270,20 +285,14 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
       });
     } else {
       static_for<MF>([&](auto g_tag) DP_INLINE {
-        constexpr int g = decltype(g_tag)::value;
-        static_for<NREQ>([&](auto r_tag) DP_INLINE {
-          if constexpr ((2 * decltype(r_tag)::value + 1) * MF / (2 * NREQ) == g) m0(r_tag);
-        });
+        constexpr int g = decltype(g_tag)::value, r = request_at(g, MF, NREQ);
+        constexpr int q0 = READ ? first_read(g, MF, NR) : 0, q1 = READ ? first_read(g + 1, MF, NR) : 0;
+        if constexpr (r >= 0) m0(Count<r>{});
         __builtin_amdgcn_sched_barrier(0);
         acc[g / FN][g % FN] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[USE][g % FN], a[USE][g / FN], acc[g / FN][g % FN], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        static_for<NREQ>([&](auto r_tag) DP_INLINE {
-          if constexpr ((2 * decltype(r_tag)::value + 1) * MF / (2 * NREQ) == g) ld(r_tag);
-        });
-        if constexpr (READ)
-          static_for<NR>([&](auto q_tag) DP_INLINE {
-            if constexpr (decltype(q_tag)::value * MF * 3 / 4 / NR == g) read(q_tag);
-          });
+        if constexpr (r >= 0) ld(Count<r>{});
+        static_for<q1 - q0>([&](auto q_tag) DP_INLINE { read(Count<q0 + decltype(q_tag)::value>{}); });
         __builtin_amdgcn_sched_barrier(0);
       });
     }

@@ -119,9 +119,6 @@ hipError_t launch_gemm_simple(int dtype, const GemmArgs &a, hipStream_t s);
 hipError_t launch_gemm_mfma(const GemmArgs &a, hipStream_t s);   // bf16 only
 bool gemm_f32_supported(const GemmArgs &a);             // fp32 on the matrix cores: whole 16-byte pieces of every row
 hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s);
-// fp32 operands on the matrix cores
-bool gemm_f32_supported(const GemmArgs &a);
-hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s);
 // kernels with LDS-direct operand loads; launch_gemm_mfma routes to them when the shape is supported
 bool gemm_dma_supported(const GemmArgs &a);
 hipError_t launch_gemm_dma(const GemmArgs &a, hipStream_t s);

@@ -544,6 +544,9 @@ dp_status dp_op_gelu_bwd(int32_t dtype, int32_t gelu_kind, int32_t rows, int32_t
  * (C += op(A)*op(B), how gradients are accumulated); no other overlap. */
 dp_status dp_op_gemm(int32_t dtype, int32_t mode, int32_t M, int32_t N, int32_t K, const void *A, const void *B,
                      const void *bias, const void *res, void *C, void *hip_stream);
+/* Diagnostic, no device work: the output tile a workgroup of dp_op_gemm takes for a bf16 product
+ * of these sizes (16-byte aligned operands); 0 x 0 where a kernel without that choice has it. */
+dp_status dp_op_gemm_tile(int32_t mode, int32_t M, int32_t N, int32_t K, int32_t *tile_m, int32_t *tile_n);
 /* out[cols] = sum over rows of x[rows, cols] */
 dp_status dp_op_colsum(int32_t dtype, int32_t rows, int32_t cols, const void *x, void *out, void *ws,
                        void *hip_stream);

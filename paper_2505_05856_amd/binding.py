@@ -156,6 +156,7 @@ def lib() -> C.CDLL:
     L.dp_op_gelu_fwd.argtypes = [i32, i32, sz, vp, vp, vp]
     L.dp_op_gelu_bwd.argtypes = [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp]
     L.dp_op_gemm.argtypes = [i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp]
+    L.dp_op_gemm_tile.argtypes = [i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
     L.dp_op_colsum.argtypes = [i32, i32, i32, vp, vp, vp, vp]
     L.dp_op_colsum_static.argtypes = [i32, i32, i32, vp, vp, vp]
     L.dp_op_attention_fwd.argtypes = [i32, i32, i32, i32, i32, i32, vp, vp, vp, vp]
@@ -175,7 +176,7 @@ def lib() -> C.CDLL:
     L.dp_stage_measure_cost_model.argtypes = [vp, vp, vp, vp, vp, C.POINTER(LayerPtrs), vp, i32, C.POINTER(CostModel)]
     for name in ("dp_probe_mfma", "dp_partition", "dp_plan_cost", "dp_plan_generate", "dp_stage_measure_cost_model", "dp_plan_validate", "dp_stage_init", "dp_stage_step", "dp_stage_forward", "dp_stage_backward", "dp_stage_set_weights", "dp_stage_set_rng", "dp_stage_set_cross", "dp_stage_bind_memory", "dp_stage_set_profiling",
                  "dp_stage_op_times", "dp_stage_op_flops", "dp_stage_set_debug", "dp_op_layernorm_fwd", "dp_op_layernorm_bwd",
-                 "dp_op_gelu_fwd", "dp_op_gelu_bwd", "dp_op_gemm", "dp_op_colsum", "dp_op_colsum_static", "dp_op_attention_fwd",
+                 "dp_op_gelu_fwd", "dp_op_gelu_bwd", "dp_op_gemm", "dp_op_gemm_tile", "dp_op_colsum", "dp_op_colsum_static", "dp_op_attention_fwd",
                  "dp_op_attention_bwd", "dp_op_dropout", "dp_op_attention_dropout_fwd", "dp_op_attention_dropout_bwd",
                  "dp_op_cross_attention_fwd", "dp_op_cross_attention_bwd",
                  "dp_op_rmsnorm_fwd", "dp_op_rmsnorm_bwd"):
@@ -474,6 +475,13 @@ def op_gelu_bwd(dy, x, dx, dbias, ws, kind=0, stream=None):
 def op_gemm(mode, M, N, K, A, B, bias, res, Cout, stream=None):
     _check(lib().dp_op_gemm(_dt(A), mode, M, N, K, _ptr(A), _ptr(B), _ptr(bias), _ptr(res), _ptr(Cout),
                             _stream_ptr(stream)))
+
+
+def op_gemm_tile(mode, M, N, K):
+    """(rows, columns) of the output tile a bf16 product of these sizes is computed in; (0, 0): another kernel's."""
+    tm, tn = C.c_int32(), C.c_int32()
+    _check(lib().dp_op_gemm_tile(mode, M, N, K, C.byref(tm), C.byref(tn)))
+    return tm.value, tn.value
 
 
 def op_colsum(x, out, ws, stream=None):

@@ -615,6 +615,12 @@ bool gemm_dma_supported(const GemmArgs &a) {
   return ((uint64_t)a.K + 4) * ld + 4096 <= 0xffffffffull;
 }
 
+void gemm_dma_tile(const GemmArgs &a, int *bm, int *bn) {
+  const TileTime &t = kTileTimes[choose_tile(a)];
+  *bm = t.bm;
+  *bn = t.bn;
+}
+
 hipError_t launch_gemm_dma(const GemmArgs &a, hipStream_t s) {
   return a.mode == kGemmNT ? launch_dma_mode<false>(a, s) : launch_dma_mode<true>(a, s);
 }

@@ -122,6 +122,7 @@ hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s);
 // kernels with LDS-direct operand loads; launch_gemm_mfma routes to them when the shape is supported
 bool gemm_dma_supported(const GemmArgs &a);
 hipError_t launch_gemm_dma(const GemmArgs &a, hipStream_t s);
+void gemm_dma_tile(const GemmArgs &a, int *bm, int *bn);   // the tile launch_gemm_dma takes for it
 
 // ---- attention ----------------------------------------------------------------
 // qkv [T,3H]; o [T,H] (nullable); lse [B,nh,S] fp32 (nullable); drop: dropout of the

@@ -89,6 +89,14 @@ dp_status dp_op_gemm(int32_t dtype, int32_t mode, int32_t M, int32_t N, int32_t 
   return op_done(dp::launch_gemm_simple(dtype, a, (hipStream_t)hip_stream), "gemm");
 }
 
+dp_status dp_op_gemm_tile(int32_t mode, int32_t M, int32_t N, int32_t K, int32_t *tile_m, int32_t *tile_n) {
+  if ((mode != 0 && mode != 1) || M < 0 || N < 0 || K < 0 || !tile_m || !tile_n) return fail(DP_E_INVAL, "gemm_tile: bad argument");
+  *tile_m = *tile_n = 0;
+  const dp::GemmArgs a{mode, M, N, K, nullptr, nullptr, nullptr, nullptr, nullptr};
+  if (dp::gemm_mfma_supported(a) && dp::gemm_dma_supported(a)) dp::gemm_dma_tile(a, tile_m, tile_n);
+  return DP_OK;
+}
+
 dp_status dp_op_colsum(int32_t dtype, int32_t rows, int32_t cols, const void *x, void *out, void *ws,
                        void *hip_stream) {
   if (bad_dtype(dtype) || rows < 0 || cols <= 0 || !out || (rows > 0 && (!x || !ws))) return fail(DP_E_INVAL, "colsum: bad argument");

@@ -1,0 +1,20 @@
+"""The tile a product is computed in, as the library's host code states it (no GPU)."""
+import pytest
+
+from paper_2505_05856_amd import binding as B
+from test_ops_gpu import GEMM_TILES
+
+
+@pytest.mark.parametrize("tile,mode,M,N,ks", GEMM_TILES)
+def test_the_gpu_tests_reach_every_tile_ragged(tile, mode, M, N, ks):
+    assert M % tile[0] and N % tile[1] and all(k % 64 for k in ks)
+    for k in ks:
+        assert B.op_gemm_tile(mode, M, N, k) == tile
+
+
+def test_other_kernels_products_have_no_tile():
+    for mode, m, n, k in ((0, 128, 128, 63), (0, 127, 128, 64), (0, 128, 130, 64), (0, 128, 128, 68), (1, 132, 128, 64),
+                          (0, 0, 128, 64)):
+        assert B.op_gemm_tile(mode, m, n, k) == (0, 0)
+    with pytest.raises(B.DpError):
+        B.op_gemm_tile(2, 128, 128, 64)

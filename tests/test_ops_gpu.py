@@ -108,8 +108,9 @@ def test_colsum(dt, rows, cols):
 
 GEMM_SHAPES = [(1, 8, 8), (5, 16, 24), (64, 64, 64), (100, 72, 40), (128, 384, 128), (257, 136, 520),
                (300, 1600, 96), (512, 256, 1024), (1000, 520, 1032), (264, 136, 4104), (2048, 1024, 512),
-               (4096, 4096, 192), (3900, 4200, 128),   # these two take the 256x256-tile path
-               # ragged edges on each tile size of the LDS-direct kernel, both forms (rows of 8 elements for TN)
+               (4096, 4096, 192),   # the 256x256 tile in both forms
+               (3900, 4200, 128),
+               # ragged edges, both forms (rows of 8 elements for TN); every tile of the LDS-direct kernel: GEMM_TILES
                (200, 328, 192), (1096, 1304, 256), (3904, 4200, 128), (3900, 4200, 448)]
 
 
@@ -135,8 +136,8 @@ def test_gemm(dt, mode, M, N, K):
     assert O.max_rel_err(host(c), ref + res) < TOL[dt]
 
 
-# K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, the shortest
-# that take the 256x256 tile's operand ring, and C, bias and residual rows of 8-byte alignment only (N a multiple of 4)
+# K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, four and more,
+# and C, bias and residual rows of 8-byte alignment only (N a multiple of 4)
 GEMM_RAGGED_K = [(0, 256, 264, 72), (0, 1096, 1304, 248), (0, 3904, 4200, 200), (0, 3904, 4200, 456), (0, 200, 132, 136),
                  (0, 3904, 4204, 200), (1, 256, 264, 65), (1, 264, 328, 127), (1, 1096, 1304, 250), (1, 3904, 4200, 193),
                  (1, 3904, 4200, 451), (1, 768, 3072, 1000)]
@@ -160,6 +161,23 @@ def test_gemm_ragged_k(mode, M, N, K):
     c8 = pad[4:].view(M, N)
     B.op_gemm(mode, M, N, K, ta, tb, None, c8, c8)
     assert O.max_rel_err(host(c8), ref + res) < TOL[dt]
+
+
+# Every tile of the LDS-direct kernel in both forms: ragged against it in rows, columns and K (no k-step divides it), rows of
+# 8-byte alignment (NT) or of 8 elements (TN); the fewest k-steps the tile's ring of stages takes, one more, several rounds
+GEMM_TILES = [((256, 256), 0, 2310, 3332, (136, 200, 456)), ((256, 256), 1, 3336, 2312, (131, 193, 451)),
+              ((256, 128), 0, 1667, 2308, (72, 136, 456)), ((256, 128), 1, 1672, 2336, (65, 131, 451)),
+              ((128, 256), 0, 2316, 1668, (72, 136, 456)), ((128, 256), 1, 2312, 1672, (65, 131, 451)),
+              ((128, 128), 0, 451, 4100, (72, 136, 456)), ((128, 128), 1, 4112, 456, (65, 131, 451)),
+              ((128, 64), 0, 193, 4148, (72, 136, 456)), ((128, 64), 1, 200, 4136, (65, 131, 451)),
+              ((64, 128), 0, 4143, 196, (72, 136, 456)), ((64, 128), 1, 4136, 200, (65, 131, 451)),
+              ((64, 64), 0, 146, 132, (72, 136, 456)), ((64, 64), 1, 136, 168, (65, 131, 451))]
+
+
+@pytest.mark.parametrize("tile,mode,M,N,K", [(t, mode, M, N, K) for t, mode, M, N, ks in GEMM_TILES for K in ks])
+def test_gemm_every_tile_ragged(tile, mode, M, N, K):
+    assert B.op_gemm_tile(mode, M, N, K) == tile     # (a change of the rule has to bring other sizes here)
+    test_gemm_ragged_k(mode, M, N, K)
 
 
 # fp32 on the matrix cores: ragged against the 32- and 64-row parts and the 16-deep chunks, both waves' arrangements

@@ -21,7 +21,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2516.6     # MI355X dense bf16 MFMA: 256 CU x 4096 flop/clk x 2.4 GHz
-PEAK_FP32_TFLOPS = 157.3      # vector fp32 (fp32 debug mode runs on the vector ALUs)
+PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 MFMA (v_mfma_f32_16x16x4): 256 CU x 256 flop/clk x 2.4 GHz
 # Bytes per launch of the dominant kernel that cross the L2 towards memory (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000,
 # the factors a 256 MiB device copy gives), from the rocprofv3 --pmc runs summarised in
 # profiles/c2_step_hbm_traffic_pmc.md and profiles/c5_step_hbm_traffic_pmc.md.
@@ -215,7 +215,7 @@ def op_times_and_roofline(run, cfg, name, plan_name, plan, budget, k):
     nt_flops = (flops["gemm_fwd"] + flops["gemm_dgrad"]) / k
     peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_FP32_TFLOPS
     achieved = nt_flops / (nt_ms * 1e-3) / 1e12
-    roof = {"kernel": "gemm_nt (forward + input-gradient GEMMs)", "bound": "mfma" if cfg.dtype == "bf16" else "alu",
+    roof = {"kernel": "gemm_nt (forward + input-gradient GEMMs)", "bound": "mfma" if cfg.dtype == "bf16" else "latency",
             "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
             "avg_launch_us": round(nt_ms * 1e3 / max(nt_launches, 1), 2),
             "avg_launch_us_source": "HIP event pairs recorded around every launch on the launch stream (event overhead "

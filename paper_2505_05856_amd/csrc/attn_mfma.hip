@@ -2,8 +2,7 @@
 //
 // Forward: a block owns 128 query rows of one (batch, head); each of its 4 waves
 // owns 32 of them.  K/V tiles of 64 keys stream through a double-buffered LDS
-// stage, brought in by the load unit itself (forward; the backward kernels still
-// stage their tiles through registers).  A wave computes S^T = K Q^T with v_mfma_f32_32x32x16_bf16, so that a
+// stage, brought in by the load unit itself.  A wave computes S^T = K Q^T with v_mfma_f32_32x32x16_bf16, so that a
 // lane holds one query row's logits for 16 keys of every 32-key block: the
 // softmax row reductions are in-lane plus one exchange between the two half
 // waves, and the probabilities already sit in the register layout the second
@@ -166,8 +165,6 @@ __device__ __forceinline__ void dma_tile_both(unsigned lds_byte, const char *src
 #pragma unroll
   for (int i = 0; i < DH / 32; ++i) dma_req_both<DH>(i, lds_byte, src_col0, ldb, row0, nrows, wave, lane);
 }
-// max / sum of a value over the two halves of the wave (lanes l and l ^ 32), in every lane: the swap
-// leaves lanes 0..31 of x beside lanes 32..63 of x in both registers, in the one or the other order
 // A wave's 32 x DH result (lane l holds row l % 32; accumulator element e of block d is column
 // 32 d + 8 (e / 4) + 4 (l / 32) + e % 4) goes out as whole rows: a store from the accumulators would
 // touch 32 rows with 16 bytes each, so the tile is turned through `ew`, 64 DH bytes of LDS that only
@@ -195,6 +192,8 @@ __device__ __forceinline__ void store_rows_via_lds(unsigned char *ew, const f32x
     if (r < nrows) *reinterpret_cast<uint4 *>(dst + (long)r * ld + c * 8) = q;
   }
 }
+// maximum of a value over the two halves of the wave (lanes l and l ^ 32), in every lane: the swap
+// leaves lanes 0..31 of x beside lanes 32..63 of x in both registers, in the one or the other order
 __device__ __forceinline__ float halves_max(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));

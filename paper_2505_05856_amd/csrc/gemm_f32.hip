@@ -72,11 +72,15 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
       }
     }
   };
-  f32x4 acc[F][F];
+  // NT without the division (at most four chunks): a sum for each chunk, added in their order, which is what the divided
+  // form's waves do with a chunk each: the same bits, and half the error of one chain over all of K.
+  constexpr bool BY_CHUNK = !TN && !SPLIT;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[F][F], sum[BY_CHUNK ? F : 1][F];
 #pragma unroll
   for (int i = 0; i < F; ++i)
 #pragma unroll
-    for (int j = 0; j < F; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < F; ++j) { acc[i][j] = zero; sum[BY_CHUNK ? i : 0][j] = zero; }
 #pragma unroll
   for (int s = 0; s < D; ++s) load(first + s * stride, a[s], b[s]);
   for (int c0 = first; c0 < nch; c0 += D * stride) {
@@ -99,7 +103,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 #pragma unroll
             for (int j = 0; j < F; ++j)
               acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(TN ? a[s][t][i] : a[s][i][t], TN ? b[s][t][j] : b[s][j][t],
-                                                               acc[i][j], 0, 0, 0);
+                                                               BY_CHUNK && t == 0 ? zero : acc[i][j], 0, 0, 0);
+        if (BY_CHUNK) {
+#pragma unroll
+          for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int j = 0; j < F; ++j) sum[BY_CHUNK ? i : 0][j] += acc[i][j];
+        }
       }
       load(c + D * stride, a[s], b[s]);
     }
@@ -119,7 +129,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
       for (int e = 0; e < 4; ++e) {
         vecF v;
 #pragma unroll
-        for (int j = 0; j < F; ++j) v[j] = acc[i][j][e];
+        for (int j = 0; j < F; ++j) v[j] = BY_CHUNK ? sum[BY_CHUNK ? i : 0][j][e] : acc[i][j][e];
         put(m0 + F * (4 * g + e) + i, n0 + F * r, v);
       }
   } else {
@@ -169,10 +179,10 @@ bool gemm_f32_supported(const GemmArgs &a) {
 // TN with enough tiles of 128x128 for half the chip: a wave each 64x64, no division ([1024 x 4096] x 4096: 257 us
 // against 311).  In NT form, whose loads take 16 rows at a time, the division stays ahead ([4096 x 4096] x 1024 352
 // against 505) but for contractions of at most four chunks, which leave its waves one each at most to share the turn
-// of the output through LDS over: [7588 x 3192] x 8, 24, 40, 64: 35.6, 43.8, 58.3, 65.4 us without it and 60.2, 71.6,
-// 78.8, 85.0 with it, [3076 x 1488] 11.0, 13.8, 19.1, 20.1 and 14.3, 17.1, 18.7, 19.6.
-// The vector-ALU kernel takes 52, 139, 168, 769 and 545 us for the products named so far with K > 64, 52.5 to 89.9 and
-// 13.9 to 22.4 us for the two of K <= 64, and 20 to 70 us where these kernels take under 7 ([128 x 128..512] x
+// of the output through LDS over: [7588 x 3192] x 8, 24, 40, 64: 39.2, 42.1, 51.2, 54.5 us without it and 60.2, 71.6,
+// 78.8, 85.0 with it, [3076 x 1488] 10.6, 12.2, 15.1, 16.4 and 14.3, 17.1, 18.7, 19.6.
+// The vector-ALU kernel takes 52, 139, 168, 769 and 545 us for the products named so far with K > 64, 52.4 to 87.9 and
+// 13.9 to 21.9 us for the two of K <= 64, and 20 to 70 us where these kernels take under 7 ([128 x 128..512] x
 // 128..512, the products of a stage 128 wide).
 hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
   auto tiles = [&](int t) { return (long)((a.M + t - 1) / t) * ((a.N + t - 1) / t); };

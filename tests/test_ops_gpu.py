@@ -205,6 +205,19 @@ def test_gemm_f32(mode, M, N, K):
     assert O.max_rel_err(host(c), ref + res) < tol
 
 
+# a short contraction over a large output takes a form of its own, which adds chunk sums as the waves of the other form do:
+# the first rows alone (too few tiles for it) have the same bits
+@pytest.mark.parametrize("K", [4, 20, 40, 64])
+def test_gemm_f32_short_contraction_keeps_its_sums(K):
+    M, N = 1501, 1412
+    a, b = dev(rnd((M, K), 45, torch.float32), torch.float32), dev(rnd((N, K), 46, torch.float32), torch.float32)
+    c, part = torch.full((M, N), float("nan"), device=DEV), torch.full((64, N), float("nan"), device=DEV)
+    B.op_gemm(0, M, N, K, a, b, None, None, c)
+    B.op_gemm(0, 64, N, K, a[:64].contiguous(), b, None, None, part)
+    torch.cuda.synchronize()
+    assert torch.equal(c[:64], part)
+
+
 ATTN_SHAPES = [(1, 8, 1, 8), (2, 5, 2, 16), (2, 64, 2, 64), (1, 200, 3, 64), (2, 96, 2, 128), (1, 384, 2, 64),
                (1, 1024, 3, 64), (1, 2048, 2, 128)]     # the last two: sequence and head width of C3/C4 and of C5
 

@@ -611,18 +611,18 @@ __global__ __launch_bounds__(256) void gelu_fwd_kernel(const T *__restrict__ x, 
 // dx = dy * gelu'(x) over [rows, cols] plus the column sums of the stored dx (the bias
 // gradient of the linear layer in front of the GELU): block (cx, rb) covers 512 columns
 // and rows [rb*rpb, (rb+1)*rpb); its partial sums go to part[rb][cols].
-template <typename T>
-__global__ __launch_bounds__(256) void gelu_bwd_colsum_kernel(const T *dy /* may alias dx */,
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void gelu_bwd_colsum_kernel(const T *dy /* may alias dx */,
                                                               const T *__restrict__ x, T *dx,
                                                               float *__restrict__ part, int rows, int cols, int rpb,
                                                               int kind) {
-  __shared__ float red[4][512];
+  __shared__ float red[NW][512];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = (blockIdx.x * 64 + lane) * 8;
   const int row_end = min(rows, (int)(blockIdx.y + 1) * rpb);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (col < cols) {
-    for (int row = blockIdx.y * rpb + wave; row < row_end; row += 4) {
+    for (int row = blockIdx.y * rpb + wave; row < row_end; row += NW) {
       const size_t at = (size_t)row * cols + col;
       float v[8], d[8];
       load8(x + at, v);
@@ -638,9 +638,182 @@ __global__ __launch_bounds__(256) void gelu_bwd_colsum_kernel(const T *dy /* may
 #pragma unroll
   for (int i = 0; i < 8; ++i) red[wave][lane * 8 + i] = acc[i];
   __syncthreads();
-  for (int k = threadIdx.x; k < 512; k += 256) {
+  for (int k = threadIdx.x; k < 512; k += 64 * NW) {
     const int c = blockIdx.x * 512 + k;
-    if (c < cols) part[(size_t)blockIdx.y * cols + c] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
+    if (c < cols) {
+      float t = red[0][k];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) t += red[w][k];
+      part[(size_t)blockIdx.y * cols + c] = t;
+    }
+  }
+}
+
+// ------------------------------------------------------------------ few rows: whole columns in one launch
+// With few rows a launch is a chain of latencies, and a second launch for the column sums (reduce_partials_kernel) costs
+// as much as the work: here a block of 1024 threads owns SC columns (a slab) over all rows, so the sums are complete in it.
+// A thread owns 8 of the columns in every 1024/(SC/8)-th row; its loads of four rows are in flight together.
+
+// The block's sums of one vector: `acc` holds a thread's 8 columns.  Rows of a wave by lane exchange, waves through LDS, in a
+// fixed order.
+template <typename T, int SC>
+__device__ __forceinline__ void slab_sums(float (&acc)[8], float (&red)[16][SC], T *__restrict__ out, int col0, int cols) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int m = SC / 8; m <= 32; m <<= 1) acc[i] += __shfl_xor(acc[i], m, 64);
+  if (lane < SC / 8)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) red[wave][lane * 8 + i] = acc[i];
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k < SC && col0 + k < cols) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += red[w][k];
+    stf(out + col0 + k, t);
+  }
+}
+
+// f(row) for every row of this thread's, four of its `load`s ahead of their `use`s
+template <int SC, typename Load, typename Use>
+__device__ __forceinline__ void slab_rows(int rows, Load &&load, Use &&use) {
+  constexpr int STEP = 1024 / (SC / 8);   // rows the block takes at a time
+  for (int r0 = threadIdx.x / (SC / 8); r0 < rows; r0 += 4 * STEP) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) load(min(r0 + STEP * u, rows - 1), u);   // (rows past the last: not used)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (r0 + STEP * u < rows) use(r0 + STEP * u, u);
+  }
+}
+
+template <typename T, int SC>
+__global__ __launch_bounds__(1024) void colsum_slab_kernel(const T *__restrict__ x, T *__restrict__ out, int rows, int cols) {
+  __shared__ float red[16][SC];
+  const int col0 = blockIdx.x * SC, col = col0 + (threadIdx.x % (SC / 8)) * 8;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (col < cols) {
+    Raw8<T> v[4];
+    slab_rows<SC>(rows, [&](int row, int u) { v[u].load(x + (size_t)row * cols + col); },
+              [&](int, int u) {
+                float a[8];
+                v[u].unpack(a);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] += a[i];
+              });
+  }
+  slab_sums(acc, red, out, col0, cols);
+}
+
+template <typename T, int SC>
+__global__ __launch_bounds__(1024) void gelu_bwd_slab_kernel(const T *dy /* may alias dx */, const T *__restrict__ x, T *dx,
+                                                             T *__restrict__ dbias, int rows, int cols, int kind) {
+  __shared__ float red[16][SC];
+  const int col0 = blockIdx.x * SC, col = col0 + (threadIdx.x % (SC / 8)) * 8;
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (col < cols) {
+    Raw8<T> v[4], g[4];
+    slab_rows<SC>(rows,
+              [&](int row, int u) {
+                const size_t at = (size_t)row * cols + col;
+                v[u].load(x + at);
+                g[u].load(dy + at);
+              },
+              [&](int row, int u) {
+                float a[8], d[8];
+                v[u].unpack(a);
+                g[u].unpack(d);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                  a[i] = d[i] * gelu_df(a[i], kind);
+                  acc[i] += (float)(T)a[i];   // the value as stored
+                }
+                store8(dx + (size_t)row * cols + col, a);
+              });
+  }
+  slab_sums(acc, red, dbias, col0, cols);
+}
+
+// LayerNorm backward: dgamma and dbeta need no row reductions (the statistics are given), so they come from blocks of their own
+// beside those of dx: blocks 0 .. row_blocks-1 take 16 rows each, a wave a row, the others a slab each.  x and dy are read twice,
+// the second time out of the caches.  No output may overlap an input (dx may be dres).
+constexpr int kLnSlabCols = 32;
+template <typename T, int NC>
+__global__ __launch_bounds__(1024) void ln_bwd_few_kernel(const T *__restrict__ dy, const T *__restrict__ x,
+                                                          const float *__restrict__ stats, const T *__restrict__ gamma,
+                                                          const T *__restrict__ dres, T *__restrict__ dx, T *__restrict__ dgamma,
+                                                          T *__restrict__ dbeta, int rows, int cols, int n_row_blocks, int rms) {
+  constexpr int SC = kLnSlabCols;
+  __shared__ float red[2][16][SC];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if ((int)blockIdx.x >= n_row_blocks) {
+    const int col0 = ((int)blockIdx.x - n_row_blocks) * SC, col = col0 + (threadIdx.x % (SC / 8)) * 8;
+    float dg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, db[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (col < cols) {
+      Raw8<T> v[4], g[4];
+      float mean[4], rstd[4];
+      slab_rows<SC>(rows,
+                [&](int row, int u) {
+                  const size_t at = (size_t)row * cols + col;
+                  v[u].load(x + at);
+                  g[u].load(dy + at);
+                  mean[u] = stats[2 * (size_t)row];
+                  rstd[u] = stats[2 * (size_t)row + 1];
+                },
+                [&](int, int u) {
+                  float a[8], d[8];
+                  v[u].unpack(a);
+                  g[u].unpack(d);
+#pragma unroll
+                  for (int i = 0; i < 8; ++i) {
+                    dg[i] += d[i] * ((a[i] - mean[u]) * rstd[u]);
+                    db[i] += d[i];
+                  }
+                });
+    }
+    slab_sums(dg, red[0], dgamma, col0, cols);
+    slab_sums(db, red[1], dbeta, col0, cols);
+    return;
+  }
+  const int row = blockIdx.x * 16 + wave;
+  if (row >= rows) return;
+  const size_t base = (size_t)row * cols;
+  const float mean = stats[2 * (size_t)row], rstd = stats[2 * (size_t)row + 1], inv_n = 1.0f / (float)cols;
+  float xh[NC][8], g[NC][8], r[NC][8];
+  float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int col = (c * 64 + lane) * 8;
+    if (col < cols) {
+      float d[8], gm[8];
+      load8(x + base + col, xh[c]);
+      load8(dy + base + col, d);
+      load8(gamma + col, gm);
+      if (dres != nullptr) load8(dres + base + col, r[c]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        xh[c][i] = (xh[c][i] - mean) * rstd;
+        g[c][i] = d[i] * gm[i];
+        s1 += g[c][i];
+        s2 += g[c][i] * xh[c][i];
+      }
+    }
+  }
+  const float m1 = rms ? 0.f : wave_sum(s1) * inv_n, m2 = wave_sum(s2) * inv_n;
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    const int col = (c * 64 + lane) * 8;
+    if (col < cols) {
+      float o[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) o[i] = rstd * (g[c][i] - m1 - xh[c][i] * m2);
+      if (dres != nullptr)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) o[i] += r[c][i];
+      store8(dx + base + col, o);
+    }
   }
 }
 
@@ -696,6 +869,36 @@ hipError_t launch_ln_fwd(int dtype, int rows, int cols, float eps, const void *x
   if (rows <= 0) return hipSuccess;
   return dtype == kBF16 ? ln_fwd_t<bf16>(rows, cols, eps, x, gamma, beta, y, stats, s, rms ? 1 : 0)
                         : ln_fwd_t<float>(rows, cols, eps, x, gamma, beta, y, stats, s, rms ? 1 : 0);
+}
+
+// Where the one-launch forms end (two launches / one, us, operands in the caches):
+//   column sums, bf16: 128x128 4.3 / 3.1, 1000x3072 5.6 / 3.8, 2048x2048 5.1 / 4.6; fp32 2048x2048 5.7 / 4.5
+//   GELU backward, bf16: 128x128 8.4 / 3.5, 512x512 8.4 / 4.8, 1000x768 9.3 / 6.7, 512x4096 9.4 / 6.6, but
+//     1000x1600 7.2 / 8.5 (few slabs, and the derivative is vector work: up to 1024 columns 16 a slab, not 32, for twice the blocks)
+//   LayerNorm backward, bf16: 128x128 5.9 / 4.8, 1000x768 9.4 / 6.0, 1000x2048 14.3 / 7.7, 2048x768 8.8 / 7.8; fp32, twice the
+//     bytes a slab: 1000x2048 18.4 / 11.5, but 2048x768 10.2 / 15.7
+constexpr int kSlabRows = 2048, kLnSlabBytes = 4096;
+// The sums are written while other blocks still read: calls whose outputs lie in what those read keep the two launches.
+static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return a != nullptr && b != nullptr && x < y + nb && y < x + na;
+}
+
+template <typename T>
+static hipError_t ln_bwd_few_t(int rows, int cols, const void *dy, const void *x, const float *stats, const void *gamma,
+                               const void *dres, void *dx, void *dgamma, void *dbeta, hipStream_t s, int rms) {
+  const int nrb = (rows + 15) / 16;
+  const dim3 grid(nrb + (cols + kLnSlabCols - 1) / kLnSlabCols);
+#define DP_LN_BWD_FEW(NC)                                                                                              \
+  hipLaunchKernelGGL((ln_bwd_few_kernel<T, NC>), grid, dim3(1024), 0, s, (const T *)dy, (const T *)x, stats,             \
+                     (const T *)gamma, (const T *)dres, (T *)dx, (T *)dgamma, (T *)dbeta, rows, cols, nrb, rms)
+  switch (ln_chunks(cols)) {
+    case 1: DP_LN_BWD_FEW(1); break;
+    case 2: DP_LN_BWD_FEW(2); break;
+    default: DP_LN_BWD_FEW(4); break;
+  }
+#undef DP_LN_BWD_FEW
+  return hipGetLastError();
 }
 
 // second pass now, or left to the caller as a job
@@ -765,6 +968,14 @@ hipError_t launch_ln_bwd(int dtype, int rows, int cols, const void *dy, const vo
     if (e == hipSuccess) e = zero_vec(dtype, dxsum, cols, s);
     return e;
   }
+  const size_t vec = (size_t)cols * dtype_size(dtype), mat = (size_t)rows * vec;
+  const auto in_inputs = [&](const void *p, size_t n) {
+    return overlap(p, n, dy, mat) || overlap(p, n, x, mat) || overlap(p, n, gamma, vec) || overlap(p, n, stats, 8 * (size_t)rows);
+  };
+  if (job == nullptr && dxsum == nullptr && rows <= kLnSlabBytes / (int)dtype_size(dtype) && cols <= 2048 && !in_inputs(dx, mat) &&
+      !in_inputs(dgamma, vec) && !in_inputs(dbeta, vec) && !overlap(dgamma, vec, dres, mat) && !overlap(dbeta, vec, dres, mat))
+    return dtype == kBF16 ? ln_bwd_few_t<bf16>(rows, cols, dy, x, stats, gamma, dres, dx, dgamma, dbeta, s, r)
+                          : ln_bwd_few_t<float>(rows, cols, dy, x, stats, gamma, dres, dx, dgamma, dbeta, s, r);
   if (dxsum != nullptr)
     return dtype == kBF16
                ? ln_bwd_t<bf16, true>(rows, cols, dy, x, stats, gamma, dres, dx, dgamma, dbeta, dxsum, ws, s, job, r)
@@ -774,14 +985,33 @@ hipError_t launch_ln_bwd(int dtype, int rows, int cols, const void *dy, const vo
              : ln_bwd_t<float, false>(rows, cols, dy, x, stats, gamma, dres, dx, dgamma, dbeta, nullptr, ws, s, job, r);
 }
 
+// The derivative is vector work: up to four blocks a CU their 16 rows go to 16 waves, one each, not to four with four rows each
+// one after the other (four waves / 16, us with the second pass, bf16: 700x3072 9.6 / 7.9, 1000x1600 10.9 / 7.2, 4096x1024 10.8 /
+// 9.2; the rest is memory: 4096x4096 20.3 / 20.9).
+constexpr int kGeluFewBlocks = 1024;
 template <typename T>
 static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy, const void *x, void *dx,
                                     void *dbias, void *ws, hipStream_t s, ReduceJob *job) {
+  const size_t mat = (size_t)rows * cols * sizeof(T), vec = (size_t)cols * sizeof(T);
+  if (job == nullptr && rows <= (cols <= 1024 ? 1024 : 512) && !overlap(dbias, vec, dy, mat) && !overlap(dbias, vec, x, mat)) {
+    if (cols <= 1024)
+      hipLaunchKernelGGL((gelu_bwd_slab_kernel<T, 16>), dim3((cols + 15) / 16), dim3(1024), 0, s, (const T *)dy, (const T *)x,
+                         (T *)dx, (T *)dbias, rows, cols, kind);
+    else
+      hipLaunchKernelGGL((gelu_bwd_slab_kernel<T, 32>), dim3((cols + 31) / 32), dim3(1024), 0, s, (const T *)dy, (const T *)x,
+                         (T *)dx, (T *)dbias, rows, cols, kind);
+    return hipGetLastError();
+  }
   int rpb;
   const int nb = row_blocks(rows, 16, &rpb);
   float *part = (float *)ws;
-  hipLaunchKernelGGL((gelu_bwd_colsum_kernel<T>), dim3((cols + 511) / 512, nb), dim3(256), 0, s, (const T *)dy,
-                     (const T *)x, (T *)dx, part, rows, cols, rpb, kind);
+  const dim3 grid((cols + 511) / 512, nb);
+  if ((int)(grid.x * grid.y) <= kGeluFewBlocks)
+    hipLaunchKernelGGL((gelu_bwd_colsum_kernel<T, 16>), grid, dim3(1024), 0, s, (const T *)dy, (const T *)x, (T *)dx, part, rows,
+                       cols, rpb, kind);
+  else
+    hipLaunchKernelGGL((gelu_bwd_colsum_kernel<T, 4>), grid, dim3(256), 0, s, (const T *)dy, (const T *)x, (T *)dx, part, rows,
+                       cols, rpb, kind);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   return reduce_or_defer<T>(part, nb, cols, cols, dbias, dbias, dbias, s, job);
@@ -828,6 +1058,10 @@ hipError_t launch_dropout(int dtype, size_t n, const void *x, const void *res, v
 
 template <typename T>
 static hipError_t colsum_t(int rows, int cols, const void *x, void *out, void *ws, hipStream_t s, ReduceJob *job) {
+  if (job == nullptr && rows <= kSlabRows && !overlap(out, (size_t)cols * sizeof(T), x, (size_t)rows * cols * sizeof(T))) {
+    hipLaunchKernelGGL((colsum_slab_kernel<T, 32>), dim3((cols + 31) / 32), dim3(1024), 0, s, (const T *)x, (T *)out, rows, cols);
+    return hipGetLastError();
+  }
   int rpb;
   const int nb = row_blocks(rows, 16, &rpb);
   float *part = (float *)ws;

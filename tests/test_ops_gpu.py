@@ -136,6 +136,40 @@ def test_gemm(dt, mode, M, N, K):
     assert O.max_rel_err(host(c), ref + res) < TOL[dt]
 
 
+# one launch up to 1024 / 2048 rows: waves and passes of rows cut short, slabs of 16 and 32 columns cut short, the last row count
+# on either side of each rule; outputs that lie in the inputs (in place, the sums over gamma) take the two launches
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(1, 8), (15, 24), (17, 136), (128, 128), (257, 40), (1000, 776), (1024, 2048), (1025, 48),
+                                       (2048, 520), (2049, 72), (33, 2056)])
+def test_column_sums_of_few_rows(dt, rows, cols):
+    x, dy, dres = rnd((rows, cols), 11, dt, 2.0), rnd((rows, cols), 14, dt), rnd((rows, cols), 15, dt)
+    g = rnd((cols,), 12, dt) * 0.1 + 1
+    g = syn.round_to_bf16(g) if dt == torch.bfloat16 else g
+    tx, tg, tdy, tres = (dev(a, dt) for a in (x, g, dy, dres))
+    ws = ws_for(rows, cols)
+    new = lambda *shape: torch.full(shape, float("nan"), dtype=dt, device=DEV)
+    y, stats = new(rows, cols), torch.empty(rows, 2, dtype=torch.float32, device=DEV)
+    B.op_layernorm_fwd(tx, tg, dev(g, dt), 1e-5, y, stats)
+    _, mu, r = O.layernorm_fwd(x.astype(np.float64), g.astype(np.float64), g.astype(np.float64), 1e-5)
+    dx_ref, dg_ref, db_ref = O.layernorm_bwd(dy.astype(np.float64), x.astype(np.float64), mu, r, g.astype(np.float64))
+    for in_place in (False, True):
+        src = tdy.clone()
+        dx, dg, db = (src, tg.clone(), new(cols)) if in_place else (new(rows, cols), new(cols), new(cols))
+        B.op_layernorm_bwd(src, tx, stats, dg if in_place else tg, tres, dx, dg, db, ws)
+        assert O.max_rel_err(host(dx), dx_ref + dres) < TOL[dt]
+        assert O.max_rel_err(host(dg), dg_ref) < TOL[dt] and O.max_rel_err(host(db), db_ref) < TOL[dt]
+    out = new(cols)
+    B.op_colsum(tdy, out, ws)
+    assert O.max_rel_err(host(out), dy.astype(np.float64).sum(axis=0)) < TOL[dt]
+    ref = dy * O.gelu_grad(x.astype(np.float64), "erf")
+    dx, src = new(rows, cols), tdy.clone()
+    B.op_gelu_bwd(tdy, tx, dx, out, ws, 0)
+    assert O.max_rel_err(host(dx), ref) < TOL[dt]
+    assert O.max_rel_err(host(out), host(dx).sum(axis=0)) < TOL[dt]   # of dx as stored
+    B.op_gelu_bwd(src, tx, src, out, ws, 0)                           # in place
+    assert torch.equal(src, dx)
+
+
 # K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, four and more,
 # and C, bias and residual rows of 8-byte alignment only (N a multiple of 4)
 GEMM_RAGGED_K = [(0, 256, 264, 72), (0, 1096, 1304, 248), (0, 3904, 4200, 200), (0, 3904, 4200, 456), (0, 200, 132, 136),

@@ -136,6 +136,13 @@ def test_gemm(dt, mode, M, N, K):
     assert O.max_rel_err(host(c), ref + res) < TOL[dt]
 
 
+def test_calls_go_to_the_current_stream():
+    side = torch.cuda.Stream()
+    for s in (torch.cuda.current_stream(), side, torch.cuda.current_stream()):
+        with torch.cuda.stream(s):
+            assert (B._stream_ptr(None) or 0) == torch.cuda.current_stream().cuda_stream == (B._stream_ptr(s) or 0)
+
+
 # one launch up to 1024 / 2048 rows: waves and passes of rows cut short, slabs of 16 and 32 columns cut short, the last row count
 # on either side of each rule; outputs that lie in the inputs (in place, the sums over gamma) take the two launches
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])

@@ -80,15 +80,17 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T *__restrict__ x, co
 // bias gradient of the linear layer that produced LayerNorm's input).
 // AHEAD: a wave asks for its next row while it works on the current one (pays when a wave has
 // several rows; with two rows a wave the registers it takes cost more than it returns).
-template <typename T, int NC, bool SUMDX, bool AHEAD>
-__global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx */, const T *__restrict__ x,
+// NW waves a block: with 4 a wave has two rows and more; the forms of 8 and 16 (not AHEAD) give each row of a block a wave of its
+// own, and 16 waves halve the blocks and with them the partial rows.
+template <typename T, int NC, bool SUMDX, bool AHEAD, int NW>
+__global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alias dx */, const T *__restrict__ x,
                                                      const float *__restrict__ stats, const T *__restrict__ gamma,
                                                      const T *__restrict__ dres, T *dx,
                                                      float *__restrict__ part, int rows, int cols, int rpb, int rms) {
   // rms: the forward subtracted no mean (its statistics say mean = 0), so the term that carries the
   // derivative of the mean, mean(g), drops out: dx = rstd (g - xhat mean(g xhat))
   constexpr int NV = SUMDX ? 3 : 2;
-  __shared__ float red[4][NV][512];
+  __shared__ float red[NW][NV][512];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int row_end = min(rows, (int)(blockIdx.x + 1) * rpb);
   float dg[NC][8], db[NC][8], ds[SUMDX ? NC : 1][8];
@@ -139,7 +141,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx
     }
     fetch(blockIdx.x * rpb + wave);
     fetch_res(blockIdx.x * rpb + wave);
-    for (int row = blockIdx.x * rpb + wave; row < row_end; row += 4) {
+    for (int row = blockIdx.x * rpb + wave; row < row_end; row += NW) {
       const float mean = mean_n, rstd = rstd_n;
       const size_t base = (size_t)row * cols;
       float xh[NC][8], g[NC][8];
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx
           }
         }
       }
-      fetch(row + 4);   // the wave's next row (another row of dy: the store below cannot touch it)
+      fetch(row + NW);   // the wave's next row (another row of dy: the store below cannot touch it)
       const float m1 = rms ? 0.f : wave_sum(s1) * inv_n, m2 = wave_sum(s2) * inv_n;
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
@@ -185,14 +187,22 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx
           }
         }
       }
-      fetch_res(row + 4);
+      fetch_res(row + NW);
     }
   } else if constexpr (NC <= 4) {
-    for (int row = blockIdx.x * rpb + wave; row < row_end; row += 4) {
+    for (int row = blockIdx.x * rpb + wave; row < row_end; row += NW) {
       const float mean = stats[2 * (size_t)row], rstd = stats[2 * (size_t)row + 1];
       const size_t base = (size_t)row * cols;
       float xh[NC][8], g[NC][8];
       float s1 = 0.f, s2 = 0.f;
+      Raw8<T> rr[NW > 4 ? NC : 1];   // the residual gradient, asked for with the rest where a wave has one row
+      if (NW > 4 && dres != nullptr) {
+  #pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const int col = (c * 64 + lane) * 8;
+          if (col < cols) rr[NW > 4 ? c : 0].load(dres + base + col);
+        }
+      }
   #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const int col = (c * 64 + lane) * 8;
@@ -222,7 +232,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx
           for (int i = 0; i < 8; ++i) o[i] = rstd * (g[c][i] - m1 - xh[c][i] * m2);
           if (dres != nullptr) {
             float r[8];
-            load8(dres + base + col, r);
+            if (NW > 4) rr[NW > 4 ? c : 0].unpack(r); else load8(dres + base + col, r);
   #pragma unroll
             for (int i = 0; i < 8; ++i) o[i] += r[i];
           }
@@ -235,7 +245,7 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx
       }
     }
   } else {
-    for (int row = blockIdx.x * rpb + wave; row < row_end; row += 4) {
+    for (int row = blockIdx.x * rpb + wave; row < row_end; row += NW) {
       const float mean = stats[2 * (size_t)row], rstd = stats[2 * (size_t)row + 1];
       const size_t base = (size_t)row * cols;
         float s1 = 0.f, s2 = 0.f;
@@ -300,11 +310,13 @@ __global__ __launch_bounds__(256) void ln_bwd_kernel(const T *dy /* may alias dx
       if (SUMDX) red[wave][NV - 1][lane * 8 + i] = ds[c][i];
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < NV * 512; j += 256) {
+    for (int j = threadIdx.x; j < NV * 512; j += 64 * NW) {
       const int which = j >> 9, k = j & 511;
       const int col = c * 512 + k;
       if (col < cols) {
-        const float t = ((red[0][which][k] + red[1][which][k]) + red[2][which][k]) + red[3][which][k];
+        float t = red[0][which][k];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t += red[w][which][k];
         prow[(size_t)which * cols + col] = t;
       }
     }
@@ -592,6 +604,46 @@ __global__ __launch_bounds__(256) void dropout_kernel(const T *x /* may alias y 
       v[q] = res != nullptr ? r[q] + d : d;
     }
     store8(y + i * 8, v);
+  }
+}
+
+// y = keep * scale * x over [rows, cols] and the column sums of the stored y, in partial rows as colsum_kernel's: the gradient of
+// a dropped hidden state on its way into the linear layer, whose bias gradient the sums are.  One wave a row up to four blocks a CU
+// (the draws are vector work, see gelu_bwd_colsum_kernel).
+template <typename T, int NW>
+__global__ __launch_bounds__(64 * NW) void dropout_colsum_kernel(const T *__restrict__ x, T *__restrict__ y,
+                                                                 float *__restrict__ part, int rows, int cols, int rpb, DropArgs a) {
+  __shared__ float red[NW][512];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = (blockIdx.x * 64 + lane) * 8;
+  const int row_end = min(rows, (int)(blockIdx.y + 1) * rpb);
+  const DropKeys k = drop_keys(a.base, 0u);
+  float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (col < cols) {
+    for (int row = blockIdx.y * rpb + wave; row < row_end; row += NW) {
+      const size_t at = (size_t)row * cols + col;
+      float v[8];
+      load8(x + at, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool keep = drop_bits((uint32_t)(at + i), k.k0, k.k1) >= a.thr;
+        v[i] = keep ? v[i] * a.scale : 0.f;
+        acc[i] += (float)(T)v[i];
+      }
+      store8(y + at, v);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) red[wave][lane * 8 + i] = acc[i];
+  __syncthreads();
+  for (int j = threadIdx.x; j < 512; j += 64 * NW) {
+    const int c = blockIdx.x * 512 + j;
+    if (c < cols) {
+      float t = red[0][j];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) t += red[w][j];
+      part[(size_t)blockIdx.y * cols + c] = t;
+    }
   }
 }
 
@@ -915,16 +967,23 @@ template <typename T, bool SUMDX>
 static hipError_t ln_bwd_t(int rows, int cols, const void *dy, const void *x, const float *stats,
                            const void *gamma, const void *dres, void *dx, void *dgamma, void *dbeta, void *dxsum,
                            void *ws, hipStream_t s, ReduceJob *job, int rms) {
+  // One row a wave (us, both passes, bf16 with the column sums of dx, 4 waves a block / this): up to 2048 rows 8 waves, 512x512
+  // 7.4 / 6.5, 1000x1600 15.5 / 12.5, 2048x2048 18.4 / 15.3 (fp32 21.0 / 19.1); then 16 waves in half the blocks, 4096x1024
+  // 14.4 / 12.6, where the registers hold a row: in bf16 up to 1024 columns (4096x1600 21 / 54).
+  const bool wide_block = rows > 2048 && rows <= 4096 && cols <= 1024 && sizeof(T) == 2;
   int rpb;
-  const int nb = row_blocks(rows, 8, &rpb);
+  const int nb = row_blocks(rows, wide_block ? 16 : 8, &rpb);
   const int nv = SUMDX ? 3 : 2;
   float *part = (float *)ws;
-#define DP_LN_BWD_AS(NC, AHEAD)                                                                                    \
-  hipLaunchKernelGGL((ln_bwd_kernel<T, NC, SUMDX, AHEAD>), dim3(nb), dim3(256), 0, s, (const T *)dy, (const T *)x, \
+#define DP_LN_BWD_AS(NC, AHEAD, NW)                                                                                    \
+  hipLaunchKernelGGL((ln_bwd_kernel<T, NC, SUMDX, AHEAD, NW>), dim3(nb), dim3(64 * NW), 0, s, (const T *)dy, (const T *)x, \
                      stats, (const T *)gamma, (const T *)dres, (T *)dx, part, rows, cols, rpb, rms)
 #define DP_LN_BWD(NC)                                                               \
   do {                                                                              \
-    if (NC <= 2 || rpb >= 16) DP_LN_BWD_AS(NC, true); else DP_LN_BWD_AS(NC, false);               \
+    if (rows <= 2048) DP_LN_BWD_AS(NC, false, 8);                                   \
+    else if (wide_block) DP_LN_BWD_AS((NC < 2 ? NC : 2), false, 16);                \
+    else if (NC <= 2 || rpb >= 16) DP_LN_BWD_AS(NC, true, 4);                       \
+    else DP_LN_BWD_AS(NC, false, 4);                                                \
   } while (0)
 #define DP_LN_BWD_WIDE_AS(NP, FULL, RES)                                                                      \
   hipLaunchKernelGGL((ln_bwd_wide_kernel<T, NP, SUMDX, FULL, RES>), dim3(nb), dim3(256), 0, s, (const T *)dy, \
@@ -988,7 +1047,7 @@ hipError_t launch_ln_bwd(int dtype, int rows, int cols, const void *dy, const vo
 // The derivative is vector work: up to four blocks a CU their 16 rows go to 16 waves, one each, not to four with four rows each
 // one after the other (four waves / 16, us with the second pass, bf16: 700x3072 9.6 / 7.9, 1000x1600 10.9 / 7.2, 4096x1024 10.8 /
 // 9.2; the rest is memory: 4096x4096 20.3 / 20.9).
-constexpr int kGeluFewBlocks = 1024;
+constexpr int kFewBlocks = 1024;
 template <typename T>
 static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy, const void *x, void *dx,
                                     void *dbias, void *ws, hipStream_t s, ReduceJob *job) {
@@ -1006,7 +1065,7 @@ static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy
   const int nb = row_blocks(rows, 16, &rpb);
   float *part = (float *)ws;
   const dim3 grid((cols + 511) / 512, nb);
-  if ((int)(grid.x * grid.y) <= kGeluFewBlocks)
+  if ((int)(grid.x * grid.y) <= kFewBlocks)
     hipLaunchKernelGGL((gelu_bwd_colsum_kernel<T, 16>), grid, dim3(1024), 0, s, (const T *)dy, (const T *)x, (T *)dx, part, rows,
                        cols, rpb, kind);
   else
@@ -1054,6 +1113,30 @@ hipError_t launch_dropout(int dtype, size_t n, const void *x, const void *res, v
     hipLaunchKernelGGL((dropout_kernel<float>), dim3(ew_grid(n8)), dim3(256), 0, s, (const float *)x,
                        (const float *)res, (float *)y, n8, a);
   return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t dropout_colsum_t(int rows, int cols, const void *x, void *y, void *sums, void *ws, const DropArgs &a,
+                                   hipStream_t s, ReduceJob *job) {
+  int rpb;
+  const int nb = row_blocks(rows, 16, &rpb);
+  float *part = (float *)ws;
+  const dim3 grid((cols + 511) / 512, nb);
+  if ((int)(grid.x * grid.y) <= kFewBlocks)
+    hipLaunchKernelGGL((dropout_colsum_kernel<T, 16>), grid, dim3(1024), 0, s, (const T *)x, (T *)y, part, rows, cols, rpb, a);
+  else
+    hipLaunchKernelGGL((dropout_colsum_kernel<T, 4>), grid, dim3(256), 0, s, (const T *)x, (T *)y, part, rows, cols, rpb, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return reduce_or_defer<T>(part, nb, cols, cols, sums, sums, sums, s, job);
+}
+
+hipError_t launch_dropout_colsum(int dtype, int rows, int cols, const void *x, void *y, void *sums, void *ws, const DropArgs &a,
+                                 hipStream_t s, ReduceJob *job) {
+  job->nb = 0;
+  if (rows <= 0) return zero_vec(dtype, sums, cols, s);
+  return dtype == kBF16 ? dropout_colsum_t<bf16>(rows, cols, x, y, sums, ws, a, s, job)
+                        : dropout_colsum_t<float>(rows, cols, x, y, sums, ws, a, s, job);
 }
 
 template <typename T>

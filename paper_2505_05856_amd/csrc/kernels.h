@@ -102,6 +102,9 @@ hipError_t launch_gelu_bwd_colsum(int dtype, int kind, int rows, int cols, const
 // y = (res ? res : 0) + keep * scale * x, n a multiple of 8 and below 2^32; x and res may be y
 hipError_t launch_dropout(int dtype, size_t n, const void *x, const void *res, void *y, const DropArgs &a,
                           hipStream_t s);
+// y = keep * scale * x over [rows, cols] (one micro-batch's mask, below 2^32 elements) and `sums` = column sums of the stored y
+hipError_t launch_dropout_colsum(int dtype, int rows, int cols, const void *x, void *y, void *sums, void *ws, const DropArgs &a,
+                                 hipStream_t s, ReduceJob *job);
 hipError_t launch_gelu_fwd(int dtype, int kind, size_t n, const void *x, void *y, hipStream_t s);
 hipError_t launch_colsum(int dtype, int rows, int cols, const void *x, void *out, void *ws, hipStream_t s,
                          ReduceJob *job = nullptr);

@@ -657,8 +657,15 @@ struct Walk {
   // are that layer's bias gradient.
   Buf masked_grad(int l, int site, const void *dyp, void *dbias) {
     Buf m = tmp((size_t)c.T * c.H * c.esz);
-    hidden_dropout(l, site, dyp, nullptr, bptr(m));
-    colsum(c.T, c.H, bptr(m), dbias);
+    if (!no_arena) arena.tick();   // (the spans a plan's blocks are held for count two launch sites here)
+    Buf ws = tmp(dp::reduce_ws_bytes((int)c.T, c.H));
+    dp::ReduceJob job{};
+    prof_begin(DP_OPC_DROPOUT);
+    if (live)
+      check(dp::launch_dropout_colsum(c.dtype, (int)c.T, c.H, dyp, bptr(m), dbias, bptr(ws),
+                                      dp::make_drop_args(rng_seed, rng_mb, l, site, c.p_hidden), cs, &job));
+    prof_end();
+    defer_reduce(job, ws);
     return m;
   }
   void ln_bwd(const void *dyp, const void *x, const void *stats, const void *gamma, const void *dres, void *dx,

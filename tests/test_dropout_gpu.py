@@ -50,6 +50,22 @@ def test_hidden_mask_is_the_oracles_bit_for_bit(dt, T, H, p):
     assert np.array_equal(host(tx)[~keep], res.astype(np.float64)[~keep])     # dropped: the residual, untouched
 
 
+# the masked gradient and its column sums come from one kernel: one wave a row up to 1024 blocks, then four waves a block; its
+# sums are those of the standalone operator's output (pre-LN: dy itself is masked on its way into FC2)
+@pytest.mark.parametrize("dtype,batch,seq,heads", [("f32", 1, 37, 1), ("bf16", 2, 65, 3), ("bf16", 4, 513, 8), ("bf16", 8, 1025, 24)])
+def test_bias_gradient_under_dropout_is_the_masked_gradients_sum(dtype, batch, seq, heads):
+    cfg = syn.StageConfig(1, 64 * heads, heads, 64, seq, batch, "pre", True, "erf", dtype, p_attn=0.0, p_hidden=0.3)
+    run = StageRunner(cfg, syn.make_weights(cfg), *syn.make_activations(cfg))
+    B.stage_set_rng(run.stage, 99, 4)
+    run.step(syn.plan_keep_all(cfg))
+    _, _, g = run.results()
+    ty = torch.empty_like(run.dy)
+    B.op_dropout(run.dy, None, ty, B.Dropout(0.3, 99, 4, 0), B.SITE_FC2)
+    ref = host(ty).sum(axis=0)
+    run.close()
+    assert O.max_rel_err(g[0]["b_fc2"], ref) < TOL[torch.float32 if dtype == "f32" else torch.bfloat16]
+
+
 def test_dropout_rate_zero_and_bad_arguments():
     x = dev(rnd((16, 16), 1, torch.float32), torch.float32)
     y = torch.empty_like(x)

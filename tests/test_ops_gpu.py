@@ -177,6 +177,27 @@ def test_column_sums_of_few_rows(dt, rows, cols):
     assert torch.equal(src, dx)
 
 
+# the norm backward with the column sums of dx: 8 waves a block up to 2048 rows, 16 up to 4096 (bf16, 1024 columns), 4 from there on
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(9, 1608), (1000, 776), (2048, 2048), (2049, 520), (4090, 1024), (2300, 1032), (4097, 72)])
+def test_norm_backward_waves(dt, rows, cols):
+    x, dy, dres = rnd((rows, cols), 11, dt, 2.0), rnd((rows, cols), 14, dt), rnd((rows, cols), 15, dt)
+    g = rnd((cols,), 12, dt) * 0.1 + 1
+    g = syn.round_to_bf16(g) if dt == torch.bfloat16 else g
+    tx, tg, tdy, tres = (dev(a, dt) for a in (x, g, dy, dres))
+    y, stats = torch.empty_like(tx), torch.empty(rows, 2, dtype=torch.float32, device=DEV)
+    B.op_layernorm_fwd(tx, tg, tg, 1e-5, y, stats)
+    _, mu, r = O.layernorm_fwd(x.astype(np.float64), g.astype(np.float64), g.astype(np.float64), 1e-5)
+    dx_ref, dg_ref, db_ref = O.layernorm_bwd(dy.astype(np.float64), x.astype(np.float64), mu, r, g.astype(np.float64))
+    for res in (tres, None):
+        dx, (dg, db, ds) = torch.full_like(tx, float("nan")), (torch.full_like(tg, float("nan")) for _ in range(3))
+        B.op_layernorm_bwd(tdy, tx, stats, tg, res, dx, dg, db, ws_for(rows, cols), dx_colsum=ds)
+        assert O.max_rel_err(host(dx), dx_ref + (dres if res is not None else 0)) < TOL[dt]
+        assert O.max_rel_err(host(dg), dg_ref) < TOL[dt] and O.max_rel_err(host(db), db_ref) < TOL[dt]
+        if res is not None:   # (without it the columns of dx nearly cancel)
+            assert O.max_rel_err(host(ds), host(dx).sum(axis=0)) < TOL[dt]
+
+
 # K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, four and more,
 # and C, bias and residual rows of 8-byte alignment only (N a multiple of 4)
 GEMM_RAGGED_K = [(0, 256, 264, 72), (0, 1096, 1304, 248), (0, 3904, 4200, 200), (0, 3904, 4200, 456), (0, 200, 132, 136),

@@ -30,6 +30,7 @@
 //       over all 16 chunk positions of the 256-byte bank period.
 //   TN: a stage holds the tiles as loaded, [64 k rows][BM] and [64 k rows][BN]; fragments
 //       come through the transpose read (ds_read_b64_tr_b16); see tn_swizzle.
+//       A tile of 192 columns is two panels of 96, [64 k rows][96] each: its 384-byte rows would not divide a request.
 #include "common.h"
 #include "kernels.h"
 
@@ -102,9 +103,10 @@ __device__ __forceinline__ const char *uniform_ptr(const char *p) {
 // TN: chunk-position swizzle of k row r of a tile whose rows are ROWB bytes.  A half wave's
 // transpose read touches k rows {0..3, 8..11} (or those 16 further) x 32 bytes: bits 0 and 1 of the
 // row choose the 64-byte quarter of the bank period, bit 3 the 32-byte half of it.  With 128-byte
-// rows (two rows a period) bit 0 of the row is part of the address already.
+// rows (two rows a period) bit 0 of the row is part of the address already, with 192-byte rows (a panel of
+// 96 columns) both bits are: four rows on end start in four quarters.
 template <int ROWB> __device__ __forceinline__ constexpr int tn_swizzle(int r) {
-  return (ROWB == 128 ? ((r >> 1) & 1) << 2 : (r & 3) << 2) | ((r >> 3) & 1) << 1;
+  return (ROWB == 192 ? 0 : ROWB == 128 ? ((r >> 1) & 1) << 2 : (r & 3) << 2) | ((r >> 3) & 1) << 1;
 }
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool ACT, bool TN, bool SPLIT>
@@ -118,7 +120,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   constexpr int kRowBytes = BK * 2;                  // NT: one LDS row
   constexpr int CPR = BK / 8;                        // NT: chunks per row
   constexpr int A_BYTES = BM * kRowBytes, B_BYTES = BN * kRowBytes, STAGE_BYTES = A_BYTES + B_BYTES;
-  constexpr int ROWB_A = BM * 2, ROWB_B = BN * 2;   // TN: bytes of one k row of a tile
+  // TN: a tile of 192 columns is two panels of 96, each [64 k rows][192 bytes], every wave's part inside one of them
+  constexpr bool PANEL_A = TN && BM == 192, PANEL_B = TN && BN == 192;
+  constexpr int ROWB_A = PANEL_A ? 192 : BM * 2, ROWB_B = PANEL_B ? 192 : BN * 2;   // TN: bytes of one k row of a tile (panel)
+  static_assert((!PANEL_A || (WM == 96 && NW == 4)) && (!PANEL_B || (WN == 96 && NW == 4)), "a wave's part is in one panel");
   constexpr int NIA = A_BYTES / 1024 / NW, NIB = B_BYTES / 1024 / NW;   // requests per wave per stage
   constexpr int NI = NIA + NIB;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -152,10 +157,13 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   //   TN: a request is RPR = 1024/ROWB k rows of ROWB bytes; lane l is k row l/(64/RPR),
   //       chunk position l%(64/RPR) and fetches logical chunk position ^ tn_swizzle(krow).  A wave
   //       takes whole groups of 8 k rows, every NW-th (their numbers are then all even or all odd).
+  //       Panels of 96 columns: three requests are 16 k rows; 16-byte chunk 64 v + l of them (v = 0, 1, 2) is k row
+  //       (64 v + l) / 12, position (64 v + l) % 12.  A wave takes its 16 of the 64 k rows in both panels.
   const unsigned lda = (unsigned)(TN ? M : K) * 2u, ldb = (unsigned)(TN ? N : K) * 2u;   // operand row bytes
-  constexpr int RPA = TN ? 1024 / ROWB_A : 8, RPB = TN ? 1024 / ROWB_B : 8;              // rows per request
-  constexpr int GA = TN ? 8 / RPA : 1, GB = TN ? 8 / RPB : 1;                            // requests per group
-  static_assert(RPA >= 2 && RPA <= 8 && RPB >= 2 && RPB <= 8, "tile width 64, 128 or 256");
+  constexpr int RPA = TN ? 1024 / ROWB_A : 8, RPB = TN ? 1024 / ROWB_B : 8;              // rows per request (panels: see row0)
+  constexpr int GA = PANEL_A ? 3 : TN ? 8 / RPA : 1, GB = PANEL_B ? 3 : TN ? 8 / RPB : 1;   // requests per group
+  constexpr int VA = PANEL_A ? 3 : 2, VB = PANEL_B ? 3 : 2;                              // values of the lane offsets
+  static_assert((PANEL_A || (RPA >= 2 && RPA <= 8)) && (PANEL_B || (RPB >= 2 && RPB <= 8)), "tile width 64, 128, 192 or 256");
   static_assert(NIA % GA == 0 && NIB % GB == 0 && NW % 2 == 0 && NIA % 2 == 0 && NIB % 2 == 0, "requests of a wave");
   // request j of a wave is number (the wave's first) + rel(j) of the tile
   const int first_a = wave * (TN ? GA : NIA), first_b = wave * (TN ? GB : NIB);
@@ -163,28 +171,37 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   // requests with consecutive numbers share an M0 (that of their first, the lead); the request's immediate says
   // how far on it is, and its base pointer makes up for that
   auto lead = [](int j, int g) constexpr { return TN ? j / g * g : j / 4 * 4; };
-  unsigned voa[2], vob[2];
-#pragma unroll
-  for (int v = 0; v < 2; ++v) {
-    if (!TN) {
+  unsigned voa[VA], vob[VB];
+  auto lane_offset = [&](int v, auto panel_tag, auto rowb_tag, int g, unsigned ld) DP_INLINE -> unsigned {
+    constexpr int ROWB = decltype(rowb_tag)::value, RPR = TN ? 1024 / ROWB : 8;
+    if constexpr (!TN) {
       const int r = lane / CPR, pc = lane % CPR;
-      voa[v] = vob[v] = (unsigned)r * lda + (unsigned)((pc ^ (((8 * v + r) >> 1) % CPR)) << 4);
+      return (unsigned)r * ld + (unsigned)((pc ^ (((8 * v + r) >> 1) % CPR)) << 4);
+    } else if constexpr (decltype(panel_tag)::value) {
+      const int k = (64 * v + lane) / 12, p = (64 * v + lane) % 12;
+      return (unsigned)k * ld + (unsigned)((p ^ tn_swizzle<ROWB>(k)) << 4);
     } else {
-      const int ka = lane / (64 / RPA), pa_ = lane % (64 / RPA);
-      voa[v] = (unsigned)ka * lda + (unsigned)((pa_ ^ tn_swizzle<ROWB_A>(8 * (wave & 1) + RPA * (v % GA) + ka)) << 4);
-      const int kb = lane / (64 / RPB), pb_ = lane % (64 / RPB);
-      vob[v] = (unsigned)kb * ldb + (unsigned)((pb_ ^ tn_swizzle<ROWB_B>(8 * (wave & 1) + RPB * (v % GB) + kb)) << 4);
+      const int k = lane / (64 / RPR), p = lane % (64 / RPR);
+      return (unsigned)k * ld + (unsigned)((p ^ tn_swizzle<ROWB>(8 * (wave & 1) + RPR * (v % g) + k)) << 4);
     }
-  }
+  };
+#pragma unroll
+  for (int v = 0; v < VA; ++v) voa[v] = lane_offset(v, std::integral_constant<bool, PANEL_A>{}, Count<ROWB_A>{}, GA, lda);
+#pragma unroll
+  for (int v = 0; v < VB; ++v) vob[v] = lane_offset(v, std::integral_constant<bool, PANEL_B>{}, Count<ROWB_B>{}, GB, ldb);
+  // first byte of request j (number q of the tile) of an operand whose tile starts at row or column `at`
+  auto start = [&](const bf16 *X, int j, int q, int rows, bool panel, size_t ld, int at) DP_INLINE {
+    if (!TN) return (const char *)X + (size_t)(at + rows * q) * ld;
+    return panel ? (const char *)X + (size_t)(16 * wave) * ld + (size_t)(at + 96 * (j / 3)) * 2
+                 : (const char *)X + (size_t)(rows * q) * ld + (size_t)at * 2;
+  };
   const char *pa[NIA], *pb[NIB];
 #pragma unroll
   for (int j = 0; j < NIA; ++j)
-    pa[j] = uniform_ptr((TN ? (const char *)A + (size_t)(RPA * (first_a + rel(j, GA))) * lda + (size_t)m0 * 2
-                            : (const char *)A + (size_t)(m0 + RPA * (first_a + rel(j, GA))) * lda) - 1024 * (j - lead(j, GA)));
+    pa[j] = uniform_ptr(start(A, j, first_a + rel(j, GA), RPA, PANEL_A, lda, m0) - 1024 * (j - lead(j, GA)));
 #pragma unroll
   for (int j = 0; j < NIB; ++j)
-    pb[j] = uniform_ptr((TN ? (const char *)B + (size_t)(RPB * (first_b + rel(j, GB))) * ldb + (size_t)n0 * 2
-                            : (const char *)B + (size_t)(n0 + RPB * (first_b + rel(j, GB))) * ldb) - 1024 * (j - lead(j, GB)));
+    pb[j] = uniform_ptr(start(B, j, first_b + rel(j, GB), RPB, PANEL_B, ldb, n0) - 1024 * (j - lead(j, GB)));
 
   const int nk = (K + BK - 1) / BK;
   // A K that is no multiple of 64: the k-steps from the second on are shifted back by `dup` elements
@@ -197,13 +214,19 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   const unsigned la0 = (unsigned)first_a * 1024u, lb0 = (unsigned)first_b * 1024u;
   auto m0_a = [&](auto j, unsigned at) DP_INLINE { dma_m0<1024 * rel(lead(j, GA), GA)>(at + la0); };
   auto m0_b = [&](auto j, unsigned at) DP_INLINE { dma_m0<1024 * rel(lead(j, GB), GB)>(at + lb0); };
-  auto ld_a = [&](auto j) DP_INLINE { dma_load<1024 * (j - lead(j, GA))>(voa[j & 1], pa[j]); };
-  auto ld_b = [&](auto j) DP_INLINE { dma_load<1024 * (j - lead(j, GB))>(vob[j & 1], pb[j]); };
+  auto ld_a = [&](auto j) DP_INLINE { dma_load<1024 * (j - lead(j, GA))>(voa[j % VA], pa[j]); };
+  auto ld_b = [&](auto j) DP_INLINE { dma_load<1024 * (j - lead(j, GB))>(vob[j % VB], pb[j]); };
   auto req_a = [&](auto j, unsigned at) DP_INLINE { m0_a(j, at); dma_gap(); ld_a(j); };
   auto req_b = [&](auto j, unsigned at) DP_INLINE { m0_b(j, at); dma_gap(); ld_b(j); };
   // lane offsets of the next k-step (from the first to the second: less by what they have in common)
-  auto adv_a = [&](bool first) DP_INLINE { const unsigned d = first ? step_a - back_a : step_a; voa[0] += d; voa[1] += d; };
-  auto adv_b = [&](bool first) DP_INLINE { const unsigned d = first ? step_b - back_b : step_b; vob[0] += d; vob[1] += d; };
+  auto adv_a = [&](bool first) DP_INLINE {
+    const unsigned d = first ? step_a - back_a : step_a;
+    static_for<VA>([&](auto v) DP_INLINE { voa[v] += d; });
+  };
+  auto adv_b = [&](bool first) DP_INLINE {
+    const unsigned d = first ? step_b - back_b : step_b;
+    static_for<VB>([&](auto v) DP_INLINE { vob[v] += d; });
+  };
 
   // ---- fragment addressing --------------------------------------------------------------
   // A fragment is 16 rows (or columns) x 32 contraction elements: lane l holds row l%16, elements
@@ -225,8 +248,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
       return *reinterpret_cast<const bf16x8 *>(lds + (((base + (is_b ? fb : fa)) ^ (unsigned)(ks << 6)) + (unsigned)blk * 16u * kRowBytes));
     }
     const unsigned rowb = is_b ? ROWB_B : ROWB_A;
-    const unsigned cw = (unsigned)((is_b ? wn : wm) / 8 + blk * 2);        // first chunk of the 16-column block
+    const bool panel = is_b ? PANEL_B : PANEL_A;
+    const unsigned cw = (unsigned)((panel ? 0 : (is_b ? wn : wm) / 8) + blk * 2);   // first chunk of the 16-column block
     const unsigned sw = is_b ? (unsigned)tn_swizzle<ROWB_B>(trow) : (unsigned)tn_swizzle<ROWB_A>(trow);
+    if (panel) base += (unsigned)((is_b ? wn : wm) / 96) * (unsigned)(BK * 192);
     const unsigned off = base + (unsigned)trow * rowb + ((cw ^ sw) << 4) + tlow + (unsigned)ks * 32u * rowb;
     union { s16x4 h[2]; bf16x8 v; } u;
     u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(lds + off));
@@ -346,37 +371,34 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   };
 
   if constexpr (SPLIT) {
-    // ---- ring of five operand tiles -------------------------------------------------------
-    // A 256x256 k-step fills 64 KB of LDS, so only two whole stages fit.  With the A and B
-    // tiles as separate ring entries a fifth tile fits: slot (2k) % 5 holds A(k), slot
-    // (2k+1) % 5 holds B(k).  Request order A0 B0 A1 B1 A2 | B2 A3 | B3 A4 ...: pass k asks
-    // for B(k+1) behind the barrier that freed A(k-1)'s slot, and for A(k+2) into the slot
-    // B(k-1) left; a B tile so has one step to land and an A tile one to two.  (The
+    // ---- rings of three A tiles and two B tiles ---------------------------------------------
+    // A 256x256 k-step fills 64 KB of LDS, so only two whole stages fit, but a third A tile does beside them.
+    // Request order A0 B0 A1 B1 A2 | B2 A3 | B3 A4 ...: pass k asks for B(k+1) and A(k+2) behind the barrier that
+    // freed the slots of B(k-1) and A(k-1); a B tile so has one step to land and an A tile one to two.  (The
     // launcher sends K < 3 * BK elsewhere.)
-    static_assert(BM == BN, "the ring entries are of one size");
-    constexpr unsigned TILE = A_BYTES;
     constexpr int EARLY_REQ = (NIA + NIB) * 3 / 4;   // requests of a pass that go out beside its first slice's MFMAs
     static_for<2>([&](auto t) DP_INLINE {
-      static_for<NIA>([&](auto i) DP_INLINE { req_a(i, 2u * t * TILE); });
+      static_for<NIA>([&](auto i) DP_INLINE { req_a(i, (unsigned)t * A_BYTES); });
       adv_a(t == 0);
-      static_for<NIB>([&](auto i) DP_INLINE { req_b(i, (2u * t + 1u) * TILE); });
+      static_for<NIB>([&](auto i) DP_INLINE { req_b(i, 3u * A_BYTES + (unsigned)t * B_BYTES); });
       adv_b(t == 0);
     });
     wait_vmcnt_mem<NIA + NIB>();
     __syncthreads();
-    // the ring, in LDS bytes: A(kt), B(kt), A(kt+1), B(kt+1), A(kt+2)
-    unsigned s0 = 0, s1 = TILE, s2 = 2 * TILE, s3 = 3 * TILE, s4 = 4 * TILE;
+    // the rings, in LDS bytes: A(kt), A(kt+1), A(kt+2); B(kt), B(kt+1)
+    unsigned a0 = 0, a1 = A_BYTES, a2 = 2 * A_BYTES, b0 = 3 * A_BYTES, b1 = 3 * A_BYTES + B_BYTES;
     // MORE: k-step kt+2 exists (its A tile is requested in this pass)
     auto step = [&](auto first_tag, auto next_tag, auto more_tag) DP_INLINE {
       constexpr bool FIRST = decltype(first_tag)::value, NEXT = decltype(next_tag)::value,
                      MORE = decltype(more_tag)::value;
-      pass(first_tag, next_tag, s0, s1,
+      pass(first_tag, next_tag, a0, b0,
            [&]() DP_INLINE { if (MORE) wait_vmcnt_mem<NIA>(); else wait_vmcnt_mem<0>(); },
-           Count<(!FIRST && NEXT ? NIB : 0)>{}, Count<(MORE ? NIA : 0)>{}, Count<EARLY_REQ>{}, s3, s4);
+           Count<(!FIRST && NEXT ? NIB : 0)>{}, Count<(MORE ? NIA : 0)>{}, Count<EARLY_REQ>{}, b1, a2);
       if (!FIRST && NEXT) adv_b(false);
       if (MORE) adv_a(false);
-      const unsigned t0 = s0, t1 = s1;
-      s0 = s2; s1 = s3; s2 = s4; s3 = t0; s4 = t1;
+      const unsigned ta = a0, tb = b0;
+      a0 = a1; a1 = a2; a2 = ta;
+      b0 = b1; b1 = tb;
     };
     step(Yes{}, Yes{}, Yes{});
     for (int left = nk - 3; left > 0; --left) step(No{}, Yes{}, Yes{});
@@ -518,7 +540,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
 
 template <int BM, int BN, int WGM, int WGN, int STAGES, bool ACT, bool TN, bool SPLIT>
 hipError_t launch_dma_act(const GemmArgs &a, hipStream_t s) {
-  constexpr size_t smem = SPLIT ? (size_t)5 * BM * 128 : (size_t)STAGES * (BM + BN) * 128;
+  constexpr size_t smem = SPLIT ? (size_t)(3 * BM + 2 * BN) * 128 : (size_t)STAGES * (BM + BN) * 128;
   static_assert(smem <= 160 * 1024, "LDS of one CU");
   static bool attr_set = false;
   auto kern = gemm_dma_kernel<BM, BN, WGM, WGN, STAGES, ACT, TN, SPLIT>;
@@ -554,11 +576,18 @@ hipError_t launch_dma_cfg(const GemmArgs &a, hipStream_t s) {
 //   [4096 x 1024] x 1024 NT: 256 of 128x128 10.5 / 13.8 us, 128 of 256x128 15.5 / 19.3, 64 of 256x256 24.5 / 26.9
 //   [2048 x 768] x 3072 NT: 192 of 128x64 17.3 / 24.9 us, 96 of 128x128 20.9 / 31.0, 384 of 64x64 21.4 / 30.3
 //   [1024 x 1024] x 4096 TN: 256 of 64x64 16.0 / 22.8 us, 64 of 128x128 27.8 / 37.0, 128 of 128x64 22.3 / 31.5
-struct TileTime { int bm, bn; float start_us, step_us; };
-enum { k256x256, k256x128, k128x256, k128x128, k128x64, k64x128, k64x64, kTiles };
-constexpr TileTime kTileTimes[kTiles] = {{256, 256, 6.0f, 1.27f}, {256, 128, 4.5f, 0.85f}, {128, 256, 4.5f, 0.85f},
-                                         {128, 128, 2.0f, 0.55f}, {128, 64, 1.5f, 0.40f},  {64, 128, 1.5f, 0.40f},
-                                         {64, 64, 1.5f, 0.26f}};
+// The tiles of 192 rows or columns are there for outputs that leave a round of the others half empty (operands from memory):
+//   [4096 x 4800] x 1600 NT: 400 of 256x192 67 us (304 of 256x256 75, 608 of 128x256 82); [4096 x 3072] x 1024 26.9 (30.0, 37.8)
+//   [1600 x 6400] x 4096 TN: 238 of 256x192 78 us (175 of 256x256 84, 350 of 256x128 108); [6144 x 6144] x 2048 128 (148, 154)
+//   [3441 x 1280] x 1280 NT: 189 of 128x192 17.0 us (135 of 128x256 20.3); [1664 x 4992] x 1896 TN 234 of 192x192 33 (520 of 128x128 37)
+// Over 30 products of drawn stages they take 4 % off the mean, up to 20 %.  Below nine k-steps, where start and output are most of
+// a launch, they gain nothing ([2304 x 3328] x 512 NT: 192x192 14.3 us, 128x256 14.0; TN 14.9 and 14.2): min_steps.
+struct TileTime { int bm, bn; float start_us, step_us; int min_steps; };
+enum { k256x256, k256x192, k192x256, k192x192, k256x128, k128x256, k192x128, k128x192, k128x128, k128x64, k64x128, k64x64, kTiles };
+constexpr TileTime kTileTimes[kTiles] = {
+    {256, 256, 6.0f, 1.27f, 3}, {256, 192, 5.2f, 1.03f, 9}, {192, 256, 5.2f, 1.03f, 9}, {192, 192, 4.0f, 0.88f, 9},
+    {256, 128, 4.5f, 0.83f, 1}, {128, 256, 4.5f, 0.83f, 1}, {192, 128, 3.5f, 0.70f, 9}, {128, 192, 3.5f, 0.70f, 9},
+    {128, 128, 2.0f, 0.55f, 1}, {128, 64, 1.5f, 0.40f, 1},  {64, 128, 1.5f, 0.40f, 1},  {64, 64, 1.5f, 0.26f, 1}};
 constexpr int kCus = 256;
 
 int choose_tile(const GemmArgs &a) {
@@ -569,7 +598,7 @@ int choose_tile(const GemmArgs &a) {
   for (int i = 0; i < kTiles; ++i) {
     const TileTime &t = kTileTimes[i];
     if (a.M < t.bm || a.N < t.bn) continue;
-    if (i == k256x256 && nk < 3) continue;   // (its operand ring)
+    if (nk < t.min_steps) continue;
     const long tiles = (long)((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn);
     const float us = (float)((tiles + kCus - 1) / kCus) * (t.start_us + t.step_us * (float)nk);
     if (best < 0 || us < best_us || (us == best_us && tiles < best_tiles)) { best = i; best_us = us; best_tiles = tiles; }
@@ -586,10 +615,15 @@ hipError_t launch_dma_mode(const GemmArgs &a, hipStream_t s) {
     int bm = 0, bn = 0;
     if (sscanf(force, "%dx%d", &bm, &bn) == 2)
       for (int i = 0; i < kTiles; ++i)
-        if (kTileTimes[i].bm == bm && kTileTimes[i].bn == bn && a.M >= bm && a.N >= bn && (i != k256x256 || a.K > 128)) tile = i;
+        if (kTileTimes[i].bm == bm && kTileTimes[i].bn == bn && a.M >= bm && a.N >= bn && a.K > 128) tile = i;
   }
   switch (tile) {
     case k256x256: return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
+    case k256x192: return launch_dma_cfg<256, 192, 2, 2, 2, TN, true>(a, s);
+    case k192x256: return launch_dma_cfg<192, 256, 2, 2, 2, TN, true>(a, s);
+    case k192x192: return launch_dma_cfg<192, 192, 2, 2, 3, TN>(a, s);
+    case k192x128: return launch_dma_cfg<192, 128, 2, 2, 3, TN>(a, s);
+    case k128x192: return launch_dma_cfg<128, 192, 2, 2, 3, TN>(a, s);
     case k256x128: return launch_dma_cfg<256, 128, 2, 2, 3, TN>(a, s);
     case k128x256: return launch_dma_cfg<128, 256, 2, 2, 3, TN>(a, s);
     // (eight waves: with four, [4096 x 1024] x 4096 NT takes 31.2 us instead of 31.7 with operands in the caches,

@@ -2,7 +2,7 @@
 import pytest
 
 from paper_2505_05856_amd import binding as B
-from test_ops_gpu import GEMM_TILES
+from test_ops_gpu import GEMM_TILES, GEMM_TILES_192
 
 
 @pytest.mark.parametrize("tile,mode,M,N,ks", GEMM_TILES)
@@ -10,6 +10,11 @@ def test_the_gpu_tests_reach_every_tile_ragged(tile, mode, M, N, ks):
     assert M % tile[0] and N % tile[1] and all(k % 64 for k in ks)
     for k in ks:
         assert B.op_gemm_tile(mode, M, N, k) == tile
+
+
+@pytest.mark.parametrize("tile,mode,M,N,ks", GEMM_TILES_192)
+def test_the_gpu_tests_reach_every_192_tile_ragged(tile, mode, M, N, ks):
+    test_the_gpu_tests_reach_every_tile_ragged(tile, mode, M, N, ks)
 
 
 def test_other_kernels_products_have_no_tile():

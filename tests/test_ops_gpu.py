@@ -242,6 +242,20 @@ def test_gemm_every_tile_ragged(tile, mode, M, N, K):
     test_gemm_ragged_k(mode, M, N, K)
 
 
+# The tiles of 192 rows or columns, which take nine k-steps or more: as above, from the fewest on
+GEMM_TILES_192 = [((256, 192), 0, 3670, 2316, (520, 584, 1096)), ((256, 192), 1, 3664, 2312, (515, 577, 1091)),
+                  ((192, 256), 0, 2312, 3656, (520, 584, 1096)), ((192, 256), 1, 2320, 3664, (515, 577, 1091)),
+                  ((192, 192), 0, 2316, 3336, (520, 584, 1096)), ((192, 192), 1, 3336, 2320, (515, 577, 1091)),
+                  ((192, 128), 0, 3212, 1160, (520, 584, 1096)), ((192, 128), 1, 3592, 1032, (515, 577, 1091)),
+                  ((128, 192), 0, 1153, 3236, (520, 584, 1096)), ((128, 192), 1, 1032, 3592, (515, 577, 1091))]
+
+
+@pytest.mark.parametrize("tile,mode,M,N,K", [(t, mode, M, N, K) for t, mode, M, N, ks in GEMM_TILES_192 for K in ks])
+def test_gemm_every_192_tile_ragged(tile, mode, M, N, K):
+    assert B.op_gemm_tile(mode, M, N, K) == tile
+    test_gemm_ragged_k(mode, M, N, K)
+
+
 # fp32 on the matrix cores: ragged against the 32- and 64-row parts and the 16-deep chunks, both waves' arrangements
 # (64x64 and 32x32 tiles with a divided contraction; 128x128 tiles, TN and short NT ones), fewer chunks than waves, rows of 4
 GEMM_F32 = [(0, 4, 4, 4), (0, 33, 36, 20), (0, 65, 132, 68), (0, 1000, 516, 332), (0, 700, 1100, 1028), (1, 4, 4, 4),

@@ -27,13 +27,27 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T *__restrict__ x, co
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= rows) return;
   const T *xr = x + (size_t)row * cols;
+  // All loads of a row go out before the first use, also those of gamma and beta where the registers hold them: with a guard around
+  // each the wave waited for one before it asked for the next.  Lanes past the row read its last columns and use none of them.
+  constexpr bool EARLY = NC * sizeof(T) <= 8;
+  Raw8<T> xv[NC], gv[EARLY ? NC : 1], bv[EARLY ? NC : 1];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) xv[c].load(xr + min((c * 64 + lane) * 8, cols - 8));
+  if (EARLY && y != nullptr) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int col = min((c * 64 + lane) * 8, cols - 8);
+      gv[EARLY ? c : 0].load(gamma + col);
+      bv[EARLY ? c : 0].load(beta + col);
+    }
+  }
   float v[NC][8];
   float sum = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
     const int col = (c * 64 + lane) * 8;
     if (col < cols) {
-      load8(xr + col, v[c]);
+      xv[c].unpack(v[c]);
 #pragma unroll
       for (int i = 0; i < 8; ++i) sum += v[c][i];
     }
@@ -65,8 +79,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T *__restrict__ x, co
     const int col = (c * 64 + lane) * 8;
     if (col < cols) {
       float g[8], b[8], o[8];
-      load8(gamma + col, g);
-      load8(beta + col, b);
+      if (EARLY) { gv[EARLY ? c : 0].unpack(g); bv[EARLY ? c : 0].unpack(b); }
+      else { load8(gamma + col, g); load8(beta + col, b); }
 #pragma unroll
       for (int i = 0; i < 8; ++i) o[i] = g[i] * ((v[c][i] - mean) * rstd) + b[i];
       store8(yr + col, o);
@@ -330,11 +344,11 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
 // thread holds 16..32 elements of a row instead of 64..128: several blocks fit a CU where the
 // wave-per-row form fits one or two waves a SIMD.  The two row sums cross the waves through LDS
 // (one barrier a row; two alternating slots); the next row's loads are issued before that.
-// FULL: the row is exactly NP * 2048 columns wide, every block has a multiple of four rows and RES
-// says whether there is a residual gradient, so the row loop has no branch in it.  (With branches around the loads the compiler
-// can no longer count which of the loads in flight a use needs and waits for all of them, which
-// leaves one row in flight instead of PF.)  Rows past the block's range are then fetched as
-// copies of its last row and never used.
+// RES says whether there is a residual gradient, and no load has a guard: rows past the block's range are fetched as
+// copies of its last row, columns past the row as its last ones, and never used.  (With branches around the loads the
+// compiler can no longer count which of the loads in flight a use needs and waits for all of them, which leaves one row
+// in flight instead of PF: 8000x2560 bf16 with a residual gradient 67 us, now 45; 16384x4000 147 and 117.)
+// FULL: the row is exactly NP * 2048 columns wide and every block has a multiple of four rows, so nothing is guarded at all.
 template <typename T, int NP, bool SUMDX, bool FULL, bool RES>
 __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may alias dx */, const T *__restrict__ x,
                                                           const float *__restrict__ stats,
@@ -359,44 +373,42 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
   // registers as loaded (8 bf16 in 4 registers) and are widened when their row is worked on; the
   // row's two statistics travel with them, and the residual gradient of a row is asked for one
   // row ahead, so that no load is issued and awaited inside a row's own work.
-  constexpr int PF = FULL ? 2 : 4;
+  constexpr int PF = NP == 1 ? 4 : 2;
   Raw8<T> xn[PF][NP], dn[PF][NP], rn[2][NP];
   float mean_n[PF], rstd_n[PF];
+  auto col_at = [&](int c) { const int col = (c * 256 + tid) * 8; return FULL ? col : min(col, cols - 8); };
   auto fetch = [&](int row, auto buf_tag) {
     constexpr int BUF = decltype(buf_tag)::value;
-    if (FULL) row = min(row, row_end - 1); else if (row >= row_end) return;
+    row = min(row, row_end - 1);
     const size_t base = (size_t)row * cols;
     mean_n[BUF] = stats[2 * (size_t)row];
     rstd_n[BUF] = stats[2 * (size_t)row + 1];
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
-      const int col = (c * 256 + tid) * 8;
-      if (FULL || col < cols) { xn[BUF][c].load(x + base + col); dn[BUF][c].load(dy + base + col); }
+      xn[BUF][c].load(x + base + col_at(c));
+      dn[BUF][c].load(dy + base + col_at(c));
     }
   };
   auto fetch_res = [&](int row, auto par_tag) {
     constexpr int PAR = decltype(par_tag)::value;
-    if (FULL) { if (!RES) return; row = min(row, row_end - 1); }
-    else if (dres == nullptr || row >= row_end) return;
-    const size_t base = (size_t)row * cols;
+    if (!RES) return;
+    const size_t base = (size_t)min(row, row_end - 1) * cols;
 #pragma unroll
-    for (int c = 0; c < NP; ++c) {
-      const int col = (c * 256 + tid) * 8;
-      if (FULL || col < cols) rn[PAR][c].load(dres + base + col);
-    }
+    for (int c = 0; c < NP; ++c) rn[PAR][c].load(dres + base + col_at(c));
   };
   auto process = [&](int row, auto buf_tag, auto par_tag) {
     constexpr int BUF = decltype(buf_tag)::value;
     constexpr int PAR = decltype(par_tag)::value;
     const float mean = mean_n[BUF], rstd = rstd_n[BUF];
     const size_t base = (size_t)row * cols;
+    const bool own = FULL || row < row_end;   // (the last rows of a block come in fours too)
     fetch_res(row + 1, std::integral_constant<int, 1 - PAR>{});
     float xh[NP][8], g[NP][8];
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
       const int col = (c * 256 + tid) * 8;
-      if (FULL || col < cols) {
+      if (FULL || (own && col < cols)) {
         float xv[8], dv[8];
         xn[BUF][c].unpack(xv);
         dn[BUF][c].unpack(dv);
@@ -421,11 +433,11 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
 #pragma unroll
     for (int c = 0; c < NP; ++c) {
       const int col = (c * 256 + tid) * 8;
-      if (FULL || col < cols) {
+      if (FULL || (own && col < cols)) {
         float o[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) o[i] = rstd * (g[c][i] - m1 - xh[c][i] * m2);
-        if (FULL ? RES : dres != nullptr) {
+        if (RES) {
           float r[8];
           rn[PAR][c].unpack(r);
 #pragma unroll
@@ -440,34 +452,23 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
     }
   };
   using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2 % PF>; using I3 = std::integral_constant<int, 3 % PF>;
   fetch(row0, I0{});
   fetch(row0 + 1, I1{});
-  if (!FULL) {
-    fetch(row0 + 2, std::integral_constant<int, FULL ? 0 : 2>{});
-    fetch(row0 + 3, std::integral_constant<int, FULL ? 1 : 3>{});
-  }
+  if (PF == 4) { fetch(row0 + 2, I2{}); fetch(row0 + 3, I3{}); }
   fetch_res(row0, I0{});
   // (the trip count of the loop is the same for every thread of the block: the barriers inside match;
-  //  rows alternate between the two residual buffers)
-  if (FULL) {   // (the launcher gives every block a multiple of four rows)
-    for (int row = row0; row < row_end; row += 4) {
-      // (fences: the rows' instruction streams stay apart, or their temporaries add up)
-      process(row, I0{}, I0{});
-      __builtin_amdgcn_sched_barrier(0);
-      process(row + 1, I1{}, I1{});
-      __builtin_amdgcn_sched_barrier(0);
-      process(row + 2, I0{}, I0{});
-      __builtin_amdgcn_sched_barrier(0);
-      process(row + 3, I1{}, I1{});
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  } else {
-    for (int row = row0; row < row_end; row += 4) {
-      process(row, I0{}, I0{});
-      if (row + 1 < row_end) process(row + 1, I1{}, I1{});
-      if (row + 2 < row_end) process(row + 2, std::integral_constant<int, FULL ? 0 : 2>{}, I0{});
-      if (row + 3 < row_end) process(row + 3, std::integral_constant<int, FULL ? 1 : 3>{}, I1{});
-    }
+  //  rows alternate between the two buffers)
+  for (int row = row0; row < row_end; row += 4) {
+    // (fences: the rows' instruction streams stay apart, or their temporaries add up)
+    process(row, I0{}, I0{});
+    __builtin_amdgcn_sched_barrier(0);
+    process(row + 1, I1{}, I1{});
+    __builtin_amdgcn_sched_barrier(0);
+    process(row + 2, I2{}, I0{});
+    __builtin_amdgcn_sched_barrier(0);
+    process(row + 3, I3{}, I1{});
+    __builtin_amdgcn_sched_barrier(0);
   }
   float *prow = part + (size_t)blockIdx.x * NV * cols;
 #pragma unroll
@@ -990,14 +991,22 @@ static hipError_t ln_bwd_t(int rows, int cols, const void *dy, const void *x, co
                      (const T *)x, stats, (const T *)gamma, (const T *)dres, (T *)dx, part, rows, cols, rpb, rms)
 #define DP_LN_BWD_WIDE(NP)                                                    \
   do {                                                                        \
-    if (cols != NP * 2048 || rows % 4 != 0 || rpb % 4 != 0) DP_LN_BWD_WIDE_AS(NP, false, false); \
-    else if (dres != nullptr) DP_LN_BWD_WIDE_AS(NP, true, true);              \
-    else DP_LN_BWD_WIDE_AS(NP, true, false);                                  \
+    const bool full = cols == NP * 2048 && rows % 4 == 0 && rpb % 4 == 0;     \
+    if (dres != nullptr) {                                                    \
+      if (full) DP_LN_BWD_WIDE_AS(NP, true, true); else DP_LN_BWD_WIDE_AS(NP, false, true);    \
+    } else {                                                                  \
+      if (full) DP_LN_BWD_WIDE_AS(NP, true, false); else DP_LN_BWD_WIDE_AS(NP, false, false);  \
+    }                                                                         \
   } while (0)
   switch (ln_chunks(cols)) {
     case 1: DP_LN_BWD(1); break;
     case 2: DP_LN_BWD(2); break;
-    case 4: DP_LN_BWD(4); break;
+    case 4:
+      // A block a row with four of them in flight, against a wave a row (us, operands from memory): with the sums of dx bf16
+      // 8000x1088 26.2 for 29.7, 8000x2048 33.4 for 38.7; fp32 8192x1600 42.8 for 46.5, with a residual gradient 50.9 for 53.3;
+      // but bf16 with a residual gradient 8000x1088 25.4 for 24.2, 8000x2048 36.1 for 35.4, and with the sums 4096x1600 21.7 for 21.4.
+      if (rpb >= 16 && (SUMDX || sizeof(T) == 4)) DP_LN_BWD_WIDE(1); else DP_LN_BWD(4);
+      break;
     case 8: DP_LN_BWD_WIDE(2); break;     // 2049..4096 columns
     default: DP_LN_BWD_WIDE(4); break;    // up to 8192
   }

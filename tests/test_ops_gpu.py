@@ -73,6 +73,14 @@ def test_layernorm(dt, rows, cols, kind):
     assert O.max_rel_err(host(dsum), host(dy2).sum(axis=0)) < TOL[dt]
 
 
+# a block a row: rows cut short (in columns; the last block's, which come in fours), whole ones, up to 2048 columns only from 16 rows
+# a block on (7681); the forward's lanes past the row
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(7681, 1032), (8192, 2048), (41, 2568), (1303, 4088), (6, 520), (33, 5000)])
+def test_layernorm_a_block_a_row(dt, rows, cols):
+    test_layernorm(dt, rows, cols, "layer")
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("kind", [0, 1, 2])
 @pytest.mark.parametrize("rows,cols", [(1237, 8), (77, 1032), (300, 4104)])

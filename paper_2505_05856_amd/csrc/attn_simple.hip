@@ -2,6 +2,7 @@
 // (forward, dQ) or per key row (dK, dV).  This is the fp32 debug mode's
 // attention and the fallback for shapes the MFMA kernels do not take.
 // Scores of one row live in LDS (4 bytes x S per wave), so S <= 4096.
+// Head dimensions up to 128 run the attn_*_rows kernels below, wider ones the attn_*_simple kernels.
 // Operands come through an AttnView: Sq queries from one tensor, Sk keys and values from
 // another (the same packed tensor for self-attention).
 // Dropout (da.thr != 0): element (i, j) of head (b, h) is kept when
@@ -194,10 +195,258 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(AttnView av,
   }
 }
 
+// ------------------------------------------------------------------ head dimensions up to 128
+// What bounds these calls is latency (a stage that checks itself has a few hundred rows), so a wave works on eight of the other side's
+// rows at a time: group g of 8 lanes has row 8 u + g of a batch, lane x of the group its elements 32 t + 4 x .. + 3, t < NT.
+// A load is 16 bytes a lane (fp32) and 128 contiguous bytes a row, all loads of a batch of 8 U rows go out together, a dot
+// product is summed over the group by lane swaps, and the backward's rows are used where they are, for the product that made P and
+// for the one that takes it.  (A lane a row, as in the kernels above, touches 64 lines a load and waits for every 32 bytes; sums over
+// rows went one row at a time.  us, fp32, forward and backward, those kernels / these: 2 x 64 rows, 2 heads of 64 7.2 + 21.4 / 5.9 + 11.4;
+// 4 x 256, 8 heads of 64 96 + 329 / 41 + 89; 4 x 256, 4 heads of 32 27 + 100 / 16 + 30; 2 x 200, 2 heads of 128 28 + 113 / 15 + 31.)
+template <typename T> struct Raw4;
+template <> struct Raw4<float> { f32x4 v; };
+template <> struct Raw4<bf16> { bf16x4 v; };
+
+template <int CTRL> __device__ __forceinline__ float lane_swap(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float group8_sum(float x) {
+  x += lane_swap<0xB1>(x);           // lanes 1 0 3 2
+  x += lane_swap<0x4E>(x);           // lanes 2 3 0 1
+  return x + lane_swap<0x141>(x);    // lane 7 - x of the group
+}
+
+// what a wave and its lanes own, and how they read a row
+template <typename T, int NT>
+struct Rows {
+  int g, x, dh;
+  __device__ __forceinline__ Rows(int lane, int dh_) : g(lane >> 3), x(lane & 7), dh(dh_) {}
+  __device__ __forceinline__ int col(int t) const { return 32 * t + 4 * x; }
+  __device__ __forceinline__ bool has(int t) const { return col(t) < dh; }
+  // this lane's elements of a row that only this wave reads (element by element: its alignment is the caller's)
+  __device__ __forceinline__ void own(const T *p, float (&v)[NT][4]) const {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[t][e] = has(t) ? ldf(p + col(t) + e) : 0.f;
+  }
+  // columns past the head's read its last four; what meets them is zero or not stored (mask() makes them zero)
+  __device__ __forceinline__ void load(const T *p, Raw4<T> (&v)[NT]) const {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) v[t].v = *reinterpret_cast<const decltype(v[t].v) *>(p + min(col(t), dh - 4));
+  }
+  __device__ __forceinline__ float dot(const float (&a)[NT][4], const Raw4<T> (&b)[NT]) const {
+    float s = 0.f;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = has(t) ? s + a[t][e] * (float)b[t].v[e] : s;
+    return group8_sum(s);
+  }
+  static __device__ __forceinline__ void add(float (&acc)[NT][4], float w, const Raw4<T> (&b)[NT]) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t][e] += w * (float)b[t].v[e];
+  }
+  // the sum over the groups, stored by the first
+  __device__ __forceinline__ void store(float (&acc)[NT][4], float mul, T *p) const {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float v = acc[t][e];
+#pragma unroll
+        for (int m = 8; m <= 32; m <<= 1) v += __shfl_xor(v, m, 64);
+        if (g == 0 && has(t)) stf(p + col(t) + e, v * mul);
+      }
+  }
+};
+
+// The row of this wave among (b, h, i), i < n; false: none (such a wave still reaches every barrier)
+__device__ __forceinline__ bool wave_row(int n, int nh, long rows, int &b, int &h, int &i) {
+  const long id = (long)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long at = id < rows ? id : 0;
+  i = (int)(at % n);
+  h = (int)((at / n) % nh);
+  b = (int)(at / ((long)n * nh));
+  return id < rows;
+}
+
+template <typename T, int NT, int U>
+__global__ __launch_bounds__(256) void attn_fwd_rows_kernel(AttnView av, T *__restrict__ o, float *__restrict__ lse, int B, int nh,
+                                                            int dh, int causal, float scale, DropArgs da) {
+  extern __shared__ float smem[];
+  const int Sq = av.Sq, S = av.Sk, lane = threadIdx.x & 63;
+  float *sc = smem + (size_t)(threadIdx.x >> 6) * S;
+  int b, h, i;
+  const bool active = wave_row(Sq, nh, (long)B * nh * Sq, b, h, i);
+  const Rows<T, NT> r(lane, dh);
+  const size_t ld = (size_t)av.ldkv;
+  const T *kb = (const T *)av.k + (size_t)b * S * ld + (size_t)h * dh, *vb = (const T *)av.v + (size_t)b * S * ld + (size_t)h * dh;
+  const int jn = !active ? 0 : causal ? i + 1 : S;
+  float q[NT][4];
+  r.own((const T *)av.q + ((size_t)b * Sq + i) * av.ldq + (size_t)h * dh, q);
+  float m = -INFINITY;
+  for (int j0 = 0; j0 < jn; j0 += 8 * U) {
+    Raw4<T> k[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r.load(kb + (size_t)min(j0 + 8 * u + r.g, jn - 1) * ld, k[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 8 * u + r.g;
+      const float s = scale * r.dot(q, k[u]);
+      if (j < jn) {
+        if (r.x == 0) sc[j] = s;
+        m = fmaxf(m, s);
+      }
+    }
+  }
+  m = wave_max(m);
+  __syncthreads();
+  const DropKeys keys = drop_keys(da.base, (uint32_t)(b * nh + h));
+  float l = 0.f, acc[NT][4] = {};
+  for (int j0 = 0; j0 < jn; j0 += 8 * U) {
+    Raw4<T> v[U][NT];
+    if (o != nullptr) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) r.load(vb + (size_t)min(j0 + 8 * u + r.g, jn - 1) * ld, v[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 8 * u + r.g;
+      if (j < jn) {
+        float p = expf(sc[j] - m);
+        l += p;
+        if (da.thr != 0 && drop_bits((uint32_t)i * (uint32_t)S + (uint32_t)j, keys.k0, keys.k1) < da.thr) p = 0.f;
+        if (o != nullptr) r.add(acc, p, v[u]);
+      }
+    }
+  }
+#pragma unroll
+  for (int x = 8; x <= 32; x <<= 1) l += __shfl_xor(l, x, 64);
+  if (!active) return;
+  if (lse != nullptr && lane == 0) lse[((size_t)b * nh + h) * Sq + i] = m + logf(l);
+  if (o != nullptr) r.store(acc, da.scale / l, o + ((size_t)b * Sq + i) * (size_t)(nh * dh) + (size_t)h * dh);
+}
+
+template <typename T, int NT, int U>
+__global__ __launch_bounds__(256) void attn_bwd_dq_rows_kernel(AttnView av, const T *__restrict__ o, const float *__restrict__ lse,
+                                                               const T *__restrict__ d_o, float *__restrict__ drow, int B, int nh,
+                                                               int dh, int causal, float scale, DropArgs da) {
+  const int Sq = av.Sq, S = av.Sk, lane = threadIdx.x & 63;
+  int b, h, i;
+  if (!wave_row(Sq, nh, (long)B * nh * Sq, b, h, i)) return;
+  const Rows<T, NT> r(lane, dh);
+  const size_t ld = (size_t)av.ldkv, qoff = ((size_t)b * Sq + i) * av.ldq + (size_t)h * dh;
+  const size_t orow = ((size_t)b * Sq + i) * (size_t)(nh * dh) + (size_t)h * dh, lrow = ((size_t)b * nh + h) * Sq + i;
+  const T *kb = (const T *)av.k + (size_t)b * S * ld + (size_t)h * dh, *vb = (const T *)av.v + (size_t)b * S * ld + (size_t)h * dh;
+  const int jn = causal ? i + 1 : S;
+  float q[NT][4], g[NT][4], acc[NT][4] = {};
+  r.own((const T *)av.q + qoff, q);
+  r.own(d_o + orow, g);
+  float dsum = 0.f;
+  {
+    float ov[NT][4];
+    r.own(o + orow, ov);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dsum += g[t][e] * ov[t][e];
+  }
+  dsum = group8_sum(dsum);
+  const float L = lse[lrow];
+  if (lane == 0) drow[lrow] = dsum;
+  const DropKeys keys = drop_keys(da.base, (uint32_t)(b * nh + h));
+  for (int j0 = 0; j0 < jn; j0 += 8 * U) {
+    Raw4<T> k[U][NT], v[U][NT];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const size_t at = (size_t)min(j0 + 8 * u + r.g, jn - 1) * ld;
+      r.load(kb + at, k[u]);
+      r.load(vb + at, v[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int j = j0 + 8 * u + r.g;
+      const float p = expf(scale * r.dot(q, k[u]) - L);
+      float dp = r.dot(g, v[u]);
+      if (da.thr != 0)
+        dp = drop_bits((uint32_t)i * (uint32_t)S + (uint32_t)j, keys.k0, keys.k1) >= da.thr ? dp * da.scale : 0.f;
+      if (j < jn) r.add(acc, p * (dp - dsum), k[u]);
+    }
+  }
+  r.store(acc, scale, (T *)av.dq + qoff);
+}
+
+template <typename T, int NT, int U>
+__global__ __launch_bounds__(256) void attn_bwd_dkv_rows_kernel(AttnView av, const float *__restrict__ lse,
+                                                                const T *__restrict__ d_o, const float *__restrict__ drow, int B,
+                                                                int nh, int dh, int causal, float scale, DropArgs da) {
+  const int S = av.Sq, Sk = av.Sk, lane = threadIdx.x & 63;   // S: the query count
+  int b, h, j;
+  if (!wave_row(Sk, nh, (long)B * nh * Sk, b, h, j)) return;
+  const Rows<T, NT> r(lane, dh);
+  const size_t ld = (size_t)av.ldq, H = (size_t)nh * dh, koff = ((size_t)b * Sk + j) * av.ldkv + (size_t)h * dh;
+  const T *qb = (const T *)av.q + (size_t)b * S * ld + (size_t)h * dh, *gb = d_o + (size_t)b * S * H + (size_t)h * dh;
+  const float *Lr = lse + ((size_t)b * nh + h) * S, *Dr = drow + ((size_t)b * nh + h) * S;
+  float k[NT][4], v[NT][4], ak[NT][4] = {}, av_[NT][4] = {};
+  r.own((const T *)av.k + koff, k);
+  r.own((const T *)av.v + koff, v);
+  const DropKeys keys = drop_keys(da.base, (uint32_t)(b * nh + h));
+  for (int i0 = causal ? j : 0; i0 < S; i0 += 8 * U) {
+    Raw4<T> q[U][NT], g[U][NT];
+    float L[U], D[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = min(i0 + 8 * u + r.g, S - 1);
+      r.load(qb + (size_t)i * ld, q[u]);
+      r.load(gb + (size_t)i * H, g[u]);
+      L[u] = Lr[i];
+      D[u] = Dr[i];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = i0 + 8 * u + r.g;
+      const float p = expf(scale * r.dot(k, q[u]) - L[u]);
+      float dp = r.dot(v, g[u]), pv = p;   // pv: what multiplied V in the forward
+      if (da.thr != 0) {
+        const bool keep = drop_bits((uint32_t)i * (uint32_t)Sk + (uint32_t)j, keys.k0, keys.k1) >= da.thr;
+        pv = keep ? p * da.scale : 0.f;
+        dp = keep ? dp * da.scale : 0.f;
+      }
+      if (i < S) {
+        r.add(av_, pv, g[u]);
+        r.add(ak, p * (dp - D[u]), q[u]);
+      }
+    }
+  }
+  r.store(ak, scale, (T *)av.dk + koff);
+  r.store(av_, 1.f, (T *)av.dv + koff);
+}
+
+// One wave a block while that leaves CUs without work (their rows then come through L1s of their own), four from there on.
+static int waves_a_block(long rows) { return rows >= 2048 ? 4 : 1; }
+static unsigned row_grid(long rows, int w) { return (unsigned)((rows + w - 1) / w); }
+// the kernel of a head dimension: NT pieces of 32 columns, U batches of eight rows in flight
+#define DP_ATTN_ROWS(KERN, rows, lds, ...)                                                                                     \
+  do {                                                                                                                         \
+    const int w = waves_a_block(rows);                                                                                         \
+    const dim3 grid(row_grid(rows, w)), block(64 * w);                                                                         \
+    if (dh <= 32) hipLaunchKernelGGL((KERN<T, 1, 4>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                         \
+    else if (dh <= 64) hipLaunchKernelGGL((KERN<T, 2, 4>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                    \
+    else hipLaunchKernelGGL((KERN<T, 4, 2>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                                  \
+  } while (0)
+
 template <typename T>
 static hipError_t fwd_t(int B, int nh, int dh, int causal, const AttnView &v, void *o, float *lse, const DropArgs &da,
                         hipStream_t s) {
   const long rows = (long)B * nh * v.Sq;
+  if (dh <= 128) {
+    DP_ATTN_ROWS(attn_fwd_rows_kernel, rows, (size_t)v.Sk * sizeof(float), v, (T *)o, lse, B, nh, dh, causal,
+                 1.0f / sqrtf((float)dh), da);
+    return hipGetLastError();
+  }
   const size_t smem = 4 * (size_t)(v.Sk + dh) * sizeof(float);
   hipLaunchKernelGGL((attn_fwd_simple_kernel<T>), dim3((unsigned)((rows + 3) / 4)), dim3(256), smem, s, v, (T *)o, lse,
                      B, nh, dh, causal, 1.0f / sqrtf((float)dh), da);
@@ -218,6 +467,16 @@ static hipError_t bwd_t(int B, int nh, int dh, int causal, const AttnView &v, co
                         const void *d_o, float *ws, const DropArgs &da, hipStream_t s) {
   const long qrows = (long)B * nh * v.Sq, krows = (long)B * nh * v.Sk;
   const float scale = 1.0f / sqrtf((float)dh);
+  if (dh <= 128) {
+    if (qrows > 0 && v.Sk > 0) {
+      DP_ATTN_ROWS(attn_bwd_dq_rows_kernel, qrows, 0, v, (const T *)o, lse, (const T *)d_o, ws, B, nh, dh, causal, scale, da);
+      hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    if (krows > 0)   // (no queries: dK = dV = 0 is still written)
+      DP_ATTN_ROWS(attn_bwd_dkv_rows_kernel, krows, 0, v, lse, (const T *)d_o, ws, B, nh, dh, causal, scale, da);
+    return hipGetLastError();
+  }
   const dim3 block(256);
   if (qrows > 0 && v.Sk > 0) {
     hipLaunchKernelGGL((attn_bwd_dq_simple_kernel<T>), dim3((unsigned)((qrows + 3) / 4)), block,

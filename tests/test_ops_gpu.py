@@ -269,6 +269,9 @@ def test_gemm_every_192_tile_ragged(tile, mode, M, N, K):
 GEMM_F32 = [(0, 4, 4, 4), (0, 33, 36, 20), (0, 65, 132, 68), (0, 1000, 516, 332), (0, 700, 1100, 1028), (1, 4, 4, 4),
             (0, 1413, 1524, 4), (0, 1601, 1604, 20), (0, 1500, 1412, 64), (0, 1500, 1412, 68),
             (1, 36, 20, 5), (1, 68, 132, 67), (1, 516, 1000, 333), (1, 1412, 1524, 129), (1, 1600, 1604, 31)]
+# 16x16 tiles up to 256 of them, 32x32 from there on: cut short on either side of that line, short contractions and long ones
+GEMM_F32_LINE = [(0, 253, 252, 4), (0, 256, 256, 1028), (0, 257, 252, 132), (0, 255, 260, 516), (1, 252, 256, 3), (1, 256, 252, 515),
+                 (1, 260, 252, 67), (1, 20, 2052, 130)]
 
 
 @pytest.mark.parametrize("mode,M,N,K", GEMM_F32)
@@ -287,6 +290,11 @@ def test_gemm_f32(mode, M, N, K):
     c = dev(res, dt)
     B.op_gemm(mode, M, N, K, ta, tb, None, c, c)
     assert O.max_rel_err(host(c), ref + res) < tol
+
+
+@pytest.mark.parametrize("mode,M,N,K", GEMM_F32_LINE)
+def test_gemm_f32_small_tiles(mode, M, N, K):
+    test_gemm_f32(mode, M, N, K)
 
 
 # a short contraction over a large output takes a form of its own, which adds chunk sums as the waves of the other form do:
@@ -338,6 +346,15 @@ def test_attention(dt, causal, Bn, S, nh, dh, sharp):
     got = host(dqkv)
     for blk in range(3):
         assert O.max_rel_err(got[:, blk * H:(blk + 1) * H], dq_ref[:, blk * H:(blk + 1) * H]) < 2 * tol, blk
+
+
+# a wave a row on the vector ALUs: pieces of 32 columns cut short and whole, the widest head they take and the first they do not,
+# batches of eight rows cut short, blocks of four waves (from 2048 rows) with waves left over
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Bn,S,nh,dh", [(1, 1, 1, 32), (2, 7, 3, 24), (1, 33, 2, 40), (3, 65, 2, 72), (1, 47, 2, 128), (1, 31, 2, 136),
+                                        (1, 685, 3, 40), (2, 256, 4, 64)])
+def test_attention_rows(Bn, S, nh, dh, causal):
+    test_attention(torch.float32, causal, Bn, S, nh, dh, False)
 
 
 # the forward's tile loop: one tile, two, odd and even counts, tiles that end on and just past a boundary, with none, some and

@@ -58,17 +58,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
   constexpr int NV = TN ? 4 : F, VW = TN ? F : 4;
   typedef typename Vec<VW>::t vec;
   vec a[D][NV], b[D][NV];
+  // (NT, small tiles: of a chunk past the last, all lanes read one place.  With every lane at its own row those loads touch 16 lines
+  //  each and took the memory pipe as long as useful ones: [128 x 128] x 128 in 32x32 tiles 5.3 us, now 4.1; no gain in the other forms)
   auto load = [&](int c, vec (&va)[NV], vec (&vb)[NV]) {
+    const bool in = TN || F == 4 || c < nch;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       if (TN) {
         const size_t k = (size_t)min(16 * c + 4 * i + g, K - 1);
-        va[i] = *reinterpret_cast<const vec *>(pa[0] + k * M);
-        vb[i] = *reinterpret_cast<const vec *>(pb[0] + k * N);
+        va[i] = *reinterpret_cast<const vec *>(in ? pa[0] + k * M : A);
+        vb[i] = *reinterpret_cast<const vec *>(in ? pb[0] + k * N : B);
       } else {
         const int k = min(16 * c + 4 * g, K - 4);
-        va[i] = *reinterpret_cast<const vec *>(pa[i] + k);
-        vb[i] = *reinterpret_cast<const vec *>(pb[i] + k);
+        va[i] = *reinterpret_cast<const vec *>(in ? pa[i] + k : A);
+        vb[i] = *reinterpret_cast<const vec *>(in ? pb[i] + k : B);
       }
     }
   };
@@ -176,6 +179,9 @@ bool gemm_f32_supported(const GemmArgs &a) {
 //   [256 x 1024] x 333 TN: 64 tiles of 64x64 10.2 us, 256 of 32x32 7.6; [333 x 256] x 1024 NT 21.2 and 10.3;
 //   [1024 x 1024] x 1024 NT: 256 tiles of 64x64 23.6 us (91 TFLOP/s of the 147 the instruction reaches alone),
 //   1024 of 32x32 37.0.
+// 16x16 tiles while each has a CU to itself (256): a load touches 16 lines whatever the tile, and that many CUs share them.  32x32 / 16x16:
+//   [128 x 128] x 128, 512 NT: 4.1 / 3.0 us, 6.7 / 4.2; [128 x 512] x 128 TN 4.1 / 3.2; [256 x 256] x 1024 NT 10.1 / 5.9; past that line
+//   [256 x 768] x 256 NT 5.2 / 5.4, [512 x 512] x 300 TN 5.7 / 7.7.
 // TN with enough tiles of 128x128 for half the chip: a wave each 64x64, no division ([1024 x 4096] x 4096: 257 us
 // against 311).  In NT form, whose loads take 16 rows at a time, the division stays ahead ([4096 x 4096] x 1024 352
 // against 505) but for contractions of at most four chunks, which leave its waves one each at most to share the turn
@@ -190,6 +196,7 @@ hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
     if (a.mode == kGemmTN) return launch_f32<4, 2, true, false>(a, s);
     if (a.K <= 64) return launch_f32<4, 2, false, false>(a, s);
   }
+  if (tiles(16) <= 256) return a.mode == kGemmTN ? launch_f32<1, 4, true, true>(a, s) : launch_f32<1, 4, false, true>(a, s);
   if (a.mode == kGemmTN) {
     return tiles(64) >= 128 ? launch_f32<4, 2, true, true>(a, s) : launch_f32<2, 4, true, true>(a, s);
   }

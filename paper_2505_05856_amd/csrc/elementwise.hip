@@ -656,7 +656,7 @@ __global__ __launch_bounds__(256) void gelu_fwd_kernel(const T *__restrict__ x, 
     float v[8];
     load8(x + i * 8, v);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = gelu_f(v[k], kind);
+    for (int k = 0; k < 8; ++k) v[k] = gelu_f<T>(v[k], kind);
     store8(y + i * 8, v);
   }
 }
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(64 * NW) void gelu_bwd_colsum_kernel(const T *dy /*
       load8(dy + at, d);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        v[i] = d[i] * gelu_df(v[i], kind);
+        v[i] = d[i] * gelu_df<T>(v[i], kind);
         acc[i] += (float)(T)v[i];
       }
       store8(dx + at, v);
@@ -780,7 +780,7 @@ __global__ __launch_bounds__(1024) void gelu_bwd_slab_kernel(const T *dy /* may 
                 g[u].unpack(d);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
-                  a[i] = d[i] * gelu_df(a[i], kind);
+                  a[i] = d[i] * gelu_df<T>(a[i], kind);
                   acc[i] += (float)(T)a[i];   // the value as stored
                 }
                 store8(dx + (size_t)row * cols + col, a);

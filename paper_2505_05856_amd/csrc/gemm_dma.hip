@@ -512,8 +512,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
           // GELU of C gives the same bits
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            g0.v[q] = (bf16)gelu_f((float)o0.v[q], gelu_kind);
-            g1.v[q] = (bf16)gelu_f((float)o1.v[q], gelu_kind);
+            g0.v[q] = (bf16)gelu_f<bf16>((float)o0.v[q], gelu_kind);
+            g1.v[q] = (bf16)gelu_f<bf16>((float)o1.v[q], gelu_kind);
           }
           swap2(g0.u, g1.u);
         }

@@ -293,7 +293,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
         C[(long)row * N + col] = stored;
         // fused activation: computed from the value as stored, so that a later standalone
         // GELU of C gives the same bits
-        if (C2 != nullptr) C2[(long)row * N + col] = (bf16)gelu_f((float)stored, gelu_kind);
+        if (C2 != nullptr) C2[(long)row * N + col] = (bf16)gelu_f<bf16>((float)stored, gelu_kind);
       }
     }
   }

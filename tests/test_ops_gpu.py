@@ -104,6 +104,21 @@ def test_gelu(dt, kind, rows, cols):
     assert torch.equal(tdy, dx) and torch.equal(db2, db)
 
 
+def test_gelu_tanh_bf16_far_out():
+    """The logistic form of the tanh approximation where its exponential is 0 or overflows."""
+    x = torch.tensor([float("inf"), float("nan"), 1e15, -1e15, 3e38, -3e38, 0.0, -0.0, 20.0, -20.0, -100.0, -6.0, 6.0, 1e-30, -1e13, 2e13],
+                     dtype=torch.bfloat16, device=DEV).view(2, 8)
+    y, dx, db = torch.empty_like(x), torch.empty_like(x), torch.empty(8, dtype=torch.bfloat16, device=DEV)
+    B.op_gelu_fwd(x, y, 1)
+    B.op_gelu_bwd(torch.ones_like(x), x, dx, db, ws_for(2, 8), 1)
+    x64 = x.double()
+    s = torch.sigmoid(1.5957691216057308 * (x64 + 0.044715 * x64 ** 3))
+    assert torch.allclose(y.double(), x64 * s, rtol=2.0 ** -8, atol=1e-12, equal_nan=True)      # one rounding to bf16
+    want = s + x64 * s * (1 - s) * 1.5957691216057308 * (1 + 0.134145 * x64 ** 2)
+    far = x.abs() > 1e19    # the square overflows in 32 bits
+    assert torch.allclose(dx.double()[~far], want[~far], rtol=2.0 ** -7, atol=1e-9, equal_nan=True)
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("rows,cols", [(1, 8), (33, 24), (1000, 1600), (4096, 520)])
 def test_colsum(dt, rows, cols):

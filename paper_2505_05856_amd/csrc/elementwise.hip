@@ -924,13 +924,16 @@ hipError_t launch_ln_fwd(int dtype, int rows, int cols, float eps, const void *x
                         : ln_fwd_t<float>(rows, cols, eps, x, gamma, beta, y, stats, s, rms ? 1 : 0);
 }
 
-// Where the one-launch forms end (two launches / one, us, operands in the caches):
-//   column sums, bf16: 128x128 4.3 / 3.1, 1000x3072 5.6 / 3.8, 2048x2048 5.1 / 4.6; fp32 2048x2048 5.7 / 4.5
-//   GELU backward, bf16: 128x128 8.4 / 3.5, 512x512 8.4 / 4.8, 1000x768 9.3 / 6.7, 512x4096 9.4 / 6.6, but
-//     1000x1600 7.2 / 8.5 (few slabs, and the derivative is vector work: up to 1024 columns 16 a slab, not 32, for twice the blocks)
-//   LayerNorm backward, bf16: 128x128 5.9 / 4.8, 1000x768 9.4 / 6.0, 1000x2048 14.3 / 7.7, 2048x768 8.8 / 7.8; fp32, twice the
-//     bytes a slab: 1000x2048 18.4 / 11.5, but 2048x768 10.2 / 15.7
-constexpr int kSlabRows = 2048, kLnSlabBytes = 4096;
+// Where the one-launch forms end (two launches / one, us; warm: operands in the caches, cold: from memory, where a slab's short
+// pieces of many rows cost more):
+//   column sums: bf16 1000x3072 warm 7.7 / 4.7, cold 7.7 / 5.0, 1500x4096 cold 8.3 / 7.5, but 2048x3072 7.8 / 8.8; fp32 2048x1024 cold
+//     8.9 / 7.1, 2048x3072 8.6 / 11.1: up to 2048 rows and below 12 MiB
+//   GELU backward (16 columns a slab up to 1024, 32 from there on): bf16 500x1024 cold 7.5 / 6.1, 500x4096 warm 7.4 / 6.5, cold 7.5 / 8.2,
+//     1000x1024 cold 7.3 / 9.3; fp32 250x1024 7.4 / 5.5, 500x1024 7.4 / 7.5, 1000x1024 7.9 / 13.2: 512 and 256 rows
+//   LayerNorm backward: bf16 1000x768 warm 8.6 / 6.0, cold 9.1 / 7.5, 1000x2048 13.6 / 10.4, but 1500x1024 9.8 / 11.5, 2048x1024 10.0 / 14.2;
+//     fp32 512x1024 8.5 / 7.6, but 1024x1024 9.3 / 11.3: 1024 and 512 rows
+constexpr int kSlabRows = 2048, kLnSlabBytes = 2048, kGeluSlabBytes = 1024;
+constexpr size_t kSlabBytes = (size_t)12 << 20;
 // The sums are written while other blocks still read: calls whose outputs lie in what those read keep the two launches.
 static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
@@ -1061,7 +1064,7 @@ template <typename T>
 static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy, const void *x, void *dx,
                                     void *dbias, void *ws, hipStream_t s, ReduceJob *job) {
   const size_t mat = (size_t)rows * cols * sizeof(T), vec = (size_t)cols * sizeof(T);
-  if (job == nullptr && rows <= (cols <= 1024 ? 1024 : 512) && !overlap(dbias, vec, dy, mat) && !overlap(dbias, vec, x, mat)) {
+  if (job == nullptr && rows <= kGeluSlabBytes / (int)sizeof(T) && !overlap(dbias, vec, dy, mat) && !overlap(dbias, vec, x, mat)) {
     if (cols <= 1024)
       hipLaunchKernelGGL((gelu_bwd_slab_kernel<T, 16>), dim3((cols + 15) / 16), dim3(1024), 0, s, (const T *)dy, (const T *)x,
                          (T *)dx, (T *)dbias, rows, cols, kind);
@@ -1150,7 +1153,7 @@ hipError_t launch_dropout_colsum(int dtype, int rows, int cols, const void *x, v
 
 template <typename T>
 static hipError_t colsum_t(int rows, int cols, const void *x, void *out, void *ws, hipStream_t s, ReduceJob *job) {
-  if (job == nullptr && rows <= kSlabRows && !overlap(out, (size_t)cols * sizeof(T), x, (size_t)rows * cols * sizeof(T))) {
+  if (job == nullptr && rows <= kSlabRows && (size_t)rows * cols * sizeof(T) < kSlabBytes && !overlap(out, (size_t)cols * sizeof(T), x, (size_t)rows * cols * sizeof(T))) {
     hipLaunchKernelGGL((colsum_slab_kernel<T, 32>), dim3((cols + 31) / 32), dim3(1024), 0, s, (const T *)x, (T *)out, rows, cols);
     return hipGetLastError();
   }

@@ -216,6 +216,14 @@ __device__ __forceinline__ float group8_sum(float x) {
   return x + lane_swap<0x141>(x);    // lane 7 - x of the group
 }
 
+// P from a dot product and the row's log-sum-exp.  The scaled product is rounded as the forward rounds it (no fused multiply-subtract),
+// so that a row's only key has P = 1 exactly.
+__device__ __forceinline__ float row_prob(float dot, float scale, float lse) {
+#pragma clang fp contract(off)
+  const float s = scale * dot;
+  return expf(s - lse);
+}
+
 // what a wave and its lanes own, and how they read a row
 template <typename T, int NT>
 struct Rows {
@@ -369,7 +377,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_rows_kernel(AttnView av, cons
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = j0 + 8 * u + r.g;
-      const float p = expf(scale * r.dot(q, k[u]) - L);
+      const float p = row_prob(r.dot(q, k[u]), scale, L);
       float dp = r.dot(g, v[u]);
       if (da.thr != 0)
         dp = drop_bits((uint32_t)i * (uint32_t)S + (uint32_t)j, keys.k0, keys.k1) >= da.thr ? dp * da.scale : 0.f;
@@ -408,7 +416,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_rows_kernel(AttnView av, con
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int i = i0 + 8 * u + r.g;
-      const float p = expf(scale * r.dot(k, q[u]) - L[u]);
+      const float p = row_prob(r.dot(k, q[u]), scale, L[u]);
       float dp = r.dot(v, g[u]), pv = p;   // pv: what multiplied V in the forward
       if (da.thr != 0) {
         const bool keep = drop_bits((uint32_t)i * (uint32_t)Sk + (uint32_t)j, keys.k0, keys.k1) >= da.thr;

@@ -94,8 +94,8 @@ __global__ __launch_bounds__(256) void ln_fwd_kernel(const T *__restrict__ x, co
 // bias gradient of the linear layer that produced LayerNorm's input).
 // AHEAD: a wave asks for its next row while it works on the current one (pays when a wave has
 // several rows; with two rows a wave the registers it takes cost more than it returns).
-// NW waves a block: with 4 a wave has two rows and more; the forms of 8 and 16 (not AHEAD) give each row of a block a wave of its
-// own, and 16 waves halve the blocks and with them the partial rows.
+// NW waves a block: with 4 a wave has two rows and more; the form of 8 (not AHEAD, blocks of at most eight rows) gives each row of
+// a block a wave of its own; the second four leave xhat where the others have dgamma (their dbeta is dy), see the sums' order.
 template <typename T, int NC, bool SUMDX, bool AHEAD, int NW>
 __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alias dx */, const T *__restrict__ x,
                                                      const float *__restrict__ stats, const T *__restrict__ gamma,
@@ -105,7 +105,8 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
   // derivative of the mean, mean(g), drops out: dx = rstd (g - xhat mean(g xhat))
   constexpr int NV = SUMDX ? 3 : 2;
   __shared__ float red[NW][NV][512];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = NW == 8 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
   const int row_end = min(rows, (int)(blockIdx.x + 1) * rpb);
   float dg[NC][8], db[NC][8], ds[SUMDX ? NC : 1][8];
 #pragma unroll
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
   #pragma unroll
           for (int i = 0; i < 8; ++i) {
             xh[c][i] = (xh[c][i] - mean) * rstd;
-            dg[c][i] += d[i] * xh[c][i];
+            if (NW == 8 && wave >= 4) dg[c][i] = xh[c][i]; else dg[c][i] += d[i] * xh[c][i];
             db[c][i] += d[i];
             g[c][i] = d[i] * gm[i];
             s1 += g[c][i];
@@ -311,7 +312,7 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
       }
     }
   }
-  // ordered block reduction of the four waves' column partials, 512 columns at a time
+  // ordered block reduction of the waves' column partials, 512 columns at a time
   float *prow = part + (size_t)blockIdx.x * NV * cols;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
@@ -324,14 +325,32 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
       if (SUMDX) red[wave][NV - 1][lane * 8 + i] = ds[c][i];
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < NV * 512; j += 64 * NW) {
-      const int which = j >> 9, k = j & 511;
-      const int col = c * 512 + k;
+    if constexpr (NW == 8) {
+      // wave w + 4 has the row that comes second in wave w of four: it is added to that wave's sums first (dgamma's product
+      // unrounded), so the two forms give the same bits
+      const int k = threadIdx.x, col = c * 512 + k;
       if (col < cols) {
-        float t = red[0][which][k];
+        float t[NV];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) t += red[w][which][k];
-        prow[(size_t)which * cols + col] = t;
+        for (int w = 0; w < 4; ++w) {
+          float v[NV];
+#pragma unroll
+          for (int n = 1; n < NV; ++n) v[n] = red[w][n][k] + red[w + 4][n][k];
+          v[0] = __builtin_fmaf(red[w + 4][1][k], red[w + 4][0][k], red[w][0][k]);
+#pragma unroll
+          for (int n = 0; n < NV; ++n) t[n] = w == 0 ? v[n] : t[n] + v[n];
+        }
+#pragma unroll
+        for (int n = 0; n < NV; ++n) prow[(size_t)n * cols + col] = t[n];
+      }
+    } else {
+      for (int j = threadIdx.x; j < NV * 512; j += 256) {
+        const int which = j >> 9, k = j & 511;
+        const int col = c * 512 + k;
+        if (col < cols) {
+          const float t = ((red[0][which][k] + red[1][which][k]) + red[2][which][k]) + red[3][which][k];
+          prow[(size_t)which * cols + col] = t;
+        }
       }
     }
   }
@@ -971,12 +990,13 @@ template <typename T, bool SUMDX>
 static hipError_t ln_bwd_t(int rows, int cols, const void *dy, const void *x, const float *stats,
                            const void *gamma, const void *dres, void *dx, void *dgamma, void *dbeta, void *dxsum,
                            void *ws, hipStream_t s, ReduceJob *job, int rms) {
-  // One row a wave (us, both passes, bf16 with the column sums of dx, 4 waves a block / this): up to 2048 rows 8 waves, 512x512
-  // 7.4 / 6.5, 1000x1600 15.5 / 12.5, 2048x2048 18.4 / 15.3 (fp32 21.0 / 19.1); then 16 waves in half the blocks, 4096x1024
-  // 14.4 / 12.6, where the registers hold a row: in bf16 up to 1024 columns (4096x1600 21 / 54).
-  const bool wide_block = rows > 2048 && rows <= 4096 && cols <= 1024 && sizeof(T) == 2;
+  // A row a wave (us, both passes, 4 waves a block / 8, operands in the caches; from memory): up to 256 blocks, one a CU, at any
+  // width (with the sums of dx bf16 2048x2048 16.2 / 13.4; 17.8 / 14.4, but 2049x2048 16.2 / 17.6; 17.9 / 21.1), and for rows of up
+  // to 2 KB up to 512 blocks (bf16 4096x1024 14.2 / 13.0; 13.8 / 13.6, fp32 4096x512 11.5 / 9.9; 11.8 / 11.6, but 3072x768 12.5 / 13.1;
+  // 13.5 / 15.1), with a residual gradient too up to 384 (bf16 3072x1024 13.0 / 11.5; 13.6 / 13.2, 3600x1024 14.8 / 13.6; 15.5 / 15.6).
+  const bool row_a_wave = rows <= 2048 || (cols * sizeof(T) <= 2048 && rows <= (dres == nullptr ? 4096 : 3072));
   int rpb;
-  const int nb = row_blocks(rows, wide_block ? 16 : 8, &rpb);
+  const int nb = row_blocks(rows, 8, &rpb);
   const int nv = SUMDX ? 3 : 2;
   float *part = (float *)ws;
 #define DP_LN_BWD_AS(NC, AHEAD, NW)                                                                                    \
@@ -984,8 +1004,7 @@ static hipError_t ln_bwd_t(int rows, int cols, const void *dy, const void *x, co
                      stats, (const T *)gamma, (const T *)dres, (T *)dx, part, rows, cols, rpb, rms)
 #define DP_LN_BWD(NC)                                                               \
   do {                                                                              \
-    if (rows <= 2048) DP_LN_BWD_AS(NC, false, 8);                                   \
-    else if (wide_block) DP_LN_BWD_AS((NC < 2 ? NC : 2), false, 16);                \
+    if (row_a_wave) DP_LN_BWD_AS(NC, false, 8);                                     \
     else if (NC <= 2 || rpb >= 16) DP_LN_BWD_AS(NC, true, 4);                       \
     else DP_LN_BWD_AS(NC, false, 4);                                                \
   } while (0)

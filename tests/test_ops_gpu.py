@@ -221,6 +221,51 @@ def test_norm_backward_waves(dt, rows, cols):
             assert O.max_rel_err(host(ds), host(dx).sum(axis=0)) < TOL[dt]
 
 
+def ordered_sums(a, min_rows, factor=None):
+    """Column sums of fp32 rows in the two-pass order: blocks of at least `min_rows` rows, wave w of four adds rows w, w + 4, ...
+    (with a factor: products, unrounded), the waves in turn, then block g, g + 16, ... in 16 groups, the groups in turn."""
+    rows, cols = a.shape
+    nb = min(512, -(-rows // min_rows))
+    rpb = -(-rows // nb)
+    nb = -(-rows // rpb)
+    acc = np.zeros((nb, 4, cols), np.float32)
+    for at in range(0, rpb, 4):
+        r = np.arange(nb)[:, None] * rpb + at + np.arange(4)
+        ok = ((r < rows) & (at + np.arange(4) < rpb))[..., None]
+        r = np.minimum(r, rows - 1)
+        v = a[r] if factor is None else a[r].astype(np.longdouble) * factor[r]
+        acc = np.where(ok, (acc + v).astype(np.float32), acc)
+    part = ((acc[:, 0] + acc[:, 1]) + acc[:, 2]) + acc[:, 3]
+    out = np.zeros(cols, np.float32)
+    for g in range(16):
+        s = np.zeros(cols, np.float32)
+        for b in range(g, nb, 16):
+            s += part[b]
+        out += s
+    return out
+
+
+# however many waves take a block's rows, the sums keep the order of four: the same bits at every row count (row counts on either
+# side of each rule; blocks cut short)
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(3, 24), (9, 1608), (1000, 776), (2048, 2048), (2049, 520), (2049, 1032), (3072, 512), (3073, 512),
+                                       (4096, 1024), (4097, 72)])
+def test_norm_backward_sums_keep_their_order(dt, rows, cols):
+    tx, tdy, tres = (dev(rnd((rows, cols), seed, dt), dt) for seed in (11, 14, 15))
+    tg = dev(rnd((cols,), 12, dt) * 0.1 + 1, dt)
+    y, stats = torch.empty_like(tx), torch.empty(rows, 2, dtype=torch.float32, device=DEV)
+    B.op_layernorm_fwd(tx, tg, tg, 1e-5, y, stats)
+    st, f32 = stats.cpu().numpy(), lambda t: t.float().cpu().numpy()
+    xhat = (f32(tx) - st[:, :1]) * st[:, 1:]
+    want_dg, want_db = ordered_sums(f32(tdy), 8, xhat), ordered_sums(f32(tdy), 8)
+    for res in (None, tres):
+        dx, (dg, db, ds) = torch.empty_like(tx), (torch.empty_like(tg) for _ in range(3))
+        B.op_layernorm_bwd(tdy, tx, stats, tg, res, dx, dg, db, ws_for(rows, cols), dx_colsum=ds)
+        assert torch.equal(dg.cpu(), torch.from_numpy(want_dg).to(dt)) and torch.equal(db.cpu(), torch.from_numpy(want_db).to(dt))
+        if dt == torch.bfloat16:   # (in fp32 the sum may take the value before its rounding)
+            assert torch.equal(ds.cpu(), torch.from_numpy(ordered_sums(f32(dx), 8)).to(dt))
+
+
 # K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, four and more,
 # and C, bias and residual rows of 8-byte alignment only (N a multiple of 4)
 GEMM_RAGGED_K = [(0, 256, 264, 72), (0, 1096, 1304, 248), (0, 3904, 4200, 200), (0, 3904, 4200, 456), (0, 200, 132, 136),

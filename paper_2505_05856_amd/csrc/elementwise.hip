@@ -392,7 +392,7 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
   // registers as loaded (8 bf16 in 4 registers) and are widened when their row is worked on; the
   // row's two statistics travel with them, and the residual gradient of a row is asked for one
   // row ahead, so that no load is issued and awaited inside a row's own work.
-  constexpr int PF = NP == 1 ? 4 : 2;
+  constexpr int PF = 2;
   Raw8<T> xn[PF][NP], dn[PF][NP], rn[2][NP];
   float mean_n[PF], rstd_n[PF];
   auto col_at = [&](int c) { const int col = (c * 256 + tid) * 8; return FULL ? col : min(col, cols - 8); };
@@ -471,10 +471,8 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
     }
   };
   using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2 % PF>; using I3 = std::integral_constant<int, 3 % PF>;
   fetch(row0, I0{});
   fetch(row0 + 1, I1{});
-  if (PF == 4) { fetch(row0 + 2, I2{}); fetch(row0 + 3, I3{}); }
   fetch_res(row0, I0{});
   // (the trip count of the loop is the same for every thread of the block: the barriers inside match;
   //  rows alternate between the two buffers)
@@ -484,9 +482,9 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
     __builtin_amdgcn_sched_barrier(0);
     process(row + 1, I1{}, I1{});
     __builtin_amdgcn_sched_barrier(0);
-    process(row + 2, I2{}, I0{});
+    process(row + 2, I0{}, I0{});
     __builtin_amdgcn_sched_barrier(0);
-    process(row + 3, I3{}, I1{});
+    process(row + 3, I1{}, I1{});
     __builtin_amdgcn_sched_barrier(0);
   }
   float *prow = part + (size_t)blockIdx.x * NV * cols;
@@ -1023,12 +1021,7 @@ static hipError_t ln_bwd_t(int rows, int cols, const void *dy, const void *x, co
   switch (ln_chunks(cols)) {
     case 1: DP_LN_BWD(1); break;
     case 2: DP_LN_BWD(2); break;
-    case 4:
-      // A block a row with four of them in flight, against a wave a row (us, operands from memory): with the sums of dx bf16
-      // 8000x1088 26.2 for 29.7, 8000x2048 33.4 for 38.7; fp32 8192x1600 42.8 for 46.5, with a residual gradient 50.9 for 53.3;
-      // but bf16 with a residual gradient 8000x1088 25.4 for 24.2, 8000x2048 36.1 for 35.4, and with the sums 4096x1600 21.7 for 21.4.
-      if (rpb >= 16 && (SUMDX || sizeof(T) == 4)) DP_LN_BWD_WIDE(1); else DP_LN_BWD(4);
-      break;
+    case 4: DP_LN_BWD(4); break;
     case 8: DP_LN_BWD_WIDE(2); break;     // 2049..4096 columns
     default: DP_LN_BWD_WIDE(4); break;    // up to 8192
   }

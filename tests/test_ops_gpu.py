@@ -73,8 +73,8 @@ def test_layernorm(dt, rows, cols, kind):
     assert O.max_rel_err(host(dsum), host(dy2).sum(axis=0)) < TOL[dt]
 
 
-# a block a row: rows cut short (in columns; the last block's, which come in fours), whole ones, up to 2048 columns only from 16 rows
-# a block on (7681); the forward's lanes past the row
+# 16 rows a block and more (7681), a block a row: rows cut short (in columns; the last block's, which come in fours), whole ones;
+# the forward's lanes past the row
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("rows,cols", [(7681, 1032), (8192, 2048), (41, 2568), (1303, 4088), (6, 520), (33, 5000)])
 def test_layernorm_a_block_a_row(dt, rows, cols):
@@ -264,6 +264,22 @@ def test_norm_backward_sums_keep_their_order(dt, rows, cols):
         assert torch.equal(dg.cpu(), torch.from_numpy(want_dg).to(dt)) and torch.equal(db.cpu(), torch.from_numpy(want_db).to(dt))
         if dt == torch.bfloat16:   # (in fp32 the sum may take the value before its rounding)
             assert torch.equal(ds.cpu(), torch.from_numpy(ordered_sums(f32(dx), 8)).to(dt))
+
+
+# a row's dx does not depend on how many rows a call has (8 rows a block and 16 or more, several to a wave)
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [1032, 1600, 2048])
+def test_norm_backward_rows_alone_and_among_others(dt, cols):
+    rows, few = 8192, 3000
+    tx, tdy = dev(rnd((rows, cols), 11, dt), dt), dev(rnd((rows, cols), 14, dt), dt)
+    tg, stats = dev(rnd((cols,), 12, dt) * 0.1 + 1, dt), torch.empty(rows, 2, dtype=torch.float32, device=DEV)
+    B.op_layernorm_fwd(tx, tg, tg, 1e-5, torch.empty_like(tx), stats)
+    out = []
+    for n in (rows, few):
+        dx, (dg, db, ds) = torch.empty_like(tx[:n]), (torch.empty_like(tg) for _ in range(3))
+        B.op_layernorm_bwd(tdy[:n], tx[:n], stats[:n], tg, None, dx, dg, db, ws_for(n, cols), dx_colsum=ds)
+        out.append(dx[:few])
+    assert torch.equal(*out)
 
 
 # K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, four and more,

@@ -356,6 +356,12 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
   }
 }
 
+// a + b with both rounded before (no fused multiply-add where one of them is a product)
+__device__ __forceinline__ float add_rounded(float a, float b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
+
 // LayerNorm backward for wide rows (more than 2048 columns): a block per row, the columns
 // dealt out over its 256 threads (thread t owns the 8-column groups t, t + 256, ...), rows of
 // the block's range one after the other.  A thread's column accumulators are then complete sums
@@ -367,7 +373,8 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
 // copies of its last row, columns past the row as its last ones, and never used.  (With branches around the loads the
 // compiler can no longer count which of the loads in flight a use needs and waits for all of them, which leaves one row
 // in flight instead of PF: 8000x2560 bf16 with a residual gradient 67 us, now 45; 16384x4000 147 and 117.)
-// FULL: the row is exactly NP * 2048 columns wide and every block has a multiple of four rows, so nothing is guarded at all.
+// FULL: the row is exactly NP * 2048 columns wide and every block has a multiple of four rows, so nothing is guarded at all.  (In fp32
+// its additions of the residual gradient and to the sums of dx take dx before it is rounded, the other form's after.)
 template <typename T, int NP, bool SUMDX, bool FULL, bool RES>
 __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may alias dx */, const T *__restrict__ x,
                                                           const float *__restrict__ stats,
@@ -460,12 +467,15 @@ __global__ __launch_bounds__(256) void ln_bwd_wide_kernel(const T *dy /* may ali
           float r[8];
           rn[PAR][c].unpack(r);
 #pragma unroll
-          for (int i = 0; i < 8; ++i) o[i] += r[i];
+          for (int i = 0; i < 8; ++i) o[i] = FULL ? o[i] + r[i] : add_rounded(o[i], r[i]);
         }
         store8(dx + base + col, o);
         if (SUMDX) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) ds[c][i] += (float)(T)o[i];   // the value as stored
+          for (int i = 0; i < 8; ++i) {   // the value as stored
+            const float v = (float)(T)o[i];
+            ds[c][i] = FULL ? ds[c][i] + v : add_rounded(ds[c][i], v);
+          }
         }
       }
     }

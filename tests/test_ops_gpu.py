@@ -221,21 +221,23 @@ def test_norm_backward_waves(dt, rows, cols):
             assert O.max_rel_err(host(ds), host(dx).sum(axis=0)) < TOL[dt]
 
 
-def ordered_sums(a, min_rows, factor=None):
-    """Column sums of fp32 rows in the two-pass order: blocks of at least `min_rows` rows, wave w of four adds rows w, w + 4, ...
+def ordered_sums(a, min_rows, factor=None, waves=4):
+    """Column sums of fp32 rows in the two-pass order: blocks of at least `min_rows` rows, wave w of `waves` adds rows w, w + waves, ...
     (with a factor: products, unrounded), the waves in turn, then block g, g + 16, ... in 16 groups, the groups in turn."""
     rows, cols = a.shape
     nb = min(512, -(-rows // min_rows))
     rpb = -(-rows // nb)
     nb = -(-rows // rpb)
-    acc = np.zeros((nb, 4, cols), np.float32)
-    for at in range(0, rpb, 4):
-        r = np.arange(nb)[:, None] * rpb + at + np.arange(4)
-        ok = ((r < rows) & (at + np.arange(4) < rpb))[..., None]
+    acc = np.zeros((nb, waves, cols), np.float32)
+    for at in range(0, rpb, waves):
+        r = np.arange(nb)[:, None] * rpb + at + np.arange(waves)
+        ok = ((r < rows) & (at + np.arange(waves) < rpb))[..., None]
         r = np.minimum(r, rows - 1)
         v = a[r] if factor is None else a[r].astype(np.longdouble) * factor[r]
         acc = np.where(ok, (acc + v).astype(np.float32), acc)
-    part = ((acc[:, 0] + acc[:, 1]) + acc[:, 2]) + acc[:, 3]
+    part = acc[:, 0]
+    for w in range(1, waves):
+        part = part + acc[:, w]
     out = np.zeros(cols, np.float32)
     for g in range(16):
         s = np.zeros(cols, np.float32)
@@ -280,6 +282,23 @@ def test_norm_backward_rows_alone_and_among_others(dt, cols):
         B.op_layernorm_bwd(tdy[:n], tx[:n], stats[:n], tg, None, dx, dg, db, ws_for(n, cols), dx_colsum=ds)
         out.append(dx[:few])
     assert torch.equal(*out)
+
+
+# rows of more than 2048 columns with a guarded end: the residual gradient is added to dx as rounded without it, and the column
+# sums are those of dx as stored
+@pytest.mark.parametrize("sums", [False, True])
+@pytest.mark.parametrize("rows,cols", [(9, 2568), (1303, 4088), (33, 4096), (130, 5000)])
+def test_norm_backward_wide_adds_the_residual_to_the_rounded_gradient(rows, cols, sums):
+    dt = torch.float32
+    tx, tdy, tres = (dev(rnd((rows, cols), seed, dt), dt) for seed in (11, 14, 15))
+    tg, stats = dev(rnd((cols,), 12, dt) * 0.1 + 1, dt), torch.empty(rows, 2, dtype=torch.float32, device=DEV)
+    B.op_layernorm_fwd(tx, tg, tg, 1e-5, torch.empty_like(tx), stats)
+    dx, dxr, (dg, db, ds) = torch.empty_like(tx), torch.empty_like(tx), (torch.empty_like(tg) for _ in range(3))
+    for res, out in ((None, dx), (tres, dxr)):
+        B.op_layernorm_bwd(tdy, tx, stats, tg, res, out, dg, db, ws_for(rows, cols), dx_colsum=ds if sums else None)
+        if sums:
+            assert np.array_equal(ds.cpu().numpy(), ordered_sums(out.cpu().numpy(), 8, waves=1))
+    assert torch.equal(dxr, dx + tres)
 
 
 # K that no k-step divides (whole 8-element rows for NT; any K for TN), one k-step and a little more, two, four and more,

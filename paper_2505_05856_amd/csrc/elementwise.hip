@@ -635,6 +635,20 @@ __global__ __launch_bounds__(256) void dropout_kernel(const T *x /* may alias y 
   }
 }
 
+// The sum over a block's waves of column k in the order of four waves: with sixteen, a row each, waves w, w + 4, w + 8 and w + 12
+// have the rows that wave w of four adds up.
+template <int NW> __device__ __forceinline__ float sum_waves(const float (&red)[NW][512], int k) {
+  float t = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    float v = red[w][k];
+#pragma unroll
+    for (int u = w + 4; u < NW; u += 4) v += red[u][k];
+    t = w == 0 ? v : t + v;
+  }
+  return t;
+}
+
 // y = keep * scale * x over [rows, cols] and the column sums of the stored y, in partial rows as colsum_kernel's: the gradient of
 // a dropped hidden state on its way into the linear layer, whose bias gradient the sums are.  One wave a row up to four blocks a CU
 // (the draws are vector work, see gelu_bwd_colsum_kernel).
@@ -667,9 +681,7 @@ __global__ __launch_bounds__(64 * NW) void dropout_colsum_kernel(const T *__rest
   for (int j = threadIdx.x; j < 512; j += 64 * NW) {
     const int c = blockIdx.x * 512 + j;
     if (c < cols) {
-      float t = red[0][j];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) t += red[w][j];
+      const float t = sum_waves<NW>(red, j);
       part[(size_t)blockIdx.y * cols + c] = t;
     }
   }
@@ -721,9 +733,7 @@ __global__ __launch_bounds__(64 * NW) void gelu_bwd_colsum_kernel(const T *dy /*
   for (int k = threadIdx.x; k < 512; k += 64 * NW) {
     const int c = blockIdx.x * 512 + k;
     if (c < cols) {
-      float t = red[0][k];
-#pragma unroll
-      for (int w = 1; w < NW; ++w) t += red[w][k];
+      const float t = sum_waves<NW>(red, k);
       part[(size_t)blockIdx.y * cols + c] = t;
     }
   }
@@ -1081,7 +1091,8 @@ hipError_t launch_ln_bwd(int dtype, int rows, int cols, const void *dy, const vo
 // The derivative is vector work: up to four blocks a CU their 16 rows go to 16 waves, one each, not to four with four rows each
 // one after the other (four waves / 16, us with the second pass, bf16: 700x3072 9.6 / 7.9, 1000x1600 10.9 / 7.2, 4096x1024 10.8 /
 // 9.2; the rest is memory: 4096x4096 20.3 / 20.9).
-constexpr int kFewBlocks = 1024;
+// Blocks of more than 16 rows (8193 rows and more) keep four waves: sixteen would add the rows in another order.
+static bool wave_a_row(const dim3 &grid, int rpb) { return (int)(grid.x * grid.y) <= 1024 && rpb <= 16; }
 template <typename T>
 static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy, const void *x, void *dx,
                                     void *dbias, void *ws, hipStream_t s, ReduceJob *job) {
@@ -1099,7 +1110,7 @@ static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy
   const int nb = row_blocks(rows, 16, &rpb);
   float *part = (float *)ws;
   const dim3 grid((cols + 511) / 512, nb);
-  if ((int)(grid.x * grid.y) <= kFewBlocks)
+  if (wave_a_row(grid, rpb))
     hipLaunchKernelGGL((gelu_bwd_colsum_kernel<T, 16>), grid, dim3(1024), 0, s, (const T *)dy, (const T *)x, (T *)dx, part, rows,
                        cols, rpb, kind);
   else
@@ -1156,7 +1167,7 @@ static hipError_t dropout_colsum_t(int rows, int cols, const void *x, void *y, v
   const int nb = row_blocks(rows, 16, &rpb);
   float *part = (float *)ws;
   const dim3 grid((cols + 511) / 512, nb);
-  if ((int)(grid.x * grid.y) <= kFewBlocks)
+  if (wave_a_row(grid, rpb))
     hipLaunchKernelGGL((dropout_colsum_kernel<T, 16>), grid, dim3(1024), 0, s, (const T *)x, (T *)y, part, rows, cols, rpb, a);
   else
     hipLaunchKernelGGL((dropout_colsum_kernel<T, 4>), grid, dim3(256), 0, s, (const T *)x, (T *)y, part, rows, cols, rpb, a);

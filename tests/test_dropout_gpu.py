@@ -14,7 +14,7 @@ from oracle import dropout as D
 from oracle import stage as O
 from paper_2505_05856_amd import binding as B
 from paper_2505_05856_amd.harness import ScheduleRunner, StageRunner
-from test_ops_gpu import DEV, TOL, dev, host, rnd, ws_for
+from test_ops_gpu import DEV, TOL, dev, host, ordered_sums, rnd, ws_for
 from test_stage_gpu import compare
 
 pytestmark = pytest.mark.gpu
@@ -64,6 +64,20 @@ def test_bias_gradient_under_dropout_is_the_masked_gradients_sum(dtype, batch, s
     ref = host(ty).sum(axis=0)
     run.close()
     assert O.max_rel_err(g[0]["b_fc2"], ref) < TOL[torch.float32 if dtype == "f32" else torch.bfloat16]
+
+
+# ... and in the order of four waves a block, bit for bit, whichever number takes them (sixteen up to 8192 rows)
+@pytest.mark.parametrize("dtype,batch,seq,heads", [("f32", 1, 700, 1), ("bf16", 2, 650, 9), ("bf16", 4, 1024, 16), ("bf16", 8, 1025, 2)])
+def test_bias_gradient_under_dropout_keeps_its_order(dtype, batch, seq, heads):
+    cfg = syn.StageConfig(1, 64 * heads, heads, 64, seq, batch, "pre", True, "erf", dtype, p_attn=0.0, p_hidden=0.3)
+    run = StageRunner(cfg, syn.make_weights(cfg), *syn.make_activations(cfg))
+    B.stage_set_rng(run.stage, 99, 4)
+    run.step(syn.plan_keep_all(cfg))
+    torch.cuda.synchronize()
+    ty = torch.empty_like(run.dy)
+    B.op_dropout(run.dy, None, ty, B.Dropout(0.3, 99, 4, 0), B.SITE_FC2)
+    assert torch.equal(run.g[0]["b_fc2"].cpu(), torch.from_numpy(ordered_sums(ty.float().cpu().numpy(), 16)).to(ty.dtype))
+    run.close()
 
 
 def test_dropout_rate_zero_and_bad_arguments():

@@ -268,6 +268,17 @@ def test_norm_backward_sums_keep_their_order(dt, rows, cols):
             assert torch.equal(ds.cpu(), torch.from_numpy(ordered_sums(f32(dx), 8)).to(dt))
 
 
+# sixteen waves a block up to 1024 blocks of at most 16 rows (8192 rows), four from there on: the same order (in fp32 the last kind
+# alone: the other sums may take the value before its rounding)
+@pytest.mark.parametrize("dt,kind", [(torch.bfloat16, 0), (torch.bfloat16, 1), (torch.float32, 2)])
+@pytest.mark.parametrize("rows,cols", [(520, 520), (1000, 3072), (8192, 1024), (8193, 1024), (9001, 264), (2049, 4104)])
+def test_gelu_backward_sums_keep_their_order(dt, kind, rows, cols):
+    x, dy = dev(rnd((rows, cols), 11, dt), dt), dev(rnd((rows, cols), 14, dt), dt)
+    dx, db = torch.empty_like(x), torch.empty(cols, dtype=dt, device=DEV)
+    B.op_gelu_bwd(dy, x, dx, db, ws_for(rows, cols), kind)
+    assert torch.equal(db.cpu(), torch.from_numpy(ordered_sums(dx.float().cpu().numpy(), 16)).to(dt))
+
+
 # a row's dx does not depend on how many rows a call has (8 rows a block and 16 or more, several to a wave)
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("cols", [1032, 1600, 2048])

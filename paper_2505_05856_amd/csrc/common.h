@@ -104,8 +104,10 @@ __device__ __forceinline__ float normal_cdf_parts(float x, float *density_exp) {
 //
 // tanh form (kind 1): 0.5 x (1 + tanh u) = x s with the logistic function s = 1 / (1 + exp(-2u)), which is what bf16 results
 // take: an exponential and a reciprocal, where tanhf's instructions, not memory, bound the kernels (us, tanhf / this: forward
-// 8192x6400 41.7 / 31.6, 4096x4096 17.4 / 13.8; backward 8192x6400 66.2 / 60.9, 1500x4096 17.0 / 13.8).  In fp32 tanhf stays: s
-// has a few roundings more, 4.6e-8 of the result over N(0,1) where that has 3.8e-8, which bf16 does not show (1.55e-3 either way).
+// 8192x6400 41.7 / 31.6, 4096x4096 17.4 / 13.8; backward 8192x6400 66.2 / 60.9, 1500x4096 17.0 / 13.8).  Value and derivative of
+// every bf16 number round to the nearest bf16 (with tanhf, which loses them to 1 + tanh, 117 and 117 between -8 and -2 do not).  As
+// 32-bit numbers s has a few roundings more (error over N(0,1), of the norm: value 4.7e-8, derivative 5.8e-8, tanhf 3.8e-8 and
+// 4.7e-8), so fp32 results keep tanhf.
 // Zeros, infinities, NaN and arguments whose cube overflows give what tanhf gave.
 __device__ __forceinline__ float tanh_logistic(float x, float *e) {
 #pragma clang fp contract(off)

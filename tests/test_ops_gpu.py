@@ -119,6 +119,24 @@ def test_gelu_tanh_bf16_far_out():
     assert torch.allclose(dx.double()[~far], want[~far], rtol=2.0 ** -7, atol=1e-9, equal_nan=True)
 
 
+def test_gelu_tanh_bf16_rounds_to_the_nearest():
+    """Value and derivative of every bf16 number between -8 and 8, and -inf."""
+    x = torch.arange(-32768, 32768, dtype=torch.int32, device=DEV).to(torch.int16).view(torch.bfloat16)
+    x = x[x.float().abs() <= 8].view(-1, 2).repeat(1, 4).contiguous()
+    y, dx, db = torch.empty_like(x), torch.empty_like(x), torch.empty(8, dtype=torch.bfloat16, device=DEV)
+    B.op_gelu_fwd(x, y, 1)
+    B.op_gelu_bwd(torch.ones_like(x), x, dx, db, ws_for(*x.shape), 1)
+    x64 = x.double()
+    s = torch.sigmoid(1.5957691216057308 * (x64 + 0.044715 * x64 ** 3))
+    for got, want in ((y, x64 * s), (dx, s + x64 * s * (1 - s) * 1.5957691216057308 * (1 + 0.134145 * x64 ** 2))):
+        seen = want.abs() > 1e-30   # (smaller ones may be flushed)
+        assert torch.equal(got[seen], want.bfloat16()[seen])
+    low = torch.full((1, 8), -float("inf"), dtype=torch.bfloat16, device=DEV)
+    out = torch.empty_like(low)
+    B.op_gelu_fwd(low, out, 1)
+    assert torch.isnan(out).all()   # -inf * 0, as 0.5 x (1 + tanh u) gives
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("rows,cols", [(1, 8), (33, 24), (1000, 1600), (4096, 520)])
 def test_colsum(dt, rows, cols):

@@ -201,8 +201,10 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_simple_kernel(AttnView av,
 // A load is 16 bytes a lane (fp32) and 128 contiguous bytes a row, all loads of a batch of 8 U rows go out together, a dot
 // product is summed over the group by lane swaps, and the backward's rows are used where they are, for the product that made P and
 // for the one that takes it.  (A lane a row, as in the kernels above, touches 64 lines a load and waits for every 32 bytes; sums over
-// rows went one row at a time.  us, fp32, forward and backward, those kernels / these: 2 x 64 rows, 2 heads of 64 7.2 + 21.4 / 5.9 + 11.4;
-// 4 x 256, 8 heads of 64 96 + 329 / 41 + 89; 4 x 256, 4 heads of 32 27 + 100 / 16 + 30; 2 x 200, 2 heads of 128 28 + 113 / 15 + 31.)
+// rows went one row at a time.  us, forward + backward, those kernels / these: fp32 64 rows, 2 heads of 64 7.9 + 21.7 / 5.3 + 11.6; 256 rows, 16 heads
+// of 64 42 + 161 / 21 + 53; 4096 rows, 2 heads of 96 3314 + 14722 / 872 + 1958; bf16 64 rows, 2 heads of 40 7.1 + 15.0 / 5.2 + 12.5;
+// 1024 rows, 8 heads of 80 298 + 1188 / 181 + 431, causal 213 + 925 / 136 + 286; 4096 rows, 2 heads of 96 1778 + 12419 / 738 + 1808.
+// One row a sequence stays behind: bf16, 2 heads of 80, backward 10.7 / 11.3.)
 template <typename T> struct Raw4;
 template <> struct Raw4<float> { f32x4 v; };
 template <> struct Raw4<bf16> { bf16x4 v; };
@@ -238,7 +240,7 @@ struct Rows {
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[t][e] = has(t) ? ldf(p + col(t) + e) : 0.f;
   }
-  // columns past the head's read its last four; what meets them is zero or not stored (mask() makes them zero)
+  // columns past the head's read its last four: dot() leaves them out, and what the others make of them is not stored
   __device__ __forceinline__ void load(const T *p, Raw4<T> (&v)[NT]) const {
 #pragma unroll
     for (int t = 0; t < NT; ++t) v[t].v = *reinterpret_cast<const decltype(v[t].v) *>(p + min(col(t), dh - 4));
@@ -312,27 +314,34 @@ __global__ __launch_bounds__(256) void attn_fwd_rows_kernel(AttnView av, T *__re
   }
   m = wave_max(m);
   __syncthreads();
+  // P, a key a lane (each of a group's eight lanes working it out for the sum that follows: bf16, 1024 rows, 8 heads of 40, causal
+  // 128 us, now 92; fp32, 256 rows, 16 heads of 64 24.0, now 20.9)
   const DropKeys keys = drop_keys(da.base, (uint32_t)(b * nh + h));
   float l = 0.f, acc[NT][4] = {};
-  for (int j0 = 0; j0 < jn; j0 += 8 * U) {
-    Raw4<T> v[U][NT];
-    if (o != nullptr) {
+  for (int j = lane; j < jn; j += 64) {
+    float p = expf(sc[j] - m);
+    l += p;
+    if (da.thr != 0 && drop_bits((uint32_t)i * (uint32_t)S + (uint32_t)j, keys.k0, keys.k1) < da.thr) p = 0.f;
+    sc[j] = p;
+  }
+  l = wave_sum(l);
+  __syncthreads();
+  // (whole batches without a guard: behind one the compiler moves the loads to their uses, and a wave waits for each)
+  int j0 = 0;
+  if (o != nullptr) {
+    for (; j0 + 8 * U <= jn; j0 += 8 * U) {
+      Raw4<T> v[U][NT];
 #pragma unroll
-      for (int u = 0; u < U; ++u) r.load(vb + (size_t)min(j0 + 8 * u + r.g, jn - 1) * ld, v[u]);
+      for (int u = 0; u < U; ++u) r.load(vb + (size_t)(j0 + 8 * u + r.g) * ld, v[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) r.add(acc, sc[j0 + 8 * u + r.g], v[u]);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = j0 + 8 * u + r.g;
-      if (j < jn) {
-        float p = expf(sc[j] - m);
-        l += p;
-        if (da.thr != 0 && drop_bits((uint32_t)i * (uint32_t)S + (uint32_t)j, keys.k0, keys.k1) < da.thr) p = 0.f;
-        if (o != nullptr) r.add(acc, p, v[u]);
-      }
+    for (int j = j0 + r.g; j < jn; j += 8) {
+      Raw4<T> v[NT];
+      r.load(vb + (size_t)j * ld, v);
+      r.add(acc, sc[j], v);
     }
   }
-#pragma unroll
-  for (int x = 8; x <= 32; x <<= 1) l += __shfl_xor(l, x, 64);
   if (!active) return;
   if (lse != nullptr && lane == 0) lse[((size_t)b * nh + h) * Sq + i] = m + logf(l);
   if (o != nullptr) r.store(acc, da.scale / l, o + ((size_t)b * Sq + i) * (size_t)(nh * dh) + (size_t)h * dh);
@@ -433,17 +442,22 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_rows_kernel(AttnView av, con
   r.store(av_, 1.f, (T *)av.dv + koff);
 }
 
-// One wave a block while that leaves CUs without work (their rows then come through L1s of their own), four from there on.
+// One wave a block while that leaves CUs without work (their rows then come through L1s of their own), four from there on.  Forward +
+// backward, one / four: fp32, 64 rows, 4 heads of 128 7.1 + 17.0 / 7.7 + 18.6; 256 rows, 6 heads of 128 18.9 + 43.2 / 19.8 + 45.2, 8
+// heads 23.7 + 58.4 / 19.9 + 50.0; bf16, 256 rows, 6 heads of 40 11.4 + 30.4 / 12.6 + 31.6, 8 heads 12.6 + 31.6 / 12.5 + 31.7.
 static int waves_a_block(long rows) { return rows >= 2048 ? 4 : 1; }
 static unsigned row_grid(long rows, int w) { return (unsigned)((rows + w - 1) / w); }
-// the kernel of a head dimension: NT pieces of 32 columns, U batches of eight rows in flight
-#define DP_ATTN_ROWS(KERN, rows, lds, ...)                                                                                     \
+// The kernel of a head dimension: NT pieces of 32 columns, U (times X) batches of eight rows in flight.  Twice as many pay in the
+// forward in bf16 from 64 keys on (64 rows, 2 heads of 112 8.9 / 7.7, but 2 rows 5.4 / 5.8; the backward, which holds two operands,
+// 1024 rows, 8 heads of 40 199 / 211).  Three pieces, not four, for 65 to 96 columns: 1024 rows, 8 heads of 96, fp32 273 + 520 / 224 + 423.
+#define DP_ATTN_ROWS(KERN, X, rows, lds, ...)                                                                                  \
   do {                                                                                                                         \
     const int w = waves_a_block(rows);                                                                                         \
     const dim3 grid(row_grid(rows, w)), block(64 * w);                                                                         \
-    if (dh <= 32) hipLaunchKernelGGL((KERN<T, 1, 4>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                         \
-    else if (dh <= 64) hipLaunchKernelGGL((KERN<T, 2, 4>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                    \
-    else hipLaunchKernelGGL((KERN<T, 4, 2>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                                  \
+    if (dh <= 32) hipLaunchKernelGGL((KERN<T, 1, 4 * X>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                     \
+    else if (dh <= 64) hipLaunchKernelGGL((KERN<T, 2, 4 * X>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                \
+    else if (dh <= 96) hipLaunchKernelGGL((KERN<T, 3, 2 * X>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                \
+    else hipLaunchKernelGGL((KERN<T, 4, 2 * X>), grid, block, (size_t)w * (lds), s, __VA_ARGS__);                              \
   } while (0)
 
 template <typename T>
@@ -451,8 +465,13 @@ static hipError_t fwd_t(int B, int nh, int dh, int causal, const AttnView &v, vo
                         hipStream_t s) {
   const long rows = (long)B * nh * v.Sq;
   if (dh <= 128) {
-    DP_ATTN_ROWS(attn_fwd_rows_kernel, rows, (size_t)v.Sk * sizeof(float), v, (T *)o, lse, B, nh, dh, causal,
-                 1.0f / sqrtf((float)dh), da);
+    constexpr int X = sizeof(T) == 2 ? 2 : 1;
+    if (v.Sk >= 64)
+      DP_ATTN_ROWS(attn_fwd_rows_kernel, X, rows, (size_t)v.Sk * sizeof(float), v, (T *)o, lse, B, nh, dh, causal,
+                   1.0f / sqrtf((float)dh), da);
+    else
+      DP_ATTN_ROWS(attn_fwd_rows_kernel, 1, rows, (size_t)v.Sk * sizeof(float), v, (T *)o, lse, B, nh, dh, causal,
+                   1.0f / sqrtf((float)dh), da);
     return hipGetLastError();
   }
   const size_t smem = 4 * (size_t)(v.Sk + dh) * sizeof(float);
@@ -477,12 +496,12 @@ static hipError_t bwd_t(int B, int nh, int dh, int causal, const AttnView &v, co
   const float scale = 1.0f / sqrtf((float)dh);
   if (dh <= 128) {
     if (qrows > 0 && v.Sk > 0) {
-      DP_ATTN_ROWS(attn_bwd_dq_rows_kernel, qrows, 0, v, (const T *)o, lse, (const T *)d_o, ws, B, nh, dh, causal, scale, da);
+      DP_ATTN_ROWS(attn_bwd_dq_rows_kernel, 1, qrows, 0, v, (const T *)o, lse, (const T *)d_o, ws, B, nh, dh, causal, scale, da);
       hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
     if (krows > 0)   // (no queries: dK = dV = 0 is still written)
-      DP_ATTN_ROWS(attn_bwd_dkv_rows_kernel, krows, 0, v, lse, (const T *)d_o, ws, B, nh, dh, causal, scale, da);
+      DP_ATTN_ROWS(attn_bwd_dkv_rows_kernel, 1, krows, 0, v, lse, (const T *)d_o, ws, B, nh, dh, causal, scale, da);
     return hipGetLastError();
   }
   const dim3 block(256);

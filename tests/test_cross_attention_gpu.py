@@ -66,6 +66,13 @@ def test_cross_attention(dt, shape):
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", [(2, 37, 63, 2, 40), (2, 63, 130, 2, 72), (2, 37, 70, 2, 136)])
+@pytest.mark.parametrize("drop", [None, (0.3, 0xABCDEF0123456789, 3 + (1 << 33), 2)])
+def test_other_head_dimensions(dt, shape, drop):
+    run_case(dt, *shape, drop=drop)
+
+
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("shape", [(2, 37, 130, 2, 64), (1, 70, 257, 2, 128)])
 def test_sharp_logits(dt, shape):
     run_case(dt, *shape, sharp=True)

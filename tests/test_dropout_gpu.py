@@ -136,6 +136,13 @@ def test_attention_with_dropout(dt, causal, Bn, S, nh, dh):
     assert torch.equal(o0, o1)
 
 
+# blocks of four waves (2048 rows and more), heads of no whole piece and wider than the kernels with a wave a row take
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("Bn,S,nh,dh", [(1, 690, 3, 40), (2, 70, 2, 72), (2, 41, 2, 136)])
+def test_attention_with_dropout_other_head_dimensions(dt, Bn, S, nh, dh):
+    test_attention_with_dropout(dt, True, Bn, S, nh, dh)
+
+
 SMALL = [
     syn.StageConfig(2, 64, 2, 128, 40, 3, "pre", True, "erf", "f32", p_attn=0.2, p_hidden=0.1),
     syn.StageConfig(2, 64, 2, 128, 40, 3, "post", False, "tanh", "f32", p_attn=0.1, p_hidden=0.3),

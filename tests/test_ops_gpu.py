@@ -481,6 +481,15 @@ def test_attention_rows(Bn, S, nh, dh, causal):
     test_attention(torch.float32, causal, Bn, S, nh, dh, False)
 
 
+# three pieces and four, twice the batches from 64 keys on, in bf16 too; wider heads than the rows kernels take, more than one batch
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("Bn,S,nh,dh", [(2, 63, 2, 24), (2, 64, 2, 40), (1, 129, 2, 72), (1, 70, 1, 96), (1, 67, 2, 104), (1, 685, 3, 40),
+                                        (2, 33, 2, 136), (2, 130, 1, 160)])
+def test_attention_other_head_dimensions(dt, Bn, S, nh, dh, causal):
+    test_attention(dt, causal, Bn, S, nh, dh, False)
+
+
 # the forward's tile loop: one tile, two, odd and even counts, tiles that end on and just past a boundary, with none, some and
 # all of them masked; the last shape has more than two workgroups a CU
 @pytest.mark.parametrize("causal", [False, True])

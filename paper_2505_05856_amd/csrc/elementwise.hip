@@ -742,7 +742,8 @@ __global__ __launch_bounds__(64 * NW) void gelu_bwd_colsum_kernel(const T *dy /*
 // ------------------------------------------------------------------ few rows: whole columns in one launch
 // With few rows a launch is a chain of latencies, and a second launch for the column sums (reduce_partials_kernel) costs
 // as much as the work: here a block of 1024 threads owns SC columns (a slab) over all rows, so the sums are complete in it.
-// A thread owns 8 of the columns in every 1024/(SC/8)-th row; its loads of four rows are in flight together.
+// A thread owns 8 of the columns in every 1024/(SC/8)-th row, and its loads of U such rows (U: as many as the launcher's row limit
+// leaves it, four at most) are in flight together.
 
 // The block's sums of one vector: `acc` holds a thread's 8 columns.  Rows of a wave by lane exchange, waves through LDS, in a
 // fixed order.
@@ -766,27 +767,33 @@ __device__ __forceinline__ void slab_sums(float (&acc)[8], float (&red)[16][SC],
   }
 }
 
-// f(row) for every row of this thread's, four of its `load`s ahead of their `use`s
-template <int SC, typename Load, typename Use>
+// f(row) for every row of this thread's, U of its `load`s ahead of their `use`s
+template <int SC, int U, typename Load, typename Use>
 __device__ __forceinline__ void slab_rows(int rows, Load &&load, Use &&use) {
   constexpr int STEP = 1024 / (SC / 8);   // rows the block takes at a time
-  for (int r0 = threadIdx.x / (SC / 8); r0 < rows; r0 += 4 * STEP) {
+  for (int r0 = threadIdx.x / (SC / 8); r0 < rows; r0 += U * STEP) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) load(min(r0 + STEP * u, rows - 1), u);   // (rows past the last: not used)
+    for (int u = 0; u < U; ++u) load(min(r0 + STEP * u, rows - 1), u);   // (rows past the last: not used)
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < U; ++u)
       if (r0 + STEP * u < rows) use(r0 + STEP * u, u);
   }
 }
+// rows up to which the launchers choose the one-launch forms (figures there), and the U for a kernel of at most `limit` rows
+constexpr int kColsumSlabRows = 1800;
+template <typename T> constexpr int kGeluSlabRows = 1024 / (int)sizeof(T);
+template <typename T> constexpr int kLnSlabRows = sizeof(T) == 2 ? 1000 : 512;
+constexpr int slab_depth(int limit, int sc) { const int n = (limit * (sc / 8) + 1023) / 1024; return n > 4 ? 4 : n; }
 
 template <typename T, int SC>
 __global__ __launch_bounds__(1024) void colsum_slab_kernel(const T *__restrict__ x, T *__restrict__ out, int rows, int cols) {
   __shared__ float red[16][SC];
   const int col0 = blockIdx.x * SC, col = col0 + (threadIdx.x % (SC / 8)) * 8;
+  constexpr int U = slab_depth(kColsumSlabRows, SC);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (col < cols) {
-    Raw8<T> v[4];
-    slab_rows<SC>(rows, [&](int row, int u) { v[u].load(x + (size_t)row * cols + col); },
+    Raw8<T> v[U];
+    slab_rows<SC, U>(rows, [&](int row, int u) { v[u].load(x + (size_t)row * cols + col); },
               [&](int, int u) {
                 float a[8];
                 v[u].unpack(a);
@@ -802,10 +809,11 @@ __global__ __launch_bounds__(1024) void gelu_bwd_slab_kernel(const T *dy /* may 
                                                              T *__restrict__ dbias, int rows, int cols, int kind) {
   __shared__ float red[16][SC];
   const int col0 = blockIdx.x * SC, col = col0 + (threadIdx.x % (SC / 8)) * 8;
+  constexpr int U = slab_depth(kGeluSlabRows<T>, SC);
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (col < cols) {
-    Raw8<T> v[4], g[4];
-    slab_rows<SC>(rows,
+    Raw8<T> v[U], g[U];
+    slab_rows<SC, U>(rows,
               [&](int row, int u) {
                 const size_t at = (size_t)row * cols + col;
                 v[u].load(x + at);
@@ -835,16 +843,16 @@ __global__ __launch_bounds__(1024) void ln_bwd_few_kernel(const T *__restrict__ 
                                                           const float *__restrict__ stats, const T *__restrict__ gamma,
                                                           const T *__restrict__ dres, T *__restrict__ dx, T *__restrict__ dgamma,
                                                           T *__restrict__ dbeta, int rows, int cols, int n_row_blocks, int rms) {
-  constexpr int SC = kLnSlabCols;
+  constexpr int SC = kLnSlabCols, U = slab_depth(kLnSlabRows<T>, SC);
   __shared__ float red[2][16][SC];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if ((int)blockIdx.x >= n_row_blocks) {
     const int col0 = ((int)blockIdx.x - n_row_blocks) * SC, col = col0 + (threadIdx.x % (SC / 8)) * 8;
     float dg[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, db[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (col < cols) {
-      Raw8<T> v[4], g[4];
-      float mean[4], rstd[4];
-      slab_rows<SC>(rows,
+      Raw8<T> v[U], g[U];
+      float mean[U], rstd[U];
+      slab_rows<SC, U>(rows,
                 [&](int row, int u) {
                   const size_t at = (size_t)row * cols + col;
                   v[u].load(x + at);
@@ -961,16 +969,16 @@ hipError_t launch_ln_fwd(int dtype, int rows, int cols, float eps, const void *x
                         : ln_fwd_t<float>(rows, cols, eps, x, gamma, beta, y, stats, s, rms ? 1 : 0);
 }
 
-// Where the one-launch forms end (two launches / one, us; warm: operands in the caches, cold: from memory, where a slab's short
-// pieces of many rows cost more):
-//   column sums: bf16 1000x3072 warm 7.7 / 4.7, cold 7.7 / 5.0, 1500x4096 cold 8.3 / 7.5, but 2048x3072 7.8 / 8.8; fp32 2048x1024 cold
-//     8.9 / 7.1, 2048x3072 8.6 / 11.1: up to 2048 rows and below 12 MiB
-//   GELU backward (16 columns a slab up to 1024, 32 from there on): bf16 500x1024 cold 7.5 / 6.1, 500x4096 warm 7.4 / 6.5, cold 7.5 / 8.2,
-//     1000x1024 cold 7.3 / 9.3; fp32 250x1024 7.4 / 5.5, 500x1024 7.4 / 7.5, 1000x1024 7.9 / 13.2: 512 and 256 rows
-//   LayerNorm backward: bf16 1000x768 warm 8.6 / 6.0, cold 9.1 / 7.5, 1000x2048 13.6 / 10.4, but 1500x1024 9.8 / 11.5, 2048x1024 10.0 / 14.2;
-//     fp32 512x1024 8.5 / 7.6, but 1024x1024 9.3 / 11.3: 1024 and 512 rows
-constexpr int kSlabRows = 2048, kLnSlabBytes = 2048, kGeluSlabBytes = 1024;
-constexpr size_t kSlabBytes = (size_t)12 << 20;
+// Where the one-launch forms end (two launches / one, us, in calls one after the other; in a captured graph, where the host's part
+// is gone.  Operands from memory, where a slab's short pieces of many rows cost more; in the caches the lines would lie further out):
+//   column sums: bf16 1800x1024 9.4 / 6.2; 7.1 / 6.3, 1800x3064 9.6 / 8.3; 9.5 / 8.5, but 2048x1024 in a graph 5.6 / 6.7; fp32
+//     1800x1024 9.4 / 6.2; 8.1 / 7.7, but 1800x1528 9.4 / 9.8; 9.2 / 10.3: up to 1800 rows and 8 MiB
+//   GELU backward (16 columns a slab up to 1024, 32 from there on): bf16 512x1024 9.8 / 5.4; 9.3 / 5.6, 512x6400 11.6 / 8.9;
+//     12.1 / 9.2, but 512x11008 13.2 / 16.4; 13.6 / 15.6; fp32 256x6400 10.9 / 7.7; 11.4 / 8.2, but 256x11008 12.4 / 13.9;
+//     12.8 / 13.9, and 500x1024 7.4 / 7.5, 1000x1024 7.9 / 13.2 (on a faster host): 512 and 256 rows, and 8 MiB
+//   LayerNorm backward: bf16 1000x768 9.1 / 7.5, 850x1024 in a graph 9.9 / 8.0, but 1024x512 in a graph 7.0 / 8.3 and 1500x1024 9.8 / 11.5;
+//     fp32 512x1024 in a graph 9.1 / 7.1, but 1024x1024 9.3 / 11.3: 1000 and 512 rows
+constexpr size_t kSlabBytes = (size_t)8 << 20;
 // The sums are written while other blocks still read: calls whose outputs lie in what those read keep the two launches.
 static bool overlap(const void *a, size_t na, const void *b, size_t nb) {
   const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
@@ -1075,7 +1083,7 @@ hipError_t launch_ln_bwd(int dtype, int rows, int cols, const void *dy, const vo
   const auto in_inputs = [&](const void *p, size_t n) {
     return overlap(p, n, dy, mat) || overlap(p, n, x, mat) || overlap(p, n, gamma, vec) || overlap(p, n, stats, 8 * (size_t)rows);
   };
-  if (job == nullptr && dxsum == nullptr && rows <= kLnSlabBytes / (int)dtype_size(dtype) && cols <= 2048 && !in_inputs(dx, mat) &&
+  if (job == nullptr && dxsum == nullptr && rows <= (dtype == kBF16 ? kLnSlabRows<bf16> : kLnSlabRows<float>) && cols <= 2048 && !in_inputs(dx, mat) &&
       !in_inputs(dgamma, vec) && !in_inputs(dbeta, vec) && !overlap(dgamma, vec, dres, mat) && !overlap(dbeta, vec, dres, mat))
     return dtype == kBF16 ? ln_bwd_few_t<bf16>(rows, cols, dy, x, stats, gamma, dres, dx, dgamma, dbeta, s, r)
                           : ln_bwd_few_t<float>(rows, cols, dy, x, stats, gamma, dres, dx, dgamma, dbeta, s, r);
@@ -1097,7 +1105,7 @@ template <typename T>
 static hipError_t gelu_bwd_colsum_t(int kind, int rows, int cols, const void *dy, const void *x, void *dx,
                                     void *dbias, void *ws, hipStream_t s, ReduceJob *job) {
   const size_t mat = (size_t)rows * cols * sizeof(T), vec = (size_t)cols * sizeof(T);
-  if (job == nullptr && rows <= kGeluSlabBytes / (int)sizeof(T) && !overlap(dbias, vec, dy, mat) && !overlap(dbias, vec, x, mat)) {
+  if (job == nullptr && rows <= kGeluSlabRows<T> && mat <= kSlabBytes && !overlap(dbias, vec, dy, mat) && !overlap(dbias, vec, x, mat)) {
     if (cols <= 1024)
       hipLaunchKernelGGL((gelu_bwd_slab_kernel<T, 16>), dim3((cols + 15) / 16), dim3(1024), 0, s, (const T *)dy, (const T *)x,
                          (T *)dx, (T *)dbias, rows, cols, kind);
@@ -1186,7 +1194,8 @@ hipError_t launch_dropout_colsum(int dtype, int rows, int cols, const void *x, v
 
 template <typename T>
 static hipError_t colsum_t(int rows, int cols, const void *x, void *out, void *ws, hipStream_t s, ReduceJob *job) {
-  if (job == nullptr && rows <= kSlabRows && (size_t)rows * cols * sizeof(T) < kSlabBytes && !overlap(out, (size_t)cols * sizeof(T), x, (size_t)rows * cols * sizeof(T))) {
+  const size_t mat = (size_t)rows * cols * sizeof(T);
+  if (job == nullptr && rows <= kColsumSlabRows && mat <= kSlabBytes && !overlap(out, (size_t)cols * sizeof(T), x, mat)) {
     hipLaunchKernelGGL((colsum_slab_kernel<T, 32>), dim3((cols + 31) / 32), dim3(1024), 0, s, (const T *)x, (T *)out, rows, cols);
     return hipGetLastError();
   }

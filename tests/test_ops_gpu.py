@@ -184,8 +184,8 @@ def test_calls_go_to_the_current_stream():
             assert (B._stream_ptr(None) or 0) == torch.cuda.current_stream().cuda_stream == (B._stream_ptr(s) or 0)
 
 
-# one launch up to 1024 / 2048 rows: waves and passes of rows cut short, slabs of 16 and 32 columns cut short, the last row count
-# on either side of each rule; outputs that lie in the inputs (in place, the sums over gamma) take the two launches
+# one launch for few rows: waves and passes of rows cut short, slabs of 16 and 32 columns cut short; outputs that lie in the inputs
+# (in place, the sums over gamma) take the two launches
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("rows,cols", [(1, 8), (15, 24), (17, 136), (128, 128), (257, 40), (1000, 776), (1024, 2048), (1025, 48),
                                        (2048, 520), (2049, 72), (33, 2056)])
@@ -216,6 +216,57 @@ def test_column_sums_of_few_rows(dt, rows, cols):
     assert O.max_rel_err(host(out), host(dx).sum(axis=0)) < TOL[dt]   # of dx as stored
     B.op_gelu_bwd(src, tx, src, out, ws, 0)                           # in place
     assert torch.equal(src, dx)
+
+
+# the last row count, column count and byte count on either side of each rule (GELU 256 and 512 rows, norms 512 and 1000, column sums
+# 1800, all but norms 8 MiB)
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("rows,cols", [(256, 1024), (256, 1032), (257, 1032), (512, 1024), (512, 1032), (513, 72), (1000, 264), (1001, 264),
+                                       (1800, 2328), (1800, 2336), (1801, 72), (1800, 1160), (1800, 1168), (512, 8192), (512, 8200),
+                                       (256, 8200)])
+def test_column_sums_on_either_side_of_each_rule(dt, rows, cols):
+    if cols <= 8192:
+        test_column_sums_of_few_rows(dt, rows, cols)
+        return
+    x, dy = dev(rnd((rows, cols), 11, dt), dt), dev(rnd((rows, cols), 14, dt), dt)   # (wider than a norm takes)
+    dx, db = torch.empty_like(x), torch.empty(cols, dtype=dt, device=DEV)
+    B.op_gelu_bwd(dy, x, dx, db, ws_for(rows, cols), 0)
+    assert O.max_rel_err(host(dx), host(dy) * O.gelu_grad(host(x), "erf")) < TOL[dt]
+    assert O.max_rel_err(host(db), host(dx).sum(axis=0)) < TOL[dt]
+
+
+def test_sums_that_lie_in_an_input_take_two_launches():
+    """One output in one input a call: the sums then have the bits of the two-pass order, and an input is whole until it is read."""
+    dt, rows, cols = torch.float32, 200, 136
+    x, dy, dres, g = (dev(rnd(s, seed, dt), dt) for seed, s in ((11, (rows, cols)), (14, (rows, cols)), (15, (rows, cols)), (12, (cols,))))
+    stats, ws = torch.empty(rows, 2, dtype=torch.float32, device=DEV), ws_for(rows, cols)
+    B.op_layernorm_fwd(x, g, g, 1e-5, torch.empty_like(x), stats)
+    st = stats.cpu().numpy()
+    sums = {"dg": ordered_sums(dy.cpu().numpy(), 8, (x.cpu().numpy() - st[:, :1]) * st[:, 1:]), "db": ordered_sums(dy.cpu().numpy(), 8)}
+    dx, out = torch.empty_like(x), {"dg": torch.empty_like(g), "db": torch.empty_like(g)}
+    B.op_layernorm_bwd(dy, x, stats, g, dres, dx, out["dg"], out["db"], ws)
+    assert not all(np.array_equal(out[k].cpu().numpy(), sums[k]) for k in sums)   # (one launch adds in another order)
+    for which in ("dg", "db"):
+        for place in ("x", "dy", "dres", "g", "stats"):
+            t = {"x": x.clone(), "dy": dy.clone(), "dres": dres.clone(), "g": g.clone(), "stats": stats.clone()}
+            into = dict(out, **{which: t[place].view(-1)[:cols]})
+            got = torch.empty_like(x)
+            B.op_layernorm_bwd(t["dy"], t["x"], t["stats"], t["g"], t["dres"], got, into["dg"], into["db"], ws)
+            assert np.array_equal(into[which].cpu().numpy(), sums[which]), (which, place)
+            assert torch.equal(got, dx), (which, place)
+    for place in ("x", "dy"):
+        t = {"x": x.clone(), "dy": dy.clone()}
+        B.op_layernorm_bwd(t["dy"], t["x"], stats, g, dres, t[place], out["dg"], out["db"], ws)
+        assert torch.equal(t[place], dx) and all(np.array_equal(out[k].cpu().numpy(), sums[k]) for k in sums)
+    want = ordered_sums(dy.cpu().numpy(), 16)
+    src = dy.clone()
+    B.op_colsum(src, src[7], ws)
+    assert np.array_equal(src[7].cpu().numpy(), want)
+    want = ordered_sums((dy * (x > 0)).cpu().numpy(), 16)   # ReLU: whole products
+    for place in ("x", "dy"):
+        t = {"x": x.clone(), "dy": dy.clone()}
+        B.op_gelu_bwd(t["dy"], t["x"], torch.empty_like(x), t[place][rows - 1], ws, 2)
+        assert np.array_equal(t[place][rows - 1].cpu().numpy(), want), place
 
 
 # the norm backward with the column sums of dx: 8 waves a block up to 2048 rows, 16 up to 4096 (bf16, 1024 columns), 4 from there on

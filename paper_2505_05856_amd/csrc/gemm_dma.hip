@@ -581,14 +581,18 @@ hipError_t launch_dma_cfg(const GemmArgs &a, hipStream_t s) {
 //   [1600 x 6400] x 4096 TN: 238 of 256x192 78 us (175 of 256x256 84, 350 of 256x128 108); [6144 x 6144] x 2048 128 (148, 154)
 //   [3441 x 1280] x 1280 NT: 189 of 128x192 17.0 us (135 of 128x256 20.3); [1664 x 4992] x 1896 TN 234 of 192x192 33 (520 of 128x128 37)
 // Over 30 products of drawn stages they take 4 % off the mean, up to 20 %.  Below nine k-steps, where start and output are most of
-// a launch, they gain nothing ([2304 x 3328] x 512 NT: 192x192 14.3 us, 128x256 14.0; TN 14.9 and 14.2): min_steps.
+// a launch, they gain nothing ([2304 x 3328] x 512 NT: 192x192 14.3 us, 128x256 14.0; TN 14.9 and 14.2): min_steps.  Nor
+// are they taken for more than four rounds of theirs (kRounds192): CUs do not start a round together, so the more rounds, the less
+// is lost in the last one than the estimate says.  52 products of 2 to 3.2 rounds of 256x256 took 0.90 of its time in three or four
+// rounds, one of them longer by more than 1 %; 21 of 4 to 4.6 rounds 1.00, eight of them longer, up to [5828 x 12576] x 840 NT
+// 145 / 157 us; 17 of 5 and 6 rounds 0.97, five longer, up to [6016 x 14232] x 1608 TN 262 / 285.
 struct TileTime { int bm, bn; float start_us, step_us; int min_steps; };
 enum { k256x256, k256x192, k192x256, k192x192, k256x128, k128x256, k192x128, k128x192, k128x128, k128x64, k64x128, k64x64, kTiles };
 constexpr TileTime kTileTimes[kTiles] = {
     {256, 256, 6.0f, 1.27f, 3}, {256, 192, 5.2f, 1.03f, 9}, {192, 256, 5.2f, 1.03f, 9}, {192, 192, 4.0f, 0.88f, 9},
     {256, 128, 4.5f, 0.83f, 1}, {128, 256, 4.5f, 0.83f, 1}, {192, 128, 3.5f, 0.70f, 9}, {128, 192, 3.5f, 0.70f, 9},
     {128, 128, 2.0f, 0.55f, 1}, {128, 64, 1.5f, 0.40f, 1},  {64, 128, 1.5f, 0.40f, 1},  {64, 64, 1.5f, 0.26f, 1}};
-constexpr int kCus = 256;
+constexpr int kCus = 256, kRounds192 = 4;
 
 int choose_tile(const GemmArgs &a) {
   const int nk = (a.K + 63) / 64;
@@ -600,7 +604,9 @@ int choose_tile(const GemmArgs &a) {
     if (a.M < t.bm || a.N < t.bn) continue;
     if (nk < t.min_steps) continue;
     const long tiles = (long)((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn);
-    const float us = (float)((tiles + kCus - 1) / kCus) * (t.start_us + t.step_us * (float)nk);
+    const long rounds = (tiles + kCus - 1) / kCus;
+    if ((t.bm == 192 || t.bn == 192) && rounds > kRounds192) continue;
+    const float us = (float)rounds * (t.start_us + t.step_us * (float)nk);
     if (best < 0 || us < best_us || (us == best_us && tiles < best_tiles)) { best = i; best_us = us; best_tiles = tiles; }
   }
   return best;

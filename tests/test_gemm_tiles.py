@@ -17,6 +17,14 @@ def test_the_gpu_tests_reach_every_192_tile_ragged(tile, mode, M, N, ks):
     test_the_gpu_tests_reach_every_tile_ragged(tile, mode, M, N, ks)
 
 
+# 192 rows or columns for at most four rounds of 256 tiles
+@pytest.mark.parametrize("tile,mode,M,N,K", [((256, 192), 0, 4096, 4800, 1600), ((256, 192), 1, 6144, 6144, 2048), ((256, 192), 1, 11648, 4200, 1208),
+                                             ((256, 256), 0, 5828, 12576, 840), ((256, 256), 0, 12143, 5960, 1256),
+                                             ((256, 256), 1, 6016, 14232, 1608), ((256, 256), 0, 8989, 8112, 2280)])
+def test_where_tiles_of_192_end(tile, mode, M, N, K):
+    assert B.op_gemm_tile(mode, M, N, K) == tile
+
+
 def test_other_kernels_products_have_no_tile():
     for mode, m, n, k in ((0, 128, 128, 63), (0, 127, 128, 64), (0, 128, 130, 64), (0, 128, 128, 68), (1, 132, 128, 64),
                           (0, 0, 128, 64)):

@@ -160,7 +160,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(WGM * WGN / 4, WGM * WGN / 4), amd
   //       Panels of 96 columns: three requests are 16 k rows; 16-byte chunk 64 v + l of them (v = 0, 1, 2) is k row
   //       (64 v + l) / 12, position (64 v + l) % 12.  A wave takes its 16 of the 64 k rows in both panels.
   const unsigned lda = (unsigned)(TN ? M : K) * 2u, ldb = (unsigned)(TN ? N : K) * 2u;   // operand row bytes
-  constexpr int RPA = TN ? 1024 / ROWB_A : 8, RPB = TN ? 1024 / ROWB_B : 8;              // rows per request (panels: see row0)
+  constexpr int RPA = TN ? 1024 / ROWB_A : 8, RPB = TN ? 1024 / ROWB_B : 8;              // rows per request (panels: see start)
   constexpr int GA = PANEL_A ? 3 : TN ? 8 / RPA : 1, GB = PANEL_B ? 3 : TN ? 8 / RPB : 1;   // requests per group
   constexpr int VA = PANEL_A ? 3 : 2, VB = PANEL_B ? 3 : 2;                              // values of the lane offsets
   static_assert((PANEL_A || (RPA >= 2 && RPA <= 8)) && (PANEL_B || (RPB >= 2 && RPB <= 8)), "tile width 64, 128, 192 or 256");
@@ -586,16 +586,29 @@ hipError_t launch_dma_cfg(const GemmArgs &a, hipStream_t s) {
 // is lost in the last one than the estimate says.  52 products of 2 to 3.2 rounds of 256x256 took 0.90 of its time in three or four
 // rounds, one of them longer by more than 1 %; 21 of 4 to 4.6 rounds 1.00, eight of them longer, up to [5828 x 12576] x 840 NT
 // 145 / 157 us; 17 of 5 and 6 rounds 0.97, five longer, up to [6016 x 14232] x 1608 TN 262 / 285.
-struct TileTime { int bm, bn; float start_us, step_us; int min_steps; };
+struct TileTime { int bm, bn; float start_us, step_us; int min_steps; };   // min_steps: the fewest k-steps it is chosen for
 enum { k256x256, k256x192, k192x256, k192x192, k256x128, k128x256, k192x128, k128x192, k128x128, k128x64, k64x128, k64x64, kTiles };
 constexpr TileTime kTileTimes[kTiles] = {
     {256, 256, 6.0f, 1.27f, 3}, {256, 192, 5.2f, 1.03f, 9}, {192, 256, 5.2f, 1.03f, 9}, {192, 192, 4.0f, 0.88f, 9},
     {256, 128, 4.5f, 0.83f, 1}, {128, 256, 4.5f, 0.83f, 1}, {192, 128, 3.5f, 0.70f, 9}, {128, 192, 3.5f, 0.70f, 9},
     {128, 128, 2.0f, 0.55f, 1}, {128, 64, 1.5f, 0.40f, 1},  {64, 128, 1.5f, 0.40f, 1},  {64, 64, 1.5f, 0.26f, 1}};
 constexpr int kCus = 256, kRounds192 = 4;
+// The fewest k-steps a tile can run: the rings of the three largest are filled before the loop (SPLIT)
+constexpr int fewest_steps(int tile) { return tile <= k192x256 ? 3 : 1; }
+
+// DPSTAGE_GEMM_TILE=256x192 and the like names the tile of every product that can run in it (tuning aid)
+int asked_tile(const GemmArgs &a, int nk) {
+  static const char *force = getenv("DPSTAGE_GEMM_TILE");
+  int bm = 0, bn = 0;
+  if (force == nullptr || sscanf(force, "%dx%d", &bm, &bn) != 2) return -1;
+  for (int i = 0; i < kTiles; ++i)
+    if (kTileTimes[i].bm == bm && kTileTimes[i].bn == bn && a.M >= bm && a.N >= bn && nk >= fewest_steps(i)) return i;
+  return -1;
+}
 
 int choose_tile(const GemmArgs &a) {
-  const int nk = (a.K + 63) / 64;
+  const int nk = (a.K + 63) / 64, asked = asked_tile(a, nk);
+  if (asked >= 0) return asked;
   int best = -1;
   float best_us = 0.f;
   long best_tiles = 0;
@@ -614,16 +627,7 @@ int choose_tile(const GemmArgs &a) {
 
 template <bool TN>
 hipError_t launch_dma_mode(const GemmArgs &a, hipStream_t s) {
-  int tile = choose_tile(a);
-  // DPSTAGE_GEMM_TILE overrides the tile choice (tuning aid)
-  static const char *force = getenv("DPSTAGE_GEMM_TILE");
-  if (force != nullptr) {
-    int bm = 0, bn = 0;
-    if (sscanf(force, "%dx%d", &bm, &bn) == 2)
-      for (int i = 0; i < kTiles; ++i)
-        if (kTileTimes[i].bm == bm && kTileTimes[i].bn == bn && a.M >= bm && a.N >= bn && a.K > 128) tile = i;
-  }
-  switch (tile) {
+  switch (choose_tile(a)) {
     case k256x256: return launch_dma_cfg<256, 256, 2, 2, 2, TN, true>(a, s);
     case k256x192: return launch_dma_cfg<256, 192, 2, 2, 2, TN, true>(a, s);
     case k192x256: return launch_dma_cfg<192, 256, 2, 2, 2, TN, true>(a, s);

@@ -1,4 +1,8 @@
 """The tile a product is computed in, as the library's host code states it (no GPU)."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 from paper_2505_05856_amd import binding as B
@@ -23,6 +27,18 @@ def test_the_gpu_tests_reach_every_192_tile_ragged(tile, mode, M, N, ks):
                                              ((256, 256), 1, 6016, 14232, 1608), ((256, 256), 0, 8989, 8112, 2280)])
 def test_where_tiles_of_192_end(tile, mode, M, N, K):
     assert B.op_gemm_tile(mode, M, N, K) == tile
+
+
+# the tuning aid names the tile of every product that can run in it: the three whose rings are filled first need three k-steps
+@pytest.mark.parametrize("asked,tiles", [("128x128", [(128, 128)] * 3), ("192x192", [(192, 192)] * 3),
+                                         ("256x192", [None, None, (256, 192)]), ("256x256", [None, None, (256, 256)])])
+def test_the_tile_asked_for_is_taken_where_it_runs(asked, tiles):
+    code = "from paper_2505_05856_amd import binding as B; print([B.op_gemm_tile(0, 4096, 1024, k) for k in (64, 128, 192)])"
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, DPSTAGE_GEMM_TILE=asked), cwd=root, capture_output=True, text=True)
+    assert out.returncode == 0, out.stderr
+    own = [B.op_gemm_tile(0, 4096, 1024, k) for k in (64, 128, 192)]
+    assert eval(out.stdout) == [t or o for t, o in zip(tiles, own)]
 
 
 def test_other_kernels_products_have_no_tile():

@@ -114,12 +114,9 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
 #pragma unroll
     for (int i = 0; i < 8; ++i) { dg[c][i] = 0.f; db[c][i] = 0.f; if (SUMDX) ds[c][i] = 0.f; }
   const float inv_n = 1.0f / (float)cols;
-  // Up to 2048 columns the row stays in registers between the row reductions and the output;
-  // wider rows are read twice (the second time out of the caches): there the column
-  // accumulators alone take 16..24 registers per 512 columns, and occupancy is what hides
-  // the latency (measured: 4096 columns 1.6 instead of 2.0 ms for the 8 launches of a step;
-  // 1024 and 1600 columns the other way round).  Same arithmetic, same order, either way.
-  if constexpr (NC <= 4 && AHEAD) {
+  // the row stays in registers between the row reductions and the output (wider ones: ln_bwd_wide_kernel)
+  static_assert(NC <= 4, "rows of up to 2048 columns");
+  if constexpr (AHEAD) {
     // Everything a row needs from memory (x, dy, its statistics, the residual gradient) is asked
     // for while the row before it is being worked on and waits in registers as loaded, so a row
     // costs the wave one trip to memory that overlaps the previous row's work, instead of two in
@@ -204,7 +201,7 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
       }
       fetch_res(row + NW);
     }
-  } else if constexpr (NC <= 4) {
+  } else {
     for (int row = blockIdx.x * rpb + wave; row < row_end; row += NW) {
       const float mean = stats[2 * (size_t)row], rstd = stats[2 * (size_t)row + 1];
       const size_t base = (size_t)row * cols;
@@ -248,58 +245,6 @@ __global__ __launch_bounds__(64 * NW) void ln_bwd_kernel(const T *dy /* may alia
           if (dres != nullptr) {
             float r[8];
             if (NW > 4) rr[NW > 4 ? c : 0].unpack(r); else load8(dres + base + col, r);
-  #pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] += r[i];
-          }
-          store8(dx + base + col, o);
-          if (SUMDX) {
-  #pragma unroll
-            for (int i = 0; i < 8; ++i) ds[c][i] += (float)(T)o[i];   // the value as stored
-          }
-        }
-      }
-    }
-  } else {
-    for (int row = blockIdx.x * rpb + wave; row < row_end; row += NW) {
-      const float mean = stats[2 * (size_t)row], rstd = stats[2 * (size_t)row + 1];
-      const size_t base = (size_t)row * cols;
-        float s1 = 0.f, s2 = 0.f;
-  #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int col = (c * 64 + lane) * 8;
-        if (col < cols) {
-          float xh[8], d[8], gm[8];
-          load8(x + base + col, xh);
-          load8(dy + base + col, d);
-          load8(gamma + col, gm);
-  #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            xh[i] = (xh[i] - mean) * rstd;
-            dg[c][i] += d[i] * xh[i];
-            db[c][i] += d[i];
-            const float g = d[i] * gm[i];
-            s1 += g;
-            s2 += g * xh[i];
-          }
-        }
-      }
-      const float m1 = rms ? 0.f : wave_sum(s1) * inv_n, m2 = wave_sum(s2) * inv_n;
-  #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        const int col = (c * 64 + lane) * 8;
-        if (col < cols) {
-          float xh[8], d[8], gm[8], o[8];
-          load8(x + base + col, xh);
-          load8(dy + base + col, d);
-          load8(gamma + col, gm);
-  #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            xh[i] = (xh[i] - mean) * rstd;
-            o[i] = rstd * (d[i] * gm[i] - m1 - xh[i] * m2);
-          }
-          if (dres != nullptr) {
-            float r[8];
-            load8(dres + base + col, r);
   #pragma unroll
             for (int i = 0; i < 8; ++i) o[i] += r[i];
           }
@@ -1032,7 +977,7 @@ static hipError_t ln_bwd_t(int rows, int cols, const void *dy, const void *x, co
   do {                                                                              \
     if (row_a_wave) DP_LN_BWD_AS(NC, false, 8);                                     \
     else if (NC <= 2 || rpb >= 16) DP_LN_BWD_AS(NC, true, 4);                       \
-    else DP_LN_BWD_AS(NC, false, 4);                                                \
+    else DP_LN_BWD_AS(4, false, 4);   /* (NC = 4) */                                \
   } while (0)
 #define DP_LN_BWD_WIDE_AS(NP, FULL, RES)                                                                      \
   hipLaunchKernelGGL((ln_bwd_wide_kernel<T, NP, SUMDX, FULL, RES>), dim3(nb), dim3(256), 0, s, (const T *)dy, \

@@ -504,8 +504,13 @@ void dp_stage_destroy(dp_stage *st);
 const char *dp_last_error(void);
 
 /* Standalone operator entry points (device pointers, row-major, enqueue on
- * `hip_stream`, no host wait).  They run the same kernels dp_stage_step uses
- * and exist for operator-level parity tests and microbenchmarks.
+ * `hip_stream`, no host wait).  They exist for operator-level parity tests and
+ * microbenchmarks and run the kernels dp_stage_step uses, with one exception: norm
+ * backward without dx_colsum, activation backward and column sums of few rows take
+ * one launch here where a step takes two.  It adds the rows in another order, so
+ * dgamma, dbeta, dbias and the column sums may differ from a step's in their last
+ * bits; dx has the same ones.  Where such an output lies in an input the two
+ * launches are kept.
  * `ws` is a device workspace of at least dp_op_workspace_bytes(...) bytes
  * (needed by the ops that reduce over rows; may be NULL otherwise).
  * Empty inputs are valid: with a zero extent nothing is read (the corresponding
@@ -533,8 +538,8 @@ dp_status dp_op_rmsnorm_bwd(int32_t dtype, int32_t rows, int32_t cols, const voi
                             void *hip_stream);
 dp_status dp_op_gelu_fwd(int32_t dtype, int32_t gelu_kind, size_t n, const void *x, void *y, void *hip_stream);
 /* dx = dy * gelu'(x) over [rows, cols], and dbias [cols] = the column sums of dx as stored (the
- * bias gradient of the linear layer in front of the activation): the one kernel the stage's
- * backward runs for this node.  dy may be dx.  ws: dp_op_workspace_bytes(rows, cols). */
+ * bias gradient of the linear layer in front of the activation), in one pass over dy and x, as
+ * the stage's backward does it.  dy may be dx.  ws: dp_op_workspace_bytes(rows, cols). */
 dp_status dp_op_gelu_bwd(int32_t dtype, int32_t gelu_kind, int32_t rows, int32_t cols, const void *dy,
                          const void *x, void *dx, void *dbias, void *ws, void *hip_stream);
 /* C[M,N] = op(A)*op(B) (+bias[N]) (+res[M,N]).  mode 0 ("NT"): A [M,K], B [N,K]

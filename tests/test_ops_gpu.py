@@ -269,7 +269,22 @@ def test_sums_that_lie_in_an_input_take_two_launches():
         assert np.array_equal(t[place][rows - 1].cpu().numpy(), want), place
 
 
-# the norm backward with the column sums of dx: 8 waves a block up to 2048 rows, 16 up to 4096 (bf16, 1024 columns), 4 from there on
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("cols", [24, 776, 1600, 2048])
+def test_norm_backward_of_few_rows_has_the_dx_of_two_launches(dt, cols):
+    rows = 200
+    tx, tdy, tres = (dev(rnd((rows, cols), seed, dt), dt) for seed in (11, 14, 15))
+    tg, stats = dev(rnd((cols,), 12, dt) * 0.1 + 1, dt), torch.empty(rows, 2, dtype=torch.float32, device=DEV)
+    B.op_layernorm_fwd(tx, tg, tg, 1e-5, torch.empty_like(tx), stats)
+    for res in (None, tres):
+        one, two, (dg, db, ds) = torch.empty_like(tx), torch.empty_like(tx), (torch.empty_like(tg) for _ in range(3))
+        B.op_layernorm_bwd(tdy, tx, stats, tg, res, one, dg, db, ws_for(rows, cols))
+        B.op_layernorm_bwd(tdy, tx, stats, tg, res, two, dg, db, ws_for(rows, cols), dx_colsum=ds)
+        assert torch.equal(one, two)
+
+
+# the norm backward with the column sums of dx: 8 waves a block up to 2048 rows, and for rows of at most 2 KB up to 4096 (with a residual
+# gradient 3072); 4 from there on
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("rows,cols", [(9, 1608), (1000, 776), (2048, 2048), (2049, 520), (4090, 1024), (2300, 1032), (4097, 72)])
 def test_norm_backward_waves(dt, rows, cols):

@@ -103,23 +103,30 @@ __device__ __forceinline__ float normal_cdf_parts(float x, float *density_exp) {
 }
 //
 // tanh form (kind 1): 0.5 x (1 + tanh u) = x s with the logistic function s = 1 / (1 + exp(-2u)), which is what bf16 results
-// take: an exponential and a reciprocal, where tanhf's instructions, not memory, bound the kernels (us, tanhf / this: forward
-// 8192x6400 41.7 / 31.6, 4096x4096 17.4 / 13.8; backward 8192x6400 66.2 / 60.9, 1500x4096 17.0 / 13.8).  Value and derivative of
+// take: an exponential and a reciprocal, where tanhf's instructions, not memory, bound the kernels (us, tanhf / this, operands from
+// memory: forward 8192x6400 47.2 / 39.1, 4096x4096 17.7 / 14.6; backward 8192x6400 67.1 / 65.3, 1500x4096 16.8 / 12.7).  Value and derivative of
 // every bf16 number round to the nearest bf16 (with tanhf, which loses them to 1 + tanh, 117 and 117 between -8 and -2 do not).  As
-// 32-bit numbers s has a few roundings more (error over N(0,1), of the norm: value 4.7e-8, derivative 5.8e-8, tanhf 3.8e-8 and
-// 4.7e-8), so fp32 results keep tanhf.
+// 32-bit numbers they are nearer to the exact ones than with tanhf as well: error of the norm over N(0,1), value and derivative,
+// 3.3e-8 and 3.7e-8 (tanhf 3.8e-8 and 4.7e-8; with the reciprocal alone 4.7e-8 and 5.8e-8, 38.6 and 64.5 us), N(0,0.3) 3.9e-8 and 3.2e-8
+// (4.1e-8 and 4.0e-8).
 // Zeros, infinities, NaN and arguments whose cube overflows give what tanhf gave.
-__device__ __forceinline__ float tanh_logistic(float x, float *e) {
+struct Logistic { float s, lo, e; };   // s, what its rounding left, exp(-2u) (finite: s is 0 where it overflows)
+__device__ __forceinline__ Logistic tanh_logistic(float x) {
 #pragma clang fp contract(off)
+  constexpr float kMax = 3.402823466e38f;
   // exp(-2u) = exp2(x (c1 + c2 x^2)), c1 = -2 log2(e) sqrt(2/pi), c2 = 0.044715 c1
-  *e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, -0.10294324f, -2.3022082f));
-  return __builtin_amdgcn_rcpf(1.0f + *e);
+  const float e = __builtin_amdgcn_exp2f(x * __builtin_fmaf(x * x, -0.10294324f, -2.3022082f));
+  // r = 1 / d is refined by one Newton step that also takes in what the rounding of d = 1 + e left
+  const float d = 1.0f + e, r = __builtin_amdgcn_rcpf(d), ec = fminf(e, kMax), dc = fminf(d, kMax);
+  const float t = __builtin_fmaf(-(ec - (dc - 1.0f)), r, __builtin_fmaf(-dc, r, 1.0f));
+  const float s = __builtin_fmaf(t, r, r);
+  return {s, __builtin_fmaf(t, r, r - s), ec};
 }
 template <typename T> __device__ __forceinline__ float gelu_f(float x, int kind) {
 #pragma clang fp contract(off)
   if (kind == 0) { float e; return x * normal_cdf_parts(x, &e); }
   if (kind == 2) return fmaxf(x, 0.f);   // ReLU
-  if constexpr (sizeof(T) == 2) { float e; return x * tanh_logistic(x, &e); }
+  if constexpr (sizeof(T) == 2) return x * tanh_logistic(x).s;
   const float u = 0.79788456080286536f * (x + 0.044715f * x * x * x);
   return 0.5f * x * (1.0f + tanhf(u));
 }
@@ -131,11 +138,9 @@ template <typename T> __device__ __forceinline__ float gelu_df(float x, int kind
     return cdf + x * (0.39894228040143268f * e);
   }
   if (kind == 2) return x > 0.f ? 1.0f : 0.f;   // ReLU: the derivative at 0 is taken as 0
-  if constexpr (sizeof(T) == 2) {   // s + x ds/dx = s + s (1 - s) x d(2u)/dx, and 1 - s = e s (finite e: s = 0 there, and so is e s s)
-    float e;
-    const float s = tanh_logistic(x, &e);
-    const float q = (fminf(e, 3.402823466e38f) * s) * s;
-    return __builtin_fmaf(q * x, __builtin_fmaf(x * x, 0.21406445f, 1.5957691f), s);
+  if constexpr (sizeof(T) == 2) {   // s + x ds/dx = s + s (1 - s) x d(2u)/dx, and 1 - s = e s
+    const Logistic g = tanh_logistic(x);
+    return __builtin_fmaf(g.e * g.s * g.s * x, __builtin_fmaf(x * x, 0.21406445f, 1.5957691f), g.lo) + g.s;
   }
   const float u = 0.79788456080286536f * (x + 0.044715f * x * x * x);
   const float t = tanhf(u);

@@ -25,16 +25,16 @@ PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 MFMA (v_mfma_f32_16x16x4): 256 CU x 
 # Bytes per launch of the dominant kernel that cross the L2 towards memory (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000,
 # the factors a 256 MiB device copy gives), from the rocprofv3 --pmc runs summarised in
 # profiles/c2_step_hbm_traffic_pmc.md and profiles/c5_step_hbm_traffic_pmc.md.
-MEASURED_TRAFFIC_BYTES = {("C2", "keep-all"): 80.4e6, ("C5", "seed7-mixed"): 2097.5e6}
+MEASURED_TRAFFIC_BYTES = {("C2", "keep-all"): 80.4e6, ("C5", "seed7-mixed"): 2097.9e6}
 # Average duration of an NT-form GEMM launch in the rocprofv3 kernel traces (profiles/*_step_kernel_trace.md).
 ROCPROF_NT_LAUNCH_US = {
-    ("C2", "keep-all"): {"us": 29.47, "hip_events_same_run_us": 33.84},
-    ("C5", "keep-all"): {"us": 880.69, "hip_events_same_run_us": 880.93},
+    ("C2", "keep-all"): {"us": 28.89, "hip_events_same_run_us": 33.22},
+    ("C5", "keep-all"): {"us": 881.36, "hip_events_same_run_us": 880.60},
     ("C5", "seed7-mixed"): {
-        "us": 1732.44, "hip_events_same_run_us": 1722.38,
+        "us": 1743.04, "hip_events_same_run_us": 1744.94,
         "note": "under the profiler this plan's device-to-host copies run as shader blit kernels beside the GEMMs and "
                 "slow them; the trace and the HIP events of that profiled run agree with each other, and the keep-all "
-                "trace (no copies: 880.69 us by rocprofv3, 880.93 us by HIP events in that run) shows the same kernels undisturbed"},
+                "trace (no copies: 881.36 us by rocprofv3, 880.60 us by HIP events in that run) shows the same kernels undisturbed"},
 }
 
 

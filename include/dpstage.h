@@ -432,7 +432,8 @@ dp_status dp_stage_bind_memory(dp_stage *st, const void *mem, void *d_mem, const
 /* Per-kernel-class timing of later steps: when enabled, every kernel launch is
  * bracketed by HIP events on the stream it runs on.  dp_stage_op_times waits
  * for the device, then returns (and clears) the summed milliseconds and launch
- * counts per class since the last call; arrays of DP_OPC_COUNT entries. */
+ * counts per class since the last call; arrays of DP_OPC_COUNT entries.  (A launch that
+ * is both products of a linear layer's backward counts for both classes, half its time each.) */
 dp_status dp_stage_set_profiling(dp_stage *st, int32_t enabled);
 dp_status dp_stage_op_times(dp_stage *st, float *ms_by_class, uint64_t *launches_by_class);
 /* Algorithmic work of the GEMM launches bracketed since the last call, 2*M*N*K each, summed per
@@ -552,6 +553,16 @@ dp_status dp_op_gemm(int32_t dtype, int32_t mode, int32_t M, int32_t N, int32_t 
 /* Diagnostic, no device work: the output tile a workgroup of dp_op_gemm takes for a bf16 product
  * of these sizes (16-byte aligned operands); 0 x 0 where a kernel without that choice has it. */
 dp_status dp_op_gemm_tile(int32_t mode, int32_t M, int32_t N, int32_t K, int32_t *tile_m, int32_t *tile_n);
+/* Both products of a linear layer's backward, y = x W + b with x [T,in], W [in,out] (as stored) and dy [T,out], as the
+ * stage's backward runs them: dx [T,in] = dy*W^T (+res), dw [in,out] = (accumulate ? dw : 0) + x^T*dy.  One launch
+ * where both are products of the matrix-core kernels, two of dp_op_gemm otherwise; the same bits either way.  res may be
+ * dx; no other overlap of an output with anything. */
+dp_status dp_op_linear_bwd(int32_t dtype, int32_t T, int32_t in, int32_t out, const void *dy, const void *w,
+                           const void *x, const void *res /*nullable*/, void *dx, void *dw, int32_t accumulate,
+                           void *hip_stream);
+/* Diagnostic, no device work: the output tiles (dx's rows and columns, dw's) of that launch in bf16; zeros where two
+ * launches are taken. */
+dp_status dp_op_linear_bwd_tiles(int32_t T, int32_t in, int32_t out, int32_t tiles[4]);
 /* out[cols] = sum over rows of x[rows, cols] */
 dp_status dp_op_colsum(int32_t dtype, int32_t rows, int32_t cols, const void *x, void *out, void *ws,
                        void *hip_stream);

@@ -157,6 +157,8 @@ def lib() -> C.CDLL:
     L.dp_op_gelu_bwd.argtypes = [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp]
     L.dp_op_gemm.argtypes = [i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, vp]
     L.dp_op_gemm_tile.argtypes = [i32, i32, i32, i32, C.POINTER(i32), C.POINTER(i32)]
+    L.dp_op_linear_bwd.argtypes = [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, i32, vp]
+    L.dp_op_linear_bwd_tiles.argtypes = [i32, i32, i32, C.POINTER(i32)]
     L.dp_op_colsum.argtypes = [i32, i32, i32, vp, vp, vp, vp]
     L.dp_op_colsum_static.argtypes = [i32, i32, i32, vp, vp, vp]
     L.dp_op_attention_fwd.argtypes = [i32, i32, i32, i32, i32, i32, vp, vp, vp, vp]
@@ -176,7 +178,7 @@ def lib() -> C.CDLL:
     L.dp_stage_measure_cost_model.argtypes = [vp, vp, vp, vp, vp, C.POINTER(LayerPtrs), vp, i32, C.POINTER(CostModel)]
     for name in ("dp_probe_mfma", "dp_partition", "dp_plan_cost", "dp_plan_generate", "dp_stage_measure_cost_model", "dp_plan_validate", "dp_stage_init", "dp_stage_step", "dp_stage_forward", "dp_stage_backward", "dp_stage_set_weights", "dp_stage_set_rng", "dp_stage_set_cross", "dp_stage_bind_memory", "dp_stage_set_profiling",
                  "dp_stage_op_times", "dp_stage_op_flops", "dp_stage_set_debug", "dp_op_layernorm_fwd", "dp_op_layernorm_bwd",
-                 "dp_op_gelu_fwd", "dp_op_gelu_bwd", "dp_op_gemm", "dp_op_gemm_tile", "dp_op_colsum", "dp_op_colsum_static", "dp_op_attention_fwd",
+                 "dp_op_gelu_fwd", "dp_op_gelu_bwd", "dp_op_gemm", "dp_op_gemm_tile", "dp_op_linear_bwd", "dp_op_linear_bwd_tiles", "dp_op_colsum", "dp_op_colsum_static", "dp_op_attention_fwd",
                  "dp_op_attention_bwd", "dp_op_dropout", "dp_op_attention_dropout_fwd", "dp_op_attention_dropout_bwd",
                  "dp_op_cross_attention_fwd", "dp_op_cross_attention_bwd",
                  "dp_op_rmsnorm_fwd", "dp_op_rmsnorm_bwd"):
@@ -485,6 +487,19 @@ def op_gemm_tile(mode, M, N, K):
     tm, tn = C.c_int32(), C.c_int32()
     _check(lib().dp_op_gemm_tile(mode, M, N, K, C.byref(tm), C.byref(tn)))
     return tm.value, tn.value
+
+
+def op_linear_bwd(dy, w, x, res, dx, dw, accumulate=False, stream=None):
+    """dx = dy w^T (+ res) and dw (+)= x^T dy for a linear layer's x [T, in], w [in, out], dy [T, out]."""
+    _check(lib().dp_op_linear_bwd(_dt(dy), dy.shape[0], w.shape[0], w.shape[1], _ptr(dy), _ptr(w), _ptr(x), _ptr(res), _ptr(dx),
+                                  _ptr(dw), 1 if accumulate else 0, _stream_ptr(stream)))
+
+
+def op_linear_bwd_tiles(T, n_in, n_out):
+    """((rows, columns) of dx's output tile, dw's) where the two bf16 products are one launch; zeros where they are two."""
+    t = (C.c_int32 * 4)()
+    _check(lib().dp_op_linear_bwd_tiles(T, n_in, n_out, t))
+    return (t[0], t[1]), (t[2], t[3])
 
 
 def op_colsum(x, out, ws, stream=None):

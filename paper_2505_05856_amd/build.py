@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdpstage.so")
-SOURCES = ["stage.cpp", "planner.cpp", "ops.cpp", "elementwise.hip", "gemm_simple.hip", "gemm_f32.hip", "attn_simple.hip", "gemm_mfma.hip", "gemm_dma.hip", "attn_mfma.hip", "probe.hip"]
+SOURCES = ["stage.cpp", "planner.cpp", "ops.cpp", "elementwise.hip", "gemm_simple.hip", "gemm_f32.hip", "attn_simple.hip", "gemm_mfma.hip", "gemm_dma.hip", "gemm_pair.hip", "attn_mfma.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
@@ -20,7 +20,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
 # Kernels that issue global loads through inline asm and count them by hand must not
 # spill: a spill store placed by the compiler right behind such a load would save the
 # register before the data has arrived.
-NO_SCRATCH = {"gemm_mfma.hip", "gemm_dma.hip"}
+NO_SCRATCH = {"gemm_mfma.hip", "gemm_dma.hip", "gemm_pair.hip"}
 
 # Per-file compiler options.  attn_mfma.hip: with head dimension 128 the backward kernels keep
 # 128 accumulator registers per wave beside 64 operand registers; by default the compiler puts
@@ -29,14 +29,14 @@ NO_SCRATCH = {"gemm_mfma.hip", "gemm_dma.hip"}
 # registers for them removes nearly all of those moves.
 EXTRA_FLAGS = {"attn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-Wno-inline-asm"],
                # the LDS-direct load names M0 as clobbered; clang warns that M0 is a reserved register
-               "gemm_dma.hip": ["-Wno-inline-asm"]}
+               "gemm_dma.hip": ["-Wno-inline-asm"], "gemm_pair.hip": ["-Wno-inline-asm"]}
 
 
 # Files whose inline asm writes M0 (the LDS-direct loads).  The asm declares the clobber, but M0 is a reserved
 # register the compiler also uses by itself (LDS-indexed operations, lane moves, spill code) without modelling
 # inline asm's writes: such a use next to the loads would be a silent miscompile.  The device assembly of these
 # files must therefore name M0 only inside the inline asm blocks.
-M0_BY_HAND = {"gemm_dma.hip", "attn_mfma.hip"}
+M0_BY_HAND = {"gemm_dma.hip", "gemm_pair.hip", "attn_mfma.hip"}
 
 
 def device_asm(src: str, asm: str) -> None:
@@ -47,20 +47,33 @@ def device_asm(src: str, asm: str) -> None:
         raise RuntimeError(f"hipcc -S failed for {src}:\n{r.stderr}")
 
 
-def _check_m0(src: str) -> None:
+# The products' main loops count their LDS-direct loads themselves and wait once a k-step.  A wait the compiler adds for a load
+# it believes to be in flight (it did, for the epilogue's of another tile of the same kernel) is no error and halves the rate.
+ONE_WAIT_A_STEP = {"gemm_dma.hip", "gemm_pair.hip"}
+
+
+def _check_device_asm(src: str) -> None:
     asm = os.path.join(OBJ, os.path.splitext(src)[0] + ".s")
     device_asm(src, asm)
     inside = False
+    ops = []                # instructions since the last label
     with open(asm) as f:
         for n, line in enumerate(f, 1):
+            code = line.split(";", 1)[0]
             if "#ASMSTART" in line:
                 inside = True
             elif "#ASMEND" in line:
                 inside = False
-            elif not inside:
-                code = line.split(";", 1)[0]
-                if re.search(r"\bm0\b", code):
-                    raise RuntimeError(f"{src}: the compiler uses M0 outside the inline asm ({asm}:{n}: {line.strip()})")
+            elif not inside and re.search(r"\bm0\b", code):
+                raise RuntimeError(f"{src}: the compiler uses M0 outside the inline asm ({asm}:{n}: {line.strip()})")
+            if re.match(r"\.L\w+:", code):
+                ops = []
+            elif code.strip():
+                ops.append(code.strip())
+                if src in ONE_WAIT_A_STEP and ops[-1].startswith("s_barrier") and any(o.startswith("v_mfma") for o in ops):
+                    if sum("vmcnt(" in o for o in ops) != 1:
+                        raise RuntimeError(f"{src}: a k-step waits for loads more than once ({asm}:{n})")
+                    ops = []
     os.remove(asm)
 
 
@@ -98,7 +111,7 @@ def _compile(src: str) -> str:
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
-        checks = [ex.submit(_check_m0, src) for src in SOURCES if src in M0_BY_HAND]
+        checks = [ex.submit(_check_device_asm, src) for src in SOURCES if src in M0_BY_HAND]
         objs = list(ex.map(_compile, SOURCES))
         for check in checks:
             check.result()

@@ -28,16 +28,17 @@ namespace {
 
 template <int F> struct Vec { typedef float t __attribute__((ext_vector_type(F))); };
 
+// One tile of the product, number `tile`, by the whole workgroup; `part`: LDS of the divided form, [4][16 F][16 F + 4].
 template <int F, int D, bool TN, bool SPLIT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ B,
-                                                       const float *__restrict__ bias, const float *res, float *C, int M,
-                                                       int N, int K, int tiles_n) {
+__device__ __forceinline__ void gemm_f32_body(const float *__restrict__ A, const float *__restrict__ B,
+                                              const float *__restrict__ bias, const float *res, float *C, int M, int N, int K,
+                                              int tiles_n, int tile, float *lds_part) {
   typedef typename Vec<F>::t vecF;
   constexpr int WT = 16 * F, LD = WT + 4;
-  __shared__ __attribute__((aligned(16))) float part[SPLIT ? 4 : 1][SPLIT ? WT : 1][LD];
+  auto part = reinterpret_cast<float (*)[WT][LD]>(lds_part);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4;
-  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
+  const int tm = tile / tiles_n, tn = tile % tiles_n;
   const int m0 = SPLIT ? tm * WT : tm * 2 * WT + (wave >> 1) * WT;
   const int n0 = SPLIT ? tn * WT : tn * 2 * WT + (wave & 1) * WT;
   const int nch = (K + 15) / 16;                           // chunks of the contraction
@@ -157,6 +158,16 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
   }
 }
 
+constexpr int part_floats(int F, bool split) { return split ? 4 * 16 * F * (16 * F + 4) : 4; }
+
+template <int F, int D, bool TN, bool SPLIT>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ A, const float *__restrict__ B,
+                                                       const float *__restrict__ bias, const float *res, float *C, int M,
+                                                       int N, int K, int tiles_n) {
+  __shared__ __attribute__((aligned(16))) float part[part_floats(F, SPLIT)];
+  gemm_f32_body<F, D, TN, SPLIT>(A, B, bias, res, C, M, N, K, tiles_n, blockIdx.x, part);
+}
+
 template <int F, int D, bool TN, bool SPLIT>
 hipError_t launch_f32(const GemmArgs &a, hipStream_t s) {
   constexpr int T = SPLIT ? 16 * F : 32 * F;
@@ -164,6 +175,31 @@ hipError_t launch_f32(const GemmArgs &a, hipStream_t s) {
   hipLaunchKernelGGL((gemm_f32_kernel<F, D, TN, SPLIT>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), 0, s,
                      (const float *)a.A, (const float *)a.B, (const float *)a.bias, (const float *)a.res, (float *)a.C, a.M,
                      a.N, a.K, tiles_n);
+  return hipGetLastError();
+}
+
+// The two products of a linear layer's backward (NT: dX = dY W^T, TN: dW = X^T dY) in one launch, in the tiles each has alone:
+// the first n_nt workgroups are dX's.
+struct F32Side {
+  const float *A, *B, *res;
+  float *C;
+  int M, N, K, tiles_n;
+};
+template <int FN, int FT>
+__global__ __launch_bounds__(256) void gemm_f32_pair_kernel(F32Side nt, F32Side tn, int n_nt) {
+  __shared__ __attribute__((aligned(16))) float part[part_floats(FN > FT ? FN : FT, true)];
+  const int b = blockIdx.x;
+  if (b < n_nt) gemm_f32_body<FN, 4, false, true>(nt.A, nt.B, nullptr, nt.res, nt.C, nt.M, nt.N, nt.K, nt.tiles_n, b, part);
+  else gemm_f32_body<FT, 4, true, true>(tn.A, tn.B, nullptr, tn.res, tn.C, tn.M, tn.N, tn.K, tn.tiles_n, b - n_nt, part);
+}
+
+template <int FN, int FT> hipError_t launch_f32_pair(const GemmArgs &nt, const GemmArgs &tn, hipStream_t s) {
+  auto side = [](const GemmArgs &a, int t) {
+    return F32Side{(const float *)a.A, (const float *)a.B, (const float *)a.res, (float *)a.C, a.M, a.N, a.K, (a.N + t - 1) / t};
+  };
+  const F32Side sn = side(nt, 16 * FN), st = side(tn, 16 * FT);
+  const int n_nt = (nt.M + 16 * FN - 1) / (16 * FN) * sn.tiles_n, n_tn = (tn.M + 16 * FT - 1) / (16 * FT) * st.tiles_n;
+  hipLaunchKernelGGL((gemm_f32_pair_kernel<FN, FT>), dim3((unsigned)(n_nt + n_tn)), dim3(256), 0, s, sn, st, n_nt);
   return hipGetLastError();
 }
 
@@ -191,17 +227,35 @@ bool gemm_f32_supported(const GemmArgs &a) {
 // The vector-ALU kernel takes 52, 139, 168, 769 and 545 us for the products named so far with K > 64, 52.4 to 87.9 and
 // 13.9 to 21.9 us for the two of K <= 64, and 20 to 70 us where these kernels take under 7 ([128 x 128..512] x
 // 128..512, the products of a stage 128 wide).
-hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
+namespace {
+enum F32Form { k16, k32, k64, kWhole };   // tiles of 16, 32 or 64 whose waves divide the contraction; a wave each 64x64
+F32Form f32_form(const GemmArgs &a) {
   auto tiles = [&](int t) { return (long)((a.M + t - 1) / t) * ((a.N + t - 1) / t); };
-  if (tiles(128) >= 128) {
-    if (a.mode == kGemmTN) return launch_f32<4, 2, true, false>(a, s);
-    if (a.K <= 64) return launch_f32<4, 2, false, false>(a, s);
+  if (tiles(128) >= 128 && (a.mode == kGemmTN || a.K <= 64)) return kWhole;
+  if (tiles(16) <= 256) return k16;
+  return tiles(64) >= 128 ? k64 : k32;
+}
+}  // namespace
+
+hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s) {
+  const bool tn = a.mode == kGemmTN;
+  switch (f32_form(a)) {
+    case kWhole: return tn ? launch_f32<4, 2, true, false>(a, s) : launch_f32<4, 2, false, false>(a, s);
+    case k16: return tn ? launch_f32<1, 4, true, true>(a, s) : launch_f32<1, 4, false, true>(a, s);
+    case k64: return tn ? launch_f32<4, 2, true, true>(a, s) : launch_f32<4, 2, false, true>(a, s);
+    default: return tn ? launch_f32<2, 4, true, true>(a, s) : launch_f32<2, 4, false, true>(a, s);
   }
-  if (tiles(16) <= 256) return a.mode == kGemmTN ? launch_f32<1, 4, true, true>(a, s) : launch_f32<1, 4, false, true>(a, s);
-  if (a.mode == kGemmTN) {
-    return tiles(64) >= 128 ? launch_f32<4, 2, true, true>(a, s) : launch_f32<2, 4, true, true>(a, s);
-  }
-  return tiles(64) >= 128 ? launch_f32<4, 2, false, true>(a, s) : launch_f32<2, 4, false, true>(a, s);
+}
+
+// Where both products run in small tiles, a launch is most of their time.
+bool gemm_f32_pair_supported(const GemmArgs &nt, const GemmArgs &tn) {
+  return nt.mode == kGemmNT && tn.mode == kGemmTN && nt.bias == nullptr && tn.bias == nullptr && gemm_f32_supported(nt) &&
+         gemm_f32_supported(tn) && f32_form(nt) <= k32 && f32_form(tn) <= k32;
+}
+
+hipError_t launch_gemm_f32_pair(const GemmArgs &nt, const GemmArgs &tn, hipStream_t s) {
+  if (f32_form(nt) == k16) return f32_form(tn) == k16 ? launch_f32_pair<1, 1>(nt, tn, s) : launch_f32_pair<1, 2>(nt, tn, s);
+  return f32_form(tn) == k16 ? launch_f32_pair<2, 1>(nt, tn, s) : launch_f32_pair<2, 2>(nt, tn, s);
 }
 
 }  // namespace dp

@@ -126,6 +126,12 @@ hipError_t launch_gemm_f32(const GemmArgs &a, hipStream_t s);
 bool gemm_dma_supported(const GemmArgs &a);
 hipError_t launch_gemm_dma(const GemmArgs &a, hipStream_t s);
 void gemm_dma_tile(const GemmArgs &a, int *bm, int *bn);   // the tile launch_gemm_dma takes for it
+// The two products of a linear layer's backward (nt: dX = dY W^T, tn: dW = X^T dY) in one launch; same bits as one by one.
+bool gemm_pair_supported(const GemmArgs &nt, const GemmArgs &tn);
+hipError_t launch_gemm_pair(const GemmArgs &nt, const GemmArgs &tn, hipStream_t s);
+void gemm_pair_tiles(const GemmArgs &nt, const GemmArgs &tn, int tiles[4]);   // nt's rows and columns, tn's
+bool gemm_f32_pair_supported(const GemmArgs &nt, const GemmArgs &tn);
+hipError_t launch_gemm_f32_pair(const GemmArgs &nt, const GemmArgs &tn, hipStream_t s);
 
 // ---- attention ----------------------------------------------------------------
 // qkv [T,3H]; o [T,H] (nullable); lse [B,nh,S] fp32 (nullable); drop: dropout of the

@@ -97,6 +97,32 @@ dp_status dp_op_gemm_tile(int32_t mode, int32_t M, int32_t N, int32_t K, int32_t
   return DP_OK;
 }
 
+dp_status dp_op_linear_bwd(int32_t dtype, int32_t T, int32_t in, int32_t out, const void *dy, const void *w, const void *x,
+                           const void *res, void *dx, void *dw, int32_t accumulate, void *hip_stream) {
+  if (bad_dtype(dtype) || T < 0 || in < 0 || out < 0) return fail(DP_E_INVAL, "linear_bwd: bad argument");
+  if (T > 0 && in > 0 && out > 0) {
+    if (!dy || !w || !x || !dx || !dw) return fail(DP_E_INVAL, "linear_bwd: null operand");
+    const dp::GemmArgs nt{dp::kGemmNT, T, in, out, dy, w, nullptr, res, dx};
+    const dp::GemmArgs tn{dp::kGemmTN, in, out, T, x, dy, nullptr, accumulate ? dw : nullptr, dw};
+    if (env_mfma_enabled()) {
+      if (dtype == DP_BF16 && dp::gemm_pair_supported(nt, tn))
+        return op_done(dp::launch_gemm_pair(nt, tn, (hipStream_t)hip_stream), "linear_bwd");
+      if (dtype == DP_F32 && dp::gemm_f32_pair_supported(nt, tn))
+        return op_done(dp::launch_gemm_f32_pair(nt, tn, (hipStream_t)hip_stream), "linear_bwd");
+    }
+  }
+  const dp_status s = dp_op_gemm(dtype, 0, T, in, out, dy, w, nullptr, res, dx, hip_stream);
+  return s != DP_OK ? s : dp_op_gemm(dtype, 1, in, out, T, x, dy, nullptr, accumulate ? dw : nullptr, dw, hip_stream);
+}
+
+dp_status dp_op_linear_bwd_tiles(int32_t T, int32_t in, int32_t out, int32_t tiles[4]) {
+  if (T < 0 || in < 0 || out < 0 || !tiles) return fail(DP_E_INVAL, "linear_bwd_tiles: bad argument");
+  for (int i = 0; i < 4; ++i) tiles[i] = 0;
+  const dp::GemmArgs nt{dp::kGemmNT, T, in, out}, tn{dp::kGemmTN, in, out, T};
+  if (dp::gemm_pair_supported(nt, tn)) dp::gemm_pair_tiles(nt, tn, tiles);
+  return DP_OK;
+}
+
 dp_status dp_op_colsum(int32_t dtype, int32_t rows, int32_t cols, const void *x, void *out, void *ws,
                        void *hip_stream) {
   if (bad_dtype(dtype) || rows < 0 || cols <= 0 || !out || (rows > 0 && (!x || !ws))) return fail(DP_E_INVAL, "colsum: bad argument");

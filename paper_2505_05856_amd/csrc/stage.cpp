@@ -288,6 +288,9 @@ struct Flight {
   SwapPolicy v_hold;
 };
 
+// bracket of a launch that is both products of a linear layer's backward
+constexpr int kProfLinearBwd = DP_OPC_COUNT;
+
 struct dp_stage {
   Cfg c;
   dp_stage_config pub;
@@ -303,7 +306,7 @@ struct dp_stage {
   std::vector<hipEvent_t> events;       // sync events (no timing)
   bool profiling = false;
   std::vector<hipEvent_t> prof_events;  // timing pairs
-  std::vector<int> prof_class;
+  std::vector<int> prof_class;          // DP_OPC_*, or kProfLinearBwd
   std::vector<uint32_t> prof_tag;       // node of each bracket: phase << 16 | layer << 4 | node
   size_t prof_used = 0;
   double prof_flops[DP_OPC_COUNT] = {};  // algorithmic FLOP of the bracketed GEMM launches, by class
@@ -614,6 +617,30 @@ struct Walk {
       else if (c.dtype == DP_F32 && st->use_mfma && dp::gemm_f32_supported(a)) check(dp::launch_gemm_f32(a, cs));
       else check(dp::launch_gemm_simple(c.dtype, a, cs));
     }
+    prof_end();
+  }
+  // The two products of a linear layer's backward, dX = dY W^T (+ res) and dW = X^T dY: one launch where both run on the
+  // kernels of gemm_pair.hip.  The spans a plan's blocks are held for count two launch sites either way.
+  void linear_bwd(long T, long in, long out, const void *dyp, const void *w, const void *res, void *dx, const void *x, void *dw_out) {
+    auto args = [&](bool ptrs, int mode) {
+      const void *any = (const void *)16;
+      if (mode == dp::kGemmNT)
+        return dp::GemmArgs{mode, (int)T, (int)in, (int)out, ptrs ? dyp : any, ptrs ? w : any, nullptr, ptrs ? res : nullptr, ptrs ? dx : nullptr};
+      return dp::GemmArgs{mode, (int)in, (int)out, (int)T, ptrs ? x : any, ptrs ? dyp : any, nullptr,
+                          ptrs && accumulate ? dw_out : nullptr, ptrs ? dw_out : nullptr};   // dW += X^T dY
+    };
+    const bool on = live ? st->use_mfma : mfma_enabled;
+    const dp::GemmArgs nt = args(live, dp::kGemmNT), tn = args(live, dp::kGemmTN);
+    if (!on || !(c.dtype == DP_BF16 ? dp::gemm_pair_supported(nt, tn) : dp::gemm_f32_pair_supported(nt, tn))) {
+      gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, in, out, dyp, w, nullptr, res, dx);
+      gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, in, out, T, x, dyp, nullptr, nullptr, dw_out);
+      return;
+    }
+    if (live && st->profiling)
+      for (int cls : {DP_OPC_GEMM_DGRAD, DP_OPC_GEMM_WGRAD}) st->prof_flops[cls] += 2.0 * (double)T * (double)in * (double)out;
+    if (!no_arena) arena.tick();
+    prof_begin(kProfLinearBwd);
+    if (live) check(c.dtype == DP_BF16 ? dp::launch_gemm_pair(nt, tn, cs) : dp::launch_gemm_f32_pair(nt, tn, cs));
     prof_end();
   }
   // The second passes of the backward's column reductions (bias and LayerNorm parameter
@@ -998,13 +1025,10 @@ struct Walk {
         Buf dg = tmp(tf);
         if (c.drop_hidden) {
           Buf dym = masked_grad(l, dp::kSiteFc2, dcur, G_(b_fc2));
-          gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, F, H, bptr(dym), W_(w_fc2), nullptr, nullptr, bptr(dg));
-          gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, F, H, T, ptr(l, DP_SLOT_GELU_OUT), bptr(dym), nullptr, nullptr,
-               G_(w_fc2));
+          linear_bwd(T, F, H, bptr(dym), W_(w_fc2), nullptr, bptr(dg), ptr(l, DP_SLOT_GELU_OUT), G_(w_fc2));
           drop(dym);
         } else {
-          gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, F, H, dcur, W_(w_fc2), nullptr, nullptr, bptr(dg));
-          gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, F, H, T, ptr(l, DP_SLOT_GELU_OUT), dcur, nullptr, nullptr, G_(w_fc2));
+          linear_bwd(T, F, H, dcur, W_(w_fc2), nullptr, bptr(dg), ptr(l, DP_SLOT_GELU_OUT), G_(w_fc2));
           // db2 = column sums of dY: below the top layer they come out of the LayerNorm backward
           // that produced dY (layer l+1's LN1)
           if (l == c.L - 1) colsum(T, H, dcur, G_(b_fc2));
@@ -1019,9 +1043,7 @@ struct Walk {
         need(l, {DP_SLOT_LN2_OUT});
         begin_node(TAG_BWD, l, 2);
         Buf dc = tmp(th);
-        gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, F, bptr(dg), W_(w_fc1), nullptr, nullptr, bptr(dc));
-        gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, F, T, ptr(l, DP_SLOT_LN2_OUT), bptr(dg), nullptr, nullptr,
-             G_(w_fc1));
+        linear_bwd(T, H, F, bptr(dg), W_(w_fc1), nullptr, bptr(dc), ptr(l, DP_SLOT_LN2_OUT), G_(w_fc1));
         drop(dg);
         done_with(l, {DP_SLOT_LN2_OUT});
         // LN2: dM = dY + LN2'(dC), in place in dC
@@ -1043,8 +1065,7 @@ struct Walk {
           Buf dmm;
           if (c.drop_hidden) dmm = masked_grad(l, dp::kSiteProj, bptr(dm), G_(b_o));
           const void *dmp = c.drop_hidden ? bptr(dmm) : bptr(dm);
-          gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, H, dmp, W_(w_o), nullptr, nullptr, bptr(dob));
-          gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, H, T, ptr(l, DP_SLOT_ATTN_OUT), dmp, nullptr, nullptr, G_(w_o));
+          linear_bwd(T, H, H, dmp, W_(w_o), nullptr, bptr(dob), ptr(l, DP_SLOT_ATTN_OUT), G_(w_o));
           if (c.drop_hidden) drop(dmm);
         }
         Buf dqkv = attention_bwd(l, dob);
@@ -1052,9 +1073,7 @@ struct Walk {
         need(l, {DP_SLOT_LN1_OUT});
         begin_node(TAG_BWD, l, 6 + xo);
         Buf da = tmp(th);
-        gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, 3 * H, bptr(dqkv), W_(w_qkv), nullptr, nullptr, bptr(da));
-        gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, 3 * H, T, ptr(l, DP_SLOT_LN1_OUT), bptr(dqkv), nullptr, nullptr,
-             G_(w_qkv));
+        linear_bwd(T, H, 3 * H, bptr(dqkv), W_(w_qkv), nullptr, bptr(da), ptr(l, DP_SLOT_LN1_OUT), G_(w_qkv));
         drop(dqkv);
         done_with(l, {DP_SLOT_LN1_OUT});
         // LN1: dX = dM + LN1'(dA)
@@ -1083,8 +1102,7 @@ struct Walk {
           Buf dr2m;
           if (c.drop_hidden) dr2m = masked_grad(l, dp::kSiteFc2, bptr(dr2), G_(b_fc2));
           const void *dp2 = c.drop_hidden ? bptr(dr2m) : bptr(dr2);
-          gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, F, H, dp2, W_(w_fc2), nullptr, nullptr, bptr(dg));
-          gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, F, H, T, ptr(l, DP_SLOT_GELU_OUT), dp2, nullptr, nullptr, G_(w_fc2));
+          linear_bwd(T, F, H, dp2, W_(w_fc2), nullptr, bptr(dg), ptr(l, DP_SLOT_GELU_OUT), G_(w_fc2));
           if (c.drop_hidden) drop(dr2m);
         }
         done_with(l, {DP_SLOT_GELU_OUT});
@@ -1097,9 +1115,7 @@ struct Walk {
         need(l, {DP_SLOT_LN1_OUT});
         begin_node(TAG_BWD, l, 3);
         Buf dm = tmp(th);
-        gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, F, bptr(dg), W_(w_fc1), nullptr, bptr(dr2), bptr(dm));
-        gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, F, T, ptr(l, DP_SLOT_LN1_OUT), bptr(dg), nullptr, nullptr,
-             G_(w_fc1));
+        linear_bwd(T, H, F, bptr(dg), W_(w_fc1), bptr(dr2), bptr(dm), ptr(l, DP_SLOT_LN1_OUT), G_(w_fc1));
         drop(dg);
         drop(dr2);
         done_with(l, {DP_SLOT_LN1_OUT});
@@ -1118,8 +1134,7 @@ struct Walk {
           Buf dr1m;
           if (c.drop_hidden) dr1m = masked_grad(l, dp::kSiteProj, bptr(dr1), G_(b_o));
           const void *dp1 = c.drop_hidden ? bptr(dr1m) : bptr(dr1);
-          gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, H, dp1, W_(w_o), nullptr, nullptr, bptr(dob));
-          gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, H, T, ptr(l, DP_SLOT_ATTN_OUT), dp1, nullptr, nullptr, G_(w_o));
+          linear_bwd(T, H, H, dp1, W_(w_o), nullptr, bptr(dob), ptr(l, DP_SLOT_ATTN_OUT), G_(w_o));
           if (c.drop_hidden) drop(dr1m);
         }
         Buf dqkv = attention_bwd(l, dob);
@@ -1129,9 +1144,7 @@ struct Walk {
         Buf dxb;
         void *dxp = dx_out;
         if (l > 0) { dxb = tmp(th); dxp = bptr(dxb); }
-        gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, 3 * H, bptr(dqkv), W_(w_qkv), nullptr, bptr(dr1), dxp);
-        gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, 3 * H, T, ptr(l, DP_SLOT_X_IN), bptr(dqkv), nullptr, nullptr,
-             G_(w_qkv));
+        linear_bwd(T, H, 3 * H, bptr(dqkv), W_(w_qkv), bptr(dr1), dxp, ptr(l, DP_SLOT_X_IN), G_(w_qkv));
         drop(dqkv);
         drop(dr1);
         done_with(l, {DP_SLOT_X_IN});
@@ -1166,8 +1179,7 @@ struct Walk {
       Buf dmm;
       if (c.drop_hidden) dmm = masked_grad(l, dp::kSiteCrossProj, bptr(dm), XG_(b_o));
       const void *dmp = c.drop_hidden ? bptr(dmm) : bptr(dm);
-      gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, H, dmp, XW_(w_o), nullptr, nullptr, bptr(doc));
-      gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, H, T, ptr(l, DP_SLOT_ATTN_C_OUT), dmp, nullptr, nullptr, XG_(w_o));
+      linear_bwd(T, H, H, dmp, XW_(w_o), nullptr, bptr(doc), ptr(l, DP_SLOT_ATTN_C_OUT), XG_(w_o));
       if (c.drop_hidden) drop(dmm);
     }
     // attention: dQc, dKVc
@@ -1198,16 +1210,13 @@ struct Walk {
     colsum(Tm, 2 * H, bptr(dkvc), XG_(b_kv));
     // key/value projection: dMem (+)= dKVc Wkv^T (the top layer writes, the others add), dWkv = mem^T dKVc
     begin_node(TAG_BWD, l, 6);
-    gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, Tm, H, 2 * H, bptr(dkvc), XW_(w_kv), nullptr, l == c.L - 1 ? nullptr : d_mem,
-         d_mem);
-    gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, 2 * H, Tm, mem, bptr(dkvc), nullptr, nullptr, XG_(w_kv));
+    linear_bwd(Tm, H, 2 * H, bptr(dkvc), XW_(w_kv), l == c.L - 1 ? nullptr : d_mem, d_mem, mem, XG_(w_kv));
     drop(dkvc);
     // query projection: dC = dQc Wq^T, dWq = LNC_OUT^T dQc
     need(l, {DP_SLOT_LNC_OUT});
     begin_node(TAG_BWD, l, 7);
     Buf dcx = tmp(th);
-    gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, H, H, bptr(dqc), XW_(w_q), nullptr, nullptr, bptr(dcx));
-    gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, H, H, T, ptr(l, DP_SLOT_LNC_OUT), bptr(dqc), nullptr, nullptr, XG_(w_q));
+    linear_bwd(T, H, H, bptr(dqc), XW_(w_q), nullptr, bptr(dcx), ptr(l, DP_SLOT_LNC_OUT), XG_(w_q));
     drop(dqc);
     done_with(l, {DP_SLOT_LNC_OUT});
     // LayerNorm of the block: dR1 = dRc + LNc'(dC), in place in dC
@@ -1972,6 +1981,10 @@ dp_status dp_stage_op_times(dp_stage *st, float *ms_by_class, uint64_t *launches
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, st->prof_events[i], st->prof_events[i + 1]), DP_E_HIP);
     const int cls = st->prof_class[i / 2];
+    if (cls == kProfLinearBwd) {   // two products of as many FLOP each
+      for (int k : {DP_OPC_GEMM_DGRAD, DP_OPC_GEMM_WGRAD}) { ms_by_class[k] += 0.5f * ms; launches_by_class[k] += 1; }
+      continue;
+    }
     ms_by_class[cls] += ms;
     launches_by_class[cls] += 1;
   }

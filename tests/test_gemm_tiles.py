@@ -6,7 +6,7 @@ import sys
 import pytest
 
 from paper_2505_05856_amd import binding as B
-from test_ops_gpu import GEMM_TILES, GEMM_TILES_192
+from test_ops_gpu import GEMM_TILES, GEMM_TILES_192, LINEAR_BWD
 
 
 @pytest.mark.parametrize("tile,mode,M,N,ks", GEMM_TILES)
@@ -27,6 +27,16 @@ def test_the_gpu_tests_reach_every_192_tile_ragged(tile, mode, M, N, ks):
                                              ((256, 256), 1, 6016, 14232, 1608), ((256, 256), 0, 8989, 8112, 2280)])
 def test_where_tiles_of_192_end(tile, mode, M, N, K):
     assert B.op_gemm_tile(mode, M, N, K) == tile
+
+
+def test_the_gpu_tests_reach_every_tile_of_a_linear_backward_ragged():
+    for T, n_in, n_out, nt, tn in LINEAR_BWD:
+        assert B.op_linear_bwd_tiles(T, n_in, n_out) == (nt, tn)
+        assert T % nt[0] and n_in % nt[1] and n_in % tn[0] and n_out % tn[1] and T % 64 and n_out % 64
+    tiles = {(256, 256), (256, 192), (192, 256), (256, 128), (128, 256), (128, 128), (128, 64), (64, 128), (64, 64)}
+    assert {c[3] for c in LINEAR_BWD} == tiles == {c[4] for c in LINEAR_BWD}
+    for T, n_in, n_out in ((127, 128, 128), (128, 120, 128), (0, 128, 128), (200, 200, 132)):   # two launches
+        assert B.op_linear_bwd_tiles(T, n_in, n_out) == ((0, 0), (0, 0))
 
 
 # the tuning aid names the tile of every product that can run in it: the three whose rings are filled first need three k-steps

@@ -454,6 +454,40 @@ def test_gemm_every_192_tile_ragged(tile, mode, M, N, K):
     test_gemm_ragged_k(mode, M, N, K)
 
 
+# Both products of a linear layer's backward in one launch: every tile on either side, ragged against it in rows, columns and
+# contraction, from the fewest k-steps its ring of stages takes
+LINEAR_BWD = [(150, 152, 136, (64, 64), (64, 64)), (283, 208, 160, (64, 128), (64, 64)), (319, 184, 136, (128, 64), (64, 64)),
+              (1006, 216, 176, (128, 128), (64, 64)), (2134, 216, 160, (256, 128), (64, 64)), (2152, 408, 184, (128, 256), (64, 64)),
+              (2885, 264, 144, (256, 192), (64, 64)), (2824, 456, 160, (192, 256), (64, 64)), (2814, 2704, 160, (256, 256), (64, 64)),
+              (143, 160, 752, (64, 64), (64, 128)), (160, 216, 1064, (64, 64), (128, 64)), (136, 224, 1816, (64, 64), (128, 128)),
+              (145, 432, 2832, (64, 64), (256, 128)), (129, 200, 3000, (64, 64), (128, 256)), (133, 2528, 2448, (64, 64), (256, 192)),
+              (129, 2208, 2208, (64, 64), (192, 256)), (136, 3224, 2704, (64, 128), (256, 256))]
+
+
+@pytest.mark.parametrize("T,n_in,n_out,nt,tn", LINEAR_BWD)
+def test_linear_backward_in_one_launch_has_the_bits_of_two(T, n_in, n_out, nt, tn, dt=torch.bfloat16):
+    if dt == torch.bfloat16:
+        assert B.op_linear_bwd_tiles(T, n_in, n_out) == (nt, tn)     # (a change of the rule has to bring other sizes here)
+    dy, w, x = (dev(rnd(s, seed, dt), dt) for s, seed in (((T, n_out), 51), ((n_in, n_out), 52), ((T, n_in), 53)))
+    res, dw0 = dev(rnd((T, n_in), 54, dt), dt), dev(rnd((n_in, n_out), 55, dt), dt)
+    want_dx, want_dw = torch.empty_like(x), torch.empty_like(w)
+    for r, acc in ((None, False), (res, True)):
+        dx, dw = torch.full_like(x, float("nan")), dw0.clone() if acc else torch.full_like(w, float("nan"))
+        B.op_gemm(0, T, n_in, n_out, dy, w, None, r, want_dx)
+        B.op_gemm(1, n_in, n_out, T, x, dy, None, dw0 if acc else None, want_dw)
+        B.op_linear_bwd(dy, w, x, r, dx, dw, acc)
+        assert torch.equal(dx, want_dx) and torch.equal(dw, want_dw)
+    dx = res.clone()                                                 # res may be dx
+    B.op_linear_bwd(dy, w, x, dx, dx, dw)
+    assert torch.equal(dx, want_dx)
+
+
+# fp32: 16x16 and 32x32 tiles on either side; tiles of 64 (two launches)
+@pytest.mark.parametrize("T,n_in,n_out", [(4, 4, 4), (37, 52, 20), (300, 260, 36), (33, 516, 300), (700, 260, 260), (1100, 700, 260)])
+def test_linear_backward_f32_has_the_bits_of_two(T, n_in, n_out):
+    test_linear_backward_in_one_launch_has_the_bits_of_two(T, n_in, n_out, None, None, torch.float32)
+
+
 # fp32 on the matrix cores: ragged against the 32- and 64-row parts and the 16-deep chunks, both waves' arrangements
 # (64x64 and 32x32 tiles with a divided contraction; 128x128 tiles, TN and short NT ones), fewer chunks than waves, rows of 4
 GEMM_F32 = [(0, 4, 4, 4), (0, 33, 36, 20), (0, 65, 132, 68), (0, 1000, 516, 332), (0, 700, 1100, 1028), (1, 4, 4, 4),

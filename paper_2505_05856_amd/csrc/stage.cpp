@@ -343,9 +343,13 @@ struct SlotState {
   uint64_t host_off = 0;   // pinned-pool offset when ON_HOST (kept after swap-in)
   int ready_event = -1;    // swap-in completion the compute stream has not waited for yet
   int out_event = -1;      // swap-out completion: the host copy is whole only after it
+  uint64_t piece = 0;      // bytes of one copy of the swap, and completions of the copies out before the last
+  std::vector<int> piece_events;
   bool consumed = false;   // its last backward consumer has run
   bool ever_produced = false;
 };
+// Pieces an express block goes out and comes back in
+constexpr uint64_t kSwapPiece = (uint64_t)16 << 20;
 
 struct Buf { uint64_t off = UINT64_MAX, bytes = 0; };
 
@@ -846,14 +850,24 @@ struct Walk {
     s.host_off = host_top;
     host_top += Arena::round(bytes);
     const int done = new_event();
+    // An express block is needed back as soon as it is out: it goes in pieces, and each comes back behind its own copy-out
+    // instead of behind the whole block's, so that the link carries both directions: the block of the top layer of two, 105 MB, was
+    // back 4.8 ms after the forward's end and is now after 3.5.  (Other blocks are out long before they are needed.)
+    s.piece = live && on_express(l) ? kSwapPiece : bytes;
+    s.piece_events.clear();
+    const uint64_t piece = s.piece;
     if (live || cm) {
       if (produced < 0) { produced = new_event(); record(produced, cs); }
       hipStream_t out = on_express(l) ? d2hx : d2h;
       (out == d2h ? used_d2h : used_d2hx) = true;
       wait(out, produced);
       span_begin(SPAN_D2H, l, slot, out, bytes);
-      if (live) check(hipMemcpyAsync(host_base + s.host_off, base() + s.off, bytes, hipMemcpyDeviceToHost, out));
-      else clk[clock_of(out)] += copy_ns(bytes, cm->d2h_bytes_per_us);
+      if (live) {
+        for (uint64_t at = 0; at < bytes; at += piece) {
+          check(hipMemcpyAsync(host_base + s.host_off + at, base() + s.off + at, std::min(piece, bytes - at), hipMemcpyDeviceToHost, out));
+          if (at + piece < bytes) { const int ev = new_event(); record(ev, out); s.piece_events.push_back(ev); }
+        }
+      } else clk[clock_of(out)] += copy_ns(bytes, cm->d2h_bytes_per_us);
       span_end(out);
       record(done, out);
     }
@@ -878,10 +892,16 @@ struct Walk {
       record(region_free, cs);
       used_h2d = true;
       wait(h2d, region_free);
-      wait(h2d, s.out_event);   // the copy-out of this slot must have landed in the host pool
+      // what comes back must have landed in the host pool
+      if (!live || s.piece_events.empty()) wait(h2d, s.out_event);
       span_begin(SPAN_H2D, l, slot, h2d, bytes);
-      if (live) check(hipMemcpyAsync(base() + s.off, host_base + s.host_off, bytes, hipMemcpyHostToDevice, h2d));
-      else clk[2] += copy_ns(bytes, cm->h2d_bytes_per_us);
+      if (live) {
+        size_t i = 0;
+        for (uint64_t at = 0; at < bytes; at += s.piece, ++i) {
+          if (!s.piece_events.empty()) wait(h2d, i < s.piece_events.size() ? s.piece_events[i] : s.out_event);
+          check(hipMemcpyAsync(base() + s.off + at, host_base + s.host_off + at, std::min(s.piece, bytes - at), hipMemcpyHostToDevice, h2d));
+        }
+      } else clk[2] += copy_ns(bytes, cm->h2d_bytes_per_us);
       span_end(h2d);
       record(done, h2d);
     }
@@ -1713,9 +1733,13 @@ dp_status dp_stage_step(dp_stage *st, const void *x_in, const void *dy, const ui
   else HIP_TRY(hipEventSynchronize(step_end), DP_E_HIP);   // the step issued kStepsInFlight calls ago
   // A plan that swaps starts on an idle device: with the previous step still running, the
   // copies and cross-stream waits queued behind it ran markedly slower (measured: 17 ms
-  // instead of 12 ms a step for 22 small swaps); the step's own launches still run ahead.
-  if (rep.n_swapped_slots > 0)
+  // instead of 12 ms a step for 22 small swaps); the step's own launches still run ahead.  That goes for another handle's
+  // step on the same stream as well: three handles of a two-layer stage of width 1600 in turn 14.2 ms a step, 8.2 with the
+  // wait for the stream (and the copies in pieces, see Walk::copy_out; 9.4 before those).
+  if (rep.n_swapped_slots > 0) {
     for (hipEvent_t e : st->step_end) if (e != nullptr && e != step_end) HIP_TRY(hipEventSynchronize(e), DP_E_HIP);
+    HIP_TRY(hipStreamSynchronize(cs), DP_E_HIP);
+  }
   Walk w(c, plan, true, st);
   w.arena_base = (char *)st->arena; w.host_base = (char *)st->host_pool; w.evs = &st->events;
   w.wts = st->current;

@@ -56,6 +56,47 @@ __device__ __forceinline__ int xcd_contiguous(int pid, int n) {
   return xcd * base + (xcd < rem ? xcd : rem) + idx;
 }
 
+// Which row tile (rank 0: the heaviest under a causal mask) of which (batch, head) a workgroup is.
+// Without an order of its own (own == 0) head after head.  A causal grid of more blocks than CUs goes by weight: the blocks of
+// one head in their order gave every CU of an XCD blocks of one weight, since head lengths of 4, 8 and 16 tiles divide the 32
+// CUs, and the CUs with the heavy ones ended last (batch 4, sequence 1024, 25 heads of 64: 48 tiles on some CUs where the mean
+// is 27).  An XCD now takes `own` whole heads in groups of `group`, the heaviest tiles of all heads of a group first, and ahead
+// of them its part of the `shared` heads that 8 XCDs cannot share out whole.  Groups hold the heads that fill the XCD's CUs, or
+// whose streamed tensors fill its L2 if that is more.  Forward / backward, us, head after head and by weight:
+//   batch 4, sequence 1024, 25 heads of 64: 31.7 / 83.7, 25.3 / 73.7    8, 1024, 16 of 64: 37.0 / 101.9, 28.6 / 81.1
+//   batch 3, sequence 512, 25 heads of 128: 18.9 / 61.8, 15.4 / 44.2    8, 2048, 16 of 128: 162 / 559, 152 / 536
+// With a block a CU at most there is nothing to share out (4, 512, 16 of 64: 9.8 / 23.8 head after head, 10.2 / 25.3 by weight).
+struct RowOrder { int own, shared, group; };
+template <int PER_CU> RowOrder row_order(int causal, int blocks, int tiles, int streamed, int dh) {
+  constexpr int kCus = 256, kL2 = 4 << 20;
+  if (!causal || blocks <= kCus || blocks / tiles < 8) return RowOrder{0, 0, 0};
+  const int heads = blocks / tiles, own = heads / 8;
+  int want = kL2 / 4 / (streamed * dh) > 0 ? kL2 / 4 / (streamed * dh) : 1;   // (two tensors of 2 bytes an element)
+  if (want < kCus / 8 * PER_CU / tiles) want = kCus / 8 * PER_CU / tiles;
+  const int groups = (own + want - 1) / want;
+  return RowOrder{own, heads % 8, (own + groups - 1) / groups};
+}
+template <bool ORDERED> __device__ __forceinline__ void row_tile(const RowOrder &o, int pid, int n, int tiles, int *rank, int *head) {
+  if (!ORDERED) {
+    const int wid = xcd_contiguous(pid, n);
+    *rank = wid % tiles;
+    *head = wid / tiles;
+    return;
+  }
+  const int xcd = pid & 7, mine = (n >> 3) + (xcd < (n & 7) ? 1 : 0), first = mine - o.own * tiles;
+  int idx = pid >> 3;
+  if (idx < first) {   // shared heads: tile by tile to the XCDs in turn
+    const int j = xcd + 8 * idx;
+    *rank = j / o.shared;
+    *head = 8 * o.own + j % o.shared;
+    return;
+  }
+  idx -= first;
+  const int g = idx / (o.group * tiles), r = idx - g * o.group * tiles, heads = min(o.group, o.own - g * o.group);
+  *rank = r / heads;
+  *head = xcd * o.own + g * o.group + r % heads;
+}
+
 // Row index, inside its 32-row block, of element e of a 32x32 MFMA result held by `lane`.
 __device__ __forceinline__ int acc_row(int e, int lane) { return 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); }
 
@@ -248,10 +289,10 @@ struct BothAddr {
 // DROP: the probabilities are masked after the softmax (the row sums and the log-sum-exp are
 // those of the plain softmax); the scale 1/(1-p) goes into the final normalisation.
 // WPE: waves a SIMD (= workgroups a CU) the registers are cut for.
-template <int DH, bool CAUSAL, bool DROP, int WPE>
+template <int DH, bool CAUSAL, bool DROP, int WPE, bool ORDERED>
 __global__ __launch_bounds__(256, WPE) void attn_fwd_mfma_kernel(AttnView av, bf16 *__restrict__ o,
                                                                float *__restrict__ lse, int nh, float scale,
-                                                               DropArgs da) {
+                                                               DropArgs da, RowOrder ro) {
   constexpr int ND = DH / 32, NK = DH / 16;
   // LDS, in bytes: [K even][K odd][V even][V odd], every tile in the dual-use layout; tile t of K
   // (of V) lives in the buffer of t's parity
@@ -260,9 +301,10 @@ __global__ __launch_bounds__(256, WPE) void attn_fwd_mfma_kernel(AttnView av, bf
 
   const int Sq = av.Sq, S = av.Sk;   // S: the key count, which bounds every key-side loop below
   const int nqt = (Sq + BROWS - 1) / BROWS;
-  const int wid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int qt = nqt - 1 - wid % nqt;   // heavy (late) causal tiles first
-  const int h = (wid / nqt) % nh, b = wid / (nqt * nh);
+  int rank, head;
+  row_tile<ORDERED>(ro, blockIdx.x, gridDim.x, nqt, &rank, &head);
+  const int qt = nqt - 1 - rank;   // (late causal tiles are the heavy ones)
+  const int h = head % nh, b = head / nh;
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int H = nh * DH;
@@ -490,18 +532,27 @@ hipError_t set_smem(K kern, size_t smem) {
                              (int)smem);
 }
 
-template <int DH, bool CAUSAL, bool DROP, int WPE>
-hipError_t fwd_go(int blocks, const AttnView &av, void *o, float *lse, int nh, float scale, const DropArgs &da, hipStream_t s) {
+template <int DH, bool CAUSAL, bool DROP, int WPE, bool ORDERED>
+hipError_t fwd_go(int blocks, const AttnView &av, void *o, float *lse, int nh, float scale, const DropArgs &da, const RowOrder &ro,
+                  hipStream_t s) {
   constexpr size_t smem = 2 * 2 * (size_t)BKV * DH * sizeof(bf16);   // two stages of a K and a V tile
-  auto kern = attn_fwd_mfma_kernel<DH, CAUSAL, DROP, WPE>;
+  auto kern = attn_fwd_mfma_kernel<DH, CAUSAL, DROP, WPE, ORDERED>;
   static bool attr_set = false;
   if (!attr_set) {
     const hipError_t e = set_smem(kern, smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, av, (bf16 *)o, lse, nh, scale, da);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, av, (bf16 *)o, lse, nh, scale, da, ro);
   return hipGetLastError();
+}
+template <int DH, bool CAUSAL, bool DROP, int WPE>
+hipError_t fwd_form(int blocks, const AttnView &av, void *o, float *lse, int nh, float scale, const DropArgs &da, hipStream_t s) {
+  const RowOrder ro = row_order<WPE>(CAUSAL, blocks, (av.Sq + BROWS - 1) / BROWS, av.Sk, DH);
+  if constexpr (CAUSAL) {
+    if (ro.own > 0) return fwd_go<DH, CAUSAL, DROP, WPE, true>(blocks, av, o, lse, nh, scale, da, ro, s);
+  }
+  return fwd_go<DH, CAUSAL, DROP, WPE, false>(blocks, av, o, lse, nh, scale, da, ro, s);
 }
 
 template <int DH>
@@ -519,8 +570,8 @@ hipError_t fwd_launch(int B, int nh, int causal, const AttnView &av, void *o, fl
   constexpr int kCus = 256;
   const bool three = DH == 64 && blocks > 2 * kCus;
 #define DP_FWD(CAUSAL, DROP)                                                                           \
-  return three ? fwd_go<DH, CAUSAL, DROP, DH == 64 ? 3 : 2>(blocks, av, o, lse, nh, scale, da, s)       \
-               : fwd_go<DH, CAUSAL, DROP, 2>(blocks, av, o, lse, nh, scale, da, s)
+  return three ? fwd_form<DH, CAUSAL, DROP, DH == 64 ? 3 : 2>(blocks, av, o, lse, nh, scale, da, s)       \
+               : fwd_form<DH, CAUSAL, DROP, 2>(blocks, av, o, lse, nh, scale, da, s)
   if (dropping) { if (causal) DP_FWD(true, true); else DP_FWD(false, true); }
   if (causal) DP_FWD(true, false); else DP_FWD(false, false);
 #undef DP_FWD
@@ -531,12 +582,12 @@ hipError_t fwd_launch(int B, int nh, int causal, const AttnView &av, void *o, fl
 // (head dimension 128: both accumulators and both key-side fragments need more than the 256
 // registers two blocks a CU leave each wave, and spills on this path cost more than the
 // lost occupancy)
-template <int DH, bool CAUSAL, bool DROP>
+template <int DH, bool CAUSAL, bool DROP, bool ORDERED>
 __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(AttnView av,
                                                               const float *__restrict__ lse,
                                                               const bf16 *__restrict__ d_o,
                                                               const float *__restrict__ drow,
-                                                              int nh, float scale, DropArgs da) {
+                                                              int nh, float scale, DropArgs da, RowOrder ro) {
   constexpr int ND = DH / 32, NK = DH / 16;
   // stage s: Q tile, dO tile (both in the dual-use layout), then 64 log-sum-exp and 64 row-dot floats
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
@@ -545,8 +596,9 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
 
   const int Sq = av.Sq, Sk = av.Sk;
   const int nkt = (Sk + BROWS - 1) / BROWS;
-  const int wid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int kt = wid % nkt, h = (wid / nkt) % nh, b = wid / (nkt * nh);
+  int kt, head;   // (early causal tiles are the heavy ones)
+  row_tile<ORDERED>(ro, blockIdx.x, gridDim.x, nkt, &kt, &head);
+  const int h = head % nh, b = head / nh;
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int H = nh * DH;
@@ -785,13 +837,13 @@ __global__ __launch_bounds__(256, DH == 128 ? 1 : 2) void attn_bwd_dkv_kernel(At
 // dQ: the block owns 128 queries (32 per wave) and streams 64-key tiles of K and V.  It also takes
 // D_i = <dO_i, O_i> over the head's columns for its queries (a lane holds half of dO_i as MFMA
 // operand already) and leaves it in drow[b, h, i] for the dK/dV kernel, which is launched after it.
-template <int DH, bool CAUSAL, bool DROP>
+template <int DH, bool CAUSAL, bool DROP, bool ORDERED>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnView av,
                                                              const float *__restrict__ lse,
                                                              const bf16 *__restrict__ o,
                                                              const bf16 *__restrict__ d_o,
                                                              float *__restrict__ drow,
-                                                             int nh, float scale, DropArgs da) {
+                                                             int nh, float scale, DropArgs da, RowOrder ro) {
   constexpr int ND = DH / 32, NK = DH / 16;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_b[];
   // LDS, in bytes: [stage 0: K, V][stage 1: K, V], every tile in the dual-use layout
@@ -799,9 +851,10 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnView av,
 
   const int Sq = av.Sq, S = av.Sk;   // S: the key count
   const int nqt = (Sq + BROWS - 1) / BROWS;
-  const int wid = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int qt = nqt - 1 - wid % nqt;
-  const int h = (wid / nqt) % nh, b = wid / (nqt * nh);
+  int rank, head;
+  row_tile<ORDERED>(ro, blockIdx.x, gridDim.x, nqt, &rank, &head);
+  const int qt = nqt - 1 - rank;
+  const int h = head % nh, b = head / nh;
   const int tid = threadIdx.x, lane = tid & 63, hh = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int H = nh * DH;
@@ -959,42 +1012,59 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(AttnView av,
                          ldq, Sq - iw0, lane);
 }
 
-template <int DH>
-hipError_t bwd_launch(int B, int nh, int causal, const AttnView &av, const void *o, const float *lse,
-                      const void *d_o, float *ws, const DropArgs *drop, hipStream_t s) {
-  constexpr size_t smem_kv = 2 * (2 * (size_t)BKV * DH * sizeof(bf16) + 2 * BKV * sizeof(float));   // Q, dO; lse, row dots
-  constexpr size_t smem_q = 2 * 2 * (size_t)BKV * DH * sizeof(bf16);                                 // K, V
+// One form of each backward kernel (`o` is the dQ kernel's alone)
+template <int DH, bool CAUSAL, bool DROP, bool ORDERED>
+hipError_t dq_go(int blocks, const AttnView &av, const void *o, const float *lse, const void *d_o, float *ws, int nh, float scale,
+                 const DropArgs &da, const RowOrder &ro, hipStream_t s) {
+  constexpr size_t smem = 2 * 2 * (size_t)BKV * DH * sizeof(bf16);   // K, V
+  auto kern = attn_bwd_dq_kernel<DH, CAUSAL, DROP, ORDERED>;
   static bool attr_set = false;
   if (!attr_set) {
-    hipError_t e = set_smem(attn_bwd_dkv_kernel<DH, true, false>, smem_kv);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<DH, false, false>, smem_kv);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<DH, true, true>, smem_kv);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dkv_kernel<DH, false, true>, smem_kv);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<DH, true, false>, smem_q);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<DH, false, false>, smem_q);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<DH, true, true>, smem_q);
-    if (e == hipSuccess) e = set_smem(attn_bwd_dq_kernel<DH, false, true>, smem_q);
+    const hipError_t e = set_smem(kern, smem);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  hipError_t e = hipSuccess;
-  const dim3 grid_q(((av.Sq + BROWS - 1) / BROWS) * nh * B), grid_k(((av.Sk + BROWS - 1) / BROWS) * nh * B), block(256);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, av, lse, (const bf16 *)o, (const bf16 *)d_o, ws, nh, scale, da, ro);
+  return hipGetLastError();
+}
+template <int DH, bool CAUSAL, bool DROP, bool ORDERED>
+hipError_t dkv_go(int blocks, const AttnView &av, const void *, const float *lse, const void *d_o, float *ws, int nh, float scale,
+                  const DropArgs &da, const RowOrder &ro, hipStream_t s) {
+  constexpr size_t smem = 2 * (2 * (size_t)BKV * DH * sizeof(bf16) + 2 * BKV * sizeof(float));   // Q, dO; lse, row dots
+  auto kern = attn_bwd_dkv_kernel<DH, CAUSAL, DROP, ORDERED>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = set_smem(kern, smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, av, lse, (const bf16 *)d_o, ws, nh, scale, da, ro);
+  return hipGetLastError();
+}
+
+template <int DH>
+hipError_t bwd_launch(int B, int nh, int causal, const AttnView &av, const void *o, const float *lse,
+                      const void *d_o, float *ws, const DropArgs *drop, hipStream_t s) {
+  const int tiles_q = (av.Sq + BROWS - 1) / BROWS, tiles_k = (av.Sk + BROWS - 1) / BROWS;
+  const int blocks_q = tiles_q * nh * B, blocks_k = tiles_k * nh * B;
   const float scale = 1.0f / sqrtf((float)DH);
   const bool dropping = drop != nullptr && drop->thr != 0;
   const DropArgs da = dropping ? *drop : DropArgs{0u, 0u, 1.f};
-#define DP_BWD(KERN, GRID, SMEM, ...)                                                                   \
-  hipLaunchKernelGGL(KERN, GRID, block, SMEM, s, av, lse, __VA_ARGS__ (const bf16 *)d_o, ws, nh, scale, da)
-#define DP_BWD4(NAME, GRID, SMEM, ...)                                                                  \
-  if (dropping) { if (causal) DP_BWD((NAME<DH, true, true>), GRID, SMEM, __VA_ARGS__); else DP_BWD((NAME<DH, false, true>), GRID, SMEM, __VA_ARGS__); } \
-  else { if (causal) DP_BWD((NAME<DH, true, false>), GRID, SMEM, __VA_ARGS__); else DP_BWD((NAME<DH, false, false>), GRID, SMEM, __VA_ARGS__); }
+  const RowOrder ro_q = row_order<2>(causal, blocks_q, tiles_q, av.Sk, DH);
+  const RowOrder ro_k = row_order<DH == 128 ? 1 : 2>(causal, blocks_k, tiles_k, av.Sq, DH);
+#define DP_GO(NAME, CAUSAL, ORDERED, BLOCKS, RO)                                                                          \
+  (dropping ? NAME<DH, CAUSAL, true, ORDERED>(BLOCKS, av, o, lse, d_o, ws, nh, scale, da, RO, s)                           \
+            : NAME<DH, CAUSAL, false, ORDERED>(BLOCKS, av, o, lse, d_o, ws, nh, scale, da, RO, s))
+#define DP_BWD(NAME, BLOCKS, RO)                                                                                          \
+  (!causal ? DP_GO(NAME, false, false, BLOCKS, RO) : RO.own > 0 ? DP_GO(NAME, true, true, BLOCKS, RO) : DP_GO(NAME, true, false, BLOCKS, RO))
   // dQ first: it leaves the row dots <dO_i, O_i> in `ws`, which the dK/dV kernel reads
-  if (av.Sq > 0 && av.Sk > 0) { DP_BWD4(attn_bwd_dq_kernel, grid_q, smem_q, (const bf16 *)o,) }
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (av.Sk > 0) { DP_BWD4(attn_bwd_dkv_kernel, grid_k, smem_kv, ) }   // (no queries: dK = dV = 0 is still written)
-#undef DP_BWD4
+  if (av.Sq > 0 && av.Sk > 0) {
+    const hipError_t e = DP_BWD(dq_go, blocks_q, ro_q);
+    if (e != hipSuccess) return e;
+  }
+  return av.Sk > 0 ? DP_BWD(dkv_go, blocks_k, ro_k) : hipSuccess;   // (no queries: dK = dV = 0 is still written)
 #undef DP_BWD
-  return hipGetLastError();
+#undef DP_GO
 }
 
 }  // namespace

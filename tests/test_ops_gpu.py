@@ -610,6 +610,34 @@ def test_attention_fwd_tiles(Bn, S, nh, dh, causal):
 
 
 
+# Causal grids of more blocks than CUs take their row tiles by weight (heads that 8 divides and not, one group of heads and more, a
+# tile a head and many): every row has the bits it has in a call of its own sample.
+@pytest.mark.parametrize("Bn,S,nh,dh", [(9, 257, 30, 64), (5, 700, 13, 64), (8, 1000, 5, 128), (2, 2048, 21, 128), (30, 100, 9, 64), (1, 1500, 32, 64)])
+@pytest.mark.parametrize("drop", [None, (0.2, 5, 7, 1)])
+def test_causal_attention_by_weight_has_the_bits_of_single_samples(Bn, S, nh, dh, drop):
+    dt, H = torch.bfloat16, nh * dh
+    qkv, d_o = dev(rnd((Bn * S, 3 * H), 61, dt), dt), dev(rnd((Bn * S, H), 62, dt), dt)
+
+    def run(q, g, n, heads):
+        o, lse = torch.full_like(g, float("nan")), torch.full((n, heads, S), float("nan"), device=DEV)
+        dqkv, ws = torch.full_like(q, float("nan")), torch.empty(n * S * heads, device=DEV)
+        extra = (B.Dropout(*drop),) if drop else ()
+        (B.op_attention_dropout_fwd if drop else B.op_attention_fwd)(q, n, S, heads, dh, True, o, lse, *extra)
+        (B.op_attention_dropout_bwd if drop else B.op_attention_bwd)(q, o, lse, g, n, S, heads, dh, True, dqkv, ws, *extra)
+        return o, lse, dqkv
+
+    o, lse, dqkv = run(qkv, d_o, Bn, nh)
+    assert all(torch.isfinite(t).all() for t in (o, lse, dqkv))
+    # (dropout masks count heads over the whole batch: the first sample's alone are the same in a call of its own)
+    for b in range(1 if drop else Bn):
+        rows = slice(b * S, (b + 1) * S)
+        heads = nh if nh * ((S + 127) // 128) <= 256 else 256 // ((S + 127) // 128)
+        q = torch.cat([t[rows, :heads * dh] for t in qkv.split(H, 1)], 1).contiguous()
+        o1, lse1, dq1 = run(q, d_o[rows, :heads * dh].contiguous(), 1, heads)
+        assert torch.equal(o1, o[rows, :heads * dh]) and torch.equal(lse1[0], lse[b, :heads])
+        assert torch.equal(dq1, torch.cat([t[rows, :heads * dh] for t in dqkv.split(H, 1)], 1))
+
+
 @pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("dh", [64, 128])
 def test_attention_with_a_maximum_that_creeps_and_then_jumps(dt, dh):

@@ -3,9 +3,9 @@
 (every kernel of the hot path) on one synthetic micro-batch resident in HBM.
 
 Prints ONE JSON line.  `value` = samples/s of the whole job on one MI355X.
-`roofline` is for the kernel class that dominates the step (the NT-form GEMM
-that runs the forward and input-gradient contractions), timed with HIP events
-on the stream the kernels run on.  `cpu_baseline` times the CPU oracle on a
+`roofline` is for the kernel that dominates the step (the two products of a
+linear layer's backward in one launch), timed with HIP events on the stream
+the kernels run on.  `cpu_baseline` times the CPU oracle on a
 bounded sample of the same workload on this machine's host cores.
 """
 from __future__ import annotations
@@ -25,16 +25,16 @@ PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 MFMA (v_mfma_f32_16x16x4): 256 CU x 
 # Bytes per launch of the dominant kernel that cross the L2 towards memory (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000,
 # the factors a 256 MiB device copy gives), from the rocprofv3 --pmc runs summarised in
 # profiles/c2_step_hbm_traffic_pmc.md and profiles/c5_step_hbm_traffic_pmc.md.
-MEASURED_TRAFFIC_BYTES = {("C2", "keep-all"): 80.4e6, ("C5", "seed7-mixed"): 2097.9e6}
-# Average duration of an NT-form GEMM launch in the rocprofv3 kernel traces (profiles/*_step_kernel_trace.md).
-ROCPROF_NT_LAUNCH_US = {
-    ("C2", "keep-all"): {"us": 28.89, "hip_events_same_run_us": 33.22},
-    ("C5", "keep-all"): {"us": 881.36, "hip_events_same_run_us": 880.60},
+MEASURED_TRAFFIC_BYTES = {("C2", "keep-all"): 171.4e6, ("C5", "seed7-mixed"): 4810.4e6}
+# Average duration of a gemm_pair_kernel launch in the rocprofv3 kernel traces (profiles/*_step_kernel_trace.md).
+ROCPROF_PAIR_LAUNCH_US = {
+    ("C2", "keep-all"): {"us": 50.50, "hip_events_same_run_us": 54.41},
+    ("C5", "keep-all"): {"us": 1725.77, "hip_events_same_run_us": 1727.62},
     ("C5", "seed7-mixed"): {
-        "us": 1743.04, "hip_events_same_run_us": 1744.94,
+        "us": 2420.27, "hip_events_same_run_us": 2422.85,
         "note": "under the profiler this plan's device-to-host copies run as shader blit kernels beside the GEMMs and "
                 "slow them; the trace and the HIP events of that profiled run agree with each other, and the keep-all "
-                "trace (no copies: 881.36 us by rocprofv3, 880.60 us by HIP events in that run) shows the same kernels undisturbed"},
+                "trace (no copies: 1725.77 us by rocprofv3, 1727.62 us by HIP events in that run) shows the same kernels undisturbed"},
 }
 
 
@@ -199,7 +199,7 @@ def time_steps(run, plan, budget, warmup, steps):
 
 def op_times_and_roofline(run, cfg, name, plan_name, plan, budget, k):
     """The same steps again with every launch bracketed by HIP events on the launch stream: per-class times and
-    the roofline of the dominant class, the NT-form GEMM (forward and input-gradient contractions)."""
+    the roofline of the dominant kernel, the two products of a linear layer's backward in one launch."""
     from paper_2505_05856_amd import binding as B
     B.stage_set_profiling(run.stage, True)
     for _ in range(k):
@@ -208,20 +208,20 @@ def op_times_and_roofline(run, cfg, name, plan_name, plan, budget, k):
     flops = B.stage_op_flops(run.stage)
     B.stage_set_profiling(run.stage, False)
     op_ms = {n: round(v[0] / k, 4) for n, v in times.items()}
-    nt_ms = (times["gemm_fwd"][0] + times["gemm_dgrad"][0]) / k
-    nt_launches = (times["gemm_fwd"][1] + times["gemm_dgrad"][1]) / k
-    # algorithmic work (2*M*N*K) of exactly the launches that were timed: the step's own forward and
-    # input-gradient GEMMs plus the forward ones a plan replays
-    nt_flops = (flops["gemm_fwd"] + flops["gemm_dgrad"]) / k
+    # (a launch counts for both classes, half its time each)
+    pair_ms = (times["gemm_dgrad"][0] + times["gemm_wgrad"][0]) / k
+    pair_launches = times["gemm_dgrad"][1] / k
+    # algorithmic work (2*M*N*K a product) of exactly the launches that were timed
+    pair_flops = (flops["gemm_dgrad"] + flops["gemm_wgrad"]) / k
     peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_FP32_TFLOPS
-    achieved = nt_flops / (nt_ms * 1e-3) / 1e12
-    roof = {"kernel": "gemm_nt (forward + input-gradient GEMMs)", "bound": "mfma" if cfg.dtype == "bf16" else "latency",
+    achieved = pair_flops / (pair_ms * 1e-3) / 1e12
+    roof = {"kernel": "gemm_pair (input- and weight-gradient product of a linear layer)", "bound": "mfma" if cfg.dtype == "bf16" else "latency",
             "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
-            "avg_launch_us": round(nt_ms * 1e3 / max(nt_launches, 1), 2),
+            "avg_launch_us": round(pair_ms * 1e3 / max(pair_launches, 1), 2),
             "avg_launch_us_source": "HIP event pairs recorded around every launch on the launch stream (event overhead "
                                     "included; the rocprofv3 kernel trace of the same command gives avg_launch_us_rocprof)",
-            "avg_launch_us_rocprof": ROCPROF_NT_LAUNCH_US.get((name, plan_name)),
-            "launches_per_step": nt_launches,
+            "avg_launch_us_rocprof": ROCPROF_PAIR_LAUNCH_US.get((name, plan_name)),
+            "launches_per_step": pair_launches,
             "traffic": MEASURED_TRAFFIC_BYTES.get((name, plan_name))}
     return op_ms, roof
 

@@ -226,6 +226,23 @@ def test_forty_seeded_plans_give_the_same_bits_inside_their_validated_memory(sty
     run.close()
 
 
+def test_swapped_blocks_that_go_in_pieces_come_back_whole():
+    """FC1_OUT and GELU_OUT of 34.1 MB: two pieces of 16 MiB and a short one, where the layer's block is needed back at once."""
+    cfg = syn.StageConfig(2, 128, 2, 8200, 520, 4, "pre", True, "erf", "bf16")
+    w, x, dy = make(cfg)
+    run = StageRunner(cfg, w, x, dy)
+    run.step(syn.plan_keep_all(cfg))
+    keep = run.raw_results()
+    plan = syn.plan_all_swap(cfg)
+    tight = B.plan_validate(run.bcfg, plan)[1]["peak_bytes"]
+    for budget in (tight, 8 << 30):
+        for _ in range(2):
+            run.poison_outputs()
+            run.step(plan, budget_bytes=budget)
+            assert all(torch.equal(a, b) for a, b in zip(keep, run.raw_results())), budget
+    run.close()
+
+
 @pytest.mark.parametrize("style", ["pre", "post"])
 def test_relu_in_bf16_gradients_under_the_stage_own_decisions(style):
     """ReLU's derivative reads the sign of a stored tensor, and in bf16 the two sides store values one rounding

@@ -324,7 +324,8 @@ dp_status dp_stage_init(const dp_stage_config *cfg, const dp_layer_weights *laye
  * which are joined back into hip_stream before return; the call does not wait
  * for this step unless `stats` is non-NULL, but it first waits (on the host) for
  * the step issued two calls earlier on the same handle, so that at most two
- * steps are in flight; a plan that swaps waits for the previous step as well.  DP_E_HIP after a partial enqueue
+ * steps are in flight; a plan that swaps waits for the previous step as well, and for steps of
+ * other handles on hip_stream that swap.  DP_E_HIP after a partial enqueue
  * leaves the outputs undefined.  One step at a time per handle.
  * The results are bit-identical for every plan. */
 dp_status dp_stage_step(dp_stage *st, const void *x_in, const void *dy, const uint8_t *plan,

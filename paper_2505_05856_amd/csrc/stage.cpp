@@ -19,6 +19,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <vector>
 
 namespace dpi {
@@ -288,6 +289,54 @@ struct Flight {
   SwapPolicy v_hold;
 };
 
+// The end of a handle's last swapping step, for the steps of other handles on the same stream.  The list names those of the live
+// handles and owns none of them.
+struct SwapEnd {
+  int device = 0;
+  hipStream_t stream = nullptr;
+  hipEvent_t event = nullptr;
+  ~SwapEnd() { if (event) (void)hipEventDestroy(event); }
+};
+static std::mutex swap_ends_lock;
+static std::vector<std::weak_ptr<SwapEnd>> swap_ends;
+
+// Waits for the last swapping step of every other handle on this stream.
+static hipError_t wait_for_swaps(int device, hipStream_t stream, const SwapEnd *own) {
+  std::vector<std::shared_ptr<SwapEnd>> wait_for;
+  {
+    std::lock_guard<std::mutex> hold(swap_ends_lock);
+    for (size_t i = 0; i < swap_ends.size();) {
+      std::shared_ptr<SwapEnd> e = swap_ends[i].lock();
+      if (e == nullptr) { swap_ends[i] = swap_ends.back(); swap_ends.pop_back(); continue; }
+      if (e.get() != own && e->device == device && e->stream == stream) wait_for.push_back(std::move(e));
+      ++i;
+    }
+  }
+  for (const auto &e : wait_for) {
+    const hipError_t r = hipEventSynchronize(e->event);
+    if (r != hipSuccess) return r;
+  }
+  return hipSuccess;
+}
+// Marks the end of a swapping step just issued to `stream`.
+static hipError_t record_swap_end(std::shared_ptr<SwapEnd> *own, int device, hipStream_t stream) {
+  if (*own == nullptr) {
+    auto e = std::make_shared<SwapEnd>();
+    const hipError_t r = hipEventCreateWithFlags(&e->event, hipEventDisableTiming);
+    if (r != hipSuccess) return r;
+    e->device = device; e->stream = stream;
+    const hipError_t q = hipEventRecord(e->event, stream);
+    if (q != hipSuccess) return q;
+    std::lock_guard<std::mutex> hold(swap_ends_lock);
+    swap_ends.push_back(e);
+    *own = std::move(e);
+    return hipSuccess;
+  }
+  std::lock_guard<std::mutex> hold(swap_ends_lock);
+  (*own)->device = device; (*own)->stream = stream;
+  return hipEventRecord((*own)->event, stream);
+}
+
 // bracket of a launch that is both products of a linear layer's backward
 constexpr int kProfLinearBwd = DP_OPC_COUNT;
 
@@ -332,6 +381,7 @@ struct dp_stage {
   static constexpr int kStepsInFlight = 2;
   hipEvent_t step_end[kStepsInFlight] = {nullptr, nullptr};
   uint64_t steps_issued = 0;
+  std::shared_ptr<SwapEnd> swap_end;   // once a step has swapped
 };
 
 namespace {
@@ -1735,10 +1785,12 @@ dp_status dp_stage_step(dp_stage *st, const void *x_in, const void *dy, const ui
   // copies and cross-stream waits queued behind it ran markedly slower (measured: 17 ms
   // instead of 12 ms a step for 22 small swaps); the step's own launches still run ahead.  That goes for another handle's
   // step on the same stream as well: three handles of a two-layer stage of width 1600 in turn 14.2 ms a step, 8.2 with the
-  // wait for the stream (and the copies in pieces, see Walk::copy_out; 9.4 before those).
+  // wait for its swapping steps (and the copies in pieces, see Walk::copy_out; 9.4 before those).
+  int device = 0;
   if (rep.n_swapped_slots > 0) {
+    HIP_TRY(hipGetDevice(&device), DP_E_HIP);
     for (hipEvent_t e : st->step_end) if (e != nullptr && e != step_end) HIP_TRY(hipEventSynchronize(e), DP_E_HIP);
-    HIP_TRY(hipStreamSynchronize(cs), DP_E_HIP);
+    HIP_TRY(wait_for_swaps(device, cs, st->swap_end.get()), DP_E_HIP);
   }
   Walk w(c, plan, true, st);
   w.arena_base = (char *)st->arena; w.host_base = (char *)st->host_pool; w.evs = &st->events;
@@ -1773,6 +1825,7 @@ dp_status dp_stage_step(dp_stage *st, const void *x_in, const void *dy, const ui
   if (!serial) w.join_copies();
   if (w.herr != hipSuccess) return fail(DP_E_HIP, "stage_step: %s", hipGetErrorString(w.herr));
   HIP_TRY(hipEventRecord(step_end, cs), DP_E_HIP);
+  if (rep.n_swapped_slots > 0) HIP_TRY(record_swap_end(&st->swap_end, device, cs), DP_E_HIP);
   HIP_TRY(hipEventRecord(st->current->last_use, cs), DP_E_HIP);
   ++st->steps_issued;
   if (w.arena.high_water != rep.arena_peak_bytes)

@@ -240,6 +240,16 @@ def test_swapped_blocks_that_go_in_pieces_come_back_whole():
             run.poison_outputs()
             run.step(plan, budget_bytes=budget)
             assert all(torch.equal(a, b) for a, b in zip(keep, run.raw_results())), budget
+    # two handles in turn on one stream, then one alone again
+    other = StageRunner(cfg, w, x, dy)
+    for _ in range(2):
+        for r in (run, other):
+            r.poison_outputs()
+            r.step(plan)
+    assert all(torch.equal(a, b) for r in (run, other) for a, b in zip(keep, r.raw_results()))
+    other.close()
+    run.step(plan)
+    assert all(torch.equal(a, b) for a, b in zip(keep, run.raw_results()))
     run.close()
 
 

@@ -269,7 +269,7 @@ typedef struct {
   int32_t n_free_swaps, n_paid_swaps, n_recomputed;
   /* DP_MEMOPT_VALIDATE only: */
   uint64_t validated_peak_bytes;  /* dp_plan_validate's peak_bytes of the plan */
-  int64_t exact_step_ns;          /* the model's clocks on the executor's own arena and hold policy */
+  int64_t exact_step_ns;          /* the model's clocks on the executor's own arena, hold policy and copies */
   int32_t refine_rounds;
 } dp_memopt_report;
 

@@ -900,10 +900,10 @@ struct Walk {
     s.host_off = host_top;
     host_top += Arena::round(bytes);
     const int done = new_event();
-    // An express block is needed back as soon as it is out: it goes in pieces, and each comes back behind its own copy-out
+    // An express block is needed back soon after it is out: it goes in pieces, and each comes back behind its own copy-out
     // instead of behind the whole block's, so that the link carries both directions: the block of the top layer of two, 105 MB, was
-    // back 4.8 ms after the forward's end and is now after 3.5.  (Other blocks are out long before they are needed.)
-    s.piece = live && on_express(l) ? kSwapPiece : bytes;
+    // back 4.8 ms after the forward's end and is now after 3.5.  (The other blocks are those of the bottom layers, needed back last.)
+    s.piece = on_express(l) ? kSwapPiece : bytes;
     s.piece_events.clear();
     const uint64_t piece = s.piece;
     if (live || cm) {
@@ -912,12 +912,12 @@ struct Walk {
       (out == d2h ? used_d2h : used_d2hx) = true;
       wait(out, produced);
       span_begin(SPAN_D2H, l, slot, out, bytes);
-      if (live) {
-        for (uint64_t at = 0; at < bytes; at += piece) {
-          check(hipMemcpyAsync(host_base + s.host_off + at, base() + s.off + at, std::min(piece, bytes - at), hipMemcpyDeviceToHost, out));
-          if (at + piece < bytes) { const int ev = new_event(); record(ev, out); s.piece_events.push_back(ev); }
-        }
-      } else clk[clock_of(out)] += copy_ns(bytes, cm->d2h_bytes_per_us);
+      for (uint64_t at = 0; at < bytes; at += piece) {
+        const uint64_t n = std::min(piece, bytes - at);
+        if (live) check(hipMemcpyAsync(host_base + s.host_off + at, base() + s.off + at, n, hipMemcpyDeviceToHost, out));
+        else clk[clock_of(out)] += copy_ns(at + n, cm->d2h_bytes_per_us) - copy_ns(at, cm->d2h_bytes_per_us);
+        if (at + n < bytes) { const int ev = new_event(); record(ev, out); s.piece_events.push_back(ev); }
+      }
       span_end(out);
       record(done, out);
     }
@@ -943,15 +943,15 @@ struct Walk {
       used_h2d = true;
       wait(h2d, region_free);
       // what comes back must have landed in the host pool
-      if (!live || s.piece_events.empty()) wait(h2d, s.out_event);
+      if (s.piece_events.empty()) wait(h2d, s.out_event);
       span_begin(SPAN_H2D, l, slot, h2d, bytes);
-      if (live) {
-        size_t i = 0;
-        for (uint64_t at = 0; at < bytes; at += s.piece, ++i) {
-          if (!s.piece_events.empty()) wait(h2d, i < s.piece_events.size() ? s.piece_events[i] : s.out_event);
-          check(hipMemcpyAsync(base() + s.off + at, host_base + s.host_off + at, std::min(s.piece, bytes - at), hipMemcpyHostToDevice, h2d));
-        }
-      } else clk[2] += copy_ns(bytes, cm->h2d_bytes_per_us);
+      size_t i = 0;
+      for (uint64_t at = 0; at < bytes; at += s.piece, ++i) {
+        const uint64_t n = std::min(s.piece, bytes - at);
+        if (!s.piece_events.empty()) wait(h2d, i < s.piece_events.size() ? s.piece_events[i] : s.out_event);
+        if (live) check(hipMemcpyAsync(base() + s.off + at, host_base + s.host_off + at, n, hipMemcpyHostToDevice, h2d));
+        else clk[2] += copy_ns(at + n, cm->h2d_bytes_per_us) - copy_ns(at, cm->h2d_bytes_per_us);
+      }
       span_end(h2d);
       record(done, h2d);
     }

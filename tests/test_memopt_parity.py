@@ -104,6 +104,23 @@ def test_validated_generation_fits_the_true_peak():
     assert B.STATUS[code] == "DP_E_BUDGET" and rep["feasible"] == 0
 
 
+def test_the_exact_step_time_plays_an_express_block_in_pieces():
+    """One layer whose GELU_OUT (64 MiB) the backward asks back as soon as the forward is over: the planner's model waits for the whole
+    copy-out before the copy-in, the executor copies pieces of 16 MiB and brings each back behind its own copy-out, so all but the last
+    are back when the block is out, and the exact step is shorter by their copy-ins (to a ns of rounding a copy)."""
+    cfg = syn.StageConfig(1, 1024, 16, 4096, 1024, 8, "pre", True, "erf", "bf16")
+    bc = to_binding_config(cfg)
+    f = [563348, 77983, 433005, 43142, 89096, 29509, 18331713, 308567]
+    b = [24032, 8732967, 603725, 441183, 27376, 2742732, 8101108, 154526]
+    bytes_per_us = 10000
+    cm = B.make_cost_model(f, b, bytes_per_us, bytes_per_us)
+    _, keep = B.plan_validate(bc, syn.plan_keep_all(cfg))
+    _, plan, rep = B.plan_generate(bc, cm, keep["peak_bytes"] * 94 // 100, flags=B.MEMOPT_VALIDATE)
+    assert plan[syn.SLOT["GELU_OUT"]] == syn.SWAP
+    saved = B.plan_cost(bc, cm, plan)["step_ns"] - rep["exact_step_ns"]
+    assert abs(saved - 3 * (16 << 20) * 1000 / bytes_per_us) < 8
+
+
 def test_argument_errors():
     cfg = SMALL[0]
     _, bc = both_sides(cfg)

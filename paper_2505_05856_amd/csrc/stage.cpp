@@ -944,15 +944,15 @@ struct Walk {
       wait(h2d, region_free);
       // what comes back must have landed in the host pool
       if (s.piece_events.empty()) wait(h2d, s.out_event);
-      span_begin(SPAN_H2D, l, slot, h2d, bytes);
       size_t i = 0;
       for (uint64_t at = 0; at < bytes; at += s.piece, ++i) {
         const uint64_t n = std::min(s.piece, bytes - at);
         if (!s.piece_events.empty()) wait(h2d, i < s.piece_events.size() ? s.piece_events[i] : s.out_event);
+        span_begin(SPAN_H2D, l, slot, h2d, n);   // (the copy alone, not what it waits for)
         if (live) check(hipMemcpyAsync(base() + s.off + at, host_base + s.host_off + at, n, hipMemcpyHostToDevice, h2d));
         else clk[2] += copy_ns(at + n, cm->h2d_bytes_per_us) - copy_ns(at, cm->h2d_bytes_per_us);
+        span_end(h2d);
       }
-      span_end(h2d);
       record(done, h2d);
     }
     h2d_bytes += bytes;

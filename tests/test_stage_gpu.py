@@ -1,6 +1,8 @@
 """Parity of dp_stage_step against the CPU oracle and bit-exactness across
 plans, through the C ABI.  Metric: max|gpu-ref| / max|ref| per output tensor;
 bounds 1e-4 (fp32 debug mode) and 2e-2 (bf16)."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -251,6 +253,33 @@ def test_swapped_blocks_that_go_in_pieces_come_back_whole():
     run.step(plan)
     assert all(torch.equal(a, b) for a, b in zip(keep, run.raw_results()))
     run.close()
+
+
+def test_copies_in_pieces_are_timed_without_what_they_wait_for(capfd, monkeypatch):
+    """Two layers' FC1_OUT (105 MB each) out and back.  The top layer's pieces come back one by one as they are out; the time of the
+    copies in is the sum of the copies: a span each, none longer than the slowest link this library has met (20 GB/s, both ways busy)
+    explains, so the wait for the other direction is not in it."""
+    cfg = syn.StageConfig(2, 256, 4, 12800, 1024, 4, "pre", True, "erf", "bf16")
+    w, x, dy = make(cfg)
+    run = StageRunner(cfg, w, x, dy)
+    plan = syn.plan_keep_all(cfg).copy()
+    slots = len(plan) // cfg.n_layers
+    for l in range(cfg.n_layers):
+        plan[l * slots + syn.SLOT["FC1_OUT"]] = syn.SWAP
+    for _ in range(2):
+        run.step(plan, budget_bytes=8 << 30)
+    monkeypatch.setenv("DPSTAGE_TIMELINE", "1")
+    torch.cuda.synchronize()
+    capfd.readouterr()
+    stats = run.step(plan, budget_bytes=8 << 30, want_stats=True)
+    spans = re.findall(r"timeline: h2d +layer +(\d+) slot/node +\d+ .*\(([\d.]+) ms, (\d+) bytes\)", capfd.readouterr().err)
+    run.close()
+    assert sum(int(b) for _, _, b in spans) == stats["h2d_bytes"] == 2 * 104857600
+    top = [int(b) for l, _, b in spans if l == "1"]
+    assert len(top) == 7 and max(top) == 16 << 20
+    for _, ms, b in spans:
+        assert float(ms) < 0.1 + int(b) / 20e6, spans
+    assert abs(sum(float(ms) for _, ms, _ in spans) - stats["h2d_busy_ms"]) < 0.01
 
 
 @pytest.mark.parametrize("style", ["pre", "post"])

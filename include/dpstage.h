@@ -556,7 +556,8 @@ dp_status dp_op_gemm(int32_t dtype, int32_t mode, int32_t M, int32_t N, int32_t 
 dp_status dp_op_gemm_tile(int32_t mode, int32_t M, int32_t N, int32_t K, int32_t *tile_m, int32_t *tile_n);
 /* Both products of a linear layer's backward, y = x W + b with x [T,in], W [in,out] (as stored) and dy [T,out], as the
  * stage's backward runs them: dx [T,in] = dy*W^T (+res), dw [in,out] = (accumulate ? dw : 0) + x^T*dy.  One launch
- * where both are products of the matrix-core kernels, two of dp_op_gemm otherwise; the same bits either way.  res may be
+ * where both are products of the matrix-core kernels and it is estimated to be the shorter, two of dp_op_gemm otherwise; the
+ * same bits either way.  res may be
  * dx; no other overlap of an output with anything. */
 dp_status dp_op_linear_bwd(int32_t dtype, int32_t T, int32_t in, int32_t out, const void *dy, const void *w,
                            const void *x, const void *res /*nullable*/, void *dx, void *dw, int32_t accumulate,

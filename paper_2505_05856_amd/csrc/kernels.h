@@ -127,9 +127,10 @@ bool gemm_dma_supported(const GemmArgs &a);
 hipError_t launch_gemm_dma(const GemmArgs &a, hipStream_t s);
 void gemm_dma_tile(const GemmArgs &a, int *bm, int *bn);   // the tile launch_gemm_dma takes for it
 // The two products of a linear layer's backward (nt: dX = dY W^T, tn: dW = X^T dY) in one launch; same bits as one by one.
-bool gemm_pair_supported(const GemmArgs &nt, const GemmArgs &tn);
-hipError_t launch_gemm_pair(const GemmArgs &nt, const GemmArgs &tn, hipStream_t s);
-void gemm_pair_tiles(const GemmArgs &nt, const GemmArgs &tn, int tiles[4]);   // nt's rows and columns, tn's
+struct PairPlan { int nt_tile, nt_tiles, tn_tile, tn_tiles; bool tn_first; };   // tiles, how many, which product's go first
+bool gemm_pair_plan(const GemmArgs &nt, const GemmArgs &tn, PairPlan *plan);    // false: two launches (kernels without a pair, or sooner)
+hipError_t launch_gemm_pair(const GemmArgs &nt, const GemmArgs &tn, const PairPlan &plan, hipStream_t s);
+void gemm_pair_tiles(const PairPlan &plan, int tiles[4]);   // nt's rows and columns, tn's
 bool gemm_f32_pair_supported(const GemmArgs &nt, const GemmArgs &tn);
 hipError_t launch_gemm_f32_pair(const GemmArgs &nt, const GemmArgs &tn, hipStream_t s);
 

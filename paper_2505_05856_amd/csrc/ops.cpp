@@ -105,8 +105,9 @@ dp_status dp_op_linear_bwd(int32_t dtype, int32_t T, int32_t in, int32_t out, co
     const dp::GemmArgs nt{dp::kGemmNT, T, in, out, dy, w, nullptr, res, dx};
     const dp::GemmArgs tn{dp::kGemmTN, in, out, T, x, dy, nullptr, accumulate ? dw : nullptr, dw};
     if (env_mfma_enabled()) {
-      if (dtype == DP_BF16 && dp::gemm_pair_supported(nt, tn))
-        return op_done(dp::launch_gemm_pair(nt, tn, (hipStream_t)hip_stream), "linear_bwd");
+      dp::PairPlan plan;
+      if (dtype == DP_BF16 && dp::gemm_pair_plan(nt, tn, &plan))
+        return op_done(dp::launch_gemm_pair(nt, tn, plan, (hipStream_t)hip_stream), "linear_bwd");
       if (dtype == DP_F32 && dp::gemm_f32_pair_supported(nt, tn))
         return op_done(dp::launch_gemm_f32_pair(nt, tn, (hipStream_t)hip_stream), "linear_bwd");
     }
@@ -119,7 +120,8 @@ dp_status dp_op_linear_bwd_tiles(int32_t T, int32_t in, int32_t out, int32_t til
   if (T < 0 || in < 0 || out < 0 || !tiles) return fail(DP_E_INVAL, "linear_bwd_tiles: bad argument");
   for (int i = 0; i < 4; ++i) tiles[i] = 0;
   const dp::GemmArgs nt{dp::kGemmNT, T, in, out}, tn{dp::kGemmTN, in, out, T};
-  if (dp::gemm_pair_supported(nt, tn)) dp::gemm_pair_tiles(nt, tn, tiles);
+  dp::PairPlan plan;
+  if (dp::gemm_pair_plan(nt, tn, &plan)) dp::gemm_pair_tiles(plan, tiles);
   return DP_OK;
 }
 

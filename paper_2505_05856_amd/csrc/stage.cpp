@@ -674,27 +674,22 @@ struct Walk {
     prof_end();
   }
   // The two products of a linear layer's backward, dX = dY W^T (+ res) and dW = X^T dY: one launch where both run on the
-  // kernels of gemm_pair.hip.  The spans a plan's blocks are held for count two launch sites either way.
+  // kernels of gemm_pair.hip and that is sooner.  The spans a plan's blocks are held for count two launch sites either way, so
+  // the dry walk need not know.
   void linear_bwd(long T, long in, long out, const void *dyp, const void *w, const void *res, void *dx, const void *x, void *dw_out) {
-    auto args = [&](bool ptrs, int mode) {
-      const void *any = (const void *)16;
-      if (mode == dp::kGemmNT)
-        return dp::GemmArgs{mode, (int)T, (int)in, (int)out, ptrs ? dyp : any, ptrs ? w : any, nullptr, ptrs ? res : nullptr, ptrs ? dx : nullptr};
-      return dp::GemmArgs{mode, (int)in, (int)out, (int)T, ptrs ? x : any, ptrs ? dyp : any, nullptr,
-                          ptrs && accumulate ? dw_out : nullptr, ptrs ? dw_out : nullptr};   // dW += X^T dY
-    };
-    const bool on = live ? st->use_mfma : mfma_enabled;
-    const dp::GemmArgs nt = args(live, dp::kGemmNT), tn = args(live, dp::kGemmTN);
-    if (!on || !(c.dtype == DP_BF16 ? dp::gemm_pair_supported(nt, tn) : dp::gemm_f32_pair_supported(nt, tn))) {
+    const dp::GemmArgs nt{dp::kGemmNT, (int)T, (int)in, (int)out, dyp, w, nullptr, res, dx};
+    const dp::GemmArgs tn{dp::kGemmTN, (int)in, (int)out, (int)T, x, dyp, nullptr, accumulate ? dw_out : nullptr, dw_out};   // dW += X^T dY
+    dp::PairPlan plan;
+    if (!live || !st->use_mfma || !(c.dtype == DP_BF16 ? dp::gemm_pair_plan(nt, tn, &plan) : dp::gemm_f32_pair_supported(nt, tn))) {
       gemm(DP_OPC_GEMM_DGRAD, dp::kGemmNT, T, in, out, dyp, w, nullptr, res, dx);
       gemm(DP_OPC_GEMM_WGRAD, dp::kGemmTN, in, out, T, x, dyp, nullptr, nullptr, dw_out);
       return;
     }
-    if (live && st->profiling)
+    if (st->profiling)
       for (int cls : {DP_OPC_GEMM_DGRAD, DP_OPC_GEMM_WGRAD}) st->prof_flops[cls] += 2.0 * (double)T * (double)in * (double)out;
     if (!no_arena) arena.tick();
     prof_begin(kProfLinearBwd);
-    if (live) check(c.dtype == DP_BF16 ? dp::launch_gemm_pair(nt, tn, cs) : dp::launch_gemm_f32_pair(nt, tn, cs));
+    check(c.dtype == DP_BF16 ? dp::launch_gemm_pair(nt, tn, plan, cs) : dp::launch_gemm_f32_pair(nt, tn, cs));
     prof_end();
   }
   // The second passes of the backward's column reductions (bias and LayerNorm parameter

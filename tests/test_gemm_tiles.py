@@ -39,6 +39,20 @@ def test_the_gpu_tests_reach_every_tile_of_a_linear_backward_ragged():
         assert B.op_linear_bwd_tiles(T, n_in, n_out) == ((0, 0), (0, 0))
 
 
+# Workgroups are dealt in turn to 32 groups of 8 CUs; a tile choice that takes the 256 CUs for one group was longer than two launches
+# here (us, two launches / that choice / these tiles): 135 / 158 / 126, 33 / 34 / 24, 192 / 209 / 177, 376 / 396 / 374
+@pytest.mark.parametrize("T,n_in,n_out,nt,tn", [(2874, 2688, 5376, (256, 128), (256, 256)), (323, 1408, 4224, (64, 64), (256, 256)),
+                                                (2471, 2432, 9728, (256, 128), (256, 256)), (10112, 2688, 5376, (256, 256), (256, 256))])
+def test_tiles_of_a_linear_backward_fit_the_groups_of_cus(T, n_in, n_out, nt, tn):
+    assert B.op_linear_bwd_tiles(T, n_in, n_out) == (nt, tn)
+
+
+# two launches / the best pair, us: 291 / 305, 177 / 181
+@pytest.mark.parametrize("T,n_in,n_out", [(6296, 2496, 7488), (6016, 1472, 5888)])
+def test_two_launches_where_they_end_sooner(T, n_in, n_out):
+    assert B.op_linear_bwd_tiles(T, n_in, n_out) == ((0, 0), (0, 0))
+
+
 # the tuning aid names the tile of every product that can run in it: the three whose rings are filled first need three k-steps
 @pytest.mark.parametrize("asked,tiles", [("128x128", [(128, 128)] * 3), ("192x192", [(192, 192)] * 3),
                                          ("256x192", [None, None, (256, 192)]), ("256x256", [None, None, (256, 256)])])

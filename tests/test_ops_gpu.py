@@ -456,12 +456,12 @@ def test_gemm_every_192_tile_ragged(tile, mode, M, N, K):
 
 # Both products of a linear layer's backward in one launch: every tile on either side, ragged against it in rows, columns and
 # contraction, from the fewest k-steps its ring of stages takes
-LINEAR_BWD = [(150, 152, 136, (64, 64), (64, 64)), (283, 208, 160, (64, 128), (64, 64)), (319, 184, 136, (128, 64), (64, 64)),
-              (1006, 216, 176, (128, 128), (64, 64)), (2134, 216, 160, (256, 128), (64, 64)), (2152, 408, 184, (128, 256), (64, 64)),
-              (2885, 264, 144, (256, 192), (64, 64)), (2824, 456, 160, (192, 256), (64, 64)), (2814, 2704, 160, (256, 256), (64, 64)),
-              (143, 160, 752, (64, 64), (64, 128)), (160, 216, 1064, (64, 64), (128, 64)), (136, 224, 1816, (64, 64), (128, 128)),
-              (145, 432, 2832, (64, 64), (256, 128)), (129, 200, 3000, (64, 64), (128, 256)), (133, 2528, 2448, (64, 64), (256, 192)),
-              (129, 2208, 2208, (64, 64), (192, 256)), (136, 3224, 2704, (64, 128), (256, 256))]
+LINEAR_BWD = [(150, 152, 136, (64, 64), (64, 64)), (216, 136, 136, (64, 128), (64, 64)), (394, 136, 152, (128, 64), (64, 64)),
+              (1006, 216, 176, (128, 128), (64, 64)), (1857, 136, 136, (256, 128), (64, 64)), (1044, 3024, 136, (128, 256), (64, 64)),
+              (2885, 264, 144, (256, 192), (64, 64)), (2070, 2696, 136, (192, 256), (64, 64)), (2814, 2704, 160, (256, 256), (64, 64)),
+              (136, 136, 712, (64, 64), (64, 128)), (160, 216, 1064, (64, 64), (128, 64)), (136, 224, 1816, (64, 64), (128, 128)),
+              (129, 272, 2160, (64, 64), (256, 128)), (130, 136, 2344, (64, 64), (128, 256)), (131, 2120, 3080, (64, 64), (256, 192)),
+              (129, 2208, 2208, (64, 64), (192, 256)), (130, 2728, 2888, (128, 64), (256, 256))]
 
 
 @pytest.mark.parametrize("T,n_in,n_out,nt,tn", LINEAR_BWD)

@@ -1776,11 +1776,12 @@ dp_status dp_stage_step(dp_stage *st, const void *x_in, const void *dy, const ui
   hipEvent_t &step_end = st->step_end[st->steps_issued % dp_stage::kStepsInFlight];
   if (step_end == nullptr) HIP_TRY(hipEventCreateWithFlags(&step_end, hipEventDisableTiming), DP_E_HIP);
   else HIP_TRY(hipEventSynchronize(step_end), DP_E_HIP);   // the step issued kStepsInFlight calls ago
-  // A plan that swaps starts on an idle device: with the previous step still running, the
-  // copies and cross-stream waits queued behind it ran markedly slower (measured: 17 ms
-  // instead of 12 ms a step for 22 small swaps); the step's own launches still run ahead.  That goes for another handle's
-  // step on the same stream as well: three handles of a two-layer stage of width 1600 in turn 14.2 ms a step, 8.2 with the
-  // wait for its swapping steps (and the copies in pieces, see Walk::copy_out; 9.4 before those).
+  // A plan that swaps starts behind the swapping steps before it, on the host: with this handle's previous step still running, the
+  // copies and cross-stream waits queued behind it ran markedly slower (measured: 17 ms instead of 12 ms a step for 22 small
+  // swaps); the step's own launches still run ahead.  That goes for another handle's swapping step on the same stream as well:
+  // three handles of a two-layer stage of width 1600 in turn 14.2 ms a step, 9.4 with the wait (8.2 with copies in pieces too,
+  // see Walk::copy_out); one handle alone 9.4 and, in pieces, 8.0.  What makes the queued copies slow is not known.  Nothing else is waited
+  // for: neither other handles' steps that swap nothing nor dp_stage_forward and dp_stage_backward, for which this was not measured.
   int device = 0;
   if (rep.n_swapped_slots > 0) {
     HIP_TRY(hipGetDevice(&device), DP_E_HIP);

@@ -57,6 +57,25 @@ SMALL = [
 ]
 
 
+def test_swapped_blocks_that_go_in_pieces_come_back_whole():
+    """FC1_OUT and GELU_OUT of 34.1 MB, two pieces of 16 MiB and a short one each, with two micro-batches in flight and gradients
+    accumulating: the bits of the schedule that keeps everything, under the tightest policy and a roomy one."""
+    cfg = syn.StageConfig(2, 128, 2, 8200, 520, 4, "pre", True, "erf", "bf16")
+    w, xs, dys = make(cfg, 3)
+    run = ScheduleRunner(cfg, w, xs, dys)
+    order = O.one_f_one_b(3, 2)
+    run.run(order, 2, syn.plan_keep_all(cfg))
+    keep = run.raw_results()
+    plan = syn.plan_all_swap(cfg)
+    tight = 2 * B.plan_validate(run.bcfg, plan)[1]["peak_bytes"]
+    for budget in (tight, 16 << 30):
+        for _ in range(2):
+            run.poison_outputs()
+            run.run(order, 2, plan, budget_bytes=budget)
+            assert all(torch.equal(a, b) for a, b in zip(keep, run.raw_results())), budget
+    run.close()
+
+
 @pytest.mark.parametrize("cfg", SMALL, ids=lambda c: f"{c.norm_style}-{c.dtype}-H{c.hidden}-S{c.seq}")
 def test_schedule_matches_oracle_for_every_plan_and_depth(cfg):
     n = 4

@@ -4,8 +4,8 @@
 
 Prints ONE JSON line.  `value` = samples/s of the whole job on one MI355X.
 `roofline` is for the kernel that dominates the step (the two products of a
-linear layer's backward in one launch), timed with HIP events on the stream
-the kernels run on.  `cpu_baseline` times the CPU oracle on a
+linear layer's backward, in one launch where the library takes one), timed with
+HIP events on the stream the kernels run on.  `cpu_baseline` times the CPU oracle on a
 bounded sample of the same workload on this machine's host cores.
 """
 from __future__ import annotations
@@ -197,9 +197,10 @@ def time_steps(run, plan, budget, warmup, steps):
     return ms, events
 
 
-def op_times_and_roofline(run, cfg, name, plan_name, plan, budget, k):
+def op_times_and_roofline(run, cfg, name, plan_name, plan, budget, k, kernel_launches):
     """The same steps again with every launch bracketed by HIP events on the launch stream: per-class times and
-    the roofline of the dominant kernel, the two products of a linear layer's backward in one launch."""
+    the roofline of the dominant kernel, the products of the linear layers' backward.  `kernel_launches` are those of
+    one step: the class counts hold a launch of both products twice, so the difference says how many there were."""
     from paper_2505_05856_amd import binding as B
     B.stage_set_profiling(run.stage, True)
     for _ in range(k):
@@ -208,21 +209,30 @@ def op_times_and_roofline(run, cfg, name, plan_name, plan, budget, k):
     flops = B.stage_op_flops(run.stage)
     B.stage_set_profiling(run.stage, False)
     op_ms = {n: round(v[0] / k, 4) for n, v in times.items()}
-    # (a launch counts for both classes, half its time each)
+    # (a launch of both products counts for both classes, half its time each)
     pair_ms = (times["gemm_dgrad"][0] + times["gemm_wgrad"][0]) / k
-    pair_launches = times["gemm_dgrad"][1] / k
+    products = (times["gemm_dgrad"][1] + times["gemm_wgrad"][1]) // k
+    pairs = sum(v[1] for v in times.values()) // k - kernel_launches
+    all_pairs = 2 * pairs == products
+    pair_kernel = "gemm_pair" if cfg.dtype == "bf16" else "gemm_f32_pair"
+    if all_pairs:
+        kernel = f"{pair_kernel} (input- and weight-gradient product of a linear layer)"
+    else:
+        kernel = (f"input- and weight-gradient products of linear layers: {pairs} launches of both ({pair_kernel}), "
+                  f"{products - 2 * pairs} of one")
+    pair_launches = products - pairs
     # algorithmic work (2*M*N*K a product) of exactly the launches that were timed
     pair_flops = (flops["gemm_dgrad"] + flops["gemm_wgrad"]) / k
     peak = PEAK_BF16_TFLOPS if cfg.dtype == "bf16" else PEAK_FP32_TFLOPS
     achieved = pair_flops / (pair_ms * 1e-3) / 1e12
-    roof = {"kernel": "gemm_pair (input- and weight-gradient product of a linear layer)", "bound": "mfma" if cfg.dtype == "bf16" else "latency",
+    roof = {"kernel": kernel, "bound": "mfma" if cfg.dtype == "bf16" else "latency",
             "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
             "avg_launch_us": round(pair_ms * 1e3 / max(pair_launches, 1), 2),
             "avg_launch_us_source": "HIP event pairs recorded around every launch on the launch stream (event overhead "
                                     "included; the rocprofv3 kernel trace of the same command gives avg_launch_us_rocprof)",
-            "avg_launch_us_rocprof": ROCPROF_PAIR_LAUNCH_US.get((name, plan_name)),
+            "avg_launch_us_rocprof": ROCPROF_PAIR_LAUNCH_US.get((name, plan_name)) if all_pairs else None,
             "launches_per_step": pair_launches,
-            "traffic": MEASURED_TRAFFIC_BYTES.get((name, plan_name))}
+            "traffic": MEASURED_TRAFFIC_BYTES.get((name, plan_name)) if all_pairs else None}
     return op_ms, roof
 
 
@@ -277,10 +287,10 @@ def measure(run, name, cfg, plan_name, plan, budget, warmup, steps, op_times=Tru
     _, rep = B.plan_validate(run.bcfg, plan, budget_bytes=budget)
     _, tight = B.plan_validate(run.bcfg, plan, budget_bytes=0)   # no budget: the tightest arena policy
     ms, events = time_steps(run, plan, budget, warmup, steps)
+    stats = run.step(plan, budget, want_stats=True)
     op_ms = roof = None
     if op_times:
-        op_ms, roof = op_times_and_roofline(run, cfg, name, plan_name, plan, budget, max(1, min(steps, 10)))
-    stats = run.step(plan, budget, want_stats=True)
+        op_ms, roof = op_times_and_roofline(run, cfg, name, plan_name, plan, budget, max(1, min(steps, 10)), stats["n_kernel_launches"])
     tf = cfg.model_flops() / (ms * 1e-3) / 1e12
     out = {"workload": workload_text(name, cfg), "plan": plan_name, "budget_bytes": budget,
            "validator_peak_bytes": rep["peak_bytes"], "arena_peak_bytes": rep["arena_peak_bytes"],

@@ -25,16 +25,16 @@ PEAK_FP32_TFLOPS = 157.3      # MI355X fp32 MFMA (v_mfma_f32_16x16x4): 256 CU x 
 # Bytes per launch of the dominant kernel that cross the L2 towards memory (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000,
 # the factors a 256 MiB device copy gives), from the rocprofv3 --pmc runs summarised in
 # profiles/c2_step_hbm_traffic_pmc.md and profiles/c5_step_hbm_traffic_pmc.md.
-MEASURED_TRAFFIC_BYTES = {("C2", "keep-all"): 171.4e6, ("C5", "seed7-mixed"): 4810.4e6}
+MEASURED_TRAFFIC_BYTES = {("C2", "keep-all"): 169.4e6, ("C5", "seed7-mixed"): 4810.4e6}
 # Average duration of a gemm_pair_kernel launch in the rocprofv3 kernel traces (profiles/*_step_kernel_trace.md).
 ROCPROF_PAIR_LAUNCH_US = {
-    ("C2", "keep-all"): {"us": 50.50, "hip_events_same_run_us": 54.41},
-    ("C5", "keep-all"): {"us": 1725.77, "hip_events_same_run_us": 1727.62},
+    ("C2", "keep-all"): {"us": 51.92, "hip_events_same_run_us": 56.16},
+    ("C5", "keep-all"): {"us": 1768.67, "hip_events_same_run_us": 1769.01},
     ("C5", "seed7-mixed"): {
-        "us": 2420.27, "hip_events_same_run_us": 2422.85,
+        "us": 2435.60, "hip_events_same_run_us": 2433.97,
         "note": "under the profiler this plan's device-to-host copies run as shader blit kernels beside the GEMMs and "
                 "slow them; the trace and the HIP events of that profiled run agree with each other, and the keep-all "
-                "trace (no copies: 1725.77 us by rocprofv3, 1727.62 us by HIP events in that run) shows the same kernels undisturbed"},
+                "trace (no copies: 1768.67 us by rocprofv3, 1769.01 us by HIP events in that run) shows the same kernels undisturbed"},
 }
 
 
